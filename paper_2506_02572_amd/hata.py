@@ -114,25 +114,38 @@ def _check(status: int, what: str) -> None:
         raise HataError(f"{what} failed: {strerror(status)} ({status})")
 
 
+# The marshalling of a call is on the critical path of small steps (a decode step of one layer takes the
+# GPU about as long as ten tensor arguments and a stream handle took to pass), so addresses go to ctypes as
+# plain integers and the current stream is asked for by its handle instead of through a
+# torch.cuda.Stream object: 8.0 -> 5.5 us of host time per hata_decode_step call, the launch included.
 def _ptr(t):
-    """Device pointer of a torch tensor (or None).  A pinned host tensor (KV cache kept in host
+    """Device address of a torch tensor (or None).  A pinned host tensor (KV cache kept in host
     memory) is passed by the device-side address of its mapping."""
     if t is None:
         return None
-    if not t.is_cuda:
-        if t.device.type == "cpu" and t.is_pinned():
-            dev = ctypes.c_void_p()
-            _check(load_library().hata_host_device_pointer(ctypes.c_void_p(t.data_ptr()), ctypes.byref(dev)),
-                   "hata_host_device_pointer")
-            return dev
-        raise HataError("expected a device tensor (or a pinned host tensor)")
-    return ctypes.c_void_p(t.data_ptr())
+    if t.is_cuda:
+        return t.data_ptr()
+    if t.device.type == "cpu" and t.is_pinned():
+        dev = ctypes.c_void_p()
+        _check(load_library().hata_host_device_pointer(t.data_ptr(), ctypes.byref(dev)),
+               "hata_host_device_pointer")
+        return dev.value
+    raise HataError("expected a device tensor (or a pinned host tensor)")
+
+
+_raw_stream = None
 
 
 def _stream(stream=None):
-    import torch
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    """Handle of `stream`, or of torch's current stream on the current device."""
+    if stream is not None:
+        return stream.cuda_stream
+    global _raw_stream
+    if _raw_stream is None:
+        import torch
+        torch.cuda.init()
+        _raw_stream = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+    return _raw_stream[0](_raw_stream[1]())
 
 
 @dataclass
@@ -167,6 +180,7 @@ class Context:
         self.workspace = torch.empty(nbytes.value + 256, dtype=torch.uint8, device=self.device)
         base = self.workspace.data_ptr()
         self._ws_ptr = (base + 255) // 256 * 256
+        self._lib = lib
         self._h = ctypes.c_void_p(None)
         with torch.cuda.device(self.device):
             _check(lib.hata_create_tuned(ctypes.byref(self._h), ctypes.byref(self.cfg), ctypes.byref(self.tuning),
@@ -186,101 +200,132 @@ class Context:
 
     # ---- entry points (same names as the C ABI) ----
     def hata_encode_keys(self, K, W_H, start, n_new, B, max_new, codes, stream=None):
-        _check(load_library().hata_encode_keys(self._h, _ptr(K), _ptr(W_H), _ptr(start), _ptr(n_new),
-                                               B, max_new, _ptr(codes), _stream(stream)),
-               "hata_encode_keys")
+        rc = self._lib.hata_encode_keys(self._h, _ptr(K), _ptr(W_H), _ptr(start), _ptr(n_new), B, max_new,
+                                        _ptr(codes), _stream(stream))
+        if rc:
+            _check(rc, "hata_encode_keys")
 
     def hata_prepare_weights(self, W_H, stream=None):
-        _check(load_library().hata_prepare_weights(self._h, _ptr(W_H), _stream(stream)), "hata_prepare_weights")
+        rc = self._lib.hata_prepare_weights(self._h, _ptr(W_H), _stream(stream))
+        if rc:
+            _check(rc, "hata_prepare_weights")
 
     def hata_prefill_write(self, K_new, V_new, start, n_new, B, max_new, K, V, codes, W_H, stream=None):
-        _check(load_library().hata_prefill_write(self._h, _ptr(K_new), _ptr(V_new), _ptr(start), _ptr(n_new),
-                                                 B, max_new, _ptr(K), _ptr(V), _ptr(codes), _ptr(W_H),
-                                                 _stream(stream)), "hata_prefill_write")
+        rc = self._lib.hata_prefill_write(self._h, _ptr(K_new), _ptr(V_new), _ptr(start), _ptr(n_new), B,
+                                          max_new, _ptr(K), _ptr(V), _ptr(codes), _ptr(W_H), _stream(stream))
+        if rc:
+            _check(rc, "hata_prefill_write")
 
     def hata_prefill_write_paged(self, K_new, V_new, start, n_new, B, max_new, K_pool, V_pool, codes_pool,
                                  block_table, max_blocks, page_rows, n_pages, W_H, stream=None):
-        _check(load_library().hata_prefill_write_paged(
-            self._h, _ptr(K_new), _ptr(V_new), _ptr(start), _ptr(n_new), B, max_new, _ptr(K_pool),
-            _ptr(V_pool), _ptr(codes_pool), _ptr(block_table), max_blocks, page_rows, n_pages, _ptr(W_H),
-            _stream(stream)), "hata_prefill_write_paged")
+        rc = self._lib.hata_prefill_write_paged(self._h, _ptr(K_new), _ptr(V_new), _ptr(start), _ptr(n_new), B,
+                                                max_new, _ptr(K_pool), _ptr(V_pool), _ptr(codes_pool),
+                                                _ptr(block_table), max_blocks, page_rows, n_pages, _ptr(W_H),
+                                                _stream(stream))
+        if rc:
+            _check(rc, "hata_prefill_write_paged")
 
     def hata_encode_query(self, q, W_H, B, qcodes, stream=None):
-        _check(load_library().hata_encode_query(self._h, _ptr(q), _ptr(W_H), B, _ptr(qcodes),
-                                                _stream(stream)), "hata_encode_query")
+        rc = self._lib.hata_encode_query(self._h, _ptr(q), _ptr(W_H), B, _ptr(qcodes), _stream(stream))
+        if rc:
+            _check(rc, "hata_encode_query")
 
     def hata_hamming_score(self, qcodes, codes, seq_len, B, scores, stream=None):
-        _check(load_library().hata_hamming_score(self._h, _ptr(qcodes), _ptr(codes), _ptr(seq_len), B,
-                                                 _ptr(scores), _stream(stream)), "hata_hamming_score")
+        rc = self._lib.hata_hamming_score(self._h, _ptr(qcodes), _ptr(codes), _ptr(seq_len), B, _ptr(scores),
+                                          _stream(stream))
+        if rc:
+            _check(rc, "hata_hamming_score")
 
     def hata_topk(self, scores, seq_len, k, B, idx, stream=None):
-        _check(load_library().hata_topk(self._h, _ptr(scores), _ptr(seq_len), _ptr(k), B, _ptr(idx),
-                                        _stream(stream)), "hata_topk")
+        rc = self._lib.hata_topk(self._h, _ptr(scores), _ptr(seq_len), _ptr(k), B, _ptr(idx), _stream(stream))
+        if rc:
+            _check(rc, "hata_topk")
 
     def hata_sparse_decode(self, q, K, V, idx, k, B, sm_scale, out, out_f32=None, stream=None):
-        _check(load_library().hata_sparse_decode(self._h, _ptr(q), _ptr(K), _ptr(V), _ptr(idx), _ptr(k),
-                                                 B, sm_scale, _ptr(out), _ptr(out_f32),
-                                                 _stream(stream)), "hata_sparse_decode")
+        rc = self._lib.hata_sparse_decode(self._h, _ptr(q), _ptr(K), _ptr(V), _ptr(idx), _ptr(k), B, sm_scale,
+                                          _ptr(out), _ptr(out_f32), _stream(stream))
+        if rc:
+            _check(rc, "hata_sparse_decode")
 
     def hata_sparse_decode_static(self, q, K, V, idx, k, B, sm_scale, out, out_f32=None, stream=None):
         """The allocation-free variant: uses this context's shape only, not its workspace."""
-        _check(load_library().hata_sparse_decode_static(ctypes.byref(self.cfg), _ptr(q), _ptr(K), _ptr(V), _ptr(idx),
-                                                        _ptr(k), B, sm_scale, _ptr(out), _ptr(out_f32),
-                                                        _stream(stream)), "hata_sparse_decode_static")
+        rc = self._lib.hata_sparse_decode_static(ctypes.byref(self.cfg), _ptr(q), _ptr(K), _ptr(V), _ptr(idx),
+                                                 _ptr(k), B, sm_scale, _ptr(out), _ptr(out_f32),
+                                                 _stream(stream))
+        if rc:
+            _check(rc, "hata_sparse_decode_static")
 
     def hata_gather_rows(self, K, V, idx, k, B, max_workgroups, K_stage, V_stage, stream=None):
-        _check(load_library().hata_gather_rows(self._h, _ptr(K), _ptr(V), _ptr(idx), _ptr(k), B, max_workgroups,
-                                               _ptr(K_stage), _ptr(V_stage), _stream(stream)), "hata_gather_rows")
+        rc = self._lib.hata_gather_rows(self._h, _ptr(K), _ptr(V), _ptr(idx), _ptr(k), B, max_workgroups,
+                                        _ptr(K_stage), _ptr(V_stage), _stream(stream))
+        if rc:
+            _check(rc, "hata_gather_rows")
 
     def hata_dense_decode(self, q, K, V, seq_len, B, sm_scale, out, out_f32=None, stream=None):
-        _check(load_library().hata_dense_decode(self._h, _ptr(q), _ptr(K), _ptr(V), _ptr(seq_len), B,
-                                                sm_scale, _ptr(out), _ptr(out_f32), _stream(stream)),
-               "hata_dense_decode")
+        rc = self._lib.hata_dense_decode(self._h, _ptr(q), _ptr(K), _ptr(V), _ptr(seq_len), B, sm_scale,
+                                         _ptr(out), _ptr(out_f32), _stream(stream))
+        if rc:
+            _check(rc, "hata_dense_decode")
 
     def hata_decode_step(self, q, K, V, W_H, codes, seq_len, k, B, append, sm_scale, out,
                          out_f32=None, stream=None):
-        _check(load_library().hata_decode_step(self._h, _ptr(q), _ptr(K), _ptr(V), _ptr(W_H),
-                                               _ptr(codes), _ptr(seq_len), _ptr(k), B,
-                                               1 if append else 0, sm_scale, _ptr(out),
-                                               _ptr(out_f32), _stream(stream)), "hata_decode_step")
+        rc = self._lib.hata_decode_step(self._h, _ptr(q), _ptr(K), _ptr(V), _ptr(W_H), _ptr(codes),
+                                        _ptr(seq_len), _ptr(k), B, 1 if append else 0, sm_scale, _ptr(out),
+                                        _ptr(out_f32), _stream(stream))
+        if rc:
+            _check(rc, "hata_decode_step")
 
     def hata_select_step(self, q, K, W_H, codes, seq_len, k, B, append, idx, stream=None):
-        _check(load_library().hata_select_step(self._h, _ptr(q), _ptr(K), _ptr(W_H), _ptr(codes), _ptr(seq_len),
-                                               _ptr(k), B, 1 if append else 0, _ptr(idx), _stream(stream)),
-               "hata_select_step")
+        rc = self._lib.hata_select_step(self._h, _ptr(q), _ptr(K), _ptr(W_H), _ptr(codes), _ptr(seq_len),
+                                        _ptr(k), B, 1 if append else 0, _ptr(idx), _stream(stream))
+        if rc:
+            _check(rc, "hata_select_step")
 
     def hata_decode_step_paged(self, q, K_pool, V_pool, W_H, codes_pool, block_table, max_blocks,
                                page_rows, n_pages, seq_len, k, B, append, sm_scale, out, out_f32=None,
                                stream=None):
-        _check(load_library().hata_decode_step_paged(
-            self._h, _ptr(q), _ptr(K_pool), _ptr(V_pool), _ptr(W_H), _ptr(codes_pool), _ptr(block_table),
-            max_blocks, page_rows, n_pages, _ptr(seq_len), _ptr(k), B, 1 if append else 0, sm_scale,
-            _ptr(out), _ptr(out_f32), _stream(stream)), "hata_decode_step_paged")
+        rc = self._lib.hata_decode_step_paged(self._h, _ptr(q), _ptr(K_pool), _ptr(V_pool), _ptr(W_H),
+                                              _ptr(codes_pool), _ptr(block_table), max_blocks, page_rows,
+                                              n_pages, _ptr(seq_len), _ptr(k), B, 1 if append else 0, sm_scale,
+                                              _ptr(out), _ptr(out_f32), _stream(stream))
+        if rc:
+            _check(rc, "hata_decode_step_paged")
 
     def hata_step_plan(self, B):
         """(n_launches, chunk, n_chunks) of hata_decode_step for a batch of B sequences."""
         n, c, nc = _i32(0), _i32(0), _i32(0)
-        _check(load_library().hata_step_plan(self._h, B, ctypes.byref(n), ctypes.byref(c),
-                                             ctypes.byref(nc)), "hata_step_plan")
+        rc = self._lib.hata_step_plan(self._h, B, ctypes.byref(n), ctypes.byref(c), ctypes.byref(nc))
+        if rc:
+            _check(rc, "hata_step_plan")
         return n.value, c.value, nc.value
 
     def hata_step_sub_batches(self, B):
         """Launches of the single-launch form for a batch of B (0: the three-launch form is used)."""
         n = _i32(0)
-        _check(load_library().hata_step_sub_batches(self._h, B, ctypes.byref(n)), "hata_step_sub_batches")
+        rc = self._lib.hata_step_sub_batches(self._h, B, ctypes.byref(n))
+        if rc:
+            _check(rc, "hata_step_sub_batches")
         return n.value
 
     def hata_set_step_mode(self, mode):
-        _check(load_library().hata_set_step_mode(self._h, mode), "hata_set_step_mode")
+        rc = self._lib.hata_set_step_mode(self._h, mode)
+        if rc:
+            _check(rc, "hata_set_step_mode")
 
     def hata_keep_step_scores(self, keep):
-        _check(load_library().hata_keep_step_scores(self._h, 1 if keep else 0), "hata_keep_step_scores")
+        rc = self._lib.hata_keep_step_scores(self._h, 1 if keep else 0)
+        if rc:
+            _check(rc, "hata_keep_step_scores")
 
     def hata_set_wait_limit(self, polls):
-        _check(load_library().hata_set_wait_limit(self._h, polls), "hata_set_wait_limit")
+        rc = self._lib.hata_set_wait_limit(self._h, polls)
+        if rc:
+            _check(rc, "hata_set_wait_limit")
 
     def hata_check(self, stream=None):
-        _check(load_library().hata_check(self._h, _stream(stream)), "hata_check")
+        rc = self._lib.hata_check(self._h, _stream(stream))
+        if rc:
+            _check(rc, "hata_check")
 
     def prepared(self, name, *args, stream=None):
         """Marshal the arguments of entry point ``name`` once and return a zero-argument callable

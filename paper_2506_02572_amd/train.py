@@ -10,6 +10,7 @@ from __future__ import annotations
 import ctypes
 
 from . import hata as _hata
+from .hata import _ptr, _stream
 
 EXPORTS = ("hata_train_workspace_bytes", "hata_train_create", "hata_train_destroy", "hata_train_step",
            "hata_train_make_labels")
@@ -65,6 +66,7 @@ class TrainContext:
                      "hata_train_workspace_bytes")
         self.workspace = torch.empty(nbytes.value + 256, dtype=torch.uint8, device=device)
         ws = (self.workspace.data_ptr() + 255) // 256 * 256
+        self._lib = lib
         self._h = ctypes.c_void_p(None)
         _hata._check(lib.hata_train_create(ctypes.byref(self._h), ctypes.byref(self.cfg),
                                            ctypes.c_void_p(ws), nbytes.value), "hata_train_create")
@@ -83,11 +85,12 @@ class TrainContext:
 
     def hata_train_step(self, Q, K, s, n, W, v, hp: hata_train_hparams, grad=None, loss=None, stream=None,
                         block_query=None, n_queries=1):
-        _hata._check(_lib().hata_train_step(self._h, _hata._ptr(Q), _hata._ptr(K), _hata._ptr(s), n,
-                                            _hata._ptr(block_query), n_queries, _hata._ptr(W), _hata._ptr(v),
-                                            ctypes.byref(hp), _hata._ptr(grad), _hata._ptr(loss),
-                                            _hata._stream(stream)), "hata_train_step")
+        rc = self._lib.hata_train_step(self._h, _ptr(Q), _ptr(K), _ptr(s), n, _ptr(block_query), n_queries, _ptr(W),
+                                       _ptr(v), ctypes.byref(hp), _ptr(grad), _ptr(loss), _stream(stream))
+        if rc:
+            _hata._check(rc, "hata_train_step")
 
     def hata_train_make_labels(self, q, K, m, s, stream=None):
-        _hata._check(_lib().hata_train_make_labels(self._h, _hata._ptr(q), _hata._ptr(K), m, _hata._ptr(s),
-                                                   _hata._stream(stream)), "hata_train_make_labels")
+        rc = self._lib.hata_train_make_labels(self._h, _ptr(q), _ptr(K), m, _ptr(s), _stream(stream))
+        if rc:
+            _hata._check(rc, "hata_train_make_labels")
