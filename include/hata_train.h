@@ -62,7 +62,8 @@ typedef struct hata_train_ctx hata_train_ctx; /* opaque, host memory */
 int hata_train_workspace_bytes(const hata_train_config* cfg, size_t* out);
 
 /* Creates a context over `workspace` (device, 256-byte aligned, >= hata_train_workspace_bytes()
- * bytes, owned by the caller, must outlive the context). */
+ * bytes, owned by the caller, must outlive the context); the label builder's histogram in it is
+ * cleared here with a hipMemset on the current device. */
 int hata_train_create(hata_train_ctx** ctx_out, const hata_train_config* cfg, void* workspace,
                       size_t workspace_bytes);
 
@@ -71,8 +72,8 @@ int hata_train_destroy(hata_train_ctx* ctx);
 /* One SGD step on W (and v) from the n triplets (Q[i], K[i], s[i]), 1 <= n <= n_max.
  * block_query (device, may be NULL = one query) and n_queries (1 <= n_queries <= number of blocks;
  * ignored when block_query is NULL) select the per-query balance term; ids outside [0, n_queries)
- * count as the nearest valid id.  hp: host pointer.  grad and loss may be NULL.  Six small
- * launches on `stream`; the projections and the weight-gradient contraction run on the matrix
+ * count as the nearest valid id.  hp: host pointer.  grad and loss may be NULL.  Three launches
+ * (four above 65536 triplets) on `stream`; the projections and the weight-gradient contraction run on the matrix
  * cores (bf16 MFMA over exact three-way bf16 splits of the fp32 operands, fp32 accumulation). */
 int hata_train_step(hata_train_ctx* ctx, const void* Q, const void* K, const float* s, int32_t n,
                     const int32_t* block_query, int32_t n_queries, float* W, float* v,
@@ -81,7 +82,7 @@ int hata_train_step(hata_train_ctx* ctx, const void* Q, const void* K, const flo
 /* Training-data construction of App. B.1 (steps 3-4) for ONE sampled query: the qk scores of the
  * query against m keys (accumulated in fp64), the best floor(m / 10) pairs (at least one) labelled
  * 20 .. 1 in equal steps by rank -- the earlier key first on equal scores -- and the others -1.
- *   q [d] bf16, K [m, d] bf16, s [m] fp32 (output), 1 <= m <= n_max; two launches on `stream`. */
+ *   q [d] bf16, K [m, d] bf16, s [m] fp32 (output), 1 <= m <= n_max; three launches on `stream`. */
 int hata_train_make_labels(hata_train_ctx* ctx, const void* q, const void* K, int32_t m, float* s,
                            void* stream);
 
