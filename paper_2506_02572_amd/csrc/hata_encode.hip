@@ -1,156 +1,61 @@
 // HashEncode kernels (Alg. 2 of the paper): codes = BitPack(Sign(x . W_H)).
 //
-//   encode_vectors_kernel  one workgroup per vector (query heads, appended keys);
-//                          fp64 accumulation, so the sign agrees with an exact
-//                          evaluation unless |projection| is below ~1e-13.
+//   encode_few_kernel      the query heads of a unit and up to eight keys of it; fp64 accumulation (hata_hash.h).
 //   encode_bulk_kernel     64 keys per workgroup, fp32 accumulation (prefill, the key-code fill of Alg. 1).
 #include "hata_device.h"
+#include "hata_hash.h"
 #include "hata_internal.h"
 
 namespace hata {
 
 // Bit j of a code goes to word j/32, bit position j%32; bit = (projection >= 0).
-// 1024 threads = (column j, part p): every thread sums 128 / parts channels with all its W_H
-// loads in flight at once, so the kernel costs about one memory round trip.
-#define HATA_ENC_THREADS 1024
-__global__ __launch_bounds__(HATA_ENC_THREADS) void encode_vectors_kernel(
-    const uint16_t* __restrict__ q, uint32_t* __restrict__ qcodes, int nq_blocks,
-    const uint16_t* __restrict__ K, const int32_t* __restrict__ start,
-    const int32_t* __restrict__ n_new, int max_new, int from_seq_len,
-    uint32_t* __restrict__ codes, const float* __restrict__ W_H,
-    int Hq, int Hkv, int G, int r, int Wd, int L_cap,
+// grid = (slices of COLS hash columns, B * Hkv): the workgroup encodes, on its columns, the G query heads of its unit (q
+// not null) and n_new[b] <= max_new keys from row start[b] on (K not null; from_seq_len: the one key at row
+// start[b] - 1), four vectors at a time, the next four's channels fetched ahead.  Bound by latency, the
+// launch and two round trips to memory; a workgroup of 1024 threads per unit (queries) or per key on the vector
+// ALU took 4.0 and 11.5 us at 64 units, r = 128, this takes 3.9 for both.
+template <int COLS>
+__global__ __launch_bounds__(256) void encode_few_kernel(
+    const uint16_t* __restrict__ q, uint32_t* __restrict__ qcodes, const uint16_t* __restrict__ K,
+    const int32_t* __restrict__ start, const int32_t* __restrict__ n_new, int max_new, int from_seq_len,
+    uint32_t* __restrict__ codes, const float* __restrict__ W_H, int Hq, int Hkv, int G, int r, int L_cap,
     int64_t sb, int64_t sh, int64_t sn) {
-    __shared__ float xs[HATA_D];
-    __shared__ double part[HATA_ENC_THREADS];
+    constexpr int WPS = COLS / 32;  // code words of a slice
+    __shared__ uint32_t s_codes[(16 + 8) * WPS];
     const int tid = threadIdx.x;
-    int blk = blockIdx.x;
-    const uint16_t* x;
-    uint32_t* dst;
-    int h;
-    if (blk < nq_blocks) {
-        const int hq = blk % Hq;
-        h = hq / G;
-        x = q + (int64_t)blk * HATA_D;
-        dst = qcodes + (int64_t)blk * Wd;
-    } else {
-        blk -= nq_blocks;
-        const int t = blk % max_new;
-        const int u = blk / max_new;
-        const int b = u / Hkv;
-        h = u % Hkv;
-        int n, cnt;
-        if (from_seq_len) { n = start[b] - 1; cnt = 1; }
-        else { n = start[b] + t; cnt = n_new[b]; }
-        if (t >= cnt || n < 0 || n >= L_cap) return;  // uniform over the workgroup
-        x = K + b * sb + h * sh + n * sn;
-        dst = codes + ((int64_t)u * L_cap + n) * Wd;
+    const int u = blockIdx.y, b = u / Hkv, h = u % Hkv;
+    HashWeights<COLS> hw;
+    hw.fetch(W_H + (int64_t)h * HATA_D * r + blockIdx.x * COLS, r);
+    const int nq = q ? G : 0;
+    int row0 = 0, nk = 0;  // keys: rows row0 .. row0 + nk - 1 that lie in the cache
+    if (K) {
+        row0 = from_seq_len ? start[b] - 1 : start[b];
+        nk = from_seq_len ? 1 : clampi(n_new[b], 0, max_new);
+        if (row0 < 0) { nk = max(nk + row0, 0); row0 = 0; }
+        nk = min(nk, L_cap - row0);
     }
-    const int parts = HATA_ENC_THREADS / r;       // r <= 256 -> parts >= 4
-    const int per = (HATA_D + parts - 1) / parts; // channels per part (<= 32)
-    const int j = tid % r, p = tid / r;
-    // issue the weight loads before waiting for x
-    float wv[32];
-    const int i0 = p * per;
-    const bool active = p < parts;
-    {
-        const float* w = W_H + (int64_t)h * HATA_D * r + j;
+    const int nv = nq + max(nk, 0);
+    const uint16_t* qu = q + ((int64_t)b * Hq + (int64_t)h * G) * HATA_D;
+    const uint16_t* Ku = K + b * sb + h * sh + row0 * sn;
+    auto load = [&](int v0, uint4 (&x)[1][4]) {
+        const int v = min(v0 + (tid & 3), nv - 1);
+        hash_load_x(v < nq ? qu + v * HATA_D : Ku + (v - nq) * sn, x[0]);
+    };
+    if (nv <= 0) return;
+    uint4 x[1][4], xn[1][4];
+    load(0, x);
+    for (int v0 = 0; v0 < nv; v0 += 4) {
+        if (v0 + 4 < nv) load(v0 + 4, xn);
+        hash_pass<COLS, 1>(hw, x, s_codes, WPS, v0, nv);
 #pragma unroll
-        for (int t = 0; t < 32; ++t)
-            wv[t] = (active && t < per && i0 + t < HATA_D) ? w[(int64_t)(i0 + t) * r] : 0.f;
-    }
-    if (tid < HATA_D) xs[tid] = __uint_as_float((uint32_t)x[tid] << 16);
-    __syncthreads();
-    double acc = 0.0;
-#pragma unroll
-    for (int t = 0; t < 32; ++t)
-        if (t < per && i0 + t < HATA_D) acc += (double)xs[i0 + t] * (double)wv[t];
-    part[tid] = acc;
-    __syncthreads();
-    bool bit = false;
-    if (tid < r) {
-        double y = 0.0;
-        for (int pp = 0; pp < parts; ++pp) y += part[pp * r + tid];
-        bit = (y >= 0.0);
-    }
-    const unsigned long long mask = __ballot(bit);
-    const int wave = tid >> 6;
-    if ((tid & 63) == 0 && wave * 64 < r) {
-        dst[2 * wave] = (uint32_t)mask;
-        if (2 * wave + 1 < Wd) dst[2 * wave + 1] = (uint32_t)(mask >> 32);
-    }
-}
-
-// One workgroup per (sequence, KV head) unit: the G query heads of the group and, optionally,
-// the key appended in this step share one pass over W_H[h] (each weight is loaded once and used
-// for every vector).  1024 threads = (column j, part p); fp64 accumulation; the partial sums of
-// the parts are combined in a fixed order, so the result is deterministic.
-// grid = B * Hkv.  R = hash bits (128 or 256).
-template <int R>
-__global__ __launch_bounds__(HATA_ENC_THREADS) void encode_unit_kernel(
-    const uint16_t* __restrict__ q, uint32_t* __restrict__ qcodes,
-    const uint16_t* __restrict__ K, const int32_t* __restrict__ seq_len, int append,
-    uint32_t* __restrict__ codes, const float* __restrict__ W_H,
-    int Hq, int Hkv, int G, int L_cap, int64_t sb, int64_t sh, int64_t sn) {
-    constexpr int PARTS = HATA_ENC_THREADS / R;
-    constexpr int PER = HATA_D / PARTS;
-    constexpr int WD = R / 32;
-    constexpr int VG = 4;  // vectors reduced per round
-    __shared__ float xs[17][HATA_D];
-    __shared__ double part[PARTS][VG][R];
-    const int tid = threadIdx.x;
-    const int u = blockIdx.x;
-    const int b = u / Hkv, h = u % Hkv;
-    const int j = tid % R, p = tid / R;
-    // weights first: PER independent loads per thread
-    float wv[PER];
-    {
-        const float* w = W_H + (int64_t)h * HATA_D * R + (int64_t)p * PER * R + j;
-#pragma unroll
-        for (int t = 0; t < PER; ++t) wv[t] = w[(int64_t)t * R];
-    }
-    int n_key = -1;
-    if (append) {
-        n_key = seq_len[b] - 1;
-        if (n_key < 0 || n_key >= L_cap) n_key = -1;
-    }
-    const int nv = G + (n_key >= 0 ? 1 : 0);
-    for (int i = tid; i < nv * HATA_D; i += HATA_ENC_THREADS) {
-        const int v = i / HATA_D, ch = i % HATA_D;
-        const uint16_t* x = (v < G) ? q + ((int64_t)b * Hq + (int64_t)h * G + v) * HATA_D
-                                    : K + b * sb + h * sh + (int64_t)n_key * sn;
-        xs[v][ch] = __uint_as_float((uint32_t)x[ch] << 16);
+        for (int i = 0; i < 4; ++i) x[0][i] = xn[0][i];
     }
     __syncthreads();
-    for (int v0 = 0; v0 < nv; v0 += VG) {
-        double acc[VG];
-#pragma unroll
-        for (int i = 0; i < VG; ++i) acc[i] = 0.0;
-#pragma unroll
-        for (int t = 0; t < PER; ++t) {
-            const double wd = (double)wv[t];
-#pragma unroll
-            for (int i = 0; i < VG; ++i)  // rows past nv are read (stale LDS) but never used
-                acc[i] += (double)xs[min(v0 + i, 16)][p * PER + t] * wd;
-        }
-#pragma unroll
-        for (int i = 0; i < VG; ++i) part[p][i][j] = acc[i];
-        __syncthreads();
-        if (tid < VG * R) {
-            const int i = tid / R;  // uniform over a wave (R >= 64)
-            const int v = v0 + i;
-            double y = 0.0;
-#pragma unroll
-            for (int pp = 0; pp < PARTS; ++pp) y += part[pp][i][j];
-            const unsigned long long mask = __ballot(y >= 0.0);
-            if ((tid & 63) == 0 && v < nv) {
-                uint32_t* dst = (v < G) ? qcodes + ((int64_t)b * Hq + (int64_t)h * G + v) * WD
-                                        : codes + ((int64_t)u * L_cap + n_key) * WD;
-                const int w0 = (j >> 6) * 2;
-                dst[w0] = (uint32_t)mask;
-                dst[w0 + 1] = (uint32_t)(mask >> 32);
-            }
-        }
-        __syncthreads();
+    const int Wd = r / 32;
+    for (int i = tid; i < nv * WPS; i += 256) {
+        const int v = i / WPS, w = blockIdx.x * WPS + i % WPS;
+        if (v < nq) qcodes[((int64_t)b * Hq + (int64_t)h * G + v) * Wd + w] = s_codes[i];
+        else codes[((int64_t)u * L_cap + row0 + v - nq) * Wd + w] = s_codes[i];
     }
 }
 
@@ -629,28 +534,14 @@ hipError_t launch_encode_vectors(const hata_ctx* c, const void* q, uint32_t* qco
                                  int max_new, int from_seq_len, uint32_t* codes,
                                  const float* W_H, int B, hipStream_t s) {
     const hata_config& f = c->cfg;
-    // queries (+ the key at seq_len - 1) of a unit in one workgroup when a kernel for r exists
-    if (q && (!K || from_seq_len) && c->G <= 16 && (f.r == 128 || f.r == 256)) {
-        const int append = K ? 1 : 0;
-        if (f.r == 128)
-            hipLaunchKernelGGL((encode_unit_kernel<128>), dim3(B * f.Hkv), dim3(HATA_ENC_THREADS), 0, s,
-                               (const uint16_t*)q, qcodes, (const uint16_t*)K, start, append, codes,
-                               W_H, f.Hq, f.Hkv, c->G, f.L_cap, f.kv_stride_b, f.kv_stride_h,
-                               f.kv_stride_n);
-        else
-            hipLaunchKernelGGL((encode_unit_kernel<256>), dim3(B * f.Hkv), dim3(HATA_ENC_THREADS), 0, s,
-                               (const uint16_t*)q, qcodes, (const uint16_t*)K, start, append, codes,
-                               W_H, f.Hq, f.Hkv, c->G, f.L_cap, f.kv_stride_b, f.kv_stride_h,
-                               f.kv_stride_n);
-        return hipGetLastError();
-    }
-    const int nq = q ? B * f.Hq : 0;
-    const int nk = K ? B * f.Hkv * max_new : 0;
-    if (nq + nk == 0) return hipSuccess;
-    hipLaunchKernelGGL(encode_vectors_kernel, dim3(nq + nk), dim3(HATA_ENC_THREADS), 0, s,
-                       (const uint16_t*)q, qcodes, nq, (const uint16_t*)K, start, n_new,
-                       max_new > 0 ? max_new : 1, from_seq_len, codes, W_H, f.Hq, f.Hkv, c->G,
-                       f.r, c->Wd, f.L_cap, f.kv_stride_b, f.kv_stride_h, f.kv_stride_n);
+    if (!q && !K) return hipSuccess;
+#define HATA_LAUNCH_FEW(COLS)                                                                                       \
+    hipLaunchKernelGGL((encode_few_kernel<COLS>), dim3(f.r / COLS, B * f.Hkv), dim3(256), 0, s, (const uint16_t*)q, \
+                       qcodes, (const uint16_t*)K, start, n_new, max_new, from_seq_len, codes, W_H, f.Hq, f.Hkv,    \
+                       c->G, f.r, f.L_cap, f.kv_stride_b, f.kv_stride_h, f.kv_stride_n)
+    if (f.r % 64 == 0) HATA_LAUNCH_FEW(64);
+    else HATA_LAUNCH_FEW(32);
+#undef HATA_LAUNCH_FEW
     return hipGetLastError();
 }
 

@@ -1,0 +1,86 @@
+// HashEncode of a few vectors (Alg. 2 of the paper: Sign(x . W_H), BitPack) on the fp64 matrix instructions: query
+// vectors and appended keys.
+//
+// Four bf16 vectors at a time against 64 (or 32) hash columns of a KV head's weights [128][r], by a workgroup of
+// 256 threads, in fp64 (every product of a bf16 and an fp32 value is exact there, so the sign agrees with an
+// exact evaluation unless |projection| is below ~1e-13) on v_mfma_f64_4x4x4_4b: four blocks of [4 hash columns x
+// 4 channels] . [4 channels x 4 vectors], operands one value a lane -- A: column lane % 16, B: vector
+// lane % 4, both: channel lane / 16; result: vector lane % 4, column lane / 16 + 4 (lane / 4 % 4).  The vectors
+// are few, so the narrow instruction wastes nothing, and the contraction needs no sums across lanes.  A
+// wave owns 16 columns, and lane / 16 stands for 32 consecutive channels.  16.6 cycles per instruction and
+// SIMD: the 32 of a set of four vectors take 0.22 us, the conversions in their shadow.
+#pragma once
+#include "hata_device.h"
+
+namespace hata {
+
+// The 32 weights a lane needs: its column, its 32 channels.
+template <int COLS>
+struct HashWeights {
+    static_assert(COLS == 64 || COLS == 32, "four waves of 16 columns, or two (the other two repeat them)");
+    float w[32];
+    // W: the first of the columns, r: the weights' row pitch
+    __device__ __forceinline__ void fetch(const float* __restrict__ W, int r) {
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        uint32_t at = 4u * (uint32_t)(32 * (lane >> 4) * r + (COLS == 64 ? wave : wave & 1) * 16 + (lane & 15));
+        asm volatile("" : "+v"(at));  // (addresses are made anew for every fetch instead of being kept)
+        const char* base = reinterpret_cast<const char*>(W);
+#pragma unroll
+        for (int s = 0; s < 32; ++s) w[s] = *reinterpret_cast<const float*>(base + s * r * 4 + at);
+    }
+};
+
+// this lane's 32 channels of a vector
+__device__ __forceinline__ void hash_load_x(const uint16_t* __restrict__ x, uint4 (&r)[4]) {
+    const uint16_t* p = x + 32 * ((threadIdx.x & 63) >> 4);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r[i] = reinterpret_cast<const uint4*>(p)[i];
+}
+
+// or over the lanes that hold the other columns of this lane's vector (lane bits 2..5)
+__device__ __forceinline__ uint32_t or_columns(uint32_t v) {
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x124, 0xf, 0xf, false);  // row_ror:4
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xf, 0xf, false);  // row_ror:8
+    float x, y;
+    swap16(__uint_as_float(v), x, y);
+    v = __float_as_uint(x) | __float_as_uint(y);
+    swap32(__uint_as_float(v), x, y);
+    return __float_as_uint(x) | __float_as_uint(y);
+}
+
+// NS sets of four vectors: x[e] holds this lane's part of vector first + 4 e + lane % 4.  Vector v's code words
+// for these columns go to s_codes[v * pitch ...] where v is below `last`; complete after the caller's next
+// barrier.
+template <int COLS, int NS>
+__device__ __forceinline__ void hash_pass(const HashWeights<COLS>& W, const uint4 (&x)[NS][4], uint32_t* s_codes, int pitch,
+                                          int first, int last) {
+    double acc[NS];
+#pragma unroll
+    for (int e = 0; e < NS; ++e) acc[e] = 0.0;
+#pragma unroll
+    for (int s = 0; s < 32; ++s) {
+        // (without the barriers the compiler converts right behind the loads, or ahead of a loop around this:
+        // waits early, and twice the registers)
+        float w = W.w[s];
+        asm volatile("" : "+v"(w));
+        const double wd = (double)w;
+#pragma unroll
+        for (int e = 0; e < NS; ++e) {
+            const uint4 q = x[e][s >> 3];
+            uint32_t pair = ((s >> 1) & 3) == 0 ? q.x : ((s >> 1) & 3) == 1 ? q.y : ((s >> 1) & 3) == 2 ? q.z : q.w;
+            asm volatile("" : "+v"(pair));
+            const double xd = (double)((s & 1) ? bf16_hi(pair) : bf16_lo(pair));
+            acc[e] = __builtin_amdgcn_mfma_f64_4x4x4f64(wd, xd, acc[e], 0, 0, 0);
+        }
+    }
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int m = (lane >> 4) + (lane & 12);  // column of the result
+#pragma unroll
+    for (int e = 0; e < NS; ++e) {
+        const int v = first + 4 * e + lane;
+        const uint32_t bits = or_columns((acc[e] >= 0.0 ? 1u : 0u) << m);
+        if (lane < 4 && v < last && wave < COLS / 16) reinterpret_cast<uint16_t*>(s_codes)[v * pitch * 2 + wave] = (uint16_t)bits;
+    }
+}
+
+}  // namespace hata

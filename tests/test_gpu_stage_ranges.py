@@ -1,0 +1,34 @@
+"""The stage kernels at the edges of their launch rules, against the oracle."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+from oracle import hata_oracle as O
+from paper_2506_02572_amd import synth
+from tests import harness as H
+
+
+@pytest.mark.parametrize("r,G,max_new", [(32, 1, 1), (64, 3, 8), (96, 5, 2), (128, 16, 3), (256, 16, 7)])
+def test_encode_few_vectors(r, G, max_new):
+    import torch
+    from paper_2506_02572_amd import hata
+    B, Hkv, L_cap = 3, 2, 40
+    print(f"[stages] encode r={r} G={G} max_new={max_new}", flush=True)
+    rng = np.random.default_rng(r + G)
+    K = synth.round_to_bf16_bits(rng.standard_normal((B, Hkv, L_cap, 128)))
+    q = synth.round_to_bf16_bits(rng.standard_normal((B, Hkv * G, 128)))
+    W = rng.standard_normal((Hkv, 128, r)).astype(np.float32)
+    start = np.array([0, L_cap - max_new, 11], np.int32)
+    n_new = np.array([max_new, max_new, max_new - 1], np.int32)
+    ctx = hata.Context(B, Hkv * G, Hkv, 128, r, L_cap, 8)
+    before = rng.integers(0, 2**32, (B, Hkv, L_cap, r // 32), dtype=np.uint32)
+    codes = H.to_dev(before.copy())
+    ctx.hata_encode_keys(H.to_dev(K), H.to_dev(W), H.to_dev(start), H.to_dev(n_new), B, max_new, codes)
+    qcodes = torch.zeros((B, Hkv * G, r // 32), dtype=torch.int32, device="cuda")
+    ctx.hata_encode_query(H.to_dev(q), H.to_dev(W), B, qcodes)
+    torch.cuda.synchronize()
+    ref, near = O.encode_keys_batch(K, W, start, n_new, codes=before.copy())
+    H.check_codes(H.to_host(codes, np.uint32), ref, near, "keys")  # (rows outside the range keep their codes)
+    H.check_codes(H.to_host(qcodes, np.uint32), *O.encode_query_batch(q, W), "queries")
+    ctx.close()
