@@ -251,6 +251,7 @@ int hata_create_tuned(hata_ctx** ctx_out, const hata_config* cfg, const hata_tun
     c->unit_info = (int32_t*)(w + p.off_uinfo);
     c->unit_counter = (uint32_t*)(w + p.off_ucnt);
     c->attn_counter = (uint32_t*)(w + p.off_acnt);
+    c->attn_counter_stride = HATA_COUNTER_STRIDE;
     c->unit_hist = (uint32_t*)(w + p.off_uhist);
     c->coop_rec = (unsigned long long*)(w + p.off_uflag);
     c->coop_qrec = (unsigned long long*)(w + p.off_qrec);
@@ -263,6 +264,10 @@ int hata_create_tuned(hata_ctx** ctx_out, const hata_config* cfg, const hata_tun
     c->control_bytes = p.off_partials - p.off_cinfo;
     // control words and the self-resetting arrival counters start from zero
     if (hipMemset(c->chunk_info, 0, c->control_bytes) != hipSuccess) {
+        delete c;
+        return HATA_EHIP;
+    }
+    if (hata::prepare_topk(c) != hipSuccess) {
         delete c;
         return HATA_EHIP;
     }
@@ -393,7 +398,6 @@ int hata_hamming_score(hata_ctx* ctx, const uint32_t* qcodes, const uint32_t* co
     if (rc != HATA_OK) return rc;
     if (!qcodes || !codes || !seq_len || !scores) return HATA_EINVAL;
     if (!aligned(qcodes, 4) || !aligned(codes, 16) || !aligned(scores, 2)) return HATA_EINVAL;
-    // the chunk histograms are written too (into the workspace), as in the fused decode step
     return hip_rc(hata::launch_score(ctx, qcodes, codes, seq_len, B, scores, nullptr,
                                      (hipStream_t)stream));
 }
@@ -473,6 +477,7 @@ int hata_sparse_decode_static(const hata_config* cfg, const void* q, const void*
     c.sparse_rows = p.sparse_rows; c.sparse_splits = p.sparse_splits;
     c.dense_rows = p.dense_rows; c.dense_splits = p.dense_splits;
     c.attn_counter = (uint32_t*)base;
+    c.attn_counter_stride = 1;
     c.partials = (float*)((char*)base + counter_bytes);
     hipStream_t s = (hipStream_t)stream;
     // the counters must start at zero whatever an earlier call left behind

@@ -5,9 +5,8 @@
 
 #include "../../include/hata.h"
 
-// Words between the arrival counters of consecutive units in the single-launch step (128 bytes:
-// the workgroups of different units then never queue their arrivals on one cache line).  The
-// three-launch kernels index the same arrays densely.
+// Words between the arrival counters of consecutive units (128 bytes:
+// the workgroups of different units then never queue their arrivals on one cache line).
 #define HATA_COUNTER_STRIDE 32
 // 64-bit words between the records of consecutive chunks (two are used): a cache line per chunk, so
 // that the workgroups polling for their records do not all read the same lines
@@ -37,9 +36,10 @@ struct hata_ctx {
     uint16_t* chunk_hist;  // [B_max*Hkv, n_chunks, NBP]
     int32_t* chunk_info;   // [B_max*Hkv, n_chunks + 1, 2] = {output offset, ties taken}
     int32_t* unit_info;    // [B_max*Hkv, 2] = {threshold, selected count}
-    uint32_t* unit_counter;  // [B_max*Hkv (* HATA_COUNTER_STRIDE in the cooperative step)] scored chunks of a unit (self-resetting)
+    uint32_t* unit_counter;  // [B_max*Hkv, HATA_COUNTER_STRIDE] scored chunks of a unit (self-resetting)
     uint32_t* unit_hist;     // [B_max*Hkv, NB] total histogram of a unit (self-clearing)
-    uint32_t* attn_counter;  // [B_max*Hq (cooperative step: per unit, HATA_COUNTER_STRIDE apart)] finished attention slices (self-resetting)
+    uint32_t* attn_counter;  // [B_max*Hq (cooperative step: per unit), attn_counter_stride] finished attention slices (self-resetting)
+    int attn_counter_stride; // HATA_COUNTER_STRIDE; 1 in the static scratch of hata_sparse_decode_static
     unsigned long long* coop_rec;  // [B_max*Hkv, n_chunks, HATA_REC_STRIDE] epoch-stamped chunk records, two words used (cooperative step)
     unsigned long long* coop_qrec; // [B_max*Hkv, n_chunks, G*Wd] epoch-stamped query code words, one copy per chunk (cooperative step)
     uint32_t* error_word;    // [1] set by a cooperative launch that gave up waiting
@@ -83,6 +83,8 @@ hipError_t launch_split_weights(const hata_ctx* c, const float* W_H, hipStream_t
 hipError_t launch_score(const hata_ctx* c, const uint32_t* qcodes, const uint32_t* codes,
                         const int32_t* seq_len, int B, uint16_t* scores, const int32_t* kbud,
                         hipStream_t s);
+hipError_t prepare_topk(const hata_ctx* c);       // once per context
+hipError_t prepare_attention(const hata_ctx* c);  // once per context
 hipError_t launch_topk(const hata_ctx* c, const uint16_t* scores, const int32_t* seq_len,
                        const int32_t* k, int B, int32_t* idx, hipStream_t s);
 // mode: 0 = rows from idx, 1 = dense, 2 = select on the fly (writes idx)

@@ -3,10 +3,10 @@
 //
 // Bandwidth-bound streaming: each lane owns one cached key per iteration and pulls its
 // whole packed code with 128-bit loads (a wave reads 1 KB or 2 KB of consecutive bytes);
-// the G query codes are wave-uniform and sit in scalar registers.  Optionally the
-// workgroup also histograms its chunk's scores in LDS and writes the histogram out, which
-// is what the selection stage needs (a counting select over the <= G*r+1 score values).
-// In the fused decode step (SELECT = true) the workgroup that scores the LAST chunk of a unit
+// the G query codes are wave-uniform and sit in scalar registers.
+// In the three-launch decode step (SELECT = true) the workgroup also histograms its chunk's scores in LDS and
+// writes the histogram out, which is what the selection needs (a counting select over the <= G*r+1
+// score values), and the workgroup that scores the LAST chunk of a unit
 // to finish goes on to compute the unit's selection threshold and the per-chunk output
 // offsets, so no separate launch is needed for that.
 #include "hata_device.h"
@@ -51,7 +51,7 @@ __global__ __launch_bounds__(256) void score_kernel(
     uint32_t* __restrict__ unit_counter, uint32_t* __restrict__ unit_hist) {
     extern __shared__ uint32_t hist[];  // NB bins when chunk_hist != nullptr
     __shared__ ThresholdLds S;
-    __shared__ int last_flag;
+    __shared__ int last_flag, s_low;
     const int tid = threadIdx.x;
     const int c = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
     // wave-uniform query codes (as bit-count planes for the larger groups); their loads do not depend on
@@ -82,9 +82,10 @@ __global__ __launch_bounds__(256) void score_kernel(
     }
     const int end = min(base + chunk, L);
     HATA_TRACE_AT(0, SELECT && u == 0 && c == 0);
-    const bool do_hist = chunk_hist != nullptr;
-    if (do_hist) {
+    uint32_t low = 0xffffu;  // lowest score this thread sees
+    if constexpr (SELECT) {
         for (int i = tid; i < NB; i += 256) hist[i] = 0;
+        if (tid == 0) s_low = NB;
         __syncthreads();
     }
     const uint32_t* cp = codes + u * L_cap * WD;
@@ -111,19 +112,19 @@ __global__ __launch_bounds__(256) void score_kernel(
                         for (int w = 0; w < WD; ++w) s += __popc(qc[g][w] ^ kc[j].w[w]);
                 }
                 sp[n] = (uint16_t)s;
-                if (do_hist) atomicAdd(&hist[s], 1u);
+                if constexpr (SELECT) { atomicAdd(&hist[s], 1u); low = min(low, s); }
             }
         }
     }
     HATA_TRACE_AT(1, SELECT && u == 0 && c == 0);
-    if (do_hist) {
+    if constexpr (SELECT) {
+        low = (uint32_t)(-wave_max64(-(float)low));  // (scores <= 4096 are exact in fp32)
+        if ((tid & 63) == 0) atomicMin(&s_low, (int)low);
         __syncthreads();
         write_chunk_hist(chunk_hist + (u * n_chunks + c) * NBP, hist, NB, NBP);
-    }
-    if constexpr (SELECT) {
         const int keff = min(clampi(kbud[b], 0, k_max), L);
         finish_unit(u, (L + chunk - 1) / chunk, keff, chunk_hist + u * n_chunks * NBP, NB, NBP,
-                    n_chunks, chunk_info, unit_info, unit_counter, unit_hist, hist, S, &last_flag);
+                    n_chunks, chunk_info, unit_info, unit_counter, unit_hist, hist, s_low, S, &last_flag);
     }
 }
 
@@ -166,14 +167,14 @@ __global__ __launch_bounds__(256) void score_kernel_generic(
             for (int g = 0; g < G; ++g) s += __popc(qc[g * WD + w] ^ kw);
         }
         sp[n] = (uint16_t)s;
-        atomicAdd(&hist[s], 1u);
+        if (select) atomicAdd(&hist[s], 1u);
     }
-    __syncthreads();
-    write_chunk_hist(chunk_hist + (u * n_chunks + c) * NBP, hist, NB, NBP);
     if (select) {
+        __syncthreads();
+        write_chunk_hist(chunk_hist + (u * n_chunks + c) * NBP, hist, NB, NBP);
         const int keff = min(clampi(kbud[b], 0, k_max), L);
         finish_unit(u, (L + chunk - 1) / chunk, keff, chunk_hist + u * n_chunks * NBP, NB, NBP,
-                    n_chunks, chunk_info, unit_info, unit_counter, unit_hist, hist, S, &last_flag);
+                    n_chunks, chunk_info, unit_info, unit_counter, unit_hist, hist, -1, S, &last_flag);
     }
 }
 
@@ -196,7 +197,7 @@ static void launch_t(const hata_ctx* c, const uint32_t* qcodes, const uint32_t* 
                            c->unit_info, c->unit_counter, c->unit_hist);
 }
 
-// kbud == nullptr: scores (+ chunk histograms) only.  kbud != nullptr: the fused-step variant,
+// kbud == nullptr: scores only.  kbud != nullptr: the fused-step variant,
 // which also leaves the unit thresholds and chunk offsets of the selection in the workspace.
 hipError_t launch_score(const hata_ctx* c, const uint32_t* qcodes, const uint32_t* codes,
                         const int32_t* seq_len, int B, uint16_t* scores, const int32_t* kbud,

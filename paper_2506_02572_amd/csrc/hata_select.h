@@ -248,11 +248,11 @@ __device__ __forceinline__ void write_chunk_hist(uint16_t* hp, const uint32_t* h
 
 // Tail of a scoring workgroup in the fused step: publish the chunk histogram, count the unit's
 // finished chunks, and let the last one compute the unit's threshold.  `hist` (NB words of LDS)
-// is reused as the total histogram.
+// is reused as the total histogram.  low: the chunk's lowest score, or -1 (unit_threshold's spec_bmin).
 __device__ __forceinline__ void finish_unit(
     int64_t u, int nc, int keff, const uint16_t* __restrict__ chunk_hist_u, int NB, int NBP,
     int n_chunks, int32_t* __restrict__ chunk_info, int32_t* __restrict__ unit_info,
-    uint32_t* __restrict__ unit_counter, uint32_t* __restrict__ unit_hist, uint32_t* hist,
+    uint32_t* __restrict__ unit_counter, uint32_t* __restrict__ unit_hist, uint32_t* hist, int low,
     ThresholdLds& S, int* flag) {
     HATA_TRACE_AT(2, u == 0);
     // add this chunk's histogram to the unit's total (only occupied bins)
@@ -265,9 +265,10 @@ __device__ __forceinline__ void finish_unit(
     HATA_TRACE_AT(4, u == 0);
     __syncthreads();  // ... and so have those of the whole workgroup
     if (threadIdx.x == 0) {
-        const uint32_t done = atomicAdd(&unit_counter[u], 1u);
+        uint32_t* cnt = unit_counter + u * HATA_COUNTER_STRIDE;  // (a cache line of its own: see hata_internal.h)
+        const uint32_t done = atomicAdd(cnt, 1u);
         const int last = (done == (uint32_t)(nc - 1));
-        if (last) unit_counter[u] = 0;  // ready for the next launch
+        if (last) *cnt = 0;  // ready for the next launch
         *flag = last;
     }
     __syncthreads();
@@ -275,8 +276,69 @@ __device__ __forceinline__ void finish_unit(
     HATA_TRACE_AT(5, u == 0);
     // the other workgroups' histograms are read with device-coherent loads
     unit_threshold(chunk_hist_u, unit_hist + u * NB, nc, keff, NB, NBP, chunk_info + u * (n_chunks + 1) * 2,
-                   unit_info + u * 2, hist, S);
+                   unit_info + u * 2, hist, S, nullptr, 0, low);
     HATA_TRACE_AT(6, u == 0);
+}
+
+// Ordered compaction of a chunk whose scores lie in LDS (s_sc, 16-byte aligned, readable up to a whole number of
+// 16 keys per thread): thread t takes kpt consecutive keys (a multiple of 4, at most 128) as eight mask words,
+// one block-wide scan gives the ranks.  emit(r, n) for the r-th selected key, offset n in the chunk, r < cnt;
+// every thread has read its scores by then, so emit may write to s_sc.  All 256 threads; ends without a barrier.
+template <typename Emit>
+__device__ __forceinline__ void compact_lds(const uint16_t* s_sc, int n_keys, int kpt, int T, int take, int cnt,
+                                            uint32_t* scan4, Emit emit) {
+    const int tid = threadIdx.x, n_first = tid * kpt;
+    uint32_t mk[8];  // bits 0..15: key below the threshold, bits 16..31: key at the threshold
+    uint32_t lt = 0, eq = 0;
+#pragma unroll
+    for (int g = 0; g < 8; ++g) {
+        mk[g] = 0;
+        if (g * 16 < kpt) {
+            uint32_t m_lt = 0, m_eq = 0;
+#pragma unroll
+            for (int i4 = 0; i4 < 4; ++i4) {
+                if (g * 16 + i4 * 4 < kpt) {
+                    const uint2 v = *reinterpret_cast<const uint2*>(&s_sc[n_first + g * 16 + i4 * 4]);
+                    const uint32_t w[4] = {v.x & 0xffffu, v.x >> 16, v.y & 0xffffu, v.y >> 16};
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        m_lt |= ((int)w[i] < T ? 1u : 0u) << (i4 * 4 + i);
+                        m_eq |= ((int)w[i] == T ? 1u : 0u) << (i4 * 4 + i);
+                    }
+                }
+            }
+            const uint32_t live = (1u << clampi(n_keys - n_first - g * 16, 0, min(16, kpt - g * 16))) - 1u;
+            mk[g] = (m_lt & live) | ((m_eq & live) << 16);
+            lt += __popc(m_lt & live);
+            eq += __popc(m_eq & live);
+        }
+    }
+    const uint32_t mine = lt | (eq << 16);  // (at most 32768 keys: both halves fit)
+    const uint32_t incl = wave_incl_scan(mine);
+    if ((tid & 63) == 63) scan4[tid >> 6] = incl;
+    __syncthreads();
+    const int wv = tid >> 6;
+    const uint32_t before = (wv > 0 ? scan4[0] : 0u) + (wv > 1 ? scan4[1] : 0u) + (wv > 2 ? scan4[2] : 0u) + incl - mine;
+    // ties go to the lowest rows: this thread may keep `ties_left` of its keys at the threshold
+    const uint32_t ties_before = min(before >> 16, (uint32_t)take);
+    uint32_t ties_left = (uint32_t)take - ties_before;
+    int r = (int)((before & 0xffffu) + ties_before);
+#pragma unroll
+    for (int g = 0; g < 8; ++g) {
+        if (g * 16 < kpt) {
+            uint32_t keep = mk[g] >> 16;
+            const uint32_t avail = min((uint32_t)__popc(keep), ties_left);
+            while ((uint32_t)__popc(keep) > avail) keep &= ~(0x80000000u >> __clz(keep));  // drop the highest row
+            ties_left -= avail;
+            uint32_t sel = (mk[g] & 0xffffu) | keep;
+            while (sel) {
+                const int i = __ffs(sel) - 1;
+                sel &= sel - 1;
+                if (r < cnt) emit(r, n_first + g * 16 + i);
+                ++r;
+            }
+        }
+    }
 }
 
 // Ordered compaction of one whole chunk of 256 * KPT consecutive keys [n0, n0 + 256*KPT) by 256

@@ -32,3 +32,28 @@ def test_encode_few_vectors(r, G, max_new):
     H.check_codes(H.to_host(codes, np.uint32), ref, near, "keys")  # (rows outside the range keep their codes)
     H.check_codes(H.to_host(qcodes, np.uint32), *O.encode_query_batch(q, W), "queries")
     ctx.close()
+
+
+@pytest.mark.parametrize("L_cap", [1, 7, 900, 8192, 8193, 16381, 17003, 32768, 32771, 65533, 65536, 65537])
+@pytest.mark.parametrize("kind", ["spread", "ties", "largest"])
+def test_selection(L_cap, kind):
+    import torch
+    from paper_2506_02572_amd import hata
+    B, Hkv, G, r = 3, 2, 4, 128
+    k_max = max(1, L_cap // 3)
+    print(f"[stages] topk L_cap={L_cap} {kind}", flush=True)
+    rng = np.random.default_rng(L_cap)
+    s = {"spread": rng.normal(256, 12, (B, Hkv, L_cap)), "ties": rng.integers(3, 5, (B, Hkv, L_cap)),
+         "largest": rng.integers(508, 513, (B, Hkv, L_cap))}[kind].astype(np.uint16)
+    seq = np.array([L_cap, max(0, L_cap - 3), L_cap // 5], np.int32)
+    k = np.array([max(1, L_cap // 64), k_max, min(k_max, 40)], np.int32)
+    ctx = hata.Context(B, Hkv * G, Hkv, 128, r, L_cap, k_max)
+    for offset in (0, 3):  # of the array in its first 16-byte word
+        sd = torch.zeros(B * Hkv * L_cap + 8, dtype=torch.int16, device="cuda")[offset:offset + B * Hkv * L_cap]
+        sd.copy_(H.to_dev(s).reshape(-1))
+        idx = torch.full((B, Hkv, k_max), -7, dtype=torch.int32, device="cuda")
+        ctx.hata_topk(sd, H.to_dev(seq), H.to_dev(k), B, idx)
+        torch.cuda.synchronize()
+        ref = O.topk_batch(s, seq, k, k_max)
+        assert np.array_equal(H.to_host(idx), ref)
+    ctx.close()
