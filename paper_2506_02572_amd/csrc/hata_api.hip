@@ -267,7 +267,7 @@ int hata_create_tuned(hata_ctx** ctx_out, const hata_config* cfg, const hata_tun
         delete c;
         return HATA_EHIP;
     }
-    if (hata::prepare_topk(c) != hipSuccess) {
+    if (hata::prepare_topk(c) != hipSuccess || hata::prepare_attention(c) != hipSuccess) {
         delete c;
         return HATA_EHIP;
     }

@@ -5,10 +5,9 @@
 // One kernel template, three row sources:
 //   ROWS_IDX     rows come from an index list in memory            (hata_sparse_decode)
 //   ROWS_DENSE   rows 0 .. seq_len-1                               (hata_dense_decode)
-//   ROWS_SELECT  rows are selected on the fly from the stored scores, the unit threshold and
-//                the per-chunk offsets (ordered compaction of just the chunks that hold this
-//                workgroup's slice of the index list); the index list is written as a
-//                by-product                                         (hata_decode_step)
+//   ROWS_SELECT  the rows of one chunk of the cache (a few, of a very long one) that the unit
+//                threshold selects: ordered compaction of the chunk's stored scores; its part of
+//                the index list is written as a by-product  (hata_decode_step, three-launch form)
 //
 // Split over the rows: every workgroup handles a slice of a unit's rows for HT query heads of
 // the group at once (each K/V row is read once for all of them), keeps an online-softmax
@@ -20,11 +19,8 @@
 #include "hata_internal.h"
 #include "hata_select.h"
 #include "hata_attn_core.h"
-#include "hata_trace.h"
 
 namespace hata {
-
-#define HATA_MAX_ROWS_PER_WG 256
 
 enum { ROWS_IDX = 0, ROWS_DENSE = 1, ROWS_SELECT = 2 };
 
@@ -39,9 +35,10 @@ struct AttnArgs {
     const int32_t* seq_len;
     const int32_t* chunk_info;
     const int32_t* unit_info;
-    int chunk, n_chunks;
+    int chunk, n_chunks, chunks_per_split;
     float* partials;
     uint32_t* counter;
+    int counter_stride;
     uint16_t* out;
     float* out_f32;
     int Hq, Hkv, G, L_cap, k_max, rows_per_wg, n_splits;
@@ -50,14 +47,18 @@ struct AttnArgs {
 };
 
 // grid = (splits, Hkv * (G / HT), B); 256 threads.
+// ROWS_SELECT: a split is a chunk (or as many as leave at most 256 splits to merge), so that everything the
+// selection needs -- the chunk's scores, its offset and ties, the threshold -- is at addresses known from the
+// start.  Slices of the index list instead, which had to find their chunks first, took 18.4 us per launch at
+// 16 units of 20011 keys, this takes 10.4.
 template <int HT, int MODE>
 __global__ __launch_bounds__(256) void attn_kernel(const AttnArgs a) {
     constexpr bool MFMA = HT >= 4;  // matrix-core form of the attention core
     __shared__ __attribute__((aligned(16))) AttnLds<HT> S;
     __shared__ __attribute__((aligned(16))) uint16_t s_vt[MFMA ? HATA_VT_ELEMS : 8];
-    __shared__ int s_rows[MODE == ROWS_SELECT ? HATA_MAX_ROWS_PER_WG : 1];
+    extern __shared__ __attribute__((aligned(16))) uint16_t s_sc[];  // ROWS_SELECT: the chunk's scores, then its selected rows
     __shared__ uint32_t scan4[4];
-    __shared__ int s_clo, s_chi, s_last;
+    __shared__ int s_last;
     const int tid = threadIdx.x;
     const int split = blockIdx.x;
     const int tiles = a.G / HT;
@@ -66,119 +67,116 @@ __global__ __launch_bounds__(256) void attn_kernel(const AttnArgs a) {
     const int b = blockIdx.z;
     const int64_t u = (int64_t)b * a.Hkv + h;
     const int hq0 = h * a.G + ht * HT;
-#define TA(i) HATA_TRACE_AT(i, MODE == ROWS_SELECT && u == 0 && ht == 0 && split == 0)
-#define TL(i) HATA_TRACE_AT(i, MODE == ROWS_SELECT && u == 0 && ht == 0)
-    TA(20);
-    int count;
-    if (MODE == ROWS_DENSE) count = clampi(a.count_src[b], 0, a.L_cap);
-    else if (MODE == ROWS_IDX) count = clampi(a.count_src[b], 0, a.k_max);
-    else count = clampi(a.unit_info[u * 2 + 1], 0, a.k_max);
-    const int row_begin = split * a.rows_per_wg;
     uint16_t* outp = a.out + ((int64_t)b * a.Hq + hq0) * HATA_D;
     float* outp32 = a.out_f32 ? a.out_f32 + ((int64_t)b * a.Hq + hq0) * HATA_D : nullptr;
-    if (MODE == ROWS_SELECT && ht == 0) {
-        // slots of the index list past the selected count hold -1
-        const int p0 = max(count, row_begin), p1 = min(row_begin + a.rows_per_wg, a.k_max);
-        for (int p = p0 + tid; p < p1; p += 256) a.idx_out[u * a.k_max + p] = -1;
-    }
-    if (row_begin >= count) {
-        if (count == 0 && split == 0) {  // no row at all: the output is zero
-            for (int i = tid; i < HT * HATA_D; i += 256) {
-                outp[i] = 0;
-                if (outp32) outp32[i] = 0.f;
-            }
-        }
-        return;
-    }
-    const int row_end = min(row_begin + a.rows_per_wg, count);
     const uint16_t* Kb = a.K + b * a.sb + h * a.sh;
     const uint16_t* Vb = a.V + b * a.sb + h * a.sh;
-    const int32_t* ip = (MODE == ROWS_IDX) ? a.idx_in + u * a.k_max : nullptr;
     // query fragments first: nothing below depends on them until the rows are known
     uint32_t qr[MFMA ? 1 : HT][4];
     uint4 qb[4];
     if constexpr (MFMA) attn_load_q_mfma<HT>(a.q + ((int64_t)b * a.Hq + hq0) * HATA_D, qb);
     else attn_load_q<HT>(a.q + ((int64_t)b * a.Hq + hq0) * HATA_D, qr);
-
-    if constexpr (MODE == ROWS_SELECT) {
-        // ordered compaction of the chunks that hold positions [row_begin, row_end)
-        const int L = clampi(a.seq_len[b], 0, a.L_cap);
-        const int nc = (L + a.chunk - 1) / a.chunk;
-        const int T = a.unit_info[u * 2 + 0];
-        const int32_t* ci = a.chunk_info + u * (a.n_chunks + 1) * 2;
-        TA(21);
-        if (tid == 0) { s_clo = nc; s_chi = -1; }
-        __syncthreads();
-        for (int c = tid; c < nc; c += 256) {
-            const int o0 = ci[2 * c], o1 = ci[2 * c + 2];
-            if (o0 < row_end && o1 > row_begin) { atomicMin(&s_clo, c); atomicMax(&s_chi, c); }
+    auto zero_output = [&]() {
+        for (int i = tid; i < HT * HATA_D; i += 256) {
+            outp[i] = 0;
+            if (outp32) outp32[i] = 0.f;
         }
-        __syncthreads();
-        const int c_lo = s_clo, c_hi = s_chi;
-        TA(22);
-        const uint16_t* sp = a.scores + u * a.L_cap;
-        int32_t* io = a.idx_out + u * a.k_max;
-        for (int c = c_lo; c <= c_hi; ++c) {
-            const int off = ci[2 * c], take = ci[2 * c + 1];
-            if (ci[2 * c + 2] == off) continue;
-            const int base = c * a.chunk;
-            const int end = min(base + a.chunk, L);
-            compact_chunk_any(a.chunk / 256, sp, base, end, T, off, take, scan4,
-                              [&](int pos, int n) {
-                                  if (pos >= row_begin && pos < row_end) {
-                                      s_rows[pos - row_begin] = n;
-                                      if (ht == 0) io[pos] = n;
-                                  }
-                              });
-        }
-        __syncthreads();
-    }
-    TA(23);
-    auto row_of = [&](int row) {
-        if (MODE == ROWS_DENSE) return row;
-        if (MODE == ROWS_IDX) return (int)ip[row];
-        return s_rows[row - row_begin];
     };
-    if constexpr (MFMA)
-        attn_rows_mfma<HT, (MODE == ROWS_DENSE ? 2 : 1), false>(qb, Kb, Vb, a.sn, a.L_cap, row_begin, row_end,
-                                                         a.scale_log2, row_of, S, s_vt);
-    else
-        attn_rows<HT, 4>(qr, Kb, Vb, a.sn, a.L_cap, row_begin, row_end, a.scale_log2, row_of, S);
-    TA(24);
-    const int ns = (count + a.rows_per_wg - 1) / a.rows_per_wg;  // workgroups that contribute
+    int ns;  // workgroups that contribute
+    auto attend = [&](int row_begin, int row_end, auto row_of) {
+        if constexpr (MFMA)
+            attn_rows_mfma<HT, (MODE == ROWS_DENSE ? 2 : 1), false>(qb, Kb, Vb, a.sn, a.L_cap, row_begin, row_end,
+                                                             a.scale_log2, row_of, S, s_vt);
+        else
+            attn_rows<HT, 4>(qr, Kb, Vb, a.sn, a.L_cap, row_begin, row_end, a.scale_log2, row_of, S);
+    };
+    if constexpr (MODE == ROWS_SELECT) {
+        const int L = clampi(a.seq_len[b], 0, a.L_cap);
+        const int T = a.unit_info[u * 2 + 0], keff = clampi(a.unit_info[u * 2 + 1], 0, a.k_max);
+        const int per = a.chunks_per_split, c0 = split * per;
+        const int32_t* ci = a.chunk_info + (u * (a.n_chunks + 1) + c0) * 2;
+        const int nc = (L + a.chunk - 1) / a.chunk;  // (entry nc closes the list)
+        const int off = ci[0];
+        int take = ci[1];  // ties are granted in cache order, so those of consecutive chunks add up
+        for (int i = 1; i < min(per, nc - c0); ++i) take += ci[2 * i + 1];
+        const int next = ci[2 * clampi(nc - c0, 0, per)];
+        int32_t* io = a.idx_out + u * a.k_max;
+        const int span = per * a.chunk, base = split * span, n_keys = min(span, L - base);
+        if (split == 0) {
+            if (ht == 0)  // slots of the index list past the selected count hold -1
+                for (int p = keff + tid; p < a.k_max; p += 256) io[p] = -1;
+            if (L == 0) zero_output();
+        }
+        if (n_keys <= 0) return;
+        const uint16_t* sp = a.scores + u * a.L_cap + base;
+        const bool whole = (reinterpret_cast<uintptr_t>(sp) & 15) == 0;
+        for (int i = tid * 8; i < n_keys; i += 256 * 8) {
+            if (whole && i + 8 <= n_keys) {
+                *reinterpret_cast<uint4*>(&s_sc[i]) = *reinterpret_cast<const uint4*>(sp + i);
+            } else {
+                for (int e = i; e < min(i + 8, n_keys); ++e) s_sc[e] = sp[e];
+            }
+        }
+        __syncthreads();
+        const int cnt = clampi(next - off, 0, min(n_keys, a.k_max - clampi(off, 0, a.k_max)));
+        if (cnt > 0)  // (the same for the whole workgroup)
+            compact_lds(s_sc, n_keys, span / 256, T, take, cnt, scan4, [&](int r, int n) {
+                s_sc[r] = (uint16_t)n;
+                if (ht == 0) io[off + r] = base + n;
+            });
+        __syncthreads();
+        attend(0, cnt, [&](int row) { return base + (int)s_sc[row]; });
+        ns = (L + span - 1) / span;
+    } else {
+        const int count = clampi(a.count_src[b], 0, MODE == ROWS_DENSE ? a.L_cap : a.k_max);
+        const int row_begin = split * a.rows_per_wg;
+        if (row_begin >= count) {
+            if (count == 0 && split == 0) zero_output();  // no row at all
+            return;
+        }
+        const int row_end = min(row_begin + a.rows_per_wg, count);
+        const int32_t* ip = (MODE == ROWS_IDX) ? a.idx_in + u * a.k_max : nullptr;
+        attend(row_begin, row_end, [&](int row) { return MODE == ROWS_DENSE ? row : (int)ip[row]; });
+        ns = (count + a.rows_per_wg - 1) / a.rows_per_wg;
+    }
     const int64_t head_stride = (int64_t)a.n_splits * HATA_PSTRIDE;
     float* part0 = a.partials + ((int64_t)b * a.Hq + hq0) * head_stride;
     attn_emit<HT>(S, ns == 1, outp, outp32, part0 + (int64_t)split * HATA_PSTRIDE, head_stride);
     if (ns == 1) return;
     // count the finished slices; the last workgroup merges them (partials are written with
     // write-through stores and read back with device-coherent loads)
-    TA(25);
     wait_stores();
     __syncthreads();
     if (tid == 0) {
-        uint32_t* cnt = a.counter + u * tiles + ht;
+        uint32_t* cnt = a.counter + (u * tiles + ht) * a.counter_stride;
         const uint32_t done = atomicAdd(cnt, 1u);
         const int last = (done == (uint32_t)(ns - 1));
         if (last) *cnt = 0;
         s_last = last;
     }
     __syncthreads();
-    TA(27);
     if (!s_last) return;
-    TL(30);
     attn_merge<HT>(S, part0, head_stride, ns, outp, outp32);
-    TL(31);
-#undef TA
-#undef TL
 }
 
 template <int HT>
 static void launch_mode(int mode, const AttnArgs& a, dim3 grid, hipStream_t s) {
+    const size_t lds = mode == ROWS_SELECT ? (size_t)a.chunk * a.chunks_per_split * 2 + 32 : 0;
     switch (mode) {
         case ROWS_DENSE: hipLaunchKernelGGL((attn_kernel<HT, ROWS_DENSE>), grid, dim3(256), 0, s, a); break;
-        case ROWS_SELECT: hipLaunchKernelGGL((attn_kernel<HT, ROWS_SELECT>), grid, dim3(256), 0, s, a); break;
+        case ROWS_SELECT: hipLaunchKernelGGL((attn_kernel<HT, ROWS_SELECT>), grid, dim3(256), lds, s, a); break;
         default: hipLaunchKernelGGL((attn_kernel<HT, ROWS_IDX>), grid, dim3(256), 0, s, a); break;
     }
+}
+
+// (more than 64 KB of dynamic LDS has to be asked for: 32768 keys per split, caches above 4M rows)
+hipError_t prepare_attention(const hata_ctx* c) {
+    const void* fn = c->HT == 8   ? (const void*)attn_kernel<8, ROWS_SELECT>
+                     : c->HT == 5 ? (const void*)attn_kernel<5, ROWS_SELECT>
+                     : c->HT == 4 ? (const void*)attn_kernel<4, ROWS_SELECT>
+                     : c->HT == 2 ? (const void*)attn_kernel<2, ROWS_SELECT>
+                                  : (const void*)attn_kernel<1, ROWS_SELECT>;
+    return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 32768 * 2 + 32);
 }
 
 // mode 0: rows from idx (count from k); 1: dense (count from seq_len); 2: select on the fly
@@ -193,12 +191,20 @@ hipError_t launch_attention(const hata_ctx* c, int mode, const void* q, const vo
     a.idx_in = idx; a.idx_out = idx; a.count_src = count_src;
     a.scores = c->scores; a.seq_len = seq_len; a.chunk_info = c->chunk_info;
     a.unit_info = c->unit_info; a.chunk = c->chunk; a.n_chunks = c->n_chunks;
-    a.partials = c->partials; a.counter = c->attn_counter;
+    // splits of a selected step: single chunks, paired up while at least 16 splits and 256 workgroups remain (a
+    // long cache's many small slices cost more in the merge than they gain; 131072 keys, 8 units, k = 512, 64 / 32 /
+    // 16 splits: 29.1 / 25.0 / 26.2 us a step) and to at most 256 splits (n_chunks <= 1024, chunk <= 8192)
+    a.chunks_per_split = 1;
+    const auto splits = [&](int per) { return (c->n_chunks + per - 1) / per; };
+    while (splits(a.chunks_per_split) > 256 ||
+           (a.chunks_per_split * c->chunk < 32768 && splits(2 * a.chunks_per_split) >= 16 &&
+            (int64_t)splits(2 * a.chunks_per_split) * f.Hkv * (c->G / c->HT) * B >= 256))
+        a.chunks_per_split *= 2;
+    a.partials = c->partials; a.counter = c->attn_counter; a.counter_stride = c->attn_counter_stride;
     a.out = (uint16_t*)out; a.out_f32 = out_f32;
     a.Hq = f.Hq; a.Hkv = f.Hkv; a.G = c->G; a.L_cap = f.L_cap; a.k_max = f.k_max;
-    const bool dense = (mode == ROWS_DENSE);
-    a.rows_per_wg = dense ? c->dense_rows : c->sparse_rows;
-    a.n_splits = dense ? c->dense_splits : c->sparse_splits;
+    a.rows_per_wg = mode == ROWS_DENSE ? c->dense_rows : c->sparse_rows;
+    a.n_splits = mode == ROWS_DENSE ? c->dense_splits : mode == ROWS_SELECT ? splits(a.chunks_per_split) : c->sparse_splits;
     a.sb = f.kv_stride_b; a.sh = f.kv_stride_h; a.sn = f.kv_stride_n;
     a.scale_log2 = sm_scale * 1.4426950408889634f;
     switch (c->HT) {

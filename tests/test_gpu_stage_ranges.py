@@ -57,3 +57,29 @@ def test_selection(L_cap, kind):
         ref = O.topk_batch(s, seq, k, k_max)
         assert np.array_equal(H.to_host(idx), ref)
     ctx.close()
+
+
+@pytest.mark.parametrize("L,k_max,chunk", [(1, 1, 0), (1024, 200, 1024), (1025, 1025, 1024), (20011, 700, 1024),
+                                           (40000, 512, 1024), (40000, 3000, 8192)])
+@pytest.mark.parametrize("heads", [(5, 1), (2, 2), (8, 1)])
+def test_chunk_owned_attention(L, k_max, chunk, heads):
+    Hq, Hkv = heads
+    B = 2
+    w = synth.Workload("chunks", B, Hq, Hkv, 128, 64, (L, max(1, L // 3)), (k_max, max(1, k_max // 2)), k_max=k_max)
+    print(f"[stages] attention L={L} k={k_max} chunk={chunk} heads={heads}", flush=True)
+    c = H.Case(w, shared_device=True, chunk=chunk)
+    q = c.inp.q()
+    for clustered in (False, True):
+        codes = c.codes_ref.copy()
+        if clustered:  # half of the budget's rows in one run are as near as can be: one chunk or two hold them all
+            qc, _ = O.encode_query_batch(q, c.inp.W_H)
+            codes[:, :, L // 2: L // 2 + k_max // 2] = qc.reshape(B, Hkv, Hq // Hkv, -1)[:, :, :1]
+        cd = H.to_dev(codes.copy())
+        out, out32 = c.empty((B, Hq, 128), c.torch.int16), c.empty((B, Hq, 128), c.torch.float32)
+        c.ctx.hata_decode_step(H.to_dev(q), c.K, c.V, c.W_H, cd, c.seq_len, c.k, B, True, c.scale, out, out32)
+        c.sync()
+        ref = O.decode_step(q, c.inp.K, c.inp.V, c.inp.W_H, codes, c.inp.seq_len, c.inp.k, k_max, c.scale, append=True)
+        assert np.array_equal(H.to_host(cd, np.uint32), codes)
+        assert np.array_equal(H.to_host(c.ctx.hata_step_buffers()[2]), ref["idx"])
+        H.check_attention(H.to_host(out32), H.to_host(out, np.uint16), ref["out"], "step")
+    c.ctx.close()
