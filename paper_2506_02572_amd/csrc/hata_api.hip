@@ -40,7 +40,7 @@ constexpr int kMaxDevices = 64;
 inline size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 struct Plan {
-    int G, Wd, NB, NBP, chunk, n_chunks, coop_chunk, HT, sparse_rows, sparse_splits, dense_rows, dense_splits;
+    int G, Wd, NB, NBP, chunk, n_chunks, coop_chunk, HT, sparse_rows, sparse_splits;
     size_t off_qcodes, off_scores, off_idx, off_hist, off_cinfo, off_uinfo, off_ucnt, off_acnt, off_uflag, off_qrec, off_err, off_uhist, off_partials, off_wplanes, total;
 };
 
@@ -112,15 +112,7 @@ int make_plan(const hata_config* f, const hata_tuning* t, Plan* p) {
     p->sparse_rows = rows;
     p->sparse_splits = (f->k_max + rows - 1) / rows;
     if (p->sparse_splits > 256) return HATA_EUNSUPPORTED;  // budget above 65536 rows
-    int drows = 4096;
-    // (measured: with few units, 512 workgroups -- more slices make the last workgroup's merge the
-    // long pole, 39 -> 53 us at B = 1, L = 32K; with 32 units and more, 1024: 240 -> 209 us at B = 4, G = 8, L = 64K)
-    const int64_t dense_wgs = attn_units >= 32 ? 1024 : 512;
-    while (drows > 512 && attn_units * ((f->L_cap + drows - 1) / drows) < dense_wgs) drows >>= 1;
-    while ((f->L_cap + drows - 1) / drows > 256) drows <<= 1;  // the merge handles <= 256 slices
-    p->dense_rows = drows;
-    p->dense_splits = (f->L_cap + drows - 1) / drows;
-    int max_splits = p->sparse_splits > p->dense_splits ? p->sparse_splits : p->dense_splits;
+    int max_splits = p->sparse_splits;
     if (p->n_chunks > max_splits) max_splits = p->n_chunks;  // the cooperative step: one slice per chunk
 
     size_t o = 0;
@@ -137,7 +129,10 @@ int make_plan(const hata_config* f, const hata_tuning* t, Plan* p) {
     p->off_qrec = o;     o = align_up(o + (size_t)f->B_max * f->Hq * p->Wd * p->n_chunks * 8);
     p->off_err = o;      o = align_up(o + 4);
     p->off_uhist = o;    o = align_up(o + (size_t)units * p->NB * 4);
-    p->off_partials = o; o = align_up(o + (size_t)f->B_max * f->Hq * max_splits * (128 + 2) * 4);
+    size_t n_partials = (size_t)f->B_max * f->Hq * max_splits;
+    const size_t dense_partials = (size_t)256 * HATA_DENSE_ROUNDS * G;  // a workgroup has one per head of its group
+    if (n_partials < dense_partials) n_partials = dense_partials;
+    p->off_partials = o; o = align_up(o + n_partials * (128 + 2) * 4);
     p->off_wplanes = o;  o = align_up(o + (size_t)f->Hkv * 2 * 128 * f->r * 2);  // two fp16 planes
     p->total = o;
     return HATA_OK;
@@ -241,7 +236,6 @@ int hata_create_tuned(hata_ctx** ctx_out, const hata_config* cfg, const hata_tun
     c->G = p.G; c->Wd = p.Wd; c->NB = p.NB; c->NBP = p.NBP;
     c->chunk = p.chunk; c->n_chunks = p.n_chunks; c->HT = p.HT;
     c->sparse_rows = p.sparse_rows; c->sparse_splits = p.sparse_splits;
-    c->dense_rows = p.dense_rows; c->dense_splits = p.dense_splits;
     char* w = (char*)workspace;
     c->qcodes = (uint32_t*)(w + p.off_qcodes);
     c->scores = (uint16_t*)(w + p.off_scores);
@@ -267,7 +261,7 @@ int hata_create_tuned(hata_ctx** ctx_out, const hata_config* cfg, const hata_tun
         delete c;
         return HATA_EHIP;
     }
-    if (hata::prepare_topk(c) != hipSuccess || hata::prepare_attention(c) != hipSuccess) {
+    if (hata::prepare_topk(c) != hipSuccess || hata::prepare_attention(c) != hipSuccess || hata::prepare_dense() != hipSuccess) {
         delete c;
         return HATA_EHIP;
     }
@@ -439,8 +433,7 @@ int hata_dense_decode(hata_ctx* ctx, const void* q, const void* K, const void* V
     if (rc != HATA_OK) return rc;
     if (!q || !K || !V || !seq_len || !out) return HATA_EINVAL;
     if (!aligned(q, 16) || !aligned(K, 16) || !aligned(V, 16) || !aligned(out, 2)) return HATA_EINVAL;
-    return hip_rc(hata::launch_attention(ctx, 1, q, K, V, nullptr, seq_len, seq_len, B, sm_scale,
-                                         out, out_f32, (hipStream_t)stream));
+    return hip_rc(hata::launch_dense(ctx, q, K, V, seq_len, B, sm_scale, out, out_f32, (hipStream_t)stream));
 }
 
 int hata_sparse_decode_static(const hata_config* cfg, const void* q, const void* K, const void* V,
@@ -475,7 +468,6 @@ int hata_sparse_decode_static(const hata_config* cfg, const void* q, const void*
     c.cfg = *cfg;
     c.G = p.G; c.Wd = p.Wd; c.NB = p.NB; c.NBP = p.NBP; c.chunk = p.chunk; c.n_chunks = p.n_chunks; c.HT = p.HT;
     c.sparse_rows = p.sparse_rows; c.sparse_splits = p.sparse_splits;
-    c.dense_rows = p.dense_rows; c.dense_splits = p.dense_splits;
     c.attn_counter = (uint32_t*)base;
     c.attn_counter_stride = 1;
     c.partials = (float*)((char*)base + counter_bytes);

@@ -2,9 +2,8 @@
 // the gather fused into the attention kernel; Eq. 2 third line, scale of Eq. 1), and the
 // dense variant over the whole cache (Eq. 1) that serves as the comparison baseline.
 //
-// One kernel template, three row sources:
+// One kernel template, two row sources:
 //   ROWS_IDX     rows come from an index list in memory            (hata_sparse_decode)
-//   ROWS_DENSE   rows 0 .. seq_len-1                               (hata_dense_decode)
 //   ROWS_SELECT  the rows of one chunk of the cache (a few, of a very long one) that the unit
 //                threshold selects: ordered compaction of the chunk's stored scores; its part of
 //                the index list is written as a by-product  (hata_decode_step, three-launch form)
@@ -22,7 +21,7 @@
 
 namespace hata {
 
-enum { ROWS_IDX = 0, ROWS_DENSE = 1, ROWS_SELECT = 2 };
+enum { ROWS_IDX = 0, ROWS_SELECT = 2 };
 
 struct AttnArgs {
     const uint16_t* q;
@@ -85,8 +84,7 @@ __global__ __launch_bounds__(256) void attn_kernel(const AttnArgs a) {
     int ns;  // workgroups that contribute
     auto attend = [&](int row_begin, int row_end, auto row_of) {
         if constexpr (MFMA)
-            attn_rows_mfma<HT, (MODE == ROWS_DENSE ? 2 : 1), false>(qb, Kb, Vb, a.sn, a.L_cap, row_begin, row_end,
-                                                             a.scale_log2, row_of, S, s_vt);
+            attn_rows_mfma<HT>(qb, Kb, Vb, a.sn, a.L_cap, row_begin, row_end, a.scale_log2, row_of, S, s_vt);
         else
             attn_rows<HT, 4>(qr, Kb, Vb, a.sn, a.L_cap, row_begin, row_end, a.scale_log2, row_of, S);
     };
@@ -128,15 +126,15 @@ __global__ __launch_bounds__(256) void attn_kernel(const AttnArgs a) {
         attend(0, cnt, [&](int row) { return base + (int)s_sc[row]; });
         ns = (L + span - 1) / span;
     } else {
-        const int count = clampi(a.count_src[b], 0, MODE == ROWS_DENSE ? a.L_cap : a.k_max);
+        const int count = clampi(a.count_src[b], 0, a.k_max);
         const int row_begin = split * a.rows_per_wg;
         if (row_begin >= count) {
             if (count == 0 && split == 0) zero_output();  // no row at all
             return;
         }
         const int row_end = min(row_begin + a.rows_per_wg, count);
-        const int32_t* ip = (MODE == ROWS_IDX) ? a.idx_in + u * a.k_max : nullptr;
-        attend(row_begin, row_end, [&](int row) { return MODE == ROWS_DENSE ? row : (int)ip[row]; });
+        const int32_t* ip = a.idx_in + u * a.k_max;
+        attend(row_begin, row_end, [&](int row) { return (int)ip[row]; });
         ns = (count + a.rows_per_wg - 1) / a.rows_per_wg;
     }
     const int64_t head_stride = (int64_t)a.n_splits * HATA_PSTRIDE;
@@ -163,7 +161,6 @@ template <int HT>
 static void launch_mode(int mode, const AttnArgs& a, dim3 grid, hipStream_t s) {
     const size_t lds = mode == ROWS_SELECT ? (size_t)a.chunk * a.chunks_per_split * 2 + 32 : 0;
     switch (mode) {
-        case ROWS_DENSE: hipLaunchKernelGGL((attn_kernel<HT, ROWS_DENSE>), grid, dim3(256), 0, s, a); break;
         case ROWS_SELECT: hipLaunchKernelGGL((attn_kernel<HT, ROWS_SELECT>), grid, dim3(256), lds, s, a); break;
         default: hipLaunchKernelGGL((attn_kernel<HT, ROWS_IDX>), grid, dim3(256), 0, s, a); break;
     }
@@ -179,7 +176,7 @@ hipError_t prepare_attention(const hata_ctx* c) {
     return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 32768 * 2 + 32);
 }
 
-// mode 0: rows from idx (count from k); 1: dense (count from seq_len); 2: select on the fly
+// mode 0: rows from idx (count from k); 2: select on the fly
 // from the workspace's scores / thresholds (idx is written)
 hipError_t launch_attention(const hata_ctx* c, int mode, const void* q, const void* K,
                             const void* V, int32_t* idx, const int32_t* count_src,
@@ -203,8 +200,8 @@ hipError_t launch_attention(const hata_ctx* c, int mode, const void* q, const vo
     a.partials = c->partials; a.counter = c->attn_counter; a.counter_stride = c->attn_counter_stride;
     a.out = (uint16_t*)out; a.out_f32 = out_f32;
     a.Hq = f.Hq; a.Hkv = f.Hkv; a.G = c->G; a.L_cap = f.L_cap; a.k_max = f.k_max;
-    a.rows_per_wg = mode == ROWS_DENSE ? c->dense_rows : c->sparse_rows;
-    a.n_splits = mode == ROWS_DENSE ? c->dense_splits : mode == ROWS_SELECT ? splits(a.chunks_per_split) : c->sparse_splits;
+    a.rows_per_wg = c->sparse_rows;
+    a.n_splits = mode == ROWS_SELECT ? splits(a.chunks_per_split) : c->sparse_splits;
     a.sb = f.kv_stride_b; a.sh = f.kv_stride_h; a.sn = f.kv_stride_n;
     a.scale_log2 = sm_scale * 1.4426950408889634f;
     switch (c->HT) {

@@ -152,19 +152,22 @@ __device__ __forceinline__ void attn_rows(
 // heads padded to 16:
 //   S[row][head]   = K_tile[16 rows][128] . Q^T[128][16 heads]     4 x v_mfma_f32_16x16x32_bf16
 //   O^T[ch][head] += V_tile^T[16 ch][16 rows] . P[16 rows][16 heads]   per 16-channel tile, P split
-//                    into two bf16 terms (hi + lo) so its rounding stays below 2^-16
+//                    into two bf16 terms (hi + lo) so its rounding stays below 2^-16; the two terms are
+//                    the two halves of one v_mfma_f32_16x16x32_bf16, whose V half is repeated
 // A wave owns a tile of 16 rows.  Lane = (n = lane % 16, kg = lane / 16): for the loads n is the row
 // and kg selects 8 of every 32 channels (one 128-bit load per 32 channels, straight into the MFMA
 // operand layout); in S and in the accumulators n is the HEAD, so the online-softmax state (max,
 // sum) is one scalar per lane, and the 4 rows a lane holds of S (rows 4 kg .. 4 kg + 3) are exactly
 // the k-slice of P the second contraction wants from it.  Only V needs a transpose (its operand
-// wants 4 rows of one channel per lane): the tile goes through a wave-private LDS buffer, rows
-// padded to 264 B so that the 2-byte transposed reads are bank-conflict free.
+// wants 4 rows of one channel per lane): the tile goes through a wave-private LDS buffer and is read
+// with the transposing LDS read (groups of 16 lanes read 4 rows x 16 channels and get channel
+// lane % 16 of the four rows), rows padded to 288 B so that neither side has bank conflicts.  Reading
+// 2 bytes at a time and packing took as many instructions as everything else.
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(4))) short s16x4_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 
-#define HATA_VT_PITCH 132                    // uint16 per staged V row (264 B)
+#define HATA_VT_PITCH 144                    // uint16 per staged V row (288 B)
 #define HATA_VT_WAVE (16 * HATA_VT_PITCH)    // uint16 per wave
 #define HATA_VT_ELEMS (4 * HATA_VT_WAVE)     // uint16 of LDS a workgroup needs for attn_rows_mfma
 
@@ -179,11 +182,9 @@ __device__ __forceinline__ void attn_load_q_mfma(const uint16_t* __restrict__ q0
     }
 }
 
-// Same contract as attn_rows (state of the four waves in S after a workgroup barrier).  IT: 16-row
-// tiles per wave whose loads are in flight together; PF: software pipeline -- the loads of the
-// next IT tiles are issued before the current ones are consumed (measured on the dense baseline:
-// no faster than IT = 2 without it, so no caller turns it on).  vt: HATA_VT_ELEMS uint16 of LDS.
-template <int HT, int IT, bool PF, typename RowOf>
+// Same contract as attn_rows (state of the four waves in S after a workgroup barrier).
+// vt: HATA_VT_ELEMS uint16 of LDS.
+template <int HT, typename RowOf>
 __device__ __forceinline__ void attn_rows_mfma(
     const uint4 (&qb)[4], const uint16_t* __restrict__ Kb, const uint16_t* __restrict__ Vb, int64_t sn,
     int L_cap, int row_begin, int row_end, float scale_log2, RowOf row_of, AttnLds<HT>& S,
@@ -197,105 +198,79 @@ __device__ __forceinline__ void attn_rows_mfma(
 #pragma unroll
     for (int c = 0; c < 8; ++c) acc[c] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
 
-    struct Stage { uint4 kr[IT][4], vr[IT][4]; bool ok[IT]; };
-    // loads of the IT tiles of this wave in the 64 * IT rows from tile0 (lane: row n, channels 8 kg + 32 s)
-    auto load_stage = [&](int tile0, Stage& st) {
+    struct Tile { uint4 kr[4], vr[4]; };  // lane: row n, channels 8 kg + 32 s
+    auto load_row = [&](int64_t idx, Tile& st) {
+        const int64_t o = idx * sn + 8 * kg;
 #pragma unroll
-        for (int it = 0; it < IT; ++it) {
-            const int row = tile0 + (it * 4 + wave) * 16 + n;
-            st.ok[it] = row < row_end;
-            int idx = 0;
-            if (st.ok[it]) idx = row_of(row);
-            st.ok[it] = st.ok[it] && idx >= 0 && idx < L_cap;
-#pragma unroll
-            for (int s = 0; s < 4; ++s) { st.kr[it][s] = make_uint4(0, 0, 0, 0); st.vr[it][s] = make_uint4(0, 0, 0, 0); }
-            if (st.ok[it]) {
-                const int64_t o = (int64_t)idx * sn + 8 * kg;
-#pragma unroll
-                for (int s = 0; s < 4; ++s) {
-                    st.kr[it][s] = *reinterpret_cast<const uint4*>(Kb + o + 32 * s);
-                    st.vr[it][s] = *reinterpret_cast<const uint4*>(Vb + o + 32 * s);
-                }
-            }
+        for (int s = 0; s < 4; ++s) {
+            st.kr[s] = *reinterpret_cast<const uint4*>(Kb + o + 32 * s);
+            st.vr[s] = *reinterpret_cast<const uint4*>(Vb + o + 32 * s);
         }
     };
-    auto compute_stage = [&](int tile0, const Stage& st) {
+    // okmask: bits 0..15 tell which rows of the tile count; V of the others must be finite
+    auto compute = [&](uint32_t okmask, const Tile& st) {
+        f32x4_t sacc = (f32x4_t){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int it = 0; it < IT; ++it) {
-            if (tile0 + (it * 4 + wave) * 16 >= row_end) break;  // wave-uniform: no row in this tile
-            const unsigned long long okmask = __builtin_amdgcn_ballot_w64(st.ok[it]);  // bits 0..15: the tile's rows
-            f32x4_t sacc = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+        for (int s = 0; s < 4; ++s)
+            sacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, st.kr[s]),
+                                                           __builtin_bit_cast(bf16x8_t, qb[s]), sacc, 0, 0, 0);
+        // stage V (row n, channels 32 s + 8 kg) for the transposed reads below
 #pragma unroll
-            for (int s = 0; s < 4; ++s)
-                sacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, st.kr[it][s]),
-                                                               __builtin_bit_cast(bf16x8_t, qb[s]), sacc, 0, 0, 0);
-            // stage V (row n, channels 32 s + 8 kg) for the transposed reads below
+        for (int s = 0; s < 4; ++s) *reinterpret_cast<uint4*>(vt + n * HATA_VT_PITCH + 32 * s + 8 * kg) = st.vr[s];
+        // online softmax of head n over the rows 4 kg .. 4 kg + 3 this lane holds
+        float sv[4], m_tile = HATA_NEG_INF;
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                uint2* d = reinterpret_cast<uint2*>(vt + n * HATA_VT_PITCH + 32 * s + 8 * kg);
-                d[0] = make_uint2(st.vr[it][s].x, st.vr[it][s].y);
-                d[1] = make_uint2(st.vr[it][s].z, st.vr[it][s].w);
-            }
-            // online softmax of head n over the rows 4 kg .. 4 kg + 3 this lane holds
-            float sv[4], m_tile = HATA_NEG_INF;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const bool valid = (okmask >> (4 * kg + r)) & 1ull;
-                sv[r] = valid ? sacc[r] * scale_log2 : HATA_NEG_INF;
-                m_tile = fmaxf(m_tile, sv[r]);
-            }
-            m_tile = rows_max4(m_tile);
-            const float m_new = fmaxf(m_run, m_tile);
-            const float alpha = (m_new == HATA_NEG_INF) ? 1.f : fast_exp2(m_run - m_new);
-            float p[4], psum = 0.f;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                p[r] = (sv[r] == HATA_NEG_INF) ? 0.f : fast_exp2(sv[r] - m_new);
-                psum += p[r];
-            }
-            l_run = fmaf(l_run, alpha, psum);
-            m_run = m_new;
-            if (__builtin_amdgcn_ballot_w64(alpha != 1.f) != 0ull) {
-#pragma unroll
-                for (int c = 0; c < 8; ++c) acc[c] *= alpha;
-            }
-            // P as two bf16 terms: hi = p truncated to bf16, lo = (p - hi) truncated to bf16
-            uint32_t hb[4], lb[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                hb[r] = __float_as_uint(p[r]) & 0xffff0000u;
-                lb[r] = __float_as_uint(p[r] - __uint_as_float(hb[r]));
-            }
-            const uint2 ph = make_uint2((hb[0] >> 16) | hb[1], (hb[2] >> 16) | hb[3]);
-            const uint2 pl = make_uint2((lb[0] >> 16) | (lb[1] & 0xffff0000u), (lb[2] >> 16) | (lb[3] & 0xffff0000u));
-            const s16x4_t phv = __builtin_bit_cast(s16x4_t, ph), plv = __builtin_bit_cast(s16x4_t, pl);
-            __builtin_amdgcn_wave_barrier();  // (LDS serves a wave's accesses in order: the staged tile is visible)
-#pragma unroll
-            for (int c = 0; c < 8; ++c) {
-                const uint16_t* src = vt + (4 * kg) * HATA_VT_PITCH + 16 * c + n;
-                const uint32_t v0 = src[0], v1 = src[HATA_VT_PITCH], v2 = src[2 * HATA_VT_PITCH], v3 = src[3 * HATA_VT_PITCH];
-                const s16x4_t av = __builtin_bit_cast(s16x4_t, make_uint2(v0 | (v1 << 16), v2 | (v3 << 16)));
-                acc[c] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, phv, acc[c], 0, 0, 0);
-                acc[c] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, plv, acc[c], 0, 0, 0);
-            }
-            __builtin_amdgcn_wave_barrier();
+        for (int r = 0; r < 4; ++r) {
+            const bool valid = (okmask >> (4 * kg + r)) & 1u;
+            sv[r] = valid ? sacc[r] * scale_log2 : HATA_NEG_INF;
+            m_tile = fmaxf(m_tile, sv[r]);
         }
+        m_tile = rows_max4(m_tile);
+        const float m_new = fmaxf(m_run, m_tile);
+        const float alpha = (m_new == HATA_NEG_INF) ? 1.f : fast_exp2(m_run - m_new);
+        float p[4], psum = 0.f;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            p[r] = (sv[r] == HATA_NEG_INF) ? 0.f : fast_exp2(sv[r] - m_new);
+            psum += p[r];
+        }
+        l_run = fmaf(l_run, alpha, psum);
+        m_run = m_new;
+        if (__builtin_amdgcn_ballot_w64(alpha != 1.f) != 0ull) {
+#pragma unroll
+            for (int c = 0; c < 8; ++c) acc[c] *= alpha;
+        }
+        // P as two bf16 terms: hi = p truncated to bf16, lo = (p - hi) truncated to bf16
+        uint32_t hb[4], lb[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            hb[r] = __float_as_uint(p[r]) & 0xffff0000u;
+            lb[r] = __float_as_uint(p[r] - __uint_as_float(hb[r]));
+        }
+        const uint4 pb = make_uint4((hb[0] >> 16) | hb[1], (hb[2] >> 16) | hb[3],
+                                    (lb[0] >> 16) | (lb[1] & 0xffff0000u), (lb[2] >> 16) | (lb[3] & 0xffff0000u));
+        __builtin_amdgcn_wave_barrier();  // (LDS serves a wave's accesses in order: the staged tile is visible)
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            const uint16_t* src = vt + (4 * kg + n / 4) * HATA_VT_PITCH + 16 * c + 4 * (n & 3);
+            const s16x4_t av = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                (__attribute__((address_space(3))) s16x4_t*)const_cast<uint16_t*>(src));
+            const uint2 v = __builtin_bit_cast(uint2, av);
+            acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, make_uint4(v.x, v.y, v.x, v.y)),
+                                                             __builtin_bit_cast(bf16x8_t, pb), acc[c], 0, 0, 0);
+        }
+        __builtin_amdgcn_wave_barrier();
     };
-    if constexpr (PF) {
-        Stage cur, nxt;
-        load_stage(row_begin, cur);
-        for (int tile0 = row_begin; tile0 < row_end; tile0 += 64 * IT) {
-            const bool more = tile0 + 64 * IT < row_end;  // workgroup-uniform
-            if (more) load_stage(tile0 + 64 * IT, nxt);
-            compute_stage(tile0, cur);
-            if (more) cur = nxt;
-        }
-    } else {
-        for (int tile0 = row_begin; tile0 < row_end; tile0 += 64 * IT) {
-            Stage st;
-            load_stage(tile0, st);
-            compute_stage(tile0, st);
-        }
+    for (int tile0 = row_begin + wave * 16; tile0 < row_end; tile0 += 64) {
+        Tile st;
+        bool ok = tile0 + n < row_end;
+        int idx = 0;
+        if (ok) idx = row_of(tile0 + n);
+        ok = ok && idx >= 0 && idx < L_cap;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) { st.kr[s] = make_uint4(0, 0, 0, 0); st.vr[s] = make_uint4(0, 0, 0, 0); }
+        if (ok) load_row(idx, st);
+        compute((uint32_t)__builtin_amdgcn_ballot_w64(ok) & 0xffffu, st);
     }
     // lanes of the 4 row groups hold partial sums of the same head
     l_run = rows_sum4(l_run);

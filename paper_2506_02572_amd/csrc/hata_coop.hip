@@ -858,13 +858,13 @@ void decode_step_coop_kernel(const CoopArgs a) {
     if constexpr (PAGED) {  // rows of the pools (the host has checked that their count fits an int)
         auto row_of = [&](int row) { return (int)cache_row(base + (int)s_sc[row]); };
         const int rows = (a.pv.n_pages * a.Hkv) << a.pv.shift;
-        if constexpr (MFMA) attn_rows_mfma<G, 1, false>(qb, a.K, a.V, HATA_D, rows, 0, cnt, a.scale_log2, row_of, S, U.vt);
+        if constexpr (MFMA) attn_rows_mfma<G>(qb, a.K, a.V, HATA_D, rows, 0, cnt, a.scale_log2, row_of, S, U.vt);
         else attn_rows<G, 4>(qr, a.K, a.V, HATA_D, rows, 0, cnt, a.scale_log2, row_of, S);
     } else {
         const uint16_t* Kb = a.K + b * a.sb + h * a.sh;
         const uint16_t* Vb = a.V + b * a.sb + h * a.sh;
         auto row_of = [&](int row) { return base + (int)s_sc[row]; };
-        if constexpr (MFMA) attn_rows_mfma<G, 1, false>(qb, Kb, Vb, a.sn, a.L_cap, 0, cnt, a.scale_log2, row_of, S, U.vt);
+        if constexpr (MFMA) attn_rows_mfma<G>(qb, Kb, Vb, a.sn, a.L_cap, 0, cnt, a.scale_log2, row_of, S, U.vt);
         else attn_rows<G, 4>(qr, Kb, Vb, a.sn, a.L_cap, 0, cnt, a.scale_log2, row_of, S);
     }
     TC(47);

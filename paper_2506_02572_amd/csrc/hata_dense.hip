@@ -1,0 +1,367 @@
+// Decode attention over the whole cache (Eq. 1 of the paper; the dense layers of Alg. 1 and the baseline that the
+// method is compared with).
+//
+// Bound by the HBM stream: every K and V row is read once for all query heads of its group.
+//   - A workgroup of eight waves owns a run of 16-row tiles; the launch is sized to one workgroup per CU, so that
+//     the tail of the stream and the number of partial results to merge are both small.
+//   - Every wave requests its tiles with direct loads into a wave-private LDS ring (no registers, no barriers: the
+//     only waits in the loop are the ones for a tile's own K and V), whole 256-byte rows per 16 lanes.  The 16-byte
+//     pieces of row r are stored in the order piece ^ swizzle(r), which makes both kinds of reads below free
+//     of bank conflicts.
+//   - The contractions are those of attn_rows_mfma (hata_attn_core.h), heads padded to 16.
+// Measured at B = 1, 8 KV heads, 32768 rows (134 MB), groups of 4 and 8 heads: 25.7 and 29.2 us; four waves per
+// workgroup with loads through registers and 64 partial results per unit took 36.8 and 48.7.  B = 4, 65536 rows,
+// groups of 8 (1.07 GB): 167 us, 6.4 TB/s (209).
+#include <algorithm>
+#include "hata_device.h"
+#include "hata_internal.h"
+#include "hata_attn_core.h"
+
+namespace hata {
+
+// (measured at B = 1, 32768 rows, groups of 4, loads not yet marked non-temporal: 8 waves x 2 tiles 29.0 us; 4 x 4
+// 32.2; 6 x 3 31.3; two workgroups of 4 x 2 per CU 33.4)
+#define DENSE_WAVES 8
+#define DENSE_RING 2           // tiles in flight per wave
+#define DENSE_TILE_BYTES 8192  // 16 rows of K, 16 rows of V
+#define DENSE_BATCH 16         // partial results in flight per thread in the merge
+
+struct DenseArgs {
+    const uint16_t *q, *K, *V;
+    const int32_t* seq_len;
+    float* partials;
+    uint32_t* counter;
+    int counter_stride;
+    uint16_t* out;
+    float* out_f32;
+    int Hq, Hkv, G, L_cap, n_splits;
+    int64_t sb, sh, sn;
+    float scale_log2;
+};
+
+__device__ __forceinline__ int dense_swizzle(int r) { return ((r << 1) | (r >> 3)) & 15; }
+
+template <int N>
+__device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+
+// waits until at most FIRST requests of this tile and all of the next one, if there is one, are outstanding
+template <int FIRST>
+__device__ __forceinline__ void wait_tile(int tiles_after) {
+    static_assert(DENSE_RING == 2, "one more tile in flight");
+    if (tiles_after >= 1) wait_vm<FIRST + 8>();
+    else wait_vm<FIRST>();
+}
+
+// grid = (splits, Hkv, B)
+__global__ __launch_bounds__(DENSE_WAVES * 64) void dense_kernel(const DenseArgs a) {
+    // ring[wave][DENSE_RING][DENSE_TILE_BYTES]; afterwards the waves' states, the merge weights and sums
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    __shared__ float s_m[DENSE_WAVES][16], s_l[DENSE_WAVES][16];
+    __shared__ int s_last;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = lane & 15, kg = lane >> 4;
+    const int split = blockIdx.x, h = blockIdx.y, b = blockIdx.z, G = a.G;
+    const int64_t u = (int64_t)b * a.Hkv + h, hq0 = (int64_t)b * a.Hq + (int64_t)h * G;
+    uint16_t* outp = a.out + hq0 * HATA_D;
+    float* outp32 = a.out_f32 ? a.out_f32 + hq0 * HATA_D : nullptr;
+    const int L = clampi(a.seq_len[b], 0, a.L_cap);
+    uint4 qb[4];
+    {
+        const uint16_t* q0 = a.q + (hq0 + min(n, G - 1)) * HATA_D + 8 * kg;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) qb[s] = *reinterpret_cast<const uint4*>(q0 + 32 * s);
+    }
+    // the unit's tiles in even runs, at least one tile per wave
+    const int tiles = (L + 15) / 16;
+    const int ns = min(a.n_splits, (tiles + DENSE_WAVES - 1) / DENSE_WAVES);
+    if (split >= ns) {
+        if (split == 0) {  // no row at all
+            for (int i = tid; i < G * HATA_D; i += DENSE_WAVES * 64) {
+                outp[i] = 0;
+                if (outp32) outp32[i] = 0.f;
+            }
+        }
+        return;
+    }
+    const int t_begin = (int)((int64_t)tiles * split / ns), t_end = (int)((int64_t)tiles * (split + 1) / ns);
+    const int mine = max(0, (t_end - t_begin - wave + DENSE_WAVES - 1) / DENSE_WAVES);  // tiles t_begin + wave + 8 j
+
+    const uint16_t* Kb = a.K + b * a.sb + h * a.sh;
+    const uint16_t* Vb = a.V + b * a.sb + h * a.sh;
+    char* ring = smem + wave * (DENSE_RING * DENSE_TILE_BYTES);
+    const uint32_t ring_lds = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)ring);
+    // request: lane l of instruction i fetches piece (l % 16) ^ swizzle(row) of row 4 i + l / 16
+    int64_t off[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) off[i] = (4 * i + kg) * a.sn + (n ^ dense_swizzle(4 * i + kg)) * 8;
+    auto request = [&](int j) {
+        const int row0 = (t_begin + wave + DENSE_WAVES * j) * 16;
+        const uint16_t* kt = Kb + row0 * a.sn;
+        const uint16_t* vt = Vb + row0 * a.sn;
+        const uint32_t dst = ring_lds + (uint32_t)(j % DENSE_RING) * DENSE_TILE_BYTES;
+        const int last = L - 1 - row0;  // rows past the end repeat the last one
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            int64_t o = off[i];
+            if (last < 15 && 4 * i + kg > last) o += (int64_t)(last - 4 * i - kg) * a.sn;
+            // (written as instructions: behind the compiler's builtin for it, every LDS read waits for all
+            // requests outstanding.  nt: the rows are read once, and marked so they stream at 6.1 instead of
+            // 5.35 TB/s, 131072 rows)
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt"
+                         ::"s"(dst + i * 1024), "v"(kt + o) : "memory", "m0");
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            int64_t o = off[i];
+            if (last < 15 && 4 * i + kg > last) o += (int64_t)(last - 4 * i - kg) * a.sn;
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt"
+                         ::"s"(dst + 4096 + i * 1024), "v"(vt + o) : "memory", "m0");
+        }
+    };
+    float m_run = HATA_NEG_INF, l_run = 0.f;
+    f32x4_t acc[8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) acc[c] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+    // K operand: row n, piece 4 s + kg; V operand: row 4 kg + n / 4, channels 16 c + 4 (n % 4), piece 2 c + (n % 4) / 2
+    const uint32_t k_at = n * 256 + ((kg ^ dense_swizzle(n)) << 4);
+    const int vr = 4 * kg + n / 4;
+    const uint32_t v_at = 4096 + vr * 256 + ((((n & 3) >> 1) ^ dense_swizzle(vr)) << 4) + (n & 1) * 8;
+    auto compute = [&](int j) {
+        const char* t = ring + (j % DENSE_RING) * DENSE_TILE_BYTES;
+        const int after = mine - 1 - j;
+        const int left = min(L - (t_begin + wave + DENSE_WAVES * j) * 16, 16);
+        wait_tile<4>(after);
+        f32x4_t sacc = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+            sacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(t + (k_at ^ (s << 6)))),
+                __builtin_bit_cast(bf16x8_t, qb[s]), sacc, 0, 0, 0);
+        // online softmax of head n over the rows 4 kg .. 4 kg + 3 this lane holds
+        float sv[4], m_tile = HATA_NEG_INF;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            sv[r] = 4 * kg + r < left ? sacc[r] * a.scale_log2 : HATA_NEG_INF;
+            m_tile = fmaxf(m_tile, sv[r]);
+        }
+        m_tile = rows_max4(m_tile);
+        const float m_new = fmaxf(m_run, m_tile);
+        const float alpha = (m_new == HATA_NEG_INF) ? 1.f : fast_exp2(m_run - m_new);
+        float p[4], psum = 0.f;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            p[r] = (sv[r] == HATA_NEG_INF) ? 0.f : fast_exp2(sv[r] - m_new);
+            psum += p[r];
+        }
+        l_run = fmaf(l_run, alpha, psum);
+        m_run = m_new;
+        if (__builtin_amdgcn_ballot_w64(alpha != 1.f) != 0ull) {
+#pragma unroll
+            for (int c = 0; c < 8; ++c) acc[c] *= alpha;
+        }
+        // P as two bf16 terms: hi = p truncated to bf16, lo = (p - hi) truncated to bf16
+        uint32_t hb[4], lb[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            hb[r] = __float_as_uint(p[r]) & 0xffff0000u;
+            lb[r] = __float_as_uint(p[r] - __uint_as_float(hb[r]));
+        }
+        const uint4 pb = make_uint4((hb[0] >> 16) | hb[1], (hb[2] >> 16) | hb[3],
+                                    (lb[0] >> 16) | (lb[1] & 0xffff0000u), (lb[2] >> 16) | (lb[3] & 0xffff0000u));
+        wait_tile<0>(after);
+        uint2 v[8];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            const s16x4_t av = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                (__attribute__((address_space(3))) s16x4_t*)const_cast<char*>(t + (v_at ^ (c << 5))));
+            v[c] = __builtin_bit_cast(uint2, av);
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // every read of this slot has returned
+        if (left < 16) {  // the copies of the last row past the end: p = 0, and 0 for infinite values
+            const int keep = clampi(left - 4 * kg, 0, 4);  // rows of this lane
+            const uint32_t lo = keep >= 2 ? 0xffffffffu : keep == 1 ? 0xffffu : 0u;
+            const uint32_t hi = keep >= 4 ? 0xffffffffu : keep == 3 ? 0xffffu : 0u;
+#pragma unroll
+            for (int c = 0; c < 8; ++c) { v[c].x &= lo; v[c].y &= hi; }
+        }
+        if (after >= DENSE_RING) request(j + DENSE_RING);
+#pragma unroll
+        for (int c = 0; c < 8; ++c)
+            acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, make_uint4(v[c].x, v[c].y, v[c].x, v[c].y)),
+                                                             __builtin_bit_cast(bf16x8_t, pb), acc[c], 0, 0, 0);
+    };
+    for (int j = 0; j < min(mine, DENSE_RING); ++j) request(j);
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        if (n >= G) qb[s] = make_uint4(0, 0, 0, 0);
+        // (used here, so that the wait for these loads is not in the loop)
+        asm volatile("" : "+v"(qb[s].x), "+v"(qb[s].y), "+v"(qb[s].z), "+v"(qb[s].w));
+    }
+    for (int j = 0; j < mine; ++j) compute(j);
+
+    // ---- the eight states of the workgroup ----
+    __syncthreads();  // the ring is no longer read
+    float* s_acc = reinterpret_cast<float*>(smem);  // [DENSE_WAVES][G][HATA_D + 4]
+    l_run = rows_sum4(l_run);
+    if (n < G) {
+        if (kg == 0) { s_m[wave][n] = m_run; s_l[wave][n] = l_run; }
+#pragma unroll
+        for (int c = 0; c < 8; ++c)  // acc[c][r] = O[head n][channel 16 c + 4 kg + r]
+            *reinterpret_cast<float4*>(&s_acc[(wave * G + n) * (HATA_D + 4) + 16 * c + 4 * kg]) =
+                make_float4(acc[c][0], acc[c][1], acc[c][2], acc[c][3]);
+    }
+    __syncthreads();
+    const int64_t head_stride = (int64_t)a.n_splits * HATA_PSTRIDE;
+    float* part0 = a.partials + hq0 * head_stride;
+    for (int i = tid; i < G * HATA_D; i += DENSE_WAVES * 64) {
+        const int g = i / HATA_D, ch = i % HATA_D;
+        float M = s_m[0][g];
+#pragma unroll
+        for (int w = 1; w < DENSE_WAVES; ++w) M = fmaxf(M, s_m[w][g]);
+        float av = 0.f, l = 0.f;
+#pragma unroll
+        for (int w = 0; w < DENSE_WAVES; ++w) {
+            const float f = M == HATA_NEG_INF ? 0.f : fast_exp2(s_m[w][g] - M);
+            av = fmaf(f, s_acc[(w * G + g) * (HATA_D + 4) + ch], av);
+            l = fmaf(f, s_l[w][g], l);
+        }
+        if (ns == 1) {
+            const float o = l > 0.f ? av / l : 0.f;
+            outp[i] = (uint16_t)f32_to_bf16(o);
+            if (outp32) outp32[i] = o;
+        } else {
+            float* pp = part0 + g * head_stride + split * HATA_PSTRIDE;
+            st_dev(pp + 2 + ch, av);
+            if (ch == 0) { st_dev(pp, M); st_dev(pp + 1, l); }
+        }
+    }
+    if (ns == 1) return;
+    // ---- the last workgroup of the unit merges (partials: write-through stores, device-coherent loads) ----
+    wait_stores();
+    __syncthreads();
+    if (tid == 0) {
+        uint32_t* cnt = a.counter + u * a.counter_stride;
+        const int last = atomicAdd(cnt, 1u) == (uint32_t)(ns - 1);
+        if (last) *cnt = 0;
+        s_last = last;
+    }
+    __syncthreads();
+    if (!s_last) return;
+    // thread: slices part, part + parts, ... of one head's channel pair; the first batch of loads before the weights
+    float* s_w = reinterpret_cast<float*>(smem);                    // [G][ns] normalised weights
+    float2* s_sum = reinterpret_cast<float2*>(s_w + ((G * ns + 3) & ~3));  // [parts][G * 64]
+    const int items = G * (HATA_D / 2);
+    const int parts = max(1, DENSE_WAVES * 64 / items);
+    auto address = [&](int i) {
+        return part0 + (i / (HATA_D / 2)) * head_stride + 2 + 2 * (i % (HATA_D / 2));
+    };
+    for (int i0 = 0; i0 < items; i0 += DENSE_WAVES * 64) {  // (more than once with more than 8 heads)
+        const int item = min(i0 + (parts > 1 ? tid % items : tid), items - 1), part = parts > 1 ? tid / items : 0;
+        const float* pp = address(item);
+        uint2 x[DENSE_BATCH];
+        if (part < parts) {
+#pragma unroll
+            for (int k = 0; k < DENSE_BATCH; ++k) {
+                const int s = part + k * parts;
+                x[k] = s < ns ? ld_dev_u2(pp + (int64_t)s * HATA_PSTRIDE) : make_uint2(0, 0);
+            }
+        }
+        if (i0 == 0) {
+            for (int g = wave; g < G; g += DENSE_WAVES) {
+                const float* mp = part0 + g * head_stride;
+                uint2 ml[4];
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    if (t * 64 < ns) ml[t] = ld_dev_u2(mp + (int64_t)min(lane + 64 * t, ns - 1) * HATA_PSTRIDE);
+                float M = HATA_NEG_INF;
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    if (lane + 64 * t < ns) M = fmaxf(M, __uint_as_float(ml[t].x));
+                M = wave_max64(M);
+                float w[4], l = 0.f;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    w[t] = lane + 64 * t < ns && M != HATA_NEG_INF ? fast_exp2(__uint_as_float(ml[t].x) - M) : 0.f;
+                    if (lane + 64 * t < ns) l = fmaf(w[t], __uint_as_float(ml[t].y), l);
+                }
+                l = wave_sum64(l);
+                const float inv = l > 0.f ? 1.f / l : 0.f;
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    if (lane + 64 * t < ns) s_w[g * ns + lane + 64 * t] = w[t] * inv;
+            }
+            __syncthreads();
+        }
+        float2 sum = make_float2(0.f, 0.f);
+        if (part < parts) {
+            const float* w = s_w + item / (HATA_D / 2) * ns;
+            for (int s0 = part;;) {
+#pragma unroll
+                for (int k = 0; k < DENSE_BATCH; ++k) {
+                    const float f = w[min(s0 + k * parts, ns - 1)];  // (x is zero past the end)
+                    sum.x = fmaf(f, __uint_as_float(x[k].x), sum.x);
+                    sum.y = fmaf(f, __uint_as_float(x[k].y), sum.y);
+                }
+                s0 += DENSE_BATCH * parts;
+                if (s0 >= ns) break;
+#pragma unroll
+                for (int k = 0; k < DENSE_BATCH; ++k) {
+                    const int s = s0 + k * parts;
+                    x[k] = s < ns ? ld_dev_u2(pp + (int64_t)s * HATA_PSTRIDE) : make_uint2(0, 0);
+                }
+            }
+        }
+        if (parts > 1) {  // (a single turn)
+            if (part < parts) s_sum[part * items + item] = sum;
+            __syncthreads();
+            if (part > 0) return;
+            for (int k = 1; k < parts; ++k) {
+                sum.x += s_sum[k * items + item].x;
+                sum.y += s_sum[k * items + item].y;
+            }
+        } else if (i0 + tid >= items) {
+            return;
+        }
+        outp[2 * item] = (uint16_t)f32_to_bf16(sum.x);
+        outp[2 * item + 1] = (uint16_t)f32_to_bf16(sum.y);
+        if (outp32) { outp32[2 * item] = sum.x; outp32[2 * item + 1] = sum.y; }
+    }
+}
+
+static size_t dense_lds() { return (size_t)DENSE_WAVES * DENSE_RING * DENSE_TILE_BYTES; }
+
+// Workgroups per unit: the launch runs in rounds of one workgroup per CU, each as long as its rows and a fixed
+// cost worth about as much as 256 rows (launch, first request, merge); at most HATA_DENSE_ROUNDS rounds.
+static int dense_splits(int64_t units, int L_cap) {
+    int best = 1;
+    int64_t best_cost = INT64_MAX;
+    for (int m = 0; m <= HATA_DENSE_ROUNDS; ++m) {
+        const int64_t s = m == 0 ? 1 : std::min(256 * m / units, (int64_t)std::min(256, (L_cap + 127) / 128));
+        if (s < 1) continue;
+        const int64_t cost = (units * s + 256 - 1) / 256 * ((L_cap + s - 1) / s + 256);
+        if (cost < best_cost) { best_cost = cost; best = (int)s; }
+    }
+    return best;
+}
+
+hipError_t prepare_dense() {  // (more than 64 KB of dynamic LDS has to be asked for)
+    return hipFuncSetAttribute((const void*)dense_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dense_lds());
+}
+
+hipError_t launch_dense(const hata_ctx* c, const void* q, const void* K, const void* V, const int32_t* seq_len, int B,
+                        float sm_scale, void* out, float* out_f32, hipStream_t s) {
+    const hata_config& f = c->cfg;
+    DenseArgs a;
+    a.q = (const uint16_t*)q; a.K = (const uint16_t*)K; a.V = (const uint16_t*)V;
+    a.seq_len = seq_len;
+    a.partials = c->partials; a.counter = c->attn_counter; a.counter_stride = c->attn_counter_stride;
+    a.out = (uint16_t*)out; a.out_f32 = out_f32;
+    a.Hq = f.Hq; a.Hkv = f.Hkv; a.G = c->G; a.L_cap = f.L_cap;
+    a.n_splits = dense_splits((int64_t)f.Hkv * B, f.L_cap);
+    a.sb = f.kv_stride_b; a.sh = f.kv_stride_h; a.sn = f.kv_stride_n;
+    a.scale_log2 = sm_scale * 1.4426950408889634f;
+    hipLaunchKernelGGL(dense_kernel, dim3(a.n_splits, f.Hkv, B), dim3(DENSE_WAVES * 64), dense_lds(), s, a);
+    return hipGetLastError();
+}
+
+}  // namespace hata

@@ -8,6 +8,8 @@
 // Words between the arrival counters of consecutive units (128 bytes:
 // the workgroups of different units then never queue their arrivals on one cache line).
 #define HATA_COUNTER_STRIDE 32
+// dense attention: at most this many rounds of one workgroup per CU, with a partial result each
+#define HATA_DENSE_ROUNDS 4
 // 64-bit words between the records of consecutive chunks (two are used): a cache line per chunk, so
 // that the workgroups polling for their records do not all read the same lines
 #define HATA_REC_STRIDE 8
@@ -27,8 +29,6 @@ struct hata_ctx {
     int coop_opts, coop_opt_chunk[4], coop_opt_cap[4];
     int sparse_rows;  // selected rows per attention workgroup
     int sparse_splits;
-    int dense_rows;   // cache rows per dense-attention workgroup
-    int dense_splits;
     // regions of the caller's workspace
     uint32_t* qcodes;      // [B_max, Hq, Wd]
     uint16_t* scores;      // [B_max, Hkv, L_cap]
@@ -50,7 +50,7 @@ struct hata_ctx {
     int step_mode;           // 0 = single launch when it fits, 3 = always three launches
     int cus;                 // compute units of the device that was current in hata_create
     int coop_opt_cap_paged[4];  // the same for the block-table variant of the kernel
-    float* partials;       // [B_max*Hq, max(sparse_splits, dense_splits), d + 2]
+    float* partials;       // [B_max*Hq, max(sparse_splits, n_chunks), d + 2], at least 256 * HATA_DENSE_ROUNDS * G rows
     void* wplanes;               // [Hkv, r/32, 8, 2, 64] 16-byte fragments: the two scaled fp16 planes of the hash weights (prefill key encode)
     const float* prepared_W_H;   // the weight tensor those planes were made from (nullptr: none)
     size_t control_bytes;  // bytes from chunk_info up to the partials: the control words, cleared at creation and after a give-up
@@ -83,11 +83,14 @@ hipError_t launch_split_weights(const hata_ctx* c, const float* W_H, hipStream_t
 hipError_t launch_score(const hata_ctx* c, const uint32_t* qcodes, const uint32_t* codes,
                         const int32_t* seq_len, int B, uint16_t* scores, const int32_t* kbud,
                         hipStream_t s);
+hipError_t prepare_dense();  // once per context
+hipError_t launch_dense(const hata_ctx* c, const void* q, const void* K, const void* V, const int32_t* seq_len, int B,
+                        float sm_scale, void* out, float* out_f32, hipStream_t s);
 hipError_t prepare_topk(const hata_ctx* c);       // once per context
 hipError_t prepare_attention(const hata_ctx* c);  // once per context
 hipError_t launch_topk(const hata_ctx* c, const uint16_t* scores, const int32_t* seq_len,
                        const int32_t* k, int B, int32_t* idx, hipStream_t s);
-// mode: 0 = rows from idx, 1 = dense, 2 = select on the fly (writes idx)
+// mode: 0 = rows from idx, 2 = select on the fly (writes idx)
 hipError_t launch_attention(const hata_ctx* c, int mode, const void* q, const void* K,
                             const void* V, int32_t* idx, const int32_t* count_src,
                             const int32_t* seq_len, int B, float sm_scale, void* out,

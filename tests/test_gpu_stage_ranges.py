@@ -83,3 +83,26 @@ def test_chunk_owned_attention(L, k_max, chunk, heads):
         assert np.array_equal(H.to_host(c.ctx.hata_step_buffers()[2]), ref["idx"])
         H.check_attention(H.to_host(out32), H.to_host(out, np.uint16), ref["out"], "step")
     c.ctx.close()
+
+
+@pytest.mark.parametrize("G", [1, 3, 4, 5, 8, 16])
+@pytest.mark.parametrize("lens", [(1, 0, 15), (16, 17, 127), (129, 128, 2047), (4099, 20000, 300)])
+def test_dense_attention(G, lens):
+    import torch
+    from paper_2506_02572_amd import hata
+    B, Hkv, L_cap = len(lens), 2, max(lens)
+    print(f"[stages] dense G={G} lens={lens}", flush=True)
+    rng = np.random.default_rng(G)
+    # rows of the caches interleaved over the KV heads: [B, L_cap, Hkv, 128]
+    K, V = (synth.round_to_bf16_bits(rng.standard_normal((B, L_cap, Hkv, 128))) for _ in range(2))
+    q = synth.round_to_bf16_bits(rng.standard_normal((B, Hkv * G, 128)) * 3)
+    seq = np.array(lens, np.int32)
+    ctx = hata.Context(B, Hkv * G, Hkv, 128, 64, L_cap, 1, kv_strides=(L_cap * Hkv * 128, 128, Hkv * 128))
+    out = torch.full((B, Hkv * G, 128), -7, dtype=torch.int16, device="cuda")
+    out32 = torch.full((B, Hkv * G, 128), 7.0, dtype=torch.float32, device="cuda")
+    for _ in range(2):  # (the second call finds the arrival counters as the first one left them)
+        ctx.hata_dense_decode(H.to_dev(q), H.to_dev(K), H.to_dev(V), H.to_dev(seq), B, 128 ** -0.5, out, out32)
+    torch.cuda.synchronize()
+    ref = O.dense_decode_batch(q, K.transpose(0, 2, 1, 3), V.transpose(0, 2, 1, 3), seq, 128 ** -0.5)
+    H.check_attention(H.to_host(out32), H.to_host(out, np.uint16), np.where(seq[:, None, None] > 0, ref, 0.0), "dense")
+    ctx.close()
