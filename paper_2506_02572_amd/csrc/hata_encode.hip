@@ -161,10 +161,23 @@ __device__ __forceinline__ f16x8_t bf16x8_to_f16(const uint4 v) {
     return __builtin_bit_cast(f16x8_t, make_uint4(o[0], o[1], o[2], o[3]));
 }
 
+// 16 bytes that nobody reads again
+__device__ __forceinline__ uint4 load_once(const uint16_t* p) {
+    typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
+    return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(p)));
+}
+
+// FILL: the fused cache fill.  It is bound by the bytes it moves (512 read and 512 written a key), so all of a
+// stage's K and V pieces and the rows they go to are requested together, the stores follow when the rows are
+// put into LDS, stages are half as long (registers: three waves per SIMD instead of two) and the source is
+// read with non-temporal loads, which leave the caches to the rows just written.  Prompts of 8011, 3932, 6057
+// and 2712 tokens into a paged cache, eight heads, r = 128: 54.1 us with a load, a store and a table lookup at a
+// time, 40.3 with them batched, 35.2 with the loads non-temporal (4.9 TB/s; stores of that kind too: 38.4).
+//
 // PRESPLIT: the weights come from the planes hata_prepare_weights made, and they are the two scaled
 // fp16 planes described at encode_dma_kernel below (two MFMAs per fragment instead of three; the key
-// fragments are converted to fp16 on their way from LDS)
-template <int R, bool PAGED, bool PRESPLIT>
+// rows are converted to fp16 on their way into LDS)
+template <int R, bool FILL, bool PAGED, bool PRESPLIT>
 __global__ __launch_bounds__(R * 2) void encode_mfma_kernel(
     const uint16_t* __restrict__ K, const float* __restrict__ W_H, const uint4* __restrict__ planes,
     const int32_t* __restrict__ start, const int32_t* __restrict__ n_new,
@@ -179,7 +192,7 @@ __global__ __launch_bounds__(R * 2) void encode_mfma_kernel(
     const PageView pv) {
     constexpr int THREADS = R * 2;
     constexpr int WD = R / 32;
-    constexpr int STAGE = R >= 64 ? 128 : 64;              // keys per LDS stage
+    constexpr int STAGE = R < 64 || FILL ? 64 : 128;  // keys per LDS stage
     constexpr int NT = STAGE / 32;                         // 32-key MFMA tiles per stage
     constexpr int ROWS_PER_IT = THREADS / 16;              // rows staged per load instruction
     constexpr int NIT = STAGE / ROWS_PER_IT;               // load instructions per stage and thread
@@ -190,18 +203,16 @@ __global__ __launch_bounds__(R * 2) void encode_mfma_kernel(
     const int first = start[b];
     constexpr bool paged = PAGED;
     int cnt = min(n_new[b], (paged ? min(L_cap, pv.max_blocks << pv.shift) : L_cap) - first);
-    if (K_new != nullptr) cnt = min(cnt, max_new);  // the source holds max_new rows per unit
+    if (FILL) cnt = min(cnt, max_new);  // the source holds max_new rows per unit
     const int kb0 = blockIdx.x * keys_per_wg;
     if (first < 0 || kb0 >= cnt) return;
     const int kb1 = min(kb0 + keys_per_wg, cnt);
     const int64_t u = (int64_t)b * Hkv + h;
     const uint16_t* Kb = K + b * sb + h * sh + (int64_t)first * sn;
     uint32_t* cb = codes + (u * L_cap + first) * WD;
-    const bool fill = K_new != nullptr;
-    const uint16_t* Ksrc = fill ? K_new + u * (int64_t)max_new * HATA_D : nullptr;
-    const uint16_t* Vsrc = fill ? V_new + u * (int64_t)max_new * HATA_D : nullptr;
-    uint16_t* Kdst = fill ? K_out + b * sb + h * sh + (int64_t)first * sn : nullptr;
-    uint16_t* Vdst = fill ? V_out + b * sb + h * sh + (int64_t)first * sn : nullptr;
+    const uint16_t* Ksrc = FILL ? K_new + u * (int64_t)max_new * HATA_D : Kb;
+    const uint16_t* Vsrc = FILL ? V_new + u * (int64_t)max_new * HATA_D : nullptr;
+    const int64_t src_n = FILL ? HATA_D : sn;
     // paged destination: row (first + key) of sequence b -> row of the pools, in rows of one head
     auto pool_row = [&](int key) -> int64_t {
         const int n = first + key;
@@ -211,26 +222,30 @@ __global__ __launch_bounds__(R * 2) void encode_mfma_kernel(
 
     // stage loader: thread -> (row = it * ROWS_PER_IT + tid / 16, 16-byte piece tid % 16)
     const int lrow = tid >> 4, lsub = tid & 15;
-    uint4 pre[NIT];
+    uint4 pre[NIT], vpre[FILL ? NIT : 1];
+    int64_t dst[FILL ? NIT : 1];  // where the pieces go in the cache, in elements
     auto load_stage = [&](int k0) {
 #pragma unroll
         for (int it = 0; it < NIT; ++it) {
             const int key = k0 + it * ROWS_PER_IT + lrow;
-            pre[it] = make_uint4(0, 0, 0, 0);
-            if (key < kb1) {
-                if (fill) {
-                    pre[it] = *reinterpret_cast<const uint4*>(Ksrc + (int64_t)key * HATA_D + lsub * 8);
-                    const uint4 vv = *reinterpret_cast<const uint4*>(Vsrc + (int64_t)key * HATA_D + lsub * 8);
-                    if constexpr (paged) {
-                        const int64_t o = pool_row(key) * HATA_D + lsub * 8;
-                        *reinterpret_cast<uint4*>(K_out + o) = pre[it];
-                        *reinterpret_cast<uint4*>(V_out + o) = vv;
-                    } else {
-                        *reinterpret_cast<uint4*>(Kdst + (int64_t)key * sn + lsub * 8) = pre[it];
-                        *reinterpret_cast<uint4*>(Vdst + (int64_t)key * sn + lsub * 8) = vv;
-                    }
-                } else {
-                    pre[it] = *reinterpret_cast<const uint4*>(Kb + (int64_t)key * sn + lsub * 8);
+            if constexpr (PAGED) dst[it] = pool_row(min(key, kb1 - 1)) * HATA_D + lsub * 8;
+            else if constexpr (FILL) dst[it] = b * sb + h * sh + (int64_t)(first + key) * sn + lsub * 8;
+        }
+#pragma unroll
+        for (int it = 0; it < NIT; ++it) {
+            // (rows past the end repeat the last one and are stored nowhere)
+            const int64_t o = (int64_t)min(k0 + it * ROWS_PER_IT + lrow, kb1 - 1) * src_n + lsub * 8;
+            pre[it] = load_once(Ksrc + o);
+            if constexpr (FILL) vpre[it] = load_once(Vsrc + o);
+        }
+    };
+    auto store_stage = [&](int k0) {
+        if constexpr (FILL) {
+#pragma unroll
+            for (int it = 0; it < NIT; ++it) {
+                if (k0 + it * ROWS_PER_IT + lrow < kb1) {
+                    *reinterpret_cast<uint4*>(K_out + dst[it]) = pre[it];
+                    *reinterpret_cast<uint4*>(V_out + dst[it]) = vpre[it];
                 }
             }
         }
@@ -266,7 +281,9 @@ __global__ __launch_bounds__(R * 2) void encode_mfma_kernel(
         __syncthreads();  // the previous stage has been consumed
 #pragma unroll
         for (int it = 0; it < NIT; ++it)
-            *reinterpret_cast<uint4*>(&tile[(it * ROWS_PER_IT + lrow) * HATA_MFMA_PITCH + lsub * 8]) = pre[it];
+            *reinterpret_cast<uint4*>(&tile[(it * ROWS_PER_IT + lrow) * HATA_MFMA_PITCH + lsub * 8]) =
+                PRESPLIT ? __builtin_bit_cast(uint4, bf16x8_to_f16(pre[it])) : pre[it];
+        store_stage(k0);
         __syncthreads();
         if (k0 + STAGE < kb1) load_stage(k0 + STAGE);  // overlaps the MFMAs below
 
@@ -287,10 +304,9 @@ __global__ __launch_bounds__(R * 2) void encode_mfma_kernel(
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
                 if constexpr (PRESPLIT) {
-                    const f16x8_t b16 = bf16x8_to_f16(bfrag[t]);
 #pragma unroll
                     for (int p = 0; p < 2; ++p)
-                        acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(afrag16[p][kk], b16, acc[t], 0, 0, 0);
+                        acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(afrag16[p][kk], __builtin_bit_cast(f16x8_t, bfrag[t]), acc[t], 0, 0, 0);
                 } else {
 #pragma unroll
                     for (int p = 0; p < 3; ++p)
@@ -346,8 +362,7 @@ __global__ __launch_bounds__(R * 2) void encode_mfma_kernel(
 // LDS tile: row r at byte 256 r, unpadded; its 16-byte piece c sits in slot c ^ (r & 15), which makes
 // the operand reads (32 rows, one piece index) conflict-free.  A lane of a DMA instruction therefore
 // fetches piece slot ^ (row & 15) of its row: 16 lanes still read one whole 256-byte row.
-// Every wave converts the key fragments it reads to fp16 itself (three VALU instructions per dword, in
-// the shadow of the MFMAs).  The code words of a stage go through a small LDS array and leave as
+// The rows are converted to fp16 in LDS (three VALU instructions per dword).  The code words of a stage go through a small LDS array and leave as
 // 16-byte stores one turn later.
 #define DMA_STAGE 64
 #define DMA_NBUF 4
@@ -461,12 +476,30 @@ __global__ __launch_bounds__(R * 2) void encode_dma_kernel(
             if (tid < DMA_STAGE * WD && k0 + tid / WD < kb1) cb[(int64_t)k0 * WD + tid] = cbuf[s & 1][tid];
         }
     };
+    // At r >= 128 a tile is converted in place, each wave its own requests: four or eight waves would
+    // otherwise each convert all of it (r = 256, 131072 keys of eight heads: 146.2 -> 131.6 us; at r = 64
+    // converting what is read is the faster one, 56.3 against 59.2).
+    constexpr bool ONCE = R >= 128;
+    // This wave's part of tile s.  It has landed once at most the requests made after it are outstanding: those of
+    // the DMA_NBUF - 2 tiles that follow (stores of code words, if any, only make this wait longer).
+    auto landed = [&](int s) {
+        if (s + DMA_NBUF - 2 < n_stages) asm volatile("s_waitcnt vmcnt(%0)" :: "n"((DMA_NBUF - 2) * INSTR) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    };
+    // the 16-byte pieces of tile s that this lane requested (a lane's piece lands at the instruction's base + 16 lane)
+    auto convert = [&](int s) {
+        uint4* p = &tile[s % DMA_NBUF][w * 64 + lane];
+#pragma unroll
+        for (int it = 0; it < INSTR; ++it)
+            p[it * WAVES * 64] = __builtin_bit_cast(uint4, bf16x8_to_f16(p[it * WAVES * 64]));
+    };
+    if constexpr (ONCE) {
+        asm volatile("" ::: "memory");
+        convert(0);
+    }
     for (int s = 0; s < n_stages; ++s) {
-        // tile s has landed once at most the requests made after it are outstanding: those of the
-        // DMA_NBUF - 2 tiles that follow (stores of code words, if any, only make this wait longer)
-        if (s + DMA_NBUF - 2 < n_stages) __builtin_amdgcn_s_waitcnt(0x0F70 | (((DMA_NBUF - 2) * INSTR) & 15) | ((((DMA_NBUF - 2) * INSTR) >> 4) << 14));
-        else __builtin_amdgcn_s_waitcnt(0x0F70);
-        __syncthreads();  // every wave's part of tile s is there; everybody is done with tile s - 1
+        if constexpr (!ONCE) landed(s);
+        __syncthreads();  // every wave's part of tile s is there (and converted); everybody is done with tile s - 1
         if (s + DMA_NBUF - 1 < n_stages) request(s + DMA_NBUF - 1);
         if (s > 0) flush_codes(s - 1);
         const uint4* tl = &tile[s % DMA_NBUF][0];
@@ -475,16 +508,17 @@ __global__ __launch_bounds__(R * 2) void encode_dma_kernel(
         for (int t = 0; t < NT; ++t)
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[t][i] = 0.f;
-        // Key fragments: the raw bf16 pieces are read from LDS two channel steps ahead and converted one
+        // Key fragments are read from LDS two channel steps ahead and, where they are bf16 still, converted one
         // step ahead, so that neither the LDS latency nor the conversion stands in front of an MFMA (the
         // scheduler is told to keep the steps apart: left alone it moves each read down to its first use)
         auto piece = [&](int kk, int t) { return tl[(t * 32 + m) * 16 + ((2 * kk + half) ^ (m & 15))]; };
+        auto operand = [](const uint4& v) { return ONCE ? __builtin_bit_cast(f16x8_t, v) : bf16x8_to_f16(v); };
         uint4 raw[NT];
         f16x8_t bcur[NT], bnext[NT];
 #pragma unroll
         for (int t = 0; t < NT; ++t) raw[t] = piece(0, t);
 #pragma unroll
-        for (int t = 0; t < NT; ++t) bcur[t] = bf16x8_to_f16(raw[t]);
+        for (int t = 0; t < NT; ++t) bcur[t] = operand(raw[t]);
 #pragma unroll
         for (int t = 0; t < NT; ++t) raw[t] = piece(1, t);
 #pragma unroll
@@ -492,7 +526,7 @@ __global__ __launch_bounds__(R * 2) void encode_dma_kernel(
             __builtin_amdgcn_sched_barrier(0);
             if (kk + 1 < 8) {
 #pragma unroll
-                for (int t = 0; t < NT; ++t) bnext[t] = bf16x8_to_f16(raw[t]);
+                for (int t = 0; t < NT; ++t) bnext[t] = operand(raw[t]);
             }
             if (kk + 2 < 8) {
 #pragma unroll
@@ -503,15 +537,23 @@ __global__ __launch_bounds__(R * 2) void encode_dma_kernel(
 #pragma unroll
                 for (int t = 0; t < NT; ++t)
                     acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(afrag[p][kk], bcur[t], acc[t], 0, 0, 0);
-            // one MFMA, then a quarter of the step's conversions in its shadow
+            if constexpr (!ONCE) {
+                // one MFMA, then a quarter of the step's conversions in its shadow
 #pragma unroll
-            for (int q = 0; q < 2 * NT; ++q) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);           // MFMA
-                __builtin_amdgcn_sched_group_barrier(0x002, 12 / 2, 0);      // VALU
+                for (int q = 0; q < 2 * NT; ++q) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);           // MFMA
+                    __builtin_amdgcn_sched_group_barrier(0x002, 12 / 2, 0);      // VALU
+                }
             }
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int t = 0; t < NT; ++t) bcur[t] = bnext[t];
+        }
+        if constexpr (ONCE) {
+            if (s + 1 < n_stages) {  // in the shadow of the last MFMAs
+                landed(s + 1);
+                convert(s + 1);
+            }
         }
         // sign bits: this lane holds hash columns 8*(i/4) + 4*half + i%4 of key t*32 + m
 #pragma unroll
@@ -558,12 +600,23 @@ hipError_t launch_encode_bulk(const hata_ctx* c, const void* K, const float* W_H
     uint16_t* ko = (uint16_t*)K_out;
     uint16_t* vo = (uint16_t*)V_out;
     if (f.r == 32 || f.r == 64 || f.r == 128 || f.r == 256) {
-        // key blocks of 512..4096 keys: at least ~512 workgroups when the prefill is long enough
-        int kpw = 4096;
-        while (kpw > 512 && (int64_t)((max_new + kpw - 1) / kpw) * f.Hkv * B < 512) kpw >>= 1;
-        const dim3 grid((max_new + kpw - 1) / kpw, f.Hkv, B);
         // the weight planes prepared for exactly this weight tensor, if any (hata_prepare_weights)
         const uint4* planes = (c->prepared_W_H == W_H && c->wplanes) ? (const uint4*)c->wplanes : nullptr;
+        // Keys per workgroup, 64 to 4096.  Every workgroup fetches the head's weight planes, so no more of them than
+        // two per CU; a short prompt then has few keys a workgroup, because one after the other they take 2.6 us
+        // per stage (2048 keys, eight heads, r = 128: 512 / 128 / 64 keys a workgroup 13.0 / 5.1 / 4.4 us).  The fill
+        // takes up to eight per CU where the weights are small next to its rows: it has more to
+        // request than two can have on the way (paged fill of 8011 tokens, r = 128: 128 / 512 keys
+        // 35.0 / 38.1 us; r = 256, 2 x 32768: 128 / 1024 keys 126 / 93 us).  Weights split by the
+        // workgroup itself cost more than a second stage: 128 at least (8192 keys, r = 128: 64 / 128 keys
+        // 21.6 / 12.5 us), and with one or two waves a workgroup up to four of them per CU (32768 keys, r = 64:
+        // 256 / 512 keys 21.1 / 25.3 us).
+        const int64_t most = kn && planes && f.r <= 128 ? 2048 : !planes && f.r <= 64 ? 1024 : 512;
+        auto wgs = [&](int k) { return (int64_t)((max_new + k - 1) / k) * f.Hkv * B; };
+        int kpw = 4096;
+        while (kpw > 128 && wgs(kpw) < most) kpw >>= 1;
+        if (planes && wgs(kpw) < 512) kpw = 64;
+        const dim3 grid((max_new + kpw - 1) / kpw, f.Hkv, B);
         if (!kn && !pages && planes) {
             // keys already in a contiguous cache, weights prepared: the kernel that stages with LDS-direct loads
             const uint4* p16 = planes;
@@ -577,28 +630,28 @@ hipError_t launch_encode_bulk(const hata_ctx* c, const void* K, const float* W_H
 #undef HATA_LAUNCH_DMA
             return hipGetLastError();
         }
-#define HATA_LAUNCH_MFMA(R_, P_)                                                                           \
+#define HATA_LAUNCH_MFMA(R_, F_, P_)                                                                           \
     do {                                                                                                   \
         if (planes)                                                                                        \
-            hipLaunchKernelGGL((encode_mfma_kernel<R_, P_, true>), grid, dim3(R_ * 2), 0, s,               \
+            hipLaunchKernelGGL((encode_mfma_kernel<R_, F_, P_, true>), grid, dim3(R_ * 2), 0, s,               \
                                (const uint16_t*)K, W_H, planes, start, n_new, codes, f.Hkv, f.L_cap, kpw,  \
                                f.kv_stride_b, f.kv_stride_h, f.kv_stride_n, kn, vn, ko, vo, max_new, pv);  \
         else                                                                                               \
-            hipLaunchKernelGGL((encode_mfma_kernel<R_, P_, false>), grid, dim3(R_ * 2), 0, s,              \
+            hipLaunchKernelGGL((encode_mfma_kernel<R_, F_, P_, false>), grid, dim3(R_ * 2), 0, s,              \
                                (const uint16_t*)K, W_H, planes, start, n_new, codes, f.Hkv, f.L_cap, kpw,  \
                                f.kv_stride_b, f.kv_stride_h, f.kv_stride_n, kn, vn, ko, vo, max_new, pv);  \
     } while (0)
-        if (pages) {
-            if (f.r == 32) HATA_LAUNCH_MFMA(32, true);
-            else if (f.r == 64) HATA_LAUNCH_MFMA(64, true);
-            else if (f.r == 128) HATA_LAUNCH_MFMA(128, true);
-            else HATA_LAUNCH_MFMA(256, true);
-        } else {
-            if (f.r == 32) HATA_LAUNCH_MFMA(32, false);
-            else if (f.r == 64) HATA_LAUNCH_MFMA(64, false);
-            else if (f.r == 128) HATA_LAUNCH_MFMA(128, false);
-            else HATA_LAUNCH_MFMA(256, false);
-        }
+#define HATA_LAUNCH_WIDTH(F_, P_)                          \
+    do {                                                   \
+        if (f.r == 32) HATA_LAUNCH_MFMA(32, F_, P_);       \
+        else if (f.r == 64) HATA_LAUNCH_MFMA(64, F_, P_);  \
+        else if (f.r == 128) HATA_LAUNCH_MFMA(128, F_, P_); \
+        else HATA_LAUNCH_MFMA(256, F_, P_);                \
+    } while (0)
+        if (pages) HATA_LAUNCH_WIDTH(true, true);
+        else if (kn) HATA_LAUNCH_WIDTH(true, false);
+        else HATA_LAUNCH_WIDTH(false, false);
+#undef HATA_LAUNCH_WIDTH
 #undef HATA_LAUNCH_MFMA
         return hipGetLastError();
     }

@@ -106,3 +106,53 @@ def test_dense_attention(G, lens):
     ref = O.dense_decode_batch(q, K.transpose(0, 2, 1, 3), V.transpose(0, 2, 1, 3), seq, 128 ** -0.5)
     H.check_attention(H.to_host(out32), H.to_host(out, np.uint16), np.where(seq[:, None, None] > 0, ref, 0.0), "dense")
     ctx.close()
+
+
+@pytest.mark.parametrize("r", [32, 64, 128, 256])
+@pytest.mark.parametrize("max_new", [9, 63, 64, 65, 129, 300, 1025])
+def test_fill_and_encode_many_keys(r, max_new):
+    """Remainders of a stage and of a workgroup's keys; with prepared weights and without, both layouts."""
+    import torch
+    from paper_2506_02572_amd import hata
+    B, Hkv, P, first = 3, 2, 16, 5
+    L_cap = -(-(max_new + first) // P) * P
+    blocks = L_cap // P
+    rng = np.random.default_rng(r + max_new)
+    K_new, V_new = (synth.round_to_bf16_bits(rng.standard_normal((B, Hkv, max_new, 128))) for _ in range(2))
+    W = rng.standard_normal((Hkv, 128, r)).astype(np.float32)
+    start = np.array([0, first, L_cap - max_new // 2], np.int32)  # (the last one does not fit whole)
+    n_new = np.array([max_new, max_new - 1, max_new], np.int32)
+    K0, V0 = (rng.integers(0, 2**16, (B, Hkv, L_cap, 128), dtype=np.uint16) for _ in range(2))
+    K_ref, V_ref = K0.copy(), V0.copy()
+    for b in range(B):
+        n = min(int(n_new[b]), L_cap - int(start[b]))
+        K_ref[b, :, start[b]:start[b] + n], V_ref[b, :, start[b]:start[b] + n] = K_new[b, :, :n], V_new[b, :, :n]
+    before = rng.integers(0, 2**32, (B, Hkv, L_cap, r // 32), dtype=np.uint32)
+    n_fit = np.minimum(n_new, L_cap - start).astype(np.int32)
+    ref, near = O.encode_keys_batch(K_ref, W, start, n_fit, codes=before.copy())
+    pages = rng.permutation(B * blocks).astype(np.int32).reshape(B, blocks)
+    Wd, st, nn = H.to_dev(W), H.to_dev(start), H.to_dev(n_new)
+
+    def pool(a):  # [B, Hkv, L_cap, x] -> pages [B * blocks, Hkv, P, x]
+        out = np.empty((B * blocks, Hkv, P, a.shape[-1]), a.dtype)
+        out[pages.reshape(-1)] = a.reshape(B, Hkv, blocks, P, -1).transpose(0, 2, 1, 3, 4).reshape(B * blocks, Hkv, P, -1)
+        return out
+
+    ctx = hata.Context(B, 2 * Hkv, Hkv, 128, r, L_cap, 8)
+    for prepared in (False, True):
+        print(f"[stages] fill r={r} max_new={max_new} prepared={prepared}", flush=True)
+        if prepared:
+            ctx.hata_prepare_weights(Wd)
+        codes = H.to_dev(before.copy())
+        ctx.hata_encode_keys(H.to_dev(K_ref), Wd, st, nn, B, max_new, codes)
+        H.check_codes(H.to_host(codes, np.uint32), ref, near, "keys in the cache")
+        K, V, codes = H.to_dev(K0.copy()), H.to_dev(V0.copy()), H.to_dev(before.copy())
+        ctx.hata_prefill_write(H.to_dev(K_new), H.to_dev(V_new), st, nn, B, max_new, K, V, codes, Wd)
+        H.check_codes(H.to_host(codes, np.uint32), ref, near, "fill")
+        assert np.array_equal(H.to_host(K, np.uint16), K_ref) and np.array_equal(H.to_host(V, np.uint16), V_ref)
+        K, V, codes = H.to_dev(pool(K0)), H.to_dev(pool(V0)), H.to_dev(pool(before))
+        ctx.hata_prefill_write_paged(H.to_dev(K_new), H.to_dev(V_new), st, nn, B, max_new, K, V, codes,
+                                     H.to_dev(pages), blocks, P, B * blocks, Wd)
+        assert np.array_equal(H.to_host(K, np.uint16), pool(K_ref)) and np.array_equal(H.to_host(V, np.uint16), pool(V_ref))
+        H.check_codes(H.to_host(codes, np.uint32), pool(ref), pool(near), "paged fill")
+    ctx.close()
