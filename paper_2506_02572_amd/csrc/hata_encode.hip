@@ -361,16 +361,17 @@ __global__ __launch_bounds__(R * 2) void encode_mfma_kernel(
 // (2) The key rows are staged by the memory pipeline itself: global_load_lds_dwordx4 moves 16 bytes
 // per lane from memory straight into LDS (lane l of a wave lands at the instruction's LDS base + 16 l),
 // so a stage costs no registers and several stages can be on their way while one is being multiplied.
-// A workgroup cycles through DMA_NBUF tiles of DMA_STAGE keys: in turn s it waits for tile s, passes the
-// one barrier of the turn, requests tile s + DMA_NBUF - 1 into the buffer that turn s - 1 has just
-// finished with, and multiplies tile s.
+// A workgroup cycles through NBUF tiles of STAGE keys: in turn s it waits for tile s, passes the
+// one barrier of the turn, requests tile s + NBUF - 1 into the buffer that turn s - 1 has just
+// finished with, and multiplies tile s.  Two tiles of 128 keys where a workgroup has more than 128, four of 64 for the
+// short prompts: half the barriers, and a wave's four independent products cover each other's latency (131072 keys of
+// eight heads, r = 256: 133.6 us with four tiles of 64, 125.2 with two of 128, 127.4 with three of 128 and one workgroup per CU;
+// 2048 keys, 64 a workgroup: 5.3 and 6.3).
 // LDS tile: row r at byte 256 r, unpadded; its 16-byte piece c sits in slot c ^ (r & 15), which makes
 // the operand reads (32 rows, one piece index) conflict-free.  A lane of a DMA instruction therefore
 // fetches piece slot ^ (row & 15) of its row: 16 lanes still read one whole 256-byte row.
 // The rows are converted to fp16 in LDS (three VALU instructions per dword).  The code words of a stage go through a small LDS array and leave as
 // 16-byte stores one turn later.
-#define DMA_STAGE 64
-#define DMA_NBUF 4
 
 // Fragment order of the fp16 planes: for KV head h, wave w (hash columns 32 w .. 32 w + 31), channel
 // step kk and plane p (0 = hi, 1 = lo) the 64 lanes' 16-byte fragments lie one after the other:
@@ -409,17 +410,18 @@ __global__ __launch_bounds__(64) void split_weights_f16_kernel(const float* __re
     }
 }
 
-template <int R>
+template <int R, int STAGE>
 __global__ __launch_bounds__(R * 2) void encode_dma_kernel(
     const uint16_t* __restrict__ K, const uint4* __restrict__ planes,
     const int32_t* __restrict__ start, const int32_t* __restrict__ n_new, uint32_t* __restrict__ codes,
     int Hkv, int L_cap, int keys_per_wg, int64_t sb, int64_t sh, int64_t sn) {
     constexpr int WAVES = R / 32, WD = R / 32;
-    constexpr int NT = DMA_STAGE / 32;                 // 32-key MFMA tiles per stage
-    constexpr int INSTR = DMA_STAGE / (WAVES * 4);     // DMA instructions per wave and stage (4 rows each)
-    static_assert(INSTR >= 1 && INSTR * WAVES * 4 == DMA_STAGE, "a stage is a whole number of DMA instructions per wave");
-    __shared__ __attribute__((aligned(16))) uint4 tile[DMA_NBUF][DMA_STAGE * 16];
-    __shared__ __attribute__((aligned(16))) uint32_t cbuf[2][DMA_STAGE * WD];
+    constexpr int NBUF = 256 / STAGE;              // 64 KB of tiles
+    constexpr int NT = STAGE / 32;                 // 32-key MFMA tiles per stage
+    constexpr int INSTR = STAGE / (WAVES * 4);     // DMA instructions per wave and stage (4 rows each)
+    static_assert(INSTR >= 1 && INSTR * WAVES * 4 == STAGE, "a stage is a whole number of DMA instructions per wave");
+    __shared__ __attribute__((aligned(16))) uint4 tile[NBUF][STAGE * 16];
+    __shared__ __attribute__((aligned(16))) uint32_t cbuf[2][STAGE * WD];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int m = lane & 31, half = lane >> 5;
     const int h = blockIdx.y, b = blockIdx.z;
@@ -431,14 +433,14 @@ __global__ __launch_bounds__(R * 2) void encode_dma_kernel(
     const int64_t u = (int64_t)b * Hkv + h;
     const uint16_t* Kb = K + b * sb + h * sh + (int64_t)first * sn;
     uint32_t* cb = codes + (u * L_cap + first) * WD;
-    const int n_stages = (kb1 - kb0 + DMA_STAGE - 1) / DMA_STAGE;
+    const int n_stages = (kb1 - kb0 + STAGE - 1) / STAGE;
 
     // rows past the end of the range are fetched from the range's last row (valid memory; their code
     // words are never stored)
     const int drow = lane >> 4, dslot = lane & 15;
     auto request = [&](int s) {
-        const int k0 = kb0 + s * DMA_STAGE;
-        uint4* dst = &tile[s % DMA_NBUF][0];
+        const int k0 = kb0 + s * STAGE;
+        uint4* dst = &tile[s % NBUF][0];
 #pragma unroll
         for (int it = 0; it < INSTR; ++it) {
             const int r0 = (it * WAVES + w) * 4;
@@ -464,21 +466,23 @@ __global__ __launch_bounds__(R * 2) void encode_dma_kernel(
             for (int p = 0; p < 2; ++p) afrag[p][kk] = __builtin_bit_cast(f16x8_t, src[(kk * 2 + p) * 64]);
     }
 #pragma unroll
-    for (int s = 0; s < DMA_NBUF - 1; ++s)
+    for (int s = 0; s < NBUF - 1; ++s)
         if (s < n_stages) request(s);
     // the weight fragments are there before the loop starts (said explicitly, or the compiler guards
     // their every use inside the loop with a count of outstanding loads that fits the first turn only)
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
 
     // 16-byte pieces of the previous stage's code words that this thread stores (none for most threads)
-    constexpr int CODE_VEC = DMA_STAGE * WD / 4;
+    constexpr int CODE_VEC = STAGE * WD / 4;
+    static_assert(WD < 4 || CODE_VEC <= R * 2, "a thread stores one piece at most");
     auto flush_codes = [&](int s) {  // code words of stage s, staged in cbuf[s & 1]
-        const int k0 = kb0 + s * DMA_STAGE;
+        const int k0 = kb0 + s * STAGE;
         if constexpr (WD >= 4) {  // (a key's code is 16 bytes or more: every piece is aligned)
             if (tid < CODE_VEC && k0 + (tid * 4) / WD < kb1)
                 reinterpret_cast<uint4*>(cb + (int64_t)k0 * WD)[tid] = reinterpret_cast<const uint4*>(&cbuf[s & 1][0])[tid];
         } else {
-            if (tid < DMA_STAGE * WD && k0 + tid / WD < kb1) cb[(int64_t)k0 * WD + tid] = cbuf[s & 1][tid];
+            for (int i = tid; i < STAGE * WD; i += R * 2)
+                if (k0 + i / WD < kb1) cb[(int64_t)k0 * WD + i] = cbuf[s & 1][i];
         }
     };
     // At r >= 128 a tile is converted in place, each wave its own requests: four or eight waves would
@@ -486,14 +490,14 @@ __global__ __launch_bounds__(R * 2) void encode_dma_kernel(
     // converting what is read is the faster one, 56.3 against 59.2).
     constexpr bool ONCE = R >= 128;
     // This wave's part of tile s.  It has landed once at most the requests made after it are outstanding: those of
-    // the DMA_NBUF - 2 tiles that follow (stores of code words, if any, only make this wait longer).
+    // the NBUF - 2 tiles that follow (stores of code words, if any, only make this wait longer).
     auto landed = [&](int s) {
-        if (s + DMA_NBUF - 2 < n_stages) asm volatile("s_waitcnt vmcnt(%0)" :: "n"((DMA_NBUF - 2) * INSTR) : "memory");
+        if (s + NBUF - 2 < n_stages) asm volatile("s_waitcnt vmcnt(%0)" :: "n"((NBUF - 2) * INSTR) : "memory");
         else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     };
     // the 16-byte pieces of tile s that this lane requested (a lane's piece lands at the instruction's base + 16 lane)
     auto convert = [&](int s) {
-        uint4* p = &tile[s % DMA_NBUF][w * 64 + lane];
+        uint4* p = &tile[s % NBUF][w * 64 + lane];
 #pragma unroll
         for (int it = 0; it < INSTR; ++it)
             p[it * WAVES * 64] = __builtin_bit_cast(uint4, bf16x8_to_f16(p[it * WAVES * 64]));
@@ -505,9 +509,9 @@ __global__ __launch_bounds__(R * 2) void encode_dma_kernel(
     for (int s = 0; s < n_stages; ++s) {
         if constexpr (!ONCE) landed(s);
         __syncthreads();  // every wave's part of tile s is there (and converted); everybody is done with tile s - 1
-        if (s + DMA_NBUF - 1 < n_stages) request(s + DMA_NBUF - 1);
+        if (s + NBUF - 1 < n_stages) request(s + NBUF - 1);
         if (s > 0) flush_codes(s - 1);
-        const uint4* tl = &tile[s % DMA_NBUF][0];
+        const uint4* tl = &tile[s % NBUF][0];
         f32x16_t acc[NT];
 #pragma unroll
         for (int t = 0; t < NT; ++t)
@@ -527,6 +531,7 @@ __global__ __launch_bounds__(R * 2) void encode_dma_kernel(
         for (int t = 0; t < NT; ++t) bcur[t] = operand(raw[t]);
 #pragma unroll
         for (int t = 0; t < NT; ++t) raw[t] = piece(1, t);
+        __builtin_amdgcn_s_setprio(1);  // a wave that multiplies goes before one that converts or packs (1 %)
 #pragma unroll
         for (int kk = 0; kk < 8; ++kk) {
             __builtin_amdgcn_sched_barrier(0);
@@ -555,6 +560,7 @@ __global__ __launch_bounds__(R * 2) void encode_dma_kernel(
 #pragma unroll
             for (int t = 0; t < NT; ++t) bcur[t] = bnext[t];
         }
+        __builtin_amdgcn_s_setprio(0);
         if constexpr (ONCE) {
             if (s + 1 < n_stages) {  // in the shadow of the last MFMAs
                 landed(s + 1);
@@ -622,9 +628,10 @@ hipError_t launch_encode_bulk(const hata_ctx* c, const void* K, const float* W_H
         if (!kn && !pages && planes) {
             // keys already in a contiguous cache, weights prepared: the kernel that stages with LDS-direct loads
             const uint4* p16 = planes;
-#define HATA_LAUNCH_DMA(R_)                                                                                   \
-    hipLaunchKernelGGL((encode_dma_kernel<R_>), grid, dim3(R_ * 2), 0, s, (const uint16_t*)K, p16, start, n_new, \
-                       codes, f.Hkv, f.L_cap, kpw, f.kv_stride_b, f.kv_stride_h, f.kv_stride_n)
+#define HATA_LAUNCH_DMA(R_)                                                                                          \
+    hipLaunchKernelGGL((kpw > 128 ? encode_dma_kernel<R_, 128> : encode_dma_kernel<R_, 64>), grid, dim3(R_ * 2), 0, s, \
+                       (const uint16_t*)K, p16, start, n_new, codes, f.Hkv, f.L_cap, kpw, f.kv_stride_b,             \
+                       f.kv_stride_h, f.kv_stride_n)
             if (f.r == 32) HATA_LAUNCH_DMA(32);
             else if (f.r == 64) HATA_LAUNCH_DMA(64);
             else if (f.r == 128) HATA_LAUNCH_DMA(128);

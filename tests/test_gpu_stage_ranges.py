@@ -156,3 +156,27 @@ def test_fill_and_encode_many_keys(r, max_new):
         assert np.array_equal(H.to_host(K, np.uint16), pool(K_ref)) and np.array_equal(H.to_host(V, np.uint16), pool(V_ref))
         H.check_codes(H.to_host(codes, np.uint32), pool(ref), pool(near), "paged fill")
     ctx.close()
+
+
+@pytest.mark.parametrize("r", [32, 64, 128, 256])
+def test_encode_keys_of_many_units(r):
+    """Workgroups of many keys (512 units), ranges of all lengths round the 128 keys of a stage."""
+    import torch
+    from paper_2506_02572_amd import hata
+    B, Hkv, max_new, L_cap = 64, 8, 270, 280
+    print(f"[stages] encode r={r}, 512 units", flush=True)
+    rng = np.random.default_rng(r)
+    K = synth.round_to_bf16_bits(rng.standard_normal((B, Hkv, L_cap, 128), dtype=np.float32))
+    W = rng.standard_normal((Hkv, 128, r)).astype(np.float32)
+    start = rng.integers(0, L_cap - max_new + 1, B).astype(np.int32)
+    n_new = np.concatenate([[0, 1, 63, 64, 65, 127, 128, 129, 255, 256, 257, max_new], rng.integers(1, max_new, B - 12)]).astype(np.int32)
+    before = rng.integers(0, 2**32, (B, Hkv, L_cap, r // 32), dtype=np.uint32)
+    ctx = hata.Context(B, 2 * Hkv, Hkv, 128, r, L_cap, 8)
+    Wd = H.to_dev(W)
+    ctx.hata_prepare_weights(Wd)
+    codes = H.to_dev(before.copy())
+    ctx.hata_encode_keys(H.to_dev(K), Wd, H.to_dev(start), H.to_dev(n_new), B, max_new, codes)
+    torch.cuda.synchronize()
+    ref, near = O.encode_keys_batch(K, W, start, n_new, codes=before.copy(), bulk=True)
+    H.check_codes(H.to_host(codes, np.uint32), ref, near, "keys")
+    ctx.close()
