@@ -85,8 +85,16 @@ __device__ __forceinline__ const CoopArgs* coop_args_in_memory() {
 
 template <int WD>
 struct CodeW { uint32_t w[WD]; };
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
 
-template <int WD>
+// ONCE: marked non-temporal.  Chunks above HATA_COOP_SUB mean some 64 MB of codes or more in this launch: over the layers of
+// a model they are gone from every cache before the next pass over them, and not keeping them leaves the L2 to the
+// weights, the rows and what the workgroups exchange (32 sequences of 32768 keys, r = 128: 54.2 -> 48.8 to 52.2 us; 16 of
+// 65536: 53.3 -> 47.0; a program of one such layer alone finds them in the 256 MB cache at the memory side, and
+// loses by the hint: 48.0 -> 49.7).  Smaller launches keep them (15 sequences of up to 25733 keys, two
+// layers: 26.3 us, 27.5 with the hint).  At r = 256 a code is two loads, and the second one misses the line that the
+// first one's hint gave up (8 x 125439 keys: 66.5 and 71.8).
+template <int WD, bool ONCE>
 __device__ __forceinline__ CodeW<WD> coop_load_code(const uint32_t* p) {
     CodeW<WD> c;
     if constexpr (WD == 1) {
@@ -97,7 +105,8 @@ __device__ __forceinline__ CodeW<WD> coop_load_code(const uint32_t* p) {
     } else {
 #pragma unroll
         for (int i = 0; i < WD / 4; ++i) {
-            const uint4 v = reinterpret_cast<const uint4*>(p)[i];
+            const uint4 v = ONCE ? __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(p) + i))
+                                 : reinterpret_cast<const uint4*>(p)[i];
             c.w[4 * i] = v.x; c.w[4 * i + 1] = v.y; c.w[4 * i + 2] = v.z; c.w[4 * i + 3] = v.w;
         }
     }
@@ -338,13 +347,13 @@ void decode_step_coop_kernel(const CoopArgs a) {
 #pragma unroll
             for (int j = 0; j < UNR; ++j) {
                 const int n = n0 + j * 256;
-                if (n < stop) kc[j] = coop_load_code<WD>(a.codes + row_in_page(pg[j], n) * WD);
+                if (n < stop) kc[j] = coop_load_code<WD, BIG && WD == 4>(a.codes + row_in_page(pg[j], n) * WD);
             }
         } else {
 #pragma unroll
             for (int j = 0; j < UNR; ++j) {
                 const int n = n0 + j * 256;
-                if (n < stop) kc[j] = coop_load_code<WD>(a.codes + cache_row(n) * WD);
+                if (n < stop) kc[j] = coop_load_code<WD, BIG && WD == 4>(a.codes + cache_row(n) * WD);
             }
         }
     };
