@@ -1,6 +1,5 @@
 // Decode attention over a list of cache rows (Alg. 3 of the paper: Gather + Attention, with
-// the gather fused into the attention kernel; Eq. 2 third line, scale of Eq. 1), and the
-// dense variant over the whole cache (Eq. 1) that serves as the comparison baseline.
+// the gather fused into the attention kernel; Eq. 2 third line, scale of Eq. 1).
 //
 // One kernel template, two row sources:
 //   ROWS_IDX     rows come from an index list in memory            (hata_sparse_decode)
@@ -29,7 +28,7 @@ struct AttnArgs {
     const uint16_t* V;
     const int32_t* idx_in;      // ROWS_IDX
     int32_t* idx_out;           // ROWS_SELECT
-    const int32_t* count_src;   // ROWS_IDX: k[B]; ROWS_DENSE: seq_len[B]
+    const int32_t* count_src;   // ROWS_IDX: k[B]
     const uint16_t* scores;     // ROWS_SELECT ...
     const int32_t* seq_len;
     const int32_t* chunk_info;

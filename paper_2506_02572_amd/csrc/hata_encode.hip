@@ -370,8 +370,8 @@ __global__ __launch_bounds__(R * 2) void encode_mfma_kernel(
 // LDS tile: row r at byte 256 r, unpadded; its 16-byte piece c sits in slot c ^ (r & 15), which makes
 // the operand reads (32 rows, one piece index) conflict-free.  A lane of a DMA instruction therefore
 // fetches piece slot ^ (row & 15) of its row: 16 lanes still read one whole 256-byte row.
-// The rows are converted to fp16 in LDS (three VALU instructions per dword).  The code words of a stage go through a small LDS array and leave as
-// 16-byte stores one turn later.
+// The rows are converted to fp16 (three VALU instructions per dword) in LDS from r = 128 on, below that as they
+// are read.  The code words of a stage go through a small LDS array and leave as 16-byte stores one turn later.
 
 // Fragment order of the fp16 planes: for KV head h, wave w (hash columns 32 w .. 32 w + 31), channel
 // step kk and plane p (0 = hi, 1 = lo) the 64 lanes' 16-byte fragments lie one after the other:
