@@ -112,6 +112,9 @@ struct TrainShape {
     static constexpr int RS = CG == 4 ? 2 : 4;
     static constexpr int THREADS = CG * RS * 64;
     static constexpr int TILES = TR_ROWS / 32 / RS;  // 32-row tiles of a wave
+    static constexpr int WAVES = THREADS / 64;
+    static constexpr int SLICES = THREADS / COLS;  // threads per column (below 64 columns more than the waves)
+    static constexpr int COL_ROWS = WAVES > SLICES ? WAVES : SLICES;  // rows of LDS that per-column sums of either kind need
 };
 
 // rows [row0, row0 + TR_ROWS) of X [n, 128] (zeros past n): fetched into registers, later put into an LDS tile
@@ -290,10 +293,11 @@ __global__ __launch_bounds__(TrainShape<R>::THREADS) void train_grad_kernel(
     int n_groups, const float* __restrict__ P, float* __restrict__ dw_part, float* __restrict__ loss_part,
     float* __restrict__ bal_part, float* __restrict__ WP) {
     using S = TrainShape<R>;
-    constexpr int THREADS = S::THREADS, WAVES = THREADS / 64, SLICES = THREADS / S::COLS;
+    constexpr int THREADS = S::THREADS, WAVES = S::WAVES, SLICES = S::SLICES;
     __shared__ __attribute__((aligned(16))) uint16_t tile[2 * TR_ROWS * TR_PITCH];
     __shared__ float s_lab[TR_ROWS];
-    __shared__ __attribute__((aligned(16))) float s_col[WAVES][S::COLS];  // sum of h(k_n) over this block's query, per hash column
+    __shared__ __attribute__((aligned(16))) float s_col[S::COL_ROWS][S::COLS];  // per hash column: sums of h(k_n) over this block's query, a wave's each; or of a row of W P, a slice's each
+    static_assert(sizeof(s_col) >= sizeof(float) * S::COLS * (WAVES > SLICES ? WAVES : SLICES), "a row per wave, and per slice");
     __shared__ float s_bal[WAVES], s_loss[WAVES];
     __shared__ int s_first;
     const int tid = threadIdx.x, lane = tid & 63;
