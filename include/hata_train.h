@@ -62,8 +62,7 @@ typedef struct hata_train_ctx hata_train_ctx; /* opaque, host memory */
 int hata_train_workspace_bytes(const hata_train_config* cfg, size_t* out);
 
 /* Creates a context over `workspace` (device, 256-byte aligned, >= hata_train_workspace_bytes()
- * bytes, owned by the caller, must outlive the context); the label builder's histogram in it is
- * cleared here with a hipMemset on the current device. */
+ * bytes, owned by the caller, must outlive the context).  Nothing is written to it here. */
 int hata_train_create(hata_train_ctx** ctx_out, const hata_train_config* cfg, void* workspace,
                       size_t workspace_bytes);
 
@@ -82,7 +81,8 @@ int hata_train_step(hata_train_ctx* ctx, const void* Q, const void* K, const flo
 /* Training-data construction of App. B.1 (steps 3-4) for ONE sampled query: the qk scores of the
  * query against m keys (accumulated in fp64), the best floor(m / 10) pairs (at least one) labelled
  * 20 .. 1 in equal steps by rank -- the earlier key first on equal scores -- and the others -1.
- *   q [d] bf16, K [m, d] bf16, s [m] fp32 (output), 1 <= m <= n_max; three launches on `stream`. */
+ *   q [d] bf16, K [m, d] bf16, s [m] fp32 (output), 1 <= m <= n_max; three launches on `stream`, four in a
+ * context's first call (which clears the scratch histogram that every call leaves clear). */
 int hata_train_make_labels(hata_train_ctx* ctx, const void* q, const void* K, int32_t m, float* s,
                            void* stream);
 

@@ -51,6 +51,7 @@ struct hata_train_ctx {
     // label builder
     double* scores;      // [n_max] qk scores
     uint32_t* bins;      // [LB_COPIES, LB_BINS] how many scores fall into each bin, zero between calls
+    int bins_clear;      // a label call has left them so (the first one clears them on its own stream)
     uint32_t* n_cand;    // [1] entries of the candidate list
     LabelCand* cand;     // [n_max]
 };
@@ -575,6 +576,12 @@ __device__ __forceinline__ int score_bin(double x) {
     return (u >> 63) ? LB_BINS / 2 - 1 - step : LB_BINS / 2 + step;
 }
 
+// the histogram before the first label call: stream-ordered behind whatever the workspace's memory was used for before
+__global__ __launch_bounds__(256) void train_clear_bins_kernel(uint32_t* __restrict__ bins) {
+    static_assert(LB_COPIES * LB_BINS % 1024 == 0, "whole workgroups of four words a thread");
+    reinterpret_cast<uint4*>(bins)[blockIdx.x * 256 + threadIdx.x] = make_uint4(0, 0, 0, 0);
+}
+
 // qk scores of one query against m keys, in fp64 (every product of two bf16 values is exact there): a row
 // per 16 lanes, 8 channels per lane; `passes` passes of 16 rows per workgroup.  With several passes the
 // workgroup counts in LDS first: fewer device atomics (one copy of the histogram and one pass took 14.7 us
@@ -785,10 +792,7 @@ int hata_train_create(hata_train_ctx** ctx_out, const hata_train_config* cfg, vo
     c->bins = (uint32_t*)(w + p.off_bins);
     c->n_cand = (uint32_t*)(w + p.off_ncand);
     c->cand = (LabelCand*)(w + p.off_cand);
-    if (hipMemset(c->bins, 0, (size_t)LB_COPIES * LB_BINS * 4) != hipSuccess) {  // (every label call leaves it cleared)
-        delete c;
-        return HATA_EHIP;
-    }
+    c->bins_clear = 0;
     *ctx_out = c;
     return HATA_OK;
 }
@@ -851,6 +855,17 @@ int hata_train_make_labels(hata_train_ctx* ctx, const void* q, const void* K, in
     int n_pos = m / 10;
     if (n_pos < 1) n_pos = 1;
     const int passes = m <= 16384 ? 1 : m / 8192 < 32 ? m / 8192 : 32;
+    // Nothing is written to the workspace before the first call, which clears the histogram on its own stream; every call
+    // leaves it clear (train_labels_kernel).  A clear that is only recorded into a graph has not run yet, so it
+    // does not count: the graph clears at each replay and the next call still does.
+    bool cleared = ctx->bins_clear != 0;
+    if (!cleared) {
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusActive;
+        const hipError_t e = hipStreamIsCapturing(st, &capture);
+        if (e != hipSuccess) (void)hipGetLastError();
+        cleared = e == hipSuccess && capture == hipStreamCaptureStatusNone;
+        hipLaunchKernelGGL(hata::train_clear_bins_kernel, dim3(LB_COPIES * LB_BINS / 1024), dim3(256), 0, st, ctx->bins);
+    }
     hipLaunchKernelGGL(hata::train_scores_kernel, dim3((m + LB_PASS * passes - 1) / (LB_PASS * passes)), dim3(256), 0, st,
                        (const uint16_t*)q, (const uint16_t*)K, m, passes, ctx->scores, ctx->bins, ctx->n_cand);
     hipLaunchKernelGGL(hata::train_candidates_kernel, dim3((m + 255) / 256), dim3(256), 0, st, ctx->scores, m, n_pos,
@@ -858,7 +873,9 @@ int hata_train_make_labels(hata_train_ctx* ctx, const void* q, const void* K, in
     // enough workgroups for twice the expected list (they take more turns if it is longer)
     hipLaunchKernelGGL(hata::train_labels_kernel, dim3(n_pos / 32 + 2), dim3(1024), 0, st, ctx->cand, ctx->n_cand, n_pos,
                        ctx->bins, s);
-    return hipGetLastError() == hipSuccess ? HATA_OK : HATA_EHIP;
+    const bool ok = hipGetLastError() == hipSuccess;
+    ctx->bins_clear = ok && cleared;  // (after a call that failed half-way the next one clears again)
+    return ok ? HATA_OK : HATA_EHIP;
 }
 
 }  // extern "C"

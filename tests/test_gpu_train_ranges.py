@@ -57,3 +57,60 @@ def test_labels_of_awkward_scores(kind, m):
         torch.cuda.synchronize()
         assert np.array_equal(H.to_host(s), want)
     ctx.close()
+
+
+def labels_problem(m, seed):
+    rng = np.random.default_rng(seed)
+    K, q = np.zeros((m, 128), np.float32), np.zeros(128, np.float32)
+    K[:, 0], q[0] = rng.integers(-100, 100, m), 1.0
+    return H.to_dev(synth.round_to_bf16_bits(q)), H.to_dev(synth.round_to_bf16_bits(K)), T.make_labels(K[:, 0].astype(np.float64)).astype(np.float32)
+
+
+def test_labels_of_a_context_made_behind_pending_work():
+    """The workspace's memory is still being written on the stream that the context is made and used on."""
+    import ctypes
+    import torch
+    m = 5000
+    q, K, want = labels_problem(m, 1)
+    n = ctypes.c_size_t(0)
+    train._lib().hata_train_workspace_bytes(ctypes.byref(train.hata_train_config(128, 32, m)), ctypes.byref(n))
+    s = torch.empty(m, dtype=torch.float32, device="cuda")
+    torch.cuda.synchronize()
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        earlier = torch.empty(n.value + 256, dtype=torch.uint8, device="cuda")
+        address = earlier.data_ptr()
+        torch.cuda._sleep(20_000_000)  # some milliseconds
+        earlier.fill_(1)
+        del earlier
+        ctx = train.TrainContext(128, 32, m)
+        assert ctx.workspace.data_ptr() == address
+        ctx.hata_train_make_labels(q, K, m, s)
+    torch.cuda.synchronize()
+    assert np.array_equal(H.to_host(s), want)
+    ctx.close()
+
+
+def test_first_label_call_recorded_into_a_graph():
+    import torch
+    m = 3000
+    q, K, want = labels_problem(m, 2)
+    ctx = train.TrainContext(128, 32, m)
+    ctx.workspace.fill_(255)
+    s = torch.zeros(m, dtype=torch.float32, device="cuda")
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ctx.hata_train_make_labels(q, K, m, s)
+    torch.cuda.synchronize()
+    for turn in range(4):
+        print(f"[labels] graph, turn {turn}", flush=True)
+        s.zero_()
+        ctx.hata_train_make_labels(q, K, m, s)  # (the first one comes before any replay)
+        torch.cuda.synchronize()
+        assert np.array_equal(H.to_host(s), want)
+        s.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(H.to_host(s), want)
+    ctx.close()
