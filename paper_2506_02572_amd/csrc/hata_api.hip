@@ -56,7 +56,7 @@ int validate_config(const hata_config* f) {
     if (f->d != 128) return HATA_EUNSUPPORTED;
     if (f->r > 256) return HATA_EUNSUPPORTED;
     const int G = f->Hq / f->Hkv;
-    if (G > 16 || (int64_t)G * f->r > 4096) return HATA_EUNSUPPORTED;
+    if (G > 16 || (int64_t)G * f->r > HATA_MAX_NB - 1) return HATA_EUNSUPPORTED;
     if ((int64_t)f->B_max * f->Hkv > 65535 || f->B_max > 65535) return HATA_EUNSUPPORTED;
     return HATA_OK;
 }
@@ -261,7 +261,7 @@ int hata_create_tuned(hata_ctx** ctx_out, const hata_config* cfg, const hata_tun
         delete c;
         return HATA_EHIP;
     }
-    if (hata::prepare_topk(c) != hipSuccess || hata::prepare_attention(c) != hipSuccess || hata::prepare_dense() != hipSuccess) {
+    if (hata::prepare_topk() != hipSuccess || hata::prepare_attention(c) != hipSuccess || hata::prepare_dense() != hipSuccess) {
         delete c;
         return HATA_EHIP;
     }

@@ -8,6 +8,8 @@
 // Words between the arrival counters of consecutive units (128 bytes:
 // the workgroups of different units then never queue their arrivals on one cache line).
 #define HATA_COUNTER_STRIDE 32
+// score values of the largest group and code: G * r + 1
+#define HATA_MAX_NB 4097
 // dense attention: at most this many rounds of one workgroup per CU, with a partial result each
 #define HATA_DENSE_ROUNDS 4
 // 64-bit words between the records of consecutive chunks (two are used): a cache line per chunk, so
@@ -86,7 +88,7 @@ hipError_t launch_score(const hata_ctx* c, const uint32_t* qcodes, const uint32_
 hipError_t prepare_dense();  // once per context
 hipError_t launch_dense(const hata_ctx* c, const void* q, const void* K, const void* V, const int32_t* seq_len, int B,
                         float sm_scale, void* out, float* out_f32, hipStream_t s);
-hipError_t prepare_topk(const hata_ctx* c);       // once per context
+hipError_t prepare_topk();   // once per context
 hipError_t prepare_attention(const hata_ctx* c);  // once per context
 hipError_t launch_topk(const hata_ctx* c, const uint16_t* scores, const int32_t* seq_len,
                        const int32_t* k, int B, int32_t* idx, hipStream_t s);

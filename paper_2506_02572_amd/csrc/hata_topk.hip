@@ -224,15 +224,16 @@ __global__ __launch_bounds__(1024) void topk_unit_kernel(const uint16_t* __restr
         if (pos < keff) out[pos] = n0 + (NV > 4 ? __ffsll((unsigned long long)m) : __ffs((uint32_t)m)) - 1;
 }
 
-static size_t topk_unit_lds(const hata_ctx* c, int nv) { return (size_t)nv * 16384 + (size_t)c->NB * 4; }
+static size_t topk_unit_lds(int NB, int nv) { return (size_t)nv * 16384 + (size_t)NB * 4; }
 
-// (more than 64 KB of dynamic LDS has to be asked for)
-hipError_t prepare_topk(const hata_ctx* c) {
+// (more than 64 KB of dynamic LDS has to be asked for: what the largest number of score values takes, since the limit
+// belongs to the kernel and every context sets it)
+hipError_t prepare_topk() {
     hipError_t e = hipFuncSetAttribute((const void*)topk_unit_kernel<4>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)topk_unit_lds(c, 4));
+                                       (int)topk_unit_lds(HATA_MAX_NB, 4));
     if (e != hipSuccess) return e;
     return hipFuncSetAttribute((const void*)topk_unit_kernel<8>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)topk_unit_lds(c, 8));
+                               (int)topk_unit_lds(HATA_MAX_NB, 8));
 }
 
 hipError_t launch_topk(const hata_ctx* c, const uint16_t* scores, const int32_t* seq_len,
@@ -243,7 +244,7 @@ hipError_t launch_topk(const hata_ctx* c, const uint16_t* scores, const int32_t*
     const int words = (f.L_cap + shift + 8191) / 8192;
     if (words <= 8) {  // (the scores fit in LDS)
 #define HATA_LAUNCH_UNIT(NV)                                                                                      \
-    hipLaunchKernelGGL((topk_unit_kernel<NV>), dim3(f.Hkv, B), dim3(1024), topk_unit_lds(c, NV), s, scores, seq_len, \
+    hipLaunchKernelGGL((topk_unit_kernel<NV>), dim3(f.Hkv, B), dim3(1024), topk_unit_lds(c->NB, NV), s, scores, seq_len, \
                        k, idx, f.Hkv, f.L_cap, f.k_max, c->NB, (int64_t)B * f.Hkv * f.L_cap)
         if (words <= 1) HATA_LAUNCH_UNIT(1);
         else if (words <= 2) HATA_LAUNCH_UNIT(2);

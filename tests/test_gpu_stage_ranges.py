@@ -59,6 +59,26 @@ def test_selection(L_cap, kind):
     ctx.close()
 
 
+def test_selection_after_a_context_of_fewer_score_values():
+    """The LDS a launch may ask for is the kernel's, not a context's: a later, smaller context does not take it away."""
+    import torch
+    from paper_2506_02572_amd import hata
+    k_max = 300
+    for L_cap in (32768, 65536):
+        print(f"[stages] two contexts, L_cap={L_cap}", flush=True)
+        first = hata.Context(1, 16, 1, 128, 256, L_cap, k_max)
+        later = hata.Context(1, 1, 1, 128, 32, L_cap, k_max)
+        rng = np.random.default_rng(L_cap)
+        seq, k = np.array([L_cap], np.int32), np.array([k_max], np.int32)
+        for ctx, top in ((later, 33), (first, 4097)):
+            s = rng.integers(top // 2, top, (1, 1, L_cap)).astype(np.uint16)
+            idx = torch.full((1, 1, k_max), -7, dtype=torch.int32, device="cuda")
+            ctx.hata_topk(H.to_dev(s), H.to_dev(seq), H.to_dev(k), 1, idx)
+            torch.cuda.synchronize()
+            assert np.array_equal(H.to_host(idx), O.topk_batch(s, seq, k, k_max))
+            ctx.close()
+
+
 @pytest.mark.parametrize("L,k_max,chunk", [(1, 1, 0), (1024, 200, 1024), (1025, 1025, 1024), (20011, 700, 1024),
                                            (40000, 512, 1024), (40000, 3000, 8192)])
 @pytest.mark.parametrize("heads", [(5, 1), (2, 2), (8, 1)])
