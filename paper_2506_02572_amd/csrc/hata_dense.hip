@@ -8,7 +8,12 @@
 //     only waits in the loop are the ones for a tile's own K and V), whole 256-byte rows per 16 lanes.  The 16-byte
 //     pieces of row r are stored in the order piece ^ swizzle(r), which makes both kinds of reads below free
 //     of bank conflicts.
-//   - The contractions are those of attn_rows_mfma (hata_attn_core.h), heads padded to 16.
+//   - The contractions are those of attn_rows_mfma (hata_attn_core.h), heads padded to 16, with the softmax weights as
+//     two bf16 terms -- for the groups whose sparse attention takes them that way too (tiles of four heads or
+//     more).  The other groups' weights stay fp32, and products with them are as in plain fp32 also where a value is
+//     infinite: with one or two heads on the vector ALU (the padding repeats the heads, so a lane has the weights of
+//     its rows), else in the fp32 matrix instructions, 32 a tile instead of 8 (two heads that way,
+//     16 KV heads of 32768 rows: 52 us; on the vector ALU 45).
 // Measured at B = 1, 8 KV heads, 32768 rows (134 MB), groups of 4 and 8 heads: 25.7 and 29.2 us; four waves per
 // workgroup with loads through registers and 64 partial results per unit took 36.8 and 48.7.  B = 4, 65536 rows,
 // groups of 8 (1.07 GB): 167 us, 6.4 TB/s (209).
@@ -24,6 +29,7 @@ namespace hata {
 #define DENSE_WAVES 8
 #define DENSE_RING 2           // tiles in flight per wave
 #define DENSE_TILE_BYTES 8192  // 16 rows of K, 16 rows of V
+#define DENSE_RUN 4            // tiles (of a wave) summed in a row where the weights stay fp32
 #define DENSE_BATCH 16         // partial results in flight per thread in the merge
 
 struct DenseArgs {
@@ -39,6 +45,9 @@ struct DenseArgs {
     float scale_log2;
 };
 
+// two heads in the even and odd lanes: the neighbour's value
+__device__ __forceinline__ float other_head(float v) { return HATA_DPP(v, 0xB1); }  // quad_perm [1,0,3,2]
+
 __device__ __forceinline__ int dense_swizzle(int r) { return ((r << 1) | (r >> 3)) & 15; }
 
 template <int N>
@@ -53,6 +62,8 @@ __device__ __forceinline__ void wait_tile(int tiles_after) {
 }
 
 // grid = (splits, Hkv, B)
+enum DenseForm { DENSE_BF16X2, DENSE_FP32_ONE_HEAD, DENSE_FP32_TWO_HEADS, DENSE_FP32 };
+template <DenseForm FORM>
 __global__ __launch_bounds__(DENSE_WAVES * 64) void dense_kernel(const DenseArgs a) {
     // ring[wave][DENSE_RING][DENSE_TILE_BYTES]; afterwards the waves' states, the merge weights and sums
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -67,7 +78,7 @@ __global__ __launch_bounds__(DENSE_WAVES * 64) void dense_kernel(const DenseArgs
     const int L = clampi(a.seq_len[b], 0, a.L_cap);
     uint4 qb[4];
     {
-        const uint16_t* q0 = a.q + (hq0 + min(n, G - 1)) * HATA_D + 8 * kg;
+        const uint16_t* q0 = a.q + (hq0 + (FORM == DENSE_FP32_TWO_HEADS ? n & 1 : min(n, G - 1))) * HATA_D + 8 * kg;
 #pragma unroll
         for (int s = 0; s < 4; ++s) qb[s] = *reinterpret_cast<const uint4*>(q0 + 32 * s);
     }
@@ -122,6 +133,15 @@ __global__ __launch_bounds__(DENSE_WAVES * 64) void dense_kernel(const DenseArgs
     f32x4_t acc[8];
 #pragma unroll
     for (int c = 0; c < 8; ++c) acc[c] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+    // fp32 forms: sums of DENSE_RUN tiles are added up here, so that no sum is a long chain of small addends (a long chain
+    // doubled the error against fp64 at 32768 rows: 4.2e-7 against 2.0e-7).  On the vector ALU acc[2 i] and acc[2 i + 1]
+    // are channels 8 n .. 8 n + 7 over rows 4 kg .. 4 kg + 3, of head n % VH (i = 0) and of the other one (i = 1).
+    constexpr bool FP32W = FORM != DENSE_BF16X2;
+    constexpr int VH = FORM == DENSE_FP32_ONE_HEAD ? 1 : FORM == DENSE_FP32_TWO_HEADS ? 2 : 0;  // heads on the vector ALU
+    constexpr int NT = VH ? 2 * VH : FP32W ? 8 : 1;
+    [[maybe_unused]] f32x4_t total[NT];
+#pragma unroll
+    for (int c = 0; c < NT; ++c) total[c] = acc[c];
     // K operand: row n, piece 4 s + kg; V operand: row 4 kg + n / 4, channels 16 c + 4 (n % 4), piece 2 c + (n % 4) / 2
     const uint32_t k_at = n * 256 + ((kg ^ dense_swizzle(n)) << 4);
     const int vr = 4 * kg + n / 4;
@@ -131,12 +151,14 @@ __global__ __launch_bounds__(DENSE_WAVES * 64) void dense_kernel(const DenseArgs
         const int after = mine - 1 - j;
         const int left = min(L - (t_begin + wave + DENSE_WAVES * j) * 16, 16);
         wait_tile<4>(after);
-        f32x4_t sacc = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+        // (fp32 forms: four sums of 32 channels instead of one of 128, for the same reason as above)
+        f32x4_t sacc, part[4];
 #pragma unroll
         for (int s = 0; s < 4; ++s)
-            sacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+            part[s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
                 __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(t + (k_at ^ (s << 6)))),
-                __builtin_bit_cast(bf16x8_t, qb[s]), sacc, 0, 0, 0);
+                __builtin_bit_cast(bf16x8_t, qb[s]), s == 0 || FP32W ? (f32x4_t){0.f, 0.f, 0.f, 0.f} : part[s - (s > 0)], 0, 0, 0);
+        sacc = FP32W ? (part[0] + part[1]) + (part[2] + part[3]) : part[3];
         // online softmax of head n over the rows 4 kg .. 4 kg + 3 this lane holds
         float sv[4], m_tile = HATA_NEG_INF;
 #pragma unroll
@@ -157,24 +179,41 @@ __global__ __launch_bounds__(DENSE_WAVES * 64) void dense_kernel(const DenseArgs
         m_run = m_new;
         if (__builtin_amdgcn_ballot_w64(alpha != 1.f) != 0ull) {
 #pragma unroll
-            for (int c = 0; c < 8; ++c) acc[c] *= alpha;
+            for (int c = 0; c < (FP32W ? NT : 8); ++c) {
+                const float f = VH && c >= 2 ? other_head(alpha) : alpha;
+                acc[c] *= f;
+                if constexpr (FP32W) total[c] *= f;
+            }
         }
         // P as two bf16 terms: hi = p truncated to bf16, lo = (p - hi) truncated to bf16
-        uint32_t hb[4], lb[4];
+        [[maybe_unused]] uint4 pb;
+        if constexpr (!FP32W) {
+            uint32_t hb[4], lb[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            hb[r] = __float_as_uint(p[r]) & 0xffff0000u;
-            lb[r] = __float_as_uint(p[r] - __uint_as_float(hb[r]));
+            for (int r = 0; r < 4; ++r) {
+                hb[r] = __float_as_uint(p[r]) & 0xffff0000u;
+                lb[r] = __float_as_uint(p[r] - __uint_as_float(hb[r]));
+            }
+            pb = make_uint4((hb[0] >> 16) | hb[1], (hb[2] >> 16) | hb[3],
+                            (lb[0] >> 16) | (lb[1] & 0xffff0000u), (lb[2] >> 16) | (lb[3] & 0xffff0000u));
         }
-        const uint4 pb = make_uint4((hb[0] >> 16) | hb[1], (hb[2] >> 16) | hb[3],
-                                    (lb[0] >> 16) | (lb[1] & 0xffff0000u), (lb[2] >> 16) | (lb[3] & 0xffff0000u));
         wait_tile<0>(after);
-        uint2 v[8];
+        uint2 v[8];  // vector ALU: 8 channels of rows 4 kg .. 4 kg + 3, else four rows of channel 16 c + n
+        if constexpr (VH > 0) {
 #pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            const s16x4_t av = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                (__attribute__((address_space(3))) s16x4_t*)const_cast<char*>(t + (v_at ^ (c << 5))));
-            v[c] = __builtin_bit_cast(uint2, av);
+            for (int r = 0; r < 4; ++r) {
+                const int row = 4 * kg + r;
+                const uint4 x = *reinterpret_cast<const uint4*>(t + 4096 + row * 256 + ((n ^ dense_swizzle(row)) << 4));
+                v[2 * r] = make_uint2(x.x, x.y);
+                v[2 * r + 1] = make_uint2(x.z, x.w);
+            }
+        } else {
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                const s16x4_t av = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                    (__attribute__((address_space(3))) s16x4_t*)const_cast<char*>(t + (v_at ^ (c << 5))));
+                v[c] = __builtin_bit_cast(uint2, av);
+            }
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // every read of this slot has returned
         if (left < 16) {  // the copies of the last row past the end: p = 0, and 0 for infinite values
@@ -182,18 +221,56 @@ __global__ __launch_bounds__(DENSE_WAVES * 64) void dense_kernel(const DenseArgs
             const uint32_t lo = keep >= 2 ? 0xffffffffu : keep == 1 ? 0xffffu : 0u;
             const uint32_t hi = keep >= 4 ? 0xffffffffu : keep == 3 ? 0xffffu : 0u;
 #pragma unroll
-            for (int c = 0; c < 8; ++c) { v[c].x &= lo; v[c].y &= hi; }
+            for (int c = 0; c < 8; ++c) {
+                if constexpr (VH > 0) {
+                    if (c / 2 >= keep) v[c] = make_uint2(0, 0);
+                } else {
+                    v[c].x &= lo; v[c].y &= hi;
+                }
+            }
         }
         if (after >= DENSE_RING) request(j + DENSE_RING);
+        if constexpr (FP32W) {
+            if constexpr (VH > 0) {
 #pragma unroll
-        for (int c = 0; c < 8; ++c)
-            acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, make_uint4(v[c].x, v[c].y, v[c].x, v[c].y)),
-                                                             __builtin_bit_cast(bf16x8_t, pb), acc[c], 0, 0, 0);
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int c = 0; c < NT; ++c) {
+                        const uint2 w = v[2 * r + (c & 1)];
+                        const float f = c >= 2 ? other_head(p[r]) : p[r];
+                        acc[c][0] = fmaf(f, bf16_lo(w.x), acc[c][0]);
+                        acc[c][1] = fmaf(f, bf16_hi(w.x), acc[c][1]);
+                        acc[c][2] = fmaf(f, bf16_lo(w.y), acc[c][2]);
+                        acc[c][3] = fmaf(f, bf16_hi(w.y), acc[c][3]);
+                    }
+            } else {
+                // rows 4 kg + r in one product: lane (n, kg) has V of channel 16 c + n and the weight of head n
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int c = 0; c < 8; ++c) {
+                        const uint32_t w = r < 2 ? v[c].x : v[c].y;
+                        acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32((r & 1) ? bf16_hi(w) : bf16_lo(w), p[r], acc[c], 0, 0, 0);
+                    }
+            }
+            if (j % DENSE_RUN == DENSE_RUN - 1 || after == 0) {
+#pragma unroll
+                for (int c = 0; c < NT; ++c) {
+                    total[c] += acc[c];
+                    acc[c] = after == 0 ? total[c] : (f32x4_t){0.f, 0.f, 0.f, 0.f};
+                }
+            }
+        } else {
+#pragma unroll
+            for (int c = 0; c < 8; ++c)
+                acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, make_uint4(v[c].x, v[c].y, v[c].x, v[c].y)),
+                                                                 __builtin_bit_cast(bf16x8_t, pb), acc[c], 0, 0, 0);
+        }
     };
     for (int j = 0; j < min(mine, DENSE_RING); ++j) request(j);
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
-        if (n >= G) qb[s] = make_uint4(0, 0, 0, 0);
+        if (!VH && n >= G) qb[s] = make_uint4(0, 0, 0, 0);
         // (used here, so that the wait for these loads is not in the loop)
         asm volatile("" : "+v"(qb[s].x), "+v"(qb[s].y), "+v"(qb[s].z), "+v"(qb[s].w));
     }
@@ -203,7 +280,17 @@ __global__ __launch_bounds__(DENSE_WAVES * 64) void dense_kernel(const DenseArgs
     __syncthreads();  // the ring is no longer read
     float* s_acc = reinterpret_cast<float*>(smem);  // [DENSE_WAVES][G][HATA_D + 4]
     l_run = rows_sum4(l_run);
-    if (n < G) {
+    if constexpr (VH > 0) {
+#pragma unroll
+        for (int i = 0; i < 4 * NT; ++i) acc[i / 4][i % 4] = rows_sum4(acc[i / 4][i % 4]);
+        if (kg == 0) {
+            if (n < VH) { s_m[wave][n] = m_run; s_l[wave][n] = l_run; }
+#pragma unroll
+            for (int c = 0; c < NT; ++c)
+                *reinterpret_cast<float4*>(&s_acc[(wave * VH + (n + c / 2) % VH) * (HATA_D + 4) + 8 * n + 4 * (c & 1)]) =
+                    make_float4(acc[c][0], acc[c][1], acc[c][2], acc[c][3]);
+        }
+    } else if (n < G) {
         if (kg == 0) { s_m[wave][n] = m_run; s_l[wave][n] = l_run; }
 #pragma unroll
         for (int c = 0; c < 8; ++c)  // acc[c][r] = O[head n][channel 16 c + 4 kg + r]
@@ -345,7 +432,12 @@ static int dense_splits(int64_t units, int L_cap) {
 }
 
 hipError_t prepare_dense() {  // (more than 64 KB of dynamic LDS has to be asked for)
-    return hipFuncSetAttribute((const void*)dense_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dense_lds());
+    for (const void* fn : {(const void*)dense_kernel<DENSE_BF16X2>, (const void*)dense_kernel<DENSE_FP32>,
+                           (const void*)dense_kernel<DENSE_FP32_ONE_HEAD>, (const void*)dense_kernel<DENSE_FP32_TWO_HEADS>}) {
+        const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dense_lds());
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_dense(const hata_ctx* c, const void* q, const void* K, const void* V, const int32_t* seq_len, int B,
@@ -360,7 +452,10 @@ hipError_t launch_dense(const hata_ctx* c, const void* q, const void* K, const v
     a.n_splits = dense_splits((int64_t)f.Hkv * B, f.L_cap);
     a.sb = f.kv_stride_b; a.sh = f.kv_stride_h; a.sn = f.kv_stride_n;
     a.scale_log2 = sm_scale * 1.4426950408889634f;
-    hipLaunchKernelGGL(dense_kernel, dim3(a.n_splits, f.Hkv, B), dim3(DENSE_WAVES * 64), dense_lds(), s, a);
+    const dim3 grid(a.n_splits, f.Hkv, B);
+    const auto fn = c->HT >= 4 ? dense_kernel<DENSE_BF16X2> : c->G == 1 ? dense_kernel<DENSE_FP32_ONE_HEAD>
+                    : c->G == 2 ? dense_kernel<DENSE_FP32_TWO_HEADS> : dense_kernel<DENSE_FP32>;
+    hipLaunchKernelGGL(fn, grid, dim3(DENSE_WAVES * 64), dense_lds(), s, a);
     return hipGetLastError();
 }
 

@@ -105,7 +105,7 @@ def test_chunk_owned_attention(L, k_max, chunk, heads):
     c.ctx.close()
 
 
-@pytest.mark.parametrize("G", [1, 3, 4, 5, 8, 16])
+@pytest.mark.parametrize("G", [1, 2, 3, 4, 5, 8, 16])
 @pytest.mark.parametrize("lens", [(1, 0, 15), (16, 17, 127), (129, 128, 2047), (4099, 20000, 300)])
 def test_dense_attention(G, lens):
     import torch
@@ -200,3 +200,62 @@ def test_encode_keys_of_many_units(r):
     ref, near = O.encode_keys_batch(K, W, start, n_new, codes=before.copy(), bulk=True)
     H.check_codes(H.to_host(codes, np.uint32), ref, near, "keys")
     ctx.close()
+
+
+# groups whose weights stay fp32: no tile of four heads or more divides them
+FP32_GROUPS = [1, 2, 3, 6, 7, 9, 11, 13, 14]
+
+
+def dense(G, q, K, V, seq):
+    """One KV head per sequence; q, K, V as fp32 arrays of bf16 values.  Returns the fp32 and the bf16 output."""
+    import torch
+    from paper_2506_02572_amd import hata
+    B, L_cap = K.shape[0], K.shape[1]
+    ctx = hata.Context(B, G, 1, 128, 64, L_cap, 1)
+    out = torch.full((B, G, 128), -7, dtype=torch.int16, device="cuda")
+    out32 = torch.full((B, G, 128), 7.0, dtype=torch.float32, device="cuda")
+    qd, Kd, Vd = (H.to_dev(synth.round_to_bf16_bits(x)) for x in (q, K, V))
+    ctx.hata_dense_decode(qd, Kd, Vd, H.to_dev(seq), B, 128 ** -0.5, out, out32)
+    torch.cuda.synchronize()
+    ctx.close()
+    return H.to_host(out32), H.to_host(out, np.uint16)
+
+
+@pytest.mark.parametrize("G", FP32_GROUPS)
+def test_dense_weights_are_fp32(G):
+    """All values 1: the output is sum(w) / sum(w), 1 up to the rounding of the two sums.  Up to 41 rows a wave adds at
+    most 16 products per channel or 4 weights per lane and 4 lanes, then 8 waves and slices are merged: fewer than 40
+    roundings of 2^-24 in all, 2.4e-6.  Weights cut to 16 bits would be short by 5e-6 on average."""
+    print(f"[stages] dense weights G={G}", flush=True)
+    rng = np.random.default_rng(G)
+    seq = np.array([5, 16, 41, 33], np.int32)
+    K = rng.standard_normal((len(seq), 41, 128)).astype(np.float32)
+    q = (0.1 * rng.standard_normal((len(seq), G, 128))).astype(np.float32)
+    out32, out = dense(G, q, K, np.ones_like(K), seq)
+    assert np.max(np.abs(out32.astype(np.float64) - 1.0)) <= 40 * 2.0 ** -24
+    assert np.all(out == 0x3f80)
+
+
+@pytest.mark.parametrize("G", FP32_GROUPS)
+@pytest.mark.parametrize("L", [3, 40, 700])
+def test_dense_with_infinite_values(G, L):
+    """Infinite values in rows that count, the one with the largest score (weight exactly 1) among them: infinite outputs
+    of their sign in those channels, nothing elsewhere.  Rows past the end are infinite too, and do not count."""
+    print(f"[stages] dense infinities G={G} L={L}", flush=True)
+    rng = np.random.default_rng(L + G)
+    K = rng.standard_normal((1, L + 20, 128)).astype(np.float32)
+    q = (0.3 * rng.standard_normal((1, G, 128))).astype(np.float32)
+    V = rng.standard_normal(K.shape).astype(np.float32)
+    V[:, L:] = np.inf
+    finite = V[0].copy()
+    bits = synth.round_to_bf16_bits(q), synth.round_to_bf16_bits(K)
+    qf, Kf = (synth.bf16_to_f32(b).astype(np.float64) for b in bits)
+    best = int(np.argmax(Kf[0, :L] @ qf[0, 0]))  # of the first head
+    V[0, best, 5], V[0, best, 127], V[0, (best + 1) % L, 64] = np.inf, -np.inf, np.inf
+    out32, _ = dense(G, q, K, V, np.array([L], np.int32))
+    assert np.all(out32[0, :, [5, 64]] == np.inf) and np.all(out32[0, :, 127] == -np.inf)
+    s = qf[0] @ Kf[0, :L].T * 128 ** -0.5
+    w = np.exp(s - s.max(1, keepdims=True))
+    ref = w @ synth.bf16_to_f32(synth.round_to_bf16_bits(finite[:L])).astype(np.float64) / w.sum(1, keepdims=True)
+    rest = np.setdiff1d(np.arange(128), [5, 64, 127])
+    assert np.max(np.abs(out32[0][:, rest] - ref[:, rest])) <= H.ABS_TOL
