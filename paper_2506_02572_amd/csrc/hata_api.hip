@@ -41,6 +41,7 @@ inline size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 struct Plan {
     int G, Wd, NB, NBP, chunk, n_chunks, coop_chunk, HT, sparse_rows, sparse_splits;
+    int64_t dense_wgs_max;
     size_t off_qcodes, off_scores, off_idx, off_hist, off_cinfo, off_uinfo, off_ucnt, off_acnt, off_uflag, off_qrec, off_err, off_uhist, off_partials, off_wplanes, total;
 };
 
@@ -132,6 +133,7 @@ int make_plan(const hata_config* f, const hata_tuning* t, Plan* p) {
     size_t n_partials = (size_t)f->B_max * f->Hq * max_splits;
     const size_t dense_partials = (size_t)256 * HATA_DENSE_ROUNDS * G;  // a workgroup has one per head of its group
     if (n_partials < dense_partials) n_partials = dense_partials;
+    p->dense_wgs_max = (int64_t)(n_partials / G);
     p->off_partials = o; o = align_up(o + n_partials * (128 + 2) * 4);
     p->off_wplanes = o;  o = align_up(o + (size_t)f->Hkv * 2 * 128 * f->r * 2);  // two fp16 planes
     p->total = o;
@@ -236,6 +238,7 @@ int hata_create_tuned(hata_ctx** ctx_out, const hata_config* cfg, const hata_tun
     c->G = p.G; c->Wd = p.Wd; c->NB = p.NB; c->NBP = p.NBP;
     c->chunk = p.chunk; c->n_chunks = p.n_chunks; c->HT = p.HT;
     c->sparse_rows = p.sparse_rows; c->sparse_splits = p.sparse_splits;
+    c->dense_wgs_max = p.dense_wgs_max;
     char* w = (char*)workspace;
     c->qcodes = (uint32_t*)(w + p.off_qcodes);
     c->scores = (uint16_t*)(w + p.off_scores);

@@ -3,7 +3,8 @@
 //
 // Bound by the HBM stream: every K and V row is read once for all query heads of its group.
 //   - A workgroup of eight waves owns a run of 16-row tiles; the launch is sized to one workgroup per CU, so that
-//     the tail of the stream and the number of partial results to merge are both small.
+//     the tail of the stream and the number of partial results to merge are both small, and dealt out by the
+//     sequences' lengths (dense_share), so that it stays even when one of them is long and the others are not.
 //   - Every wave requests its tiles with direct loads into a wave-private LDS ring (no registers, no barriers: the
 //     only waits in the loop are the ones for a tile's own K and V), whole 256-byte rows per 16 lanes.  The 16-byte
 //     pieces of row r are stored in the order piece ^ swizzle(r), which makes both kinds of reads below free
@@ -30,6 +31,7 @@ namespace hata {
 #define DENSE_RING 2           // tiles in flight per wave
 #define DENSE_TILE_BYTES 8192  // 16 rows of K, 16 rows of V
 #define DENSE_RUN 4            // tiles (of a wave) summed in a row where the weights stay fp32
+#define DENSE_MAX_RUNS 256     // of a unit (four partial results per lane in the merge)
 #define DENSE_BATCH 16         // partial results in flight per thread in the merge
 
 struct DenseArgs {
@@ -40,7 +42,7 @@ struct DenseArgs {
     int counter_stride;
     uint16_t* out;
     float* out_f32;
-    int Hq, Hkv, G, L_cap, n_splits;
+    int Hq, Hkv, G, B, L_cap;
     int64_t sb, sh, sn;
     float scale_log2;
 };
@@ -61,7 +63,72 @@ __device__ __forceinline__ void wait_tile(int tiles_after) {
     else wait_vm<FIRST>();
 }
 
-// grid = (splits, Hkv, B)
+// What a workgroup of the launch works on: split `split` of the ns runs that unit (b, h) is cut into, `first` the
+// workgroup that has its first one
+struct DenseShare { int b, h, L, split, ns, first; };
+
+// The launch's workgroups (at least one per unit) in proportion to the sequences' lengths: the shortest run length, from
+// an even share of all tiles and a tile per wave up in steps of an eighth, at which the units' runs are no more than
+// the workgroups.  (Cut by the longest sequence there could be, 16 sequences of which one has 32768 rows and the others
+// 2048 took 167 us, this takes 50; 8 KV heads.)  Every wave of every workgroup computes the same; false: nothing left for this one.
+__device__ __forceinline__ bool dense_share(const int32_t* __restrict__ seq_len, int B, int Hkv, int L_cap, DenseShare& d) {
+    const int wg = blockIdx.x, wgs = gridDim.x;
+    if (B == 1) {  // nothing to weigh up: which head this is does not wait for the length
+        const int per = wgs / Hkv;
+        d.b = 0;
+        d.h = wg / per;
+        d.split = wg - d.h * per;
+        d.first = wg - d.split;
+        d.L = clampi(seq_len[0], 0, L_cap);
+        d.ns = clampi(((d.L + 15) / 16 + DENSE_WAVES - 1) / DENSE_WAVES, 1, per);
+        return d.split < d.ns;
+    }
+    const int lane = threadIdx.x & 63;
+    auto length = [&](int b) { return b < B ? clampi(seq_len[b], 0, L_cap) : -1; };
+    const int own = length(lane);  // the only round trip for up to 64 sequences
+    auto of = [&](int b0) { return b0 == 0 ? own : length(b0 + lane); };
+    // (a sequence without rows: one workgroup writes zeros)
+    auto tiles = [](int L) { return L >= 0 ? (max(L, 1) + 15) / 16 : 0; };
+    float all = 0.f, longest = 0.f;
+    for (int b0 = 0; b0 < B; b0 += 64) {
+        const float t = (float)tiles(of(b0));
+        all += wave_sum64(t);
+        longest = fmaxf(longest, wave_max64(t));
+    }
+    int run = max(max(DENSE_WAVES, (int)ceilf(all * (float)Hkv * __builtin_amdgcn_rcpf((float)wgs))),
+                  ((int)longest + DENSE_MAX_RUNS - 1) / DENSE_MAX_RUNS);
+    // (exact below 2^20, and a cache has fewer tiles)
+    auto runs = [&](int L) { return (uint32_t)(((float)(tiles(L) + run - 1) + 0.5f) * __builtin_amdgcn_rcpf((float)run)); };
+    uint32_t upto;  // runs of the sequences up to this lane's, of the last 64 looked at
+    for (;; run += max(1, run >> 3)) {  // (ends at the longest sequence's tiles at the latest: one run a unit)
+        uint32_t n = 0;
+        for (int b0 = 0; b0 < B; b0 += 64) {
+            upto = wave_incl_scan(runs(of(b0)));
+            n += (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
+        }
+        if (n * (uint32_t)Hkv <= (uint32_t)wgs || run >= (int)longest) break;
+    }
+    int before = 0;
+    for (int b0 = 0; b0 < B; b0 += 64) {
+        const int L = of(b0), n = (int)runs(L);
+        if (B > 64) upto = wave_incl_scan((uint32_t)n);
+        const unsigned long long past = __builtin_amdgcn_ballot_w64(before + Hkv * (int)upto > wg);
+        if (past) {
+            const int l = __ffsll(past) - 1;
+            d.b = b0 + l;
+            d.L = __builtin_amdgcn_readlane(L, l);
+            d.ns = __builtin_amdgcn_readlane(n, l);
+            const int in_seq = wg - before - Hkv * (__builtin_amdgcn_readlane((int)upto, l) - d.ns);
+            d.h = in_seq / d.ns;
+            d.split = in_seq - d.h * d.ns;
+            d.first = wg - d.split;
+            return true;
+        }
+        before += Hkv * __builtin_amdgcn_readlane((int)upto, 63);
+    }
+    return false;
+}
+
 enum DenseForm { DENSE_BF16X2, DENSE_FP32_ONE_HEAD, DENSE_FP32_TWO_HEADS, DENSE_FP32 };
 template <DenseForm FORM>
 __global__ __launch_bounds__(DENSE_WAVES * 64) void dense_kernel(const DenseArgs a) {
@@ -71,29 +138,26 @@ __global__ __launch_bounds__(DENSE_WAVES * 64) void dense_kernel(const DenseArgs
     __shared__ int s_last;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 15, kg = lane >> 4;
-    const int split = blockIdx.x, h = blockIdx.y, b = blockIdx.z, G = a.G;
+    DenseShare d;
+    if (!dense_share(a.seq_len, a.B, a.Hkv, a.L_cap, d)) return;
+    const int split = d.split, ns = d.ns, h = d.h, b = d.b, L = d.L, G = a.G;
     const int64_t u = (int64_t)b * a.Hkv + h, hq0 = (int64_t)b * a.Hq + (int64_t)h * G;
     uint16_t* outp = a.out + hq0 * HATA_D;
     float* outp32 = a.out_f32 ? a.out_f32 + hq0 * HATA_D : nullptr;
-    const int L = clampi(a.seq_len[b], 0, a.L_cap);
     uint4 qb[4];
     {
         const uint16_t* q0 = a.q + (hq0 + (FORM == DENSE_FP32_TWO_HEADS ? n & 1 : min(n, G - 1))) * HATA_D + 8 * kg;
 #pragma unroll
         for (int s = 0; s < 4; ++s) qb[s] = *reinterpret_cast<const uint4*>(q0 + 32 * s);
     }
-    // the unit's tiles in even runs, at least one tile per wave
-    const int tiles = (L + 15) / 16;
-    const int ns = min(a.n_splits, (tiles + DENSE_WAVES - 1) / DENSE_WAVES);
-    if (split >= ns) {
-        if (split == 0) {  // no row at all
-            for (int i = tid; i < G * HATA_D; i += DENSE_WAVES * 64) {
-                outp[i] = 0;
-                if (outp32) outp32[i] = 0.f;
-            }
+    if (L == 0) {  // no row at all
+        for (int i = tid; i < G * HATA_D; i += DENSE_WAVES * 64) {
+            outp[i] = 0;
+            if (outp32) outp32[i] = 0.f;
         }
         return;
     }
+    const int tiles = (L + 15) / 16;  // in even runs
     const int t_begin = (int)((int64_t)tiles * split / ns), t_end = (int)((int64_t)tiles * (split + 1) / ns);
     const int mine = max(0, (t_end - t_begin - wave + DENSE_WAVES - 1) / DENSE_WAVES);  // tiles t_begin + wave + 8 j
 
@@ -298,8 +362,8 @@ __global__ __launch_bounds__(DENSE_WAVES * 64) void dense_kernel(const DenseArgs
                 make_float4(acc[c][0], acc[c][1], acc[c][2], acc[c][3]);
     }
     __syncthreads();
-    const int64_t head_stride = (int64_t)a.n_splits * HATA_PSTRIDE;
-    float* part0 = a.partials + hq0 * head_stride;
+    const int64_t head_stride = (int64_t)ns * HATA_PSTRIDE;
+    float* part0 = a.partials + (int64_t)d.first * G * HATA_PSTRIDE;  // the unit's: [G][ns]
     for (int i = tid; i < G * HATA_D; i += DENSE_WAVES * 64) {
         const int g = i / HATA_D, ch = i % HATA_D;
         float M = s_m[0][g];
@@ -423,7 +487,7 @@ static int dense_splits(int64_t units, int L_cap) {
     int best = 1;
     int64_t best_cost = INT64_MAX;
     for (int m = 0; m <= HATA_DENSE_ROUNDS; ++m) {
-        const int64_t s = m == 0 ? 1 : std::min(256 * m / units, (int64_t)std::min(256, (L_cap + 127) / 128));
+        const int64_t s = m == 0 ? 1 : std::min(256 * m / units, (int64_t)std::min(DENSE_MAX_RUNS, (L_cap + 127) / 128));
         if (s < 1) continue;
         const int64_t cost = (units * s + 256 - 1) / 256 * ((L_cap + s - 1) / s + 256);
         if (cost < best_cost) { best_cost = cost; best = (int)s; }
@@ -449,10 +513,13 @@ hipError_t launch_dense(const hata_ctx* c, const void* q, const void* K, const v
     a.partials = c->partials; a.counter = c->attn_counter; a.counter_stride = c->attn_counter_stride;
     a.out = (uint16_t*)out; a.out_f32 = out_f32;
     a.Hq = f.Hq; a.Hkv = f.Hkv; a.G = c->G; a.L_cap = f.L_cap;
-    a.n_splits = dense_splits((int64_t)f.Hkv * B, f.L_cap);
+    a.B = B;
+    // one run a unit is even only among sequences of one length: workgroups to spare for the long ones
+    const int64_t units = (int64_t)f.Hkv * B, splits = dense_splits(units, f.L_cap);
+    const int64_t spare = splits == 1 && B > 1 ? std::max((int64_t)0, std::min((int64_t)256, c->dense_wgs_max - units)) : 0;
     a.sb = f.kv_stride_b; a.sh = f.kv_stride_h; a.sn = f.kv_stride_n;
     a.scale_log2 = sm_scale * 1.4426950408889634f;
-    const dim3 grid(a.n_splits, f.Hkv, B);
+    const dim3 grid((unsigned)(units * splits + spare));
     const auto fn = c->HT >= 4 ? dense_kernel<DENSE_BF16X2> : c->G == 1 ? dense_kernel<DENSE_FP32_ONE_HEAD>
                     : c->G == 2 ? dense_kernel<DENSE_FP32_TWO_HEADS> : dense_kernel<DENSE_FP32>;
     hipLaunchKernelGGL(fn, grid, dim3(DENSE_WAVES * 64), dense_lds(), s, a);

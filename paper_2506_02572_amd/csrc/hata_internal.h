@@ -31,6 +31,7 @@ struct hata_ctx {
     int coop_opts, coop_opt_chunk[4], coop_opt_cap[4];
     int sparse_rows;  // selected rows per attention workgroup
     int sparse_splits;
+    int64_t dense_wgs_max;  // dense attention: workgroups of a launch that the partials have room for
     // regions of the caller's workspace
     uint32_t* qcodes;      // [B_max, Hq, Wd]
     uint16_t* scores;      // [B_max, Hkv, L_cap]

@@ -259,3 +259,63 @@ def test_dense_with_infinite_values(G, L):
     ref = w @ synth.bf16_to_f32(synth.round_to_bf16_bits(finite[:L])).astype(np.float64) / w.sum(1, keepdims=True)
     rest = np.setdiff1d(np.arange(128), [5, 64, 127])
     assert np.max(np.abs(out32[0][:, rest] - ref[:, rest])) <= H.ABS_TOL
+
+
+def shortest_us(call, turns=9, per_turn=5):
+    import torch
+    call()
+    times = []
+    for _ in range(turns):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(per_turn):
+            call()
+        b.record()
+        torch.cuda.synchronize()
+        times.append(a.elapsed_time(b) * 1000 / per_turn)
+    return min(times)
+
+
+@pytest.mark.parametrize("B,Hkv,G", [(2, 1, 4), (2, 8, 1), (64, 1, 5), (65, 3, 2), (130, 5, 1), (200, 1, 3)])
+@pytest.mark.parametrize("lens", ["one_long", "spread", "equal", "empty"])
+def test_dense_shares_of_unequal_sequences(B, Hkv, G, lens):
+    """Batches on both sides of the 64 sequences a wave looks at together, and of one workgroup per unit."""
+    import torch
+    from paper_2506_02572_amd import hata
+    L_cap = 2500 if B * Hkv < 64 else 900
+    print(f"[stages] dense shares B={B} Hkv={Hkv} {lens}", flush=True)
+    rng = np.random.default_rng(B + G)
+    seq = {"one_long": np.where(np.arange(B) == B // 2, L_cap, rng.integers(0, 40, B)), "spread": rng.integers(0, L_cap + 1, B),
+           "equal": np.full(B, 333), "empty": np.where(np.arange(B) == B - 1, 129, 0)}[lens].astype(np.int32)
+    K, V = (synth.round_to_bf16_bits(rng.standard_normal((B, Hkv, L_cap, 128), dtype=np.float32)) for _ in range(2))
+    q = synth.round_to_bf16_bits(rng.standard_normal((B, Hkv * G, 128)) * 2)
+    ctx = hata.Context(B, Hkv * G, Hkv, 128, 32, L_cap, 1)
+    out = torch.full((B, Hkv * G, 128), -7, dtype=torch.int16, device="cuda")
+    out32 = torch.full((B, Hkv * G, 128), 7.0, dtype=torch.float32, device="cuda")
+    qd, Kd, Vd, sd = (H.to_dev(x) for x in (q, K, V, seq))
+    for _ in range(2):
+        ctx.hata_dense_decode(qd, Kd, Vd, sd, B, 128 ** -0.5, out, out32)
+    torch.cuda.synchronize()
+    ref = O.dense_decode_batch(q, K, V, seq, 128 ** -0.5)
+    H.check_attention(H.to_host(out32), H.to_host(out, np.uint16), np.where(seq[:, None, None] > 0, ref, 0.0), "dense")
+    ctx.close()
+
+
+def test_dense_spreads_the_one_long_sequence_of_a_batch():
+    """One sequence of 32768 rows among 15 of 512 costs about what it costs alone (1.35 times); cut by what the other sequences
+    could hold instead of what they hold, its stream runs on a sixteenth of the chip (5.8 times)."""
+    import torch
+    from paper_2506_02572_amd import hata
+    B, Hkv, G, L = 16, 8, 4, 32768
+    K, V = (torch.randn((B, Hkv, L, 128), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    q = torch.randn((B, Hkv * G, 128), dtype=torch.bfloat16, device="cuda")
+    out = torch.zeros_like(q)
+    seq = torch.full((B,), 512, dtype=torch.int32, device="cuda")
+    seq[0] = L
+    alone, batch = hata.Context(1, Hkv * G, Hkv, 128, 32, L, 1), hata.Context(B, Hkv * G, Hkv, 128, 32, L, 1)
+    t_alone = shortest_us(lambda: alone.hata_dense_decode(q, K, V, seq, 1, 128 ** -0.5, out))
+    t_batch = shortest_us(lambda: batch.hata_dense_decode(q, K, V, seq, B, 128 ** -0.5, out))
+    print(f"[stages] dense alone {t_alone:.1f} us, in the batch {t_batch:.1f} us", flush=True)
+    assert t_batch < 3 * t_alone
+    alone.close()
+    batch.close()
