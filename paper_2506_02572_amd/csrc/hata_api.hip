@@ -115,6 +115,10 @@ int make_plan(const hata_config* f, const hata_tuning* t, Plan* p) {
     if (p->sparse_splits > 256) return HATA_EUNSUPPORTED;  // budget above 65536 rows
     int max_splits = p->sparse_splits;
     if (p->n_chunks > max_splits) max_splits = p->n_chunks;  // the cooperative step: one slice per chunk
+    // the three-launch step: the chunks, and the further pieces of those with many selected rows (launch_attention)
+    int pieces = p->n_chunks > f->k_max / 512 ? p->n_chunks : f->k_max / 512;
+    if (pieces > f->k_max / 64) pieces = f->k_max / 64;
+    if (p->n_chunks + pieces > max_splits) max_splits = p->n_chunks + pieces;
 
     size_t o = 0;
     p->off_qcodes = o;   o = align_up(o + (size_t)f->B_max * f->Hq * p->Wd * 4);

@@ -33,7 +33,7 @@ struct AttnArgs {
     const int32_t* seq_len;
     const int32_t* chunk_info;
     const int32_t* unit_info;
-    int chunk, n_chunks, chunks_per_split;
+    int chunk, n_chunks, chunks_per_split, owners, piece_rows, B;
     float* partials;
     uint32_t* counter;
     int counter_stride;
@@ -44,11 +44,14 @@ struct AttnArgs {
     float scale_log2;
 };
 
-// grid = (splits, Hkv * (G / HT), B); 256 threads.
-// ROWS_SELECT: a split is a chunk (or as many as leave at most 256 splits to merge), so that everything the
-// selection needs -- the chunk's scores, its offset and ties, the threshold -- is at addresses known from the
-// start.  Slices of the index list instead, which had to find their chunks first, took 18.4 us per launch at
-// 16 units of 20011 keys, this takes 10.4.
+// grid = (splits, Hkv * (G / HT), B), in ROWS_SELECT (owners, .., B + layers for the further pieces); 256 threads.
+// ROWS_SELECT: the first `owners` splits are a chunk each (or as many as leave at most 256 splits to merge), so that
+// everything the selection needs -- the chunk's scores, its offset and ties, the threshold -- is at addresses known from
+// the start, and on the XCD that scored the chunk.  Slices of the index list instead, which had to find their chunks first,
+// took 18.4 us per launch at 16 units of 20011 keys, this takes 10.4.  A prompt's selected rows may all lie in a chunk or
+// two, though: an owner attends over the first piece_rows rows of its chunk only, and the further pieces go to the splits
+// behind the owners, which compact that chunk again: 8 units of 131072 keys, 2048 rows all in one place, 64.5 -> 35.0 us a step
+// (31.0 where they are spread, and those splits return at once; 30.6 without them).
 template <int HT, int MODE>
 __global__ __launch_bounds__(256) void attn_kernel(const AttnArgs a) {
     constexpr bool MFMA = HT >= 4;  // matrix-core form of the attention core
@@ -58,11 +61,16 @@ __global__ __launch_bounds__(256) void attn_kernel(const AttnArgs a) {
     __shared__ uint32_t scan4[4];
     __shared__ int s_last;
     const int tid = threadIdx.x;
-    const int split = blockIdx.x;
     const int tiles = a.G / HT;
     const int h = blockIdx.y / tiles;
     const int ht = blockIdx.y % tiles;
-    const int b = blockIdx.z;
+    int split = blockIdx.x, b = blockIdx.z;
+    if (MODE == ROWS_SELECT && b >= a.B) {
+        const int i = (b - a.B) * a.owners + split, further = a.n_splits - a.owners;
+        b = i / further;
+        if (b >= a.B) return;
+        split = a.owners + (i + blockIdx.y) % further;
+    }
     const int64_t u = (int64_t)b * a.Hkv + h;
     const int hq0 = h * a.G + ht * HT;
     uint16_t* outp = a.out + ((int64_t)b * a.Hq + hq0) * HATA_D;
@@ -80,7 +88,7 @@ __global__ __launch_bounds__(256) void attn_kernel(const AttnArgs a) {
             if (outp32) outp32[i] = 0.f;
         }
     };
-    int ns;  // workgroups that contribute
+    int ns, slot = split;  // workgroups that contribute, this one's place among their partial results
     auto attend = [&](int row_begin, int row_end, auto row_of) {
         if constexpr (MFMA)
             attn_rows_mfma<HT>(qb, Kb, Vb, a.sn, a.L_cap, row_begin, row_end, a.scale_log2, row_of, S, s_vt);
@@ -90,21 +98,59 @@ __global__ __launch_bounds__(256) void attn_kernel(const AttnArgs a) {
     if constexpr (MODE == ROWS_SELECT) {
         const int L = clampi(a.seq_len[b], 0, a.L_cap);
         const int T = a.unit_info[u * 2 + 0], keff = clampi(a.unit_info[u * 2 + 1], 0, a.k_max);
-        const int per = a.chunks_per_split, c0 = split * per;
-        const int32_t* ci = a.chunk_info + (u * (a.n_chunks + 1) + c0) * 2;
+        const int per = a.chunks_per_split, span = per * a.chunk;
+        const int32_t* ci_unit = a.chunk_info + u * (a.n_chunks + 1) * 2;
         const int nc = (L + a.chunk - 1) / a.chunk;  // (entry nc closes the list)
-        const int off = ci[0];
-        int take = ci[1];  // ties are granted in cache order, so those of consecutive chunks add up
-        for (int i = 1; i < min(per, nc - c0); ++i) take += ci[2 * i + 1];
-        const int next = ci[2 * clampi(nc - c0, 0, per)];
+        const int live = (L + span - 1) / span;      // owners with keys
         int32_t* io = a.idx_out + u * a.k_max;
-        const int span = per * a.chunk, base = split * span, n_keys = min(span, L - base);
         if (split == 0) {
             if (ht == 0)  // slots of the index list past the selected count hold -1
                 for (int p = keff + tid; p < a.k_max; p += 256) io[p] = -1;
             if (L == 0) zero_output();
         }
-        if (n_keys <= 0) return;
+        auto selected = [&](int s, int first, int next) {
+            return clampi(next - first, 0, min(min(span, L - s * span), a.k_max - clampi(first, 0, a.k_max)));
+        };
+        // pieces beyond an owner's first: lane l looks at owners l, l + 64, ... (the first of them requested now, together
+        // with all else); returns how many there are, and where number `nth` of them is
+        const int lane = tid & 63;
+        auto entry = [&](int s) { return ci_unit[2 * min(s * per, a.n_chunks)]; };
+        const int first0 = entry(lane), next0 = entry(lane + 1);
+        const float half_inv = 0.5f * __builtin_amdgcn_rcpf((float)a.piece_rows);  // (rows - 1) / piece_rows, exact below 2^20
+        auto further_pieces = [&](int nth, int& own, int& piece) {
+            int extra = 0;
+            for (int s0 = 0; s0 < live; s0 += 64) {
+                const int s = s0 + lane;
+                const int first = s0 == 0 ? first0 : entry(s);
+                const int next = (s + 1) * per > nc ? keff : s0 == 0 ? next0 : entry(s + 1);
+                const int rows = s < live ? selected(s, first, next) : 0;
+                const int more = rows > 0 ? (int)((float)(2 * rows - 1) * half_inv) : 0;
+                if (__builtin_amdgcn_ballot_w64(more > 0) == 0) continue;
+                const int upto = extra + (int)wave_incl_scan((uint32_t)more);
+                const unsigned long long past = __builtin_amdgcn_ballot_w64(extra <= nth && upto > nth);
+                if (past) {
+                    const int l = __ffsll(past) - 1;
+                    own = s0 + l;
+                    piece = nth - __builtin_amdgcn_readlane(upto - more, l) + 1;
+                }
+                extra = __builtin_amdgcn_readlane(upto, 63);
+            }
+            return min(extra, a.n_splits - a.owners);
+        };
+        int own = split, piece = 0, extra = 0;
+        if (split >= a.owners) {
+            extra = further_pieces(split - a.owners, own, piece);
+            if (split - a.owners >= extra) return;
+            slot = live + split - a.owners;
+        } else if (split >= live) {
+            return;
+        }
+        const int c0 = own * per, base = own * span, n_keys = min(span, L - base);
+        const int32_t* ci = ci_unit + c0 * 2;
+        const int off = ci[0];
+        int take = ci[1];  // ties are granted in cache order, so those of consecutive chunks add up
+        for (int i = 1; i < min(per, nc - c0); ++i) take += ci[2 * i + 1];
+        const int next = ci[2 * clampi(nc - c0, 0, per)];
         const uint16_t* sp = a.scores + u * a.L_cap + base;
         const bool whole = (reinterpret_cast<uintptr_t>(sp) & 15) == 0;
         for (int i = tid * 8; i < n_keys; i += 256 * 8) {
@@ -115,15 +161,16 @@ __global__ __launch_bounds__(256) void attn_kernel(const AttnArgs a) {
             }
         }
         __syncthreads();
-        const int cnt = clampi(next - off, 0, min(n_keys, a.k_max - clampi(off, 0, a.k_max)));
+        const int cnt = selected(own, off, next);
         if (cnt > 0)  // (the same for the whole workgroup)
             compact_lds(s_sc, n_keys, span / 256, T, take, cnt, scan4, [&](int r, int n) {
                 s_sc[r] = (uint16_t)n;
-                if (ht == 0) io[off + r] = base + n;
+                if (ht == 0 && piece == 0) io[off + r] = base + n;
             });
         __syncthreads();
-        attend(0, cnt, [&](int row) { return base + (int)s_sc[row]; });
-        ns = (L + span - 1) / span;
+        attend(piece * a.piece_rows, min(cnt, (piece + 1) * a.piece_rows), [&](int row) { return base + (int)s_sc[row]; });
+        if (piece == 0) extra = further_pieces(-1, own, piece);
+        ns = live + extra;
     } else {
         const int count = clampi(a.count_src[b], 0, a.k_max);
         const int row_begin = split * a.rows_per_wg;
@@ -138,7 +185,7 @@ __global__ __launch_bounds__(256) void attn_kernel(const AttnArgs a) {
     }
     const int64_t head_stride = (int64_t)a.n_splits * HATA_PSTRIDE;
     float* part0 = a.partials + ((int64_t)b * a.Hq + hq0) * head_stride;
-    attn_emit<HT>(S, ns == 1, outp, outp32, part0 + (int64_t)split * HATA_PSTRIDE, head_stride);
+    attn_emit<HT>(S, ns == 1, outp, outp32, part0 + (int64_t)slot * HATA_PSTRIDE, head_stride);
     if (ns == 1) return;
     // count the finished slices; the last workgroup merges them (partials are written with
     // write-through stores and read back with device-coherent loads)
@@ -197,18 +244,29 @@ hipError_t launch_attention(const hata_ctx* c, int mode, const void* q, const vo
             (int64_t)splits(2 * a.chunks_per_split) * f.Hkv * (c->G / c->HT) * B >= 256))
         a.chunks_per_split *= 2;
     a.partials = c->partials; a.counter = c->attn_counter; a.counter_stride = c->attn_counter_stride;
+    // rows an owner attends over itself: half as many again as it gets of an even spread, in turns of the four waves (64
+    // rows); above 512 only where more pieces could not be merged
+    a.owners = splits(a.chunks_per_split);
+    a.B = B;
+    a.piece_rows = 64;
+    while ((a.piece_rows < 512 && 2 * (int64_t)a.owners * a.piece_rows < 3 * (int64_t)f.k_max) ||
+           a.owners + f.k_max / a.piece_rows > 256 || B + (f.k_max / a.piece_rows * (int64_t)B + a.owners - 1) / a.owners > 65535)
+        a.piece_rows += 64;
+    const int further = f.k_max / a.piece_rows;
     a.out = (uint16_t*)out; a.out_f32 = out_f32;
     a.Hq = f.Hq; a.Hkv = f.Hkv; a.G = c->G; a.L_cap = f.L_cap; a.k_max = f.k_max;
     a.rows_per_wg = c->sparse_rows;
-    a.n_splits = mode == ROWS_SELECT ? splits(a.chunks_per_split) : c->sparse_splits;
+    a.n_splits = mode == ROWS_SELECT ? a.owners + further : c->sparse_splits;
     a.sb = f.kv_stride_b; a.sh = f.kv_stride_h; a.sn = f.kv_stride_n;
     a.scale_log2 = sm_scale * 1.4426950408889634f;
+    const dim3 grid(mode == ROWS_SELECT ? a.owners : a.n_splits, f.Hkv * (c->G / c->HT),
+                    mode == ROWS_SELECT ? B + (further * B + a.owners - 1) / a.owners : B);
     switch (c->HT) {
-        case 8: launch_mode<8>(mode, a, dim3(a.n_splits, f.Hkv * (c->G / 8), B), s); break;
-        case 5: launch_mode<5>(mode, a, dim3(a.n_splits, f.Hkv * (c->G / 5), B), s); break;
-        case 4: launch_mode<4>(mode, a, dim3(a.n_splits, f.Hkv * (c->G / 4), B), s); break;
-        case 2: launch_mode<2>(mode, a, dim3(a.n_splits, f.Hkv * (c->G / 2), B), s); break;
-        default: launch_mode<1>(mode, a, dim3(a.n_splits, f.Hkv * c->G, B), s); break;
+        case 8: launch_mode<8>(mode, a, grid, s); break;
+        case 5: launch_mode<5>(mode, a, grid, s); break;
+        case 4: launch_mode<4>(mode, a, grid, s); break;
+        case 2: launch_mode<2>(mode, a, grid, s); break;
+        default: launch_mode<1>(mode, a, grid, s); break;
     }
     return hipGetLastError();
 }

@@ -319,3 +319,57 @@ def test_dense_spreads_the_one_long_sequence_of_a_batch():
     assert t_batch < 3 * t_alone
     alone.close()
     batch.close()
+
+
+@pytest.mark.parametrize("L,k_max,chunk", [(2100, 2100, 0), (3000, 1000, 0), (9000, 4000, 1024), (30000, 600, 8192), (70000, 700, 1024)])
+@pytest.mark.parametrize("heads", [(5, 1), (2, 2), (8, 1), (4, 4)])
+def test_selected_rows_of_one_chunk_in_pieces(L, k_max, chunk, heads):
+    """Runs of selected rows that fill a chunk and more, so that the chunk's rows go to several workgroups."""
+    Hq, Hkv = heads
+    B = 3
+    w = synth.Workload("pieces", B, Hq, Hkv, 128, 64, (L, max(1, L // 3), 5), (k_max, max(1, k_max // 2), 3), k_max=k_max)
+    print(f"[stages] pieces L={L} k={k_max} chunk={chunk} heads={heads}", flush=True)
+    c = H.Case(w, shared_device=True, chunk=chunk)
+    q = c.inp.q()
+    qc, _ = O.encode_query_batch(q, c.inp.W_H)
+    near = qc.reshape(B, Hkv, Hq // Hkv, -1)[:, :, :1]
+    for first, count in ((0, k_max), (L // 4, k_max), (L // 4 - 700, k_max // 2 + 1), (L // 3 - 65, 65), (L // 3 - 200, 129)):
+        codes = c.codes_ref.copy()
+        codes[:, :, max(0, first): max(0, first) + count] = near
+        cd = H.to_dev(codes.copy())
+        out, out32 = c.empty((B, Hq, 128), c.torch.int16), c.empty((B, Hq, 128), c.torch.float32)
+        for _ in range(2):  # (the second call finds the arrival counters as the first one left them)
+            c.ctx.hata_decode_step(H.to_dev(q), c.K, c.V, c.W_H, cd, c.seq_len, c.k, B, False, c.scale, out, out32)
+        c.sync()
+        ref = O.decode_step(q, c.inp.K, c.inp.V, c.inp.W_H, codes, c.inp.seq_len, c.inp.k, k_max, c.scale, append=False)
+        assert np.array_equal(H.to_host(c.ctx.hata_step_buffers()[2]), ref["idx"])
+        H.check_attention(H.to_host(out32), H.to_host(out, np.uint16), ref["out"], "step")
+    c.ctx.close()
+
+
+def test_selected_rows_in_one_place_are_no_serial_work():
+    """2048 selected rows in a row of a 131072-key cache: 1.1 times the step with the rows spread out (2.1 times when one
+    workgroup attends over all rows of a chunk)."""
+    import torch
+    from paper_2506_02572_amd import hata
+    Hq, Hkv, L, k, r = 32, 8, 131072, 2048, 256
+    K, V = (torch.randn((1, Hkv, L, 128), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    q = torch.randn((1, Hq, 128), dtype=torch.bfloat16, device="cuda")
+    W = torch.randn((Hkv, 128, r), device="cuda")
+    ctx = hata.Context(1, Hq, Hkv, 128, r, L, k, shared_device=True)
+    seq, budget, zero = (torch.tensor([x], dtype=torch.int32, device="cuda") for x in (L, k, 0))
+    codes = torch.zeros((1, Hkv, L, r // 32), dtype=torch.int32, device="cuda")
+    qcodes = torch.zeros((1, Hq, r // 32), dtype=torch.int32, device="cuda")
+    out = torch.zeros_like(q)
+    ctx.hata_encode_keys(K, W, zero, seq, 1, L, codes)
+    ctx.hata_encode_query(q, W, 1, qcodes)
+
+    def step():
+        ctx.hata_decode_step(q, K, V, W, codes, seq, budget, 1, False, 128 ** -0.5, out)
+
+    t_spread = shortest_us(step)
+    codes[:, :, L // 2:L // 2 + k] = qcodes.view(1, Hkv, Hq // Hkv, -1)[:, :, :1]
+    t_run = shortest_us(step)
+    print(f"[stages] rows spread {t_spread:.1f} us, in one place {t_run:.1f} us", flush=True)
+    assert t_run < 1.5 * t_spread
+    ctx.close()
