@@ -87,13 +87,17 @@ template <int WD>
 struct CodeW { uint32_t w[WD]; };
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
 
-// ONCE: marked non-temporal.  Chunks above HATA_COOP_SUB mean some 64 MB of codes or more in this launch: over the layers of
-// a model they are gone from every cache before the next pass over them, and not keeping them leaves the L2 to the
-// weights, the rows and what the workgroups exchange (32 sequences of 32768 keys, r = 128: 54.2 -> 48.8 to 52.2 us; 16 of
-// 65536: 53.3 -> 47.0; a program of one such layer alone finds them in the 256 MB cache at the memory side, and
-// loses by the hint: 48.0 -> 49.7).  Smaller launches keep them (15 sequences of up to 25733 keys, two
-// layers: 26.3 us, 27.5 with the hint).  At r = 256 a code is two loads, and the second one misses the line that the
-// first one's hint gave up (8 x 125439 keys: 66.5 and 71.8).
+// ONCE: marked non-temporal, in launches whose chunks are above HATA_COOP_SUB: where a grid of 4096 keys a workgroup would not
+// be resident (more than 768 or 1024 workgroups: from 50 or 67 MB of codes, or half of that where the caches end just
+// past a chunk), or where the caller asked for such a chunk.  Whether the hint pays depends on what a launch does not
+// see: the codes of all the caches that are read between two passes over this one.  Where they are more than the
+// 256 MB cache at the memory side holds -- two to five layers of this size, and models have dozens -- they come from HBM
+// every time, and not keeping them leaves the L2 to the weights, the rows and what the workgroups exchange (r = 128;
+// 134 MB a layer, two layers 54.4 -> 49.6 us, four 54.8 -> 50.6, longer sequences 53.8 -> 49.0; 84 MB, eight layers
+// 42.2 -> 40.2; 57 MB in unequal sequences, eight layers 40.4 -> 38.7).  A program of one such layer finds them in that
+// cache and loses (47.2 -> 50.2, 46.1 -> 48.9, 37.0 -> 37.9 and 35.0 -> 36.7; two layers of 57 MB 35.7 -> 36.3).
+// Smaller launches keep them (15 sequences of up to 25733 keys, two layers: 26.3 us, 27.5 with the hint).  At r = 256 a
+// code is two loads, and the second one misses the line that the first one's hint gave up (8 x 125439 keys: 66.5 and 71.8).
 template <int WD, bool ONCE>
 __device__ __forceinline__ CodeW<WD> coop_load_code(const uint32_t* p) {
     CodeW<WD> c;
