@@ -83,7 +83,8 @@ int hata_workspace_bytes(const hata_config* cfg, size_t* out);
 /* Creates a context.  `workspace` is device memory (256-byte aligned, at least
  * hata_workspace_bytes() bytes) that stays owned by the caller and must outlive the
  * context; its control words are cleared here with a synchronous hipMemset on the
- * current device.  ctx_out, cfg: host pointers. */
+ * current device, so no work that is still pending on any stream may write to it.
+ * ctx_out, cfg: host pointers. */
 int hata_create(hata_ctx** ctx_out, const hata_config* cfg, void* workspace, size_t workspace_bytes);
 
 /* Launch-shape choices a caller may fix instead of taking the defaults (sweeps over launch

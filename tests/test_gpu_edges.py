@@ -476,3 +476,35 @@ def test_overlap_probe_runs_in_its_three_modes(torch_mod):
     with pytest.raises(hata.HataError):
         hata.hata_probe_mfma_stream(buf[: 1 << 20], 4, 3)  # 2 MiB: below the probe's minimum
 
+
+
+@pytest.mark.parametrize("shared_device", [False, True])
+def test_context_made_behind_pending_work(torch_mod, shared_device):
+    """The workspace's memory is still being written on the stream that the context is made and used on."""
+    torch = torch_mod
+    from paper_2506_02572_amd import hata
+    w = synth.Workload("pending", 2, 8, 2, 128, 128, (5000, 3000), (100, 60), k_max=100)
+    print(f"[edges] pending work, shared_device={shared_device}", flush=True)
+    c = H.Case(w, shared_device=shared_device)
+    q = c.inp.q()
+    qd, codes = H.to_dev(q), H.to_dev(c.codes_ref)
+    out, out32 = c.empty((w.B, w.Hq, w.d), torch.int16), c.empty((w.B, w.Hq, w.d), torch.float32)
+    nbytes = c.ctx.workspace.numel()
+    torch.cuda.synchronize()
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        earlier = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        address = earlier.data_ptr()
+        torch.cuda._sleep(20_000_000)  # some milliseconds
+        earlier.fill_(1)
+        del earlier
+        ctx = hata.Context(w.B, w.Hq, w.Hkv, w.d, w.r, w.L_cap, w.k_max, shared_device=shared_device)
+        assert ctx.workspace.data_ptr() == address
+        ctx.hata_decode_step(qd, c.K, c.V, c.W_H, codes, c.seq_len, c.k, w.B, False, c.scale, out, out32)
+        ctx.hata_check()
+    torch.cuda.synchronize()
+    ref = O.decode_step(q, c.inp.K, c.inp.V, c.inp.W_H, c.codes_ref, c.inp.seq_len, c.inp.k, w.k_max, c.scale, append=False)
+    assert np.array_equal(H.to_host(ctx.hata_step_buffers()[2]), ref["idx"])
+    H.check_attention(H.to_host(out32), H.to_host(out, np.uint16), ref["out"], "step")
+    ctx.close()
+    c.ctx.close()
