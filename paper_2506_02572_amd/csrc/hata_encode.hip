@@ -37,18 +37,18 @@ __global__ __launch_bounds__(256) void encode_few_kernel(
     const int nv = nq + max(nk, 0);
     const uint16_t* qu = q + ((int64_t)b * Hq + (int64_t)h * G) * HATA_D;
     const uint16_t* Ku = K + b * sb + h * sh + row0 * sn;
-    auto load = [&](int v0, uint4 (&x)[1][4]) {
+    auto load = [&](int v0, uint4 (&x)[4]) {
         const int v = min(v0 + (tid & 3), nv - 1);
-        hash_load_x(v < nq ? qu + v * HATA_D : Ku + (v - nq) * sn, x[0]);
+        hash_load_x(v < nq ? qu + v * HATA_D : Ku + (v - nq) * sn, x);
     };
     if (nv <= 0) return;
-    uint4 x[1][4], xn[1][4];
+    uint4 x[4], xn[4];
     load(0, x);
     for (int v0 = 0; v0 < nv; v0 += 4) {
         if (v0 + 4 < nv) load(v0 + 4, xn);
-        hash_pass<COLS, 1>(hw, x, s_codes, WPS, v0, nv);
+        hash_pass<COLS>(hw, x, s_codes, WPS, v0, nv);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) x[0][i] = xn[0][i];
+        for (int i = 0; i < 4; ++i) x[i] = xn[i];
     }
     __syncthreads();
     const int Wd = r / 32;
@@ -121,7 +121,7 @@ __global__ __launch_bounds__(256) void encode_bulk_kernel(
 //
 // Mapping: M = 32 hash columns (wave w owns columns [32 w, 32 w + 32), i.e. code word w),
 // N = 32 keys, K = channels.  A wave keeps its weight fragments (3 planes x 8 channel steps) in
-// registers for the whole launch; key rows are staged through LDS 128 at a time with coalesced
+// registers for the whole launch; key rows are staged through LDS 128 at a time (64 in the fill and at r = 32) with coalesced
 // 128-bit loads (next stage prefetched into registers) and read back in the operand layout
 // (lane = key, 16 B of consecutive channels).  In the 32x32 result a lane holds 16 hash columns of
 // ONE key, so the sign bits are packed inside the lane and joined with the other half-wave.
@@ -132,7 +132,8 @@ typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 
 
 // Bit 8 (i / 4) + i % 4: acc[i] >= 0, the complement of the sign bit (a sum of exact products that starts from +0 is
-// never -0).  One instruction a value and four to part the groups of four; with two a value, shift and
+// never -0; the NaN that the matrix cores make of a NaN or of infinities that cancel has its sign bit set, whatever the
+// input's was, so such a bit is 0 as in a comparison).  One instruction a value and four to part the groups of four; with two a value, shift and
 // insertion, 131072 keys of eight heads took encode_dma_kernel 135.4 us instead of 132.1 (r = 256), 70.8 instead of 68.1 (128).
 __device__ __forceinline__ uint32_t sign_bits(const f32x16_t& acc) {
     uint32_t neg = 0;
@@ -303,9 +304,9 @@ __global__ __launch_bounds__(R * 2) void encode_mfma_kernel(
         for (int t = 0; t < NT; ++t)
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[t][i] = 0.f;
-        // Key fragments come from LDS one channel step ahead: as soon as the three planes of a tile
-        // have been issued for step kk, the tile's fragment for step kk + 1 is requested into the same
-        // registers, so its LDS latency is covered by the nine MFMAs of the other tiles.
+        // Key fragments come from LDS one channel step ahead: as soon as the planes of a tile have been issued
+        // for step kk, the tile's fragment for step kk + 1 is requested into the same registers, so its LDS
+        // latency is covered by the MFMAs of the other tiles (nine with four tiles and three planes, two or three in the fill).
         uint4 bfrag[NT];
 #pragma unroll
         for (int t = 0; t < NT; ++t)
@@ -639,27 +640,22 @@ hipError_t launch_encode_bulk(const hata_ctx* c, const void* K, const float* W_H
 #undef HATA_LAUNCH_DMA
             return hipGetLastError();
         }
-#define HATA_LAUNCH_MFMA(R_, F_, P_)                                                                           \
-    do {                                                                                                   \
-        if (planes)                                                                                        \
-            hipLaunchKernelGGL((encode_mfma_kernel<R_, F_, P_, true>), grid, dim3(R_ * 2), 0, s,               \
-                               (const uint16_t*)K, W_H, planes, start, n_new, codes, f.Hkv, f.L_cap, kpw,  \
-                               f.kv_stride_b, f.kv_stride_h, f.kv_stride_n, kn, vn, ko, vo, max_new, pv);  \
-        else                                                                                               \
-            hipLaunchKernelGGL((encode_mfma_kernel<R_, F_, P_, false>), grid, dim3(R_ * 2), 0, s,              \
-                               (const uint16_t*)K, W_H, planes, start, n_new, codes, f.Hkv, f.L_cap, kpw,  \
-                               f.kv_stride_b, f.kv_stride_h, f.kv_stride_n, kn, vn, ko, vo, max_new, pv);  \
+#define HATA_LAUNCH_MFMA(R_, F_, P_, S_)                                                                       \
+    hipLaunchKernelGGL((encode_mfma_kernel<R_, F_, P_, S_>), grid, dim3(R_ * 2), 0, s, (const uint16_t*)K, W_H, planes, \
+                       start, n_new, codes, f.Hkv, f.L_cap, kpw, f.kv_stride_b, f.kv_stride_h, f.kv_stride_n, kn, vn,   \
+                       ko, vo, max_new, pv)
+#define HATA_LAUNCH_WIDTH(F_, P_, S_)                          \
+    do {                                                       \
+        if (f.r == 32) HATA_LAUNCH_MFMA(32, F_, P_, S_);       \
+        else if (f.r == 64) HATA_LAUNCH_MFMA(64, F_, P_, S_);  \
+        else if (f.r == 128) HATA_LAUNCH_MFMA(128, F_, P_, S_); \
+        else HATA_LAUNCH_MFMA(256, F_, P_, S_);                \
     } while (0)
-#define HATA_LAUNCH_WIDTH(F_, P_)                          \
-    do {                                                   \
-        if (f.r == 32) HATA_LAUNCH_MFMA(32, F_, P_);       \
-        else if (f.r == 64) HATA_LAUNCH_MFMA(64, F_, P_);  \
-        else if (f.r == 128) HATA_LAUNCH_MFMA(128, F_, P_); \
-        else HATA_LAUNCH_MFMA(256, F_, P_);                \
-    } while (0)
-        if (pages) HATA_LAUNCH_WIDTH(true, true);
-        else if (kn) HATA_LAUNCH_WIDTH(true, false);
-        else HATA_LAUNCH_WIDTH(false, false);
+        if (!kn) HATA_LAUNCH_WIDTH(false, false, false);
+        else if (pages && planes) HATA_LAUNCH_WIDTH(true, true, true);
+        else if (pages) HATA_LAUNCH_WIDTH(true, true, false);
+        else if (planes) HATA_LAUNCH_WIDTH(true, false, true);
+        else HATA_LAUNCH_WIDTH(true, false, false);
 #undef HATA_LAUNCH_WIDTH
 #undef HATA_LAUNCH_MFMA
         return hipGetLastError();

@@ -48,39 +48,29 @@ __device__ __forceinline__ uint32_t or_columns(uint32_t v) {
     return __float_as_uint(x) | __float_as_uint(y);
 }
 
-// NS sets of four vectors: x[e] holds this lane's part of vector first + 4 e + lane % 4.  Vector v's code words
-// for these columns go to s_codes[v * pitch ...] where v is below `last`; complete after the caller's next
-// barrier.
-template <int COLS, int NS>
-__device__ __forceinline__ void hash_pass(const HashWeights<COLS>& W, const uint4 (&x)[NS][4], uint32_t* s_codes, int pitch,
+// Four vectors: x holds this lane's part of vector first + lane % 4.  Vector v's code words for these columns go to
+// s_codes[v * pitch ...] where v is below `last`; complete after the caller's next barrier.
+template <int COLS>
+__device__ __forceinline__ void hash_pass(const HashWeights<COLS>& W, const uint4 (&x)[4], uint32_t* s_codes, int pitch,
                                           int first, int last) {
-    double acc[NS];
-#pragma unroll
-    for (int e = 0; e < NS; ++e) acc[e] = 0.0;
+    double acc = 0.0;
 #pragma unroll
     for (int s = 0; s < 32; ++s) {
         // (without the barriers the compiler converts right behind the loads, or ahead of a loop around this:
         // waits early, and twice the registers)
         float w = W.w[s];
         asm volatile("" : "+v"(w));
-        const double wd = (double)w;
-#pragma unroll
-        for (int e = 0; e < NS; ++e) {
-            const uint4 q = x[e][s >> 3];
-            uint32_t pair = ((s >> 1) & 3) == 0 ? q.x : ((s >> 1) & 3) == 1 ? q.y : ((s >> 1) & 3) == 2 ? q.z : q.w;
-            asm volatile("" : "+v"(pair));
-            const double xd = (double)((s & 1) ? bf16_hi(pair) : bf16_lo(pair));
-            acc[e] = __builtin_amdgcn_mfma_f64_4x4x4f64(wd, xd, acc[e], 0, 0, 0);
-        }
+        const uint4 q = x[s >> 3];
+        uint32_t pair = ((s >> 1) & 3) == 0 ? q.x : ((s >> 1) & 3) == 1 ? q.y : ((s >> 1) & 3) == 2 ? q.z : q.w;
+        asm volatile("" : "+v"(pair));
+        const double xd = (double)((s & 1) ? bf16_hi(pair) : bf16_lo(pair));
+        acc = __builtin_amdgcn_mfma_f64_4x4x4f64((double)w, xd, acc, 0, 0, 0);
     }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int m = (lane >> 4) + (lane & 12);  // column of the result
-#pragma unroll
-    for (int e = 0; e < NS; ++e) {
-        const int v = first + 4 * e + lane;
-        const uint32_t bits = or_columns((acc[e] >= 0.0 ? 1u : 0u) << m);
-        if (lane < 4 && v < last && wave < COLS / 16) reinterpret_cast<uint16_t*>(s_codes)[v * pitch * 2 + wave] = (uint16_t)bits;
-    }
+    const int v = first + lane;
+    const uint32_t bits = or_columns((acc >= 0.0 ? 1u : 0u) << m);
+    if (lane < 4 && v < last && wave < COLS / 16) reinterpret_cast<uint16_t*>(s_codes)[v * pitch * 2 + wave] = (uint16_t)bits;
 }
 
 }  // namespace hata

@@ -373,3 +373,30 @@ def test_selected_rows_in_one_place_are_no_serial_work():
     print(f"[stages] rows spread {t_spread:.1f} us, in one place {t_run:.1f} us", flush=True)
     assert t_run < 1.5 * t_spread
     ctx.close()
+
+
+@pytest.mark.parametrize("r", [32, 64, 128, 256])
+def test_codes_of_keys_with_nan(r):
+    """A projection that is no number is not >= 0: all code bits 0, whatever the NaN's sign and whichever kernel encodes."""
+    import torch
+    from paper_2506_02572_amd import hata
+    L = 300
+    print(f"[stages] NaN keys r={r}", flush=True)
+    K = torch.randn((1, 2, L, 128), device="cuda").to(torch.bfloat16)
+    K[:, :, 7, 3], K[:, :, 200, 100] = float("nan"), -float("nan")
+    W = torch.randn((2, 128, r), device="cuda")
+    ctx = hata.Context(1, 4, 2, 128, r, L, 8)
+    start, n = (torch.tensor([x], dtype=torch.int32, device="cuda") for x in (0, L))
+    for prepared in (False, True):
+        if prepared:
+            ctx.hata_prepare_weights(W)
+        bulk, fill = (torch.full((1, 2, L, r // 32), -1, dtype=torch.int32, device="cuda") for _ in range(2))
+        ctx.hata_encode_keys(K, W, start, n, 1, L, bulk)
+        ctx.hata_prefill_write(K, K, start, n, 1, L, torch.zeros_like(K), torch.zeros_like(K), fill, W)
+        for codes in (bulk, fill):
+            assert not codes[:, :, [7, 200]].any() and codes[:, :, 8].any()
+    for row in (7, 200):
+        one = torch.full((1, 2, L, r // 32), -1, dtype=torch.int32, device="cuda")
+        ctx.hata_encode_keys(K, W, start + row, n * 0 + 1, 1, 1, one)
+        assert not one[:, :, row].any()
+    ctx.close()
