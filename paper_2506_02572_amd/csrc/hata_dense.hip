@@ -89,24 +89,20 @@ __device__ __forceinline__ bool dense_share(const int32_t* __restrict__ seq_len,
     auto of = [&](int b0) { return b0 == 0 ? own : length(b0 + lane); };
     // (a sequence without rows: one workgroup writes zeros)
     auto tiles = [](int L) { return L >= 0 ? (max(L, 1) + 15) / 16 : 0; };
-    float all = 0.f, longest = 0.f;
-    for (int b0 = 0; b0 < B; b0 += 64) {
-        const float t = (float)tiles(of(b0));
-        all += wave_sum64(t);
-        longest = fmaxf(longest, wave_max64(t));
-    }
-    int run = max(max(DENSE_WAVES, (int)ceilf(all * (float)Hkv * __builtin_amdgcn_rcpf((float)wgs))),
-                  ((int)longest + DENSE_MAX_RUNS - 1) / DENSE_MAX_RUNS);
-    // (exact below 2^20, and a cache has fewer tiles)
-    auto runs = [&](int L) { return (uint32_t)(((float)(tiles(L) + run - 1) + 0.5f) * __builtin_amdgcn_rcpf((float)run)); };
+    float all = 0.f;
+    for (int b0 = 0; b0 < B; b0 += 64) all += wave_sum64((float)tiles(of(b0)));
+    int run = max(DENSE_WAVES, (int)ceilf(all * (float)Hkv * __builtin_amdgcn_rcpf((float)wgs)));
+    // (the quotients are exact below 2^20, and a cache has fewer tiles)
+    auto quotient = [](int x, int y) { return (int)(((float)x + 0.5f) * __builtin_amdgcn_rcpf((float)y)); };
+    auto runs = [&](int L) { return (uint32_t)min(quotient(tiles(L) + run - 1, run), DENSE_MAX_RUNS); };
     uint32_t upto;  // runs of the sequences up to this lane's, of the last 64 looked at
-    for (;; run += max(1, run >> 3)) {  // (ends at the longest sequence's tiles at the latest: one run a unit)
+    for (;; run += max(1, run >> 3)) {  // (ends at the cache's tiles at the latest: one run a unit)
         uint32_t n = 0;
         for (int b0 = 0; b0 < B; b0 += 64) {
             upto = wave_incl_scan(runs(of(b0)));
             n += (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
         }
-        if (n * (uint32_t)Hkv <= (uint32_t)wgs || run >= (int)longest) break;
+        if (n * (uint32_t)Hkv <= (uint32_t)wgs || run >= tiles(L_cap)) break;
     }
     int before = 0;
     for (int b0 = 0; b0 < B; b0 += 64) {
@@ -119,7 +115,7 @@ __device__ __forceinline__ bool dense_share(const int32_t* __restrict__ seq_len,
             d.L = __builtin_amdgcn_readlane(L, l);
             d.ns = __builtin_amdgcn_readlane(n, l);
             const int in_seq = wg - before - Hkv * (__builtin_amdgcn_readlane((int)upto, l) - d.ns);
-            d.h = in_seq / d.ns;
+            d.h = __builtin_amdgcn_readfirstlane(quotient(in_seq, d.ns));
             d.split = in_seq - d.h * d.ns;
             d.first = wg - d.split;
             return true;
