@@ -33,7 +33,7 @@ struct AttnArgs {
     const int32_t* seq_len;
     const int32_t* chunk_info;
     const int32_t* unit_info;
-    int chunk, n_chunks, chunks_per_split, owners, piece_rows, B;
+    int chunk, n_chunks, chunks_per_split, owners, piece_rows, B;  // (chunk, chunks_per_split: powers of two)
     float* partials;
     uint32_t* counter;
     int counter_stride;
@@ -96,12 +96,22 @@ __global__ __launch_bounds__(256) void attn_kernel(const AttnArgs a) {
             attn_rows<HT, 4>(qr, Kb, Vb, a.sn, a.L_cap, row_begin, row_end, a.scale_log2, row_of, S);
     };
     if constexpr (MODE == ROWS_SELECT) {
-        const int L = clampi(a.seq_len[b], 0, a.L_cap);
-        const int T = a.unit_info[u * 2 + 0], keff = clampi(a.unit_info[u * 2 + 1], 0, a.k_max);
+        // what an owner reads is requested together: no address depends on the sequence's length
         const int per = a.chunks_per_split, span = per * a.chunk;
         const int32_t* ci_unit = a.chunk_info + u * (a.n_chunks + 1) * 2;
-        const int nc = (L + a.chunk - 1) / a.chunk;  // (entry nc closes the list)
-        const int live = (L + span - 1) / span;      // owners with keys
+        auto entry = [&](int s) { return ci_unit + 2 * min(s * per, a.n_chunks); };
+        const int seq = a.seq_len[b], T = a.unit_info[u * 2 + 0], budget = a.unit_info[u * 2 + 1];
+        int off = 0, take = 0, next = 0;
+        if (split < a.owners) {
+            off = entry(split)[0];
+            take = entry(split)[1];
+            next = entry(split + 1)[0];
+        }
+        const int lane = tid & 63;
+        const int first0 = *entry(lane), next0 = *entry(lane + 1);
+        const int L = clampi(seq, 0, a.L_cap), keff = clampi(budget, 0, a.k_max);
+        const int nc = (L + a.chunk - 1) >> __builtin_ctz(a.chunk);  // (entry nc closes the list: keff)
+        const int live = (L + span - 1) >> __builtin_ctz(span);      // owners with keys
         int32_t* io = a.idx_out + u * a.k_max;
         if (split == 0) {
             if (ht == 0)  // slots of the index list past the selected count hold -1
@@ -111,18 +121,15 @@ __global__ __launch_bounds__(256) void attn_kernel(const AttnArgs a) {
         auto selected = [&](int s, int first, int next) {
             return clampi(next - first, 0, min(min(span, L - s * span), a.k_max - clampi(first, 0, a.k_max)));
         };
-        // pieces beyond an owner's first: lane l looks at owners l, l + 64, ... (the first of them requested now, together
-        // with all else); returns how many there are, and where number `nth` of them is
-        const int lane = tid & 63;
-        auto entry = [&](int s) { return ci_unit[2 * min(s * per, a.n_chunks)]; };
-        const int first0 = entry(lane), next0 = entry(lane + 1);
+        // pieces beyond an owner's first: lane l looks at owners l, l + 64, ... (the first of them are requested above);
+        // returns how many there are, and where number `nth` of them is
         const float half_inv = 0.5f * __builtin_amdgcn_rcpf((float)a.piece_rows);  // (rows - 1) / piece_rows, exact below 2^20
         auto further_pieces = [&](int nth, int& own, int& piece) {
             int extra = 0;
             for (int s0 = 0; s0 < live; s0 += 64) {
                 const int s = s0 + lane;
-                const int first = s0 == 0 ? first0 : entry(s);
-                const int next = (s + 1) * per > nc ? keff : s0 == 0 ? next0 : entry(s + 1);
+                const int first = s0 == 0 ? first0 : *entry(s);
+                const int next = (s + 1) * per > nc ? keff : s0 == 0 ? next0 : *entry(s + 1);
                 const int rows = s < live ? selected(s, first, next) : 0;
                 const int more = rows > 0 ? (int)((float)(2 * rows - 1) * half_inv) : 0;
                 if (__builtin_amdgcn_ballot_w64(more > 0) == 0) continue;
@@ -141,16 +148,19 @@ __global__ __launch_bounds__(256) void attn_kernel(const AttnArgs a) {
         if (split >= a.owners) {
             extra = further_pieces(split - a.owners, own, piece);
             if (split - a.owners >= extra) return;
+            own = __builtin_amdgcn_readfirstlane(own);
+            piece = __builtin_amdgcn_readfirstlane(piece);
             slot = live + split - a.owners;
+            off = entry(own)[0];
+            take = entry(own)[1];
+            next = entry(own + 1)[0];
         } else if (split >= live) {
             return;
         }
         const int c0 = own * per, base = own * span, n_keys = min(span, L - base);
-        const int32_t* ci = ci_unit + c0 * 2;
-        const int off = ci[0];
-        int take = ci[1];  // ties are granted in cache order, so those of consecutive chunks add up
-        for (int i = 1; i < min(per, nc - c0); ++i) take += ci[2 * i + 1];
-        const int next = ci[2 * clampi(nc - c0, 0, per)];
+        if (c0 + per > nc) next = keff;
+        // ties are granted in cache order, so those of consecutive chunks add up
+        for (int i = 1; i < min(per, nc - c0); ++i) take += ci_unit[2 * (c0 + i) + 1];
         const uint16_t* sp = a.scores + u * a.L_cap + base;
         const bool whole = (reinterpret_cast<uintptr_t>(sp) & 15) == 0;
         for (int i = tid * 8; i < n_keys; i += 256 * 8) {
