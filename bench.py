@@ -622,7 +622,7 @@ def train_leg(torch, dev, w, W_H, stream):
     flop = 4 * 2.0 * n_tr * w.d * w.r  # two projections + two weight-gradient contractions
     leg = {"triplets": n_tr, "r": w.r, "us_per_step": round(ms_tr * 1e3, 1),
            "TFLOPs": round(flop / (ms_tr * 1e-3) / 1e12, 1),
-           "mfma_issue_TFLOPs": round((3 * 3 + 2 * 3) / 4 * flop / (ms_tr * 1e-3) / 1e12, 1), "launches": 6}
+           "mfma_issue_TFLOPs": round((3 * 3 + 2 * 3) / 4 * flop / (ms_tr * 1e-3) / 1e12, 1), "launches": 3}
     tctx.close()
     return leg
 
