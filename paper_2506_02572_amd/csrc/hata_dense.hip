@@ -72,18 +72,17 @@ struct DenseShare { int b, h, L, split, ns, first; };
 // the workgroups.  (Cut by the longest sequence there could be, 16 sequences of which one has 32768 rows and the others
 // 2048 took 167 us, this takes 50; 8 KV heads.)  Every wave of every workgroup computes the same; false: nothing left for this one.
 __device__ __forceinline__ bool dense_share(const int32_t* __restrict__ seq_len, int B, int Hkv, int L_cap, DenseShare& d) {
-    const int wg = blockIdx.x, wgs = gridDim.x;
     if (B == 1) {  // nothing to weigh up: which head this is does not wait for the length
-        const int per = wgs / Hkv;
+        const int per = gridDim.x;
         d.b = 0;
-        d.h = wg / per;
-        d.split = wg - d.h * per;
-        d.first = wg - d.split;
+        d.h = blockIdx.y;
+        d.split = blockIdx.x;
+        d.first = d.h * per;
         d.L = clampi(seq_len[0], 0, L_cap);
         d.ns = clampi(((d.L + 15) / 16 + DENSE_WAVES - 1) / DENSE_WAVES, 1, per);
         return d.split < d.ns;
     }
-    const int lane = threadIdx.x & 63;
+    const int lane = threadIdx.x & 63, wg = blockIdx.x, wgs = gridDim.x;
     auto length = [&](int b) { return b < B ? clampi(seq_len[b], 0, L_cap) : -1; };
     const int own = length(lane);  // the only round trip for up to 64 sequences
     auto of = [&](int b0) { return b0 == 0 ? own : length(b0 + lane); };
@@ -515,7 +514,7 @@ hipError_t launch_dense(const hata_ctx* c, const void* q, const void* K, const v
     const int64_t spare = splits == 1 && B > 1 ? std::max((int64_t)0, std::min((int64_t)256, c->dense_wgs_max - units)) : 0;
     a.sb = f.kv_stride_b; a.sh = f.kv_stride_h; a.sn = f.kv_stride_n;
     a.scale_log2 = sm_scale * 1.4426950408889634f;
-    const dim3 grid((unsigned)(units * splits + spare));
+    const dim3 grid = B == 1 ? dim3((unsigned)splits, f.Hkv) : dim3((unsigned)(units * splits + spare));
     const auto fn = c->HT >= 4 ? dense_kernel<DENSE_BF16X2> : c->G == 1 ? dense_kernel<DENSE_FP32_ONE_HEAD>
                     : c->G == 2 ? dense_kernel<DENSE_FP32_TWO_HEADS> : dense_kernel<DENSE_FP32>;
     hipLaunchKernelGGL(fn, grid, dim3(DENSE_WAVES * 64), dense_lds(), s, a);

@@ -183,9 +183,10 @@ class Context:
         self._lib = lib
         self._h = ctypes.c_void_p(None)
         with torch.cuda.device(self.device):
-            # The control words are cleared on the null stream, which does not wait for torch's other streams: the memory
+            # The control words are cleared on the null stream, which does not wait for torch's side streams: the memory
             # may come from a tensor that this stream's pending work still writes to.
-            if not torch.cuda.is_current_stream_capturing():
+            side = torch.cuda.current_stream() != torch.cuda.default_stream()
+            if side and not torch.cuda.is_current_stream_capturing():
                 torch.cuda.current_stream().synchronize()
             _check(lib.hata_create_tuned(ctypes.byref(self._h), ctypes.byref(self.cfg), ctypes.byref(self.tuning),
                                          ctypes.c_void_p(self._ws_ptr), nbytes.value), "hata_create_tuned")
