@@ -487,11 +487,8 @@ class Bench:
 
     # checkpoints of decode_step_coop_kernel (slot = number % 32 of the HATA_TRACE_AT calls in csrc/)
     PHASES = [(39, "kernel start"), (40, "sequence length known"), (50, "query codes collected"),
-              (41, "chunk scored"), (42, "histogram stores issued"), (43, "histogram stores complete"),
-              (44, "arrived at the unit"), (51, "last arriver: threshold search starts"),
-              (26, "last arriver: unit histogram loaded and scanned"), (27, "last arriver: threshold known"),
-              (28, "last arriver: per-chunk counts"), (29, "last arriver: records published"),
-              (45, "record picked up"), (46, "compaction done"), (47, "attention over own rows done"),
+              (41, "chunk scored"), (42, "cumulative histogram published"), (52, "candidates listed"),
+              (51, "threshold and own place known"), (46, "compaction done"), (47, "attention over own rows done"),
               (48, "partial emitted"), (54, "merge done (merging workgroups)")]
 
     def phase_trace(self, launches=16, repeats=10):

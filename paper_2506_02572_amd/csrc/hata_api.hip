@@ -42,7 +42,7 @@ inline size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 struct Plan {
     int G, Wd, NB, NBP, chunk, n_chunks, coop_chunk, HT, sparse_rows, sparse_splits;
     int64_t dense_wgs_max;
-    size_t off_qcodes, off_scores, off_idx, off_hist, off_cinfo, off_uinfo, off_ucnt, off_acnt, off_uflag, off_qrec, off_err, off_uhist, off_partials, off_wplanes, total;
+    size_t off_qcodes, off_scores, off_idx, off_hist, off_cinfo, off_uinfo, off_ucnt, off_acnt, off_cum, off_epoch, off_qrec, off_err, off_uhist, off_partials, off_wplanes, total;
 };
 
 int validate_config(const hata_config* f) {
@@ -130,7 +130,8 @@ int make_plan(const hata_config* f, const hata_tuning* t, Plan* p) {
     // (the single-launch step keeps each unit's two arrival counters on a cache line of their own)
     p->off_ucnt = o;     o = align_up(o + (size_t)units * HATA_COUNTER_STRIDE * 4);
     p->off_acnt = o;     o = align_up(o + (size_t)f->B_max * f->Hq * HATA_COUNTER_STRIDE * 4);
-    p->off_uflag = o;    o = align_up(o + (size_t)units * p->n_chunks * HATA_REC_STRIDE * 8);
+    p->off_cum = o;      o = align_up(o + (size_t)units * hata::coop_cum_pitch(p->n_chunks, p->NBP) * 8);
+    p->off_epoch = o;    o = align_up(o + (size_t)units * HATA_COUNTER_STRIDE * 4);
     p->off_qrec = o;     o = align_up(o + (size_t)f->B_max * f->Hq * p->Wd * p->n_chunks * 8);
     p->off_err = o;      o = align_up(o + 4);
     p->off_uhist = o;    o = align_up(o + (size_t)units * p->NB * 4);
@@ -254,7 +255,8 @@ int hata_create_tuned(hata_ctx** ctx_out, const hata_config* cfg, const hata_tun
     c->attn_counter = (uint32_t*)(w + p.off_acnt);
     c->attn_counter_stride = HATA_COUNTER_STRIDE;
     c->unit_hist = (uint32_t*)(w + p.off_uhist);
-    c->coop_rec = (unsigned long long*)(w + p.off_uflag);
+    c->coop_cum = (unsigned long long*)(w + p.off_cum);
+    c->unit_epoch = (uint32_t*)(w + p.off_epoch);
     c->coop_qrec = (unsigned long long*)(w + p.off_qrec);
     c->error_word = (uint32_t*)(w + p.off_err);
     c->epoch = 0;

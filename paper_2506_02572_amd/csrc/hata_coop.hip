@@ -5,21 +5,25 @@
 // grid = n_chunks * Hkv * B workgroups; the workgroup of (unit u, chunk c)
 //   0. hash-encodes its share of the unit's query vectors, publishes the code words and collects
 //      the others' (the owner of the appended row also encodes that key);
-//   1. scores its chunk of cached key codes (as score_kernel does), keeps the scores in LDS,
-//      publishes the chunk histogram and adds it to the unit histogram, then ARRIVES at the unit;
-//   2. the last workgroup of the unit to arrive computes the unit's threshold and the ordered
-//      chunk offsets (unit_threshold) and publishes an epoch flag; the others WAIT for that flag --
-//      and meanwhile list their chunk's candidates (the keys up to a score taken from the chunk's own
-//      histogram), so that the selection is a filter over a short list once the threshold is there;
+//   1. scores its chunk of cached key codes (as score_kernel does), keeps the scores in LDS and
+//      publishes the chunk's cumulative histogram;
+//   2. lists its chunk's candidates meanwhile (the keys up to a score taken from the chunk's own
+//      histogram, so that the selection is a filter over a short list once the threshold is there),
+//      WAITS for the histograms of the unit's other chunks and finds the unit's threshold and its own place
+//      in the index list from the few columns of them that matter;
 //   3. compacts its own chunk (ordered, from the LDS scores) -- writing its part of Idx -- and
 //      attends over exactly the rows it selected, for all query heads of the group;
 //   4. writes its partial (max, sum, weighted V) and arrives; the first min(G, nc) workgroups of the
 //      unit wait for all arrivals and merge one query head each (with one head per KV head: the
 //      last workgroup to arrive merges).
-// So the scores never make a round trip through memory for the selection, and the only serial
-// pieces are the threshold tail and the merge.
+// So the scores never make a round trip through memory for the selection, and the only serial piece is the
+// merge.  What bounds a small batch is the chain of exchanges between the workgroups, about 0.5 us each, and the short
+// serial stages between them.  The threshold used to be found by the unit's last arriver from a total histogram
+// (an atomic per occupied bin, an arrival, the search, a record per chunk to wait for); found by every workgroup, the
+// step of one sequence of 32768 keys went from 16.9 to 14.5 us, that of 131072 keys at r = 256 from 28.1 to 27.3,
+// sixteen sequences of up to 32768 from 33.9 to 31.9.
 // What workgroups poll or bump lives on cache lines of its own per unit / per chunk (counters,
-// records, one copy of the query code words per chunk): polls and arrivals that share lines across
+// marks, one copy of the query code words per chunk): polls and arrivals that share lines across
 // units queue behind each other at the memory side.
 //
 // The waits need every workgroup of a unit to be running; the host launches this kernel
@@ -37,6 +41,19 @@ namespace hata {
 #define HATA_COOP_SUB 4096               // chunks above this size run the BIG instantiation (more than 16 keys per thread in the compaction)
 #define HATA_COOP_SPIN_LIMIT (1 << 18)  // default bound of every in-kernel wait (polls, ~0.1 us apart at least)
 
+// Division of workgroup numbers by launch constants with one multiplication: what stands in front of a workgroup's first
+// load is in front of everything (four divisions, one of them in 64 bits, were 0.25 us).
+struct Divisor {
+    uint32_t d, m;  // m = floor(2^32 / d), at most 2^32 - 1
+};
+static inline Divisor make_divisor(uint32_t d) { return Divisor{d, d > 1 ? (uint32_t)((1ull << 32) / d) : 0xffffffffu}; }
+__device__ __forceinline__ uint32_t divide(uint32_t x, Divisor by, uint32_t& rest) {
+    uint32_t q = __umulhi(x, by.m);  // the quotient, or one less
+    rest = x - q * by.d;
+    if (rest >= by.d) { rest -= by.d; ++q; }
+    return q;
+}
+
 struct CoopArgs {
     const uint16_t* q;
     const uint16_t* K;
@@ -48,23 +65,23 @@ struct CoopArgs {
     const int32_t* kbud;
     uint16_t* scores;
     int32_t* idx;
-    uint16_t* chunk_hist;
-    int32_t* chunk_info;
-    int32_t* unit_info;
-    uint32_t* unit_counter;
-    uint32_t* unit_hist;
-    unsigned long long* rec;
+    unsigned long long* cum;  // [units, cum_pitch], a chunk's row NBP / 2 words: cumulative chunk histograms, two scores and the unit's epoch a word
+    int cum_marks, mark_pitch;  // where a unit's marks begin, a row of them per reading chunk: the epoch too, stored behind a chunk's row for every other chunk (they tell when to look)
+    int cum_pitch;            // (the same for every chunk size: what a unit's words hold was stamped with that unit's epoch)
+    uint32_t* unit_epoch;
     unsigned long long* qrec;
     uint32_t* attn_counter;
     uint32_t* error_word;
     float* partials;
     uint16_t* out;
     float* out_f32;
-    int Hq, Hkv, L_cap, k_max, chunk, n_chunks, NB, NBP, units;
+    int Hq, Hkv, L_cap, k_max, chunk, n_chunks, NBP, units;
     int64_t sb, sh, sn;
     float scale_log2;
     uint32_t epoch;
     int append;
+    int chunk_shift;  // chunk = 1 << chunk_shift
+    Divisor by_groups, by_chunks, by_heads;  // units / 8, n_chunks, Hkv
     int spin_limit;
     int prefetch;     // fetch the first batch of key codes before the query codes are known
     int keep_scores;  // also write the score array (a by-product the kernel itself never reads back)
@@ -251,17 +268,20 @@ void decode_step_coop_kernel(const CoopArgs a) {
     extern __shared__ __attribute__((aligned(16))) uint16_t s_sc[];
     uint32_t* const hist = reinterpret_cast<uint32_t*>(s_sc + a.chunk);
     constexpr bool MFMA = G >= 4;  // matrix-core form of the attention core
-    // the threshold search (last arriver only) is over before the attention stages V tiles
+    constexpr int NB = G * WD * 32 + 1, NBR = (NB + 15) / 16 * 16;  // score values; words of LDS for their histogram
+    constexpr int CAND_MAX = 1024;
+    // the candidate list and the threshold search are over before the attention stages V tiles
     __shared__ __attribute__((aligned(16))) union {
-        ThresholdLds ts;
+        struct {
+            uint32_t cand[CAND_MAX];
+            uint4 win[4][64];  // {all, before} of a column pair, a wave's rows each
+        } sel;
         uint16_t vt[MFMA ? HATA_VT_ELEMS : 8];
     } U;
-    ThresholdLds& TS = U.ts;
     __shared__ __attribute__((aligned(16))) AttnLds<G> S;
     __shared__ uint32_t scan4[4];
-    __shared__ int s_flag;
-    __shared__ uint32_t s_rec[2];
-    __shared__ int s_low;  // lowest score of this chunk
+    __shared__ int s_flag, s_miss, s_quit;
+    __shared__ int s_est, s_Tc, s_ncand;  // scores at which the chunk's own cumulative histogram reaches its share, and the candidates'
     __shared__ int s_bad;  // this workgroup gave up a wait: the unit's outputs are invalid
     __shared__ uint32_t s_codes[(G + 1) * WD];  // codes of the G query heads and of the appended key
     // PAGED: where the pages of this chunk's rows start (pages of 16 rows or more: at most chunk / 16 + 1)
@@ -278,20 +298,23 @@ void decode_step_coop_kernel(const CoopArgs a) {
     int64_t u;
     int c;
     if (a.units % 8 == 0) {
-        const int j = blockIdx.x >> 3;
+        const uint32_t j = blockIdx.x >> 3;
         if (a.cmajor) {
-            const int ug = a.units >> 3;  // groups of 8 units
-            u = (int64_t)(j % ug) * 8 + (blockIdx.x & 7);
-            c = j / ug;
+            uint32_t group;  // of 8 units
+            c = (int)divide(j, a.by_groups, group);
+            u = (int64_t)group * 8 + (blockIdx.x & 7);
         } else {
-            u = (int64_t)(j / a.n_chunks) * 8 + (blockIdx.x & 7);
-            c = j % a.n_chunks;
+            uint32_t chunk;
+            u = (int64_t)divide(j, a.by_chunks, chunk) * 8 + (blockIdx.x & 7);
+            c = (int)chunk;
         }
     } else {
-        u = blockIdx.x / a.n_chunks;
-        c = blockIdx.x % a.n_chunks;
+        uint32_t chunk;
+        u = divide(blockIdx.x, a.by_chunks, chunk);
+        c = (int)chunk;
     }
-    const int b = (int)(u / a.Hkv), h = (int)(u % a.Hkv);
+    uint32_t head;
+    const int b = (int)divide((uint32_t)u, a.by_heads, head), h = (int)head;
     // the query vector this workgroup will encode first (vector c, if c < G) does not depend on the
     // sequence length: its loads go out before anything else
     const uint16_t* qv = a.q + ((int64_t)b * a.Hq + h * G) * HATA_D;
@@ -309,6 +332,11 @@ void decode_step_coop_kernel(const CoopArgs a) {
         nblk = min(((base + a.chunk - 1) >> a.pv.shift) + 1, a.pv.max_blocks) - blk0;
         if (threadIdx.x < nblk) my_page = a.pv.table[(int64_t)b * a.pv.max_blocks + blk0 + threadIdx.x];
     }
+    // this launch's number in the unit's count of launches (0 is the cleared state of the published words); the second
+    // word names a launch that chunk 0 gave up before all had read it: such a latecomer would take the next launch's number
+    const uint2 launches = ld_dev_u2(a.unit_epoch + u * HATA_COUNTER_STRIDE);
+    const uint32_t epoch = max(launches.x + 1u, 1u);
+    const bool publishes = launches.y != a.epoch;
     const int L = clampi(a.seq_len[b], 0, PAGED ? min(a.L_cap, a.pv.max_blocks << a.pv.shift) : a.L_cap);
     // Row n of the unit (a row of this chunk when PAGED) -> its row in the code array, in rows of
     // one (sequence or page, head): the contiguous cache is [B, Hkv, L_cap], the pools are
@@ -335,7 +363,7 @@ void decode_step_coop_kernel(const CoopArgs a) {
     // that every workgroup of the unit then picks up; the workgroup whose chunk holds the
     // appended row L - 1 also encodes that key, updates the code cache and scores the row from
     // the code it just computed.
-    const int nc = (L + a.chunk - 1) / a.chunk;
+    const int nc = (L + a.chunk - 1) >> a.chunk_shift;
     const bool own = a.append && L > 0 && base <= L - 1 && L - 1 < base + a.chunk;
     const int end_main = own ? L - 1 : end;  // the owner scores row L - 1 from the code it computes
     constexpr int UNR = (WD <= 2) ? 16 : (WD <= 4) ? 8 : 4;  // 64-128 B of codes in flight per lane
@@ -367,8 +395,8 @@ void decode_step_coop_kernel(const CoopArgs a) {
         unsigned long long* qrec_u = a.qrec + u * a.n_chunks * (G * WD);
         unsigned long long* qrec = qrec_u + c * (G * WD);
         if (tid < (G + 1) * WD) s_codes[tid] = 0;
-        if (tid == 0) { s_low = a.NB; s_bad = 0; }
-        for (int i = tid; i < a.NB; i += 256) hist[i] = 0;
+        if (tid == 0) { s_bad = 0; s_miss = 0; s_quit = 0; s_est = 0; s_Tc = -1; s_ncand = 0; }
+        for (int i = tid; i < NBR; i += 256) hist[i] = 0;
         if constexpr (PAGED) {
             if (tid < nblk) s_page[tid] = (clampi(my_page, 0, a.pv.n_pages - 1) * a.Hkv + h) << a.pv.shift;
             for (int i = tid + 256; i < nblk; i += 256)
@@ -491,7 +519,6 @@ void decode_step_coop_kernel(const CoopArgs a) {
     };
     {
         uint16_t* sp = a.scores + u * a.L_cap;
-        uint32_t low = 0xffffu;  // lowest score this thread sees
         for (int n0 = base + tid; n0 < end_main; n0 += 256 * UNR) {
             if (!a.prefetch || n0 != base + tid) load_codes(n0, end_main);  // (the first batch may be in the registers already)
 #pragma unroll
@@ -502,12 +529,9 @@ void decode_step_coop_kernel(const CoopArgs a) {
                     if (a.keep_scores) sp[n] = (uint16_t)s;
                     s_sc[n - base] = (uint16_t)s;
                     atomicAdd(&hist[s], 1u);
-                    low = min(low, s);
                 }
             }
         }
-        low = (uint32_t)(-wave_max64(-(float)low));  // (scores <= 4096 are exact in fp32)
-        if ((tid & 63) == 0 && low < (uint32_t)a.NB) atomicMin(&s_low, (int)low);
         if (own && tid == 0) {
             uint32_t kw[WD];
 #pragma unroll
@@ -516,190 +540,280 @@ void decode_step_coop_kernel(const CoopArgs a) {
             if (a.keep_scores) sp[L - 1] = (uint16_t)s;
             s_sc[L - 1 - base] = (uint16_t)s;
             atomicAdd(&hist[s], 1u);
-            atomicMin(&s_low, (int)s);
         }
     }
     __syncthreads();
     TC(41);
-    // ---- 2. publish the histogram, arrive at the unit, threshold by the last arriver
+    // ---- 2. the unit's threshold.  Every workgroup publishes the CUMULATIVE histogram of its chunk (how many keys
+    // score at most s).  Every workgroup of the unit then adds up the few columns around its own chunk's estimate of the
+    // threshold -- those of all chunks, and those of the chunks before its own -- which gives it the threshold
+    // and its own place in the index list without a further exchange.  A published word holds two counts and the unit's
+    // epoch, so the words themselves tell when they are there: no arrival counter, no wait for the stores.
+    // The epoch counts the unit's launches in device memory, so that a replay of a captured HIP graph, which
+    // freezes kernel arguments, has one of its own too; chunk 0 moves it on once it has seen every chunk's words (all
+    // have read it by then).
+    const int n_keys = end - base;
     {
-        uint32_t* hp32 = reinterpret_cast<uint32_t*>(a.chunk_hist + (u * a.n_chunks + c) * a.NBP);
-        for (int i = tid; i < a.NBP / 2; i += 256) {
-            const uint32_t lo = (2 * i < a.NB) ? hist[2 * i] : 0u;
-            const uint32_t hi = (2 * i + 1 < a.NB) ? hist[2 * i + 1] : 0u;
-            st_dev(hp32 + i, lo | (hi << 16));
+        constexpr int SEG = ((NB + 255) / 256 + 3) / 4 * 4;  // consecutive scores of a thread
+        // keys of this chunk if the unit's selection were spread evenly over its chunks
+        const int share = nc == 1 ? keff : min(n_keys, (int)((float)keff * (float)n_keys * __builtin_amdgcn_rcpf((float)L)) + 1);
+        const int want = min(n_keys, 2 * share + 64);
+        const int s0 = tid * SEG;
+        uint32_t cm[SEG];
+#pragma unroll
+        for (int j4 = 0; j4 < SEG; j4 += 4) {
+            uint4 v = make_uint4(0, 0, 0, 0);
+            if (s0 + j4 < NBR) v = *reinterpret_cast<const uint4*>(&hist[s0 + j4]);
+            cm[j4] = v.x + (j4 ? cm[j4 ? j4 - 1 : 0] : 0u);
+            cm[j4 + 1] = cm[j4] + v.y;
+            cm[j4 + 2] = cm[j4 + 1] + v.z;
+            cm[j4 + 3] = cm[j4 + 2] + v.w;
         }
-        for (int i = tid; i < a.NB; i += 256) {
-            const uint32_t hv = hist[i];
-            if (hv) atomicAdd(&a.unit_hist[u * a.NB + i], hv);
+        const uint32_t loc = cm[SEG - 1];
+        const uint32_t incl = wave_incl_scan(loc);
+        if ((tid & 63) == 63) scan4[tid >> 6] = incl;
+        __syncthreads();
+        const int wv = tid >> 6;
+        const uint32_t run = (wv > 0 ? scan4[0] : 0u) + (wv > 1 ? scan4[1] : 0u) + (wv > 2 ? scan4[2] : 0u) + incl - loc;
+#pragma unroll
+        for (int j = 0; j < SEG; ++j) cm[j] += run;
+        // smallest scores whose count reaches the share and the candidates' number
+        if (run < (uint32_t)share && run + loc >= (uint32_t)share) {
+            int at = s0;
+#pragma unroll
+            for (int j = 0; j < SEG; ++j) at += cm[j] < (uint32_t)share ? 1 : 0;
+            s_est = at;
+        }
+        if (run < (uint32_t)want && run + loc >= (uint32_t)want) {
+            int at = s0;
+            uint32_t n = 0;
+#pragma unroll
+            for (int j = SEG - 1; j >= 0; --j) {
+                at += cm[j] < (uint32_t)want ? 1 : 0;
+                if (cm[j] >= (uint32_t)want) n = cm[j];
+            }
+            s_Tc = at;
+            s_ncand = (int)n;
+        }
+        unsigned long long* hp = a.cum + u * a.cum_pitch + c * (a.NBP / 2);
+#pragma unroll
+        for (int j4 = 0; j4 < SEG; j4 += 4) {
+            if (s0 + j4 < NBR) *reinterpret_cast<uint4*>(&hist[s0 + j4]) = make_uint4(cm[j4], cm[j4 + 1], cm[j4 + 2], cm[j4 + 3]);
+            if (nc > 1 && publishes && s0 + j4 < a.NBP) {
+#pragma unroll
+                for (int j = j4; j < j4 + 4; j += 2)
+                    st_dev(hp + (s0 + j) / 2, ((unsigned long long)epoch << 32) | (cm[j] | (cm[j + 1] << 16)));
+            }
         }
     }
+    if (nc > 1 && publishes && tid < nc)  // (at most 256 chunks)
+        st_dev(reinterpret_cast<uint32_t*>(a.cum + u * a.cum_pitch + a.cum_marks) + tid * a.mark_pitch + c, epoch);
     TC(42);
-    wait_stores();
     __syncthreads();
-    TC(43);
-    if (tid == 0) {
-        const uint32_t done = atomicAdd(&a.unit_counter[u * HATA_COUNTER_STRIDE], 1u);
-        const int last = (done == (uint32_t)(nc - 1));
-        if (last) a.unit_counter[u * HATA_COUNTER_STRIDE] = 0;
-        s_flag = last;
-    }
-    __syncthreads();
-    int32_t* ci_u = a.chunk_info + u * (a.n_chunks + 1) * 2;
-    unsigned long long* rec_u = a.rec + u * a.n_chunks * HATA_REC_STRIDE;
-    TC(44);
     // query fragments for the attention: in flight across the wait below
     uint32_t qr[MFMA ? 1 : G][4];
     uint4 qb[4];
     if constexpr (MFMA) attn_load_q_mfma<G>(a.q + ((int64_t)b * a.Hq + hq0) * HATA_D, qb);
     else attn_load_q<G>(a.q + ((int64_t)b * a.Hq + hq0) * HATA_D, qr);
-    if (s_flag) {
-        TU(51);
-        unit_threshold<(G * WD * 32) / 256 + 1>(a.chunk_hist + u * a.n_chunks * a.NBP, a.unit_hist + u * a.NB, nc, keff,
-                             a.NB, a.NBP, ci_u, a.unit_info + u * 2, hist, TS, rec_u, a.epoch,
-                             s_low < a.NB ? s_low : -1);
-        TU(52);
-    }
-    // While the unit's threshold is on its way (the last arriver computes it, everybody else would only
-    // wait): an ordered list of the chunk's CANDIDATES, the keys up to a score Tc chosen from the chunk's
-    // own histogram so that the list holds about twice the chunk's share of the budget.  If the unit's
-    // threshold turns out to be at most Tc -- the rule -- the selection is a filter over this short
-    // list instead of a pass over the whole chunk.  The list lives where the last arriver keeps its
-    // threshold search and the attention later stages V (neither is in use by this workgroup now).
-    constexpr int CAND_MAX = 1024;
-    uint32_t* const s_cand = reinterpret_cast<uint32_t*>(&U);
-    __shared__ int s_Tc, s_ncand;
-    {
-        if (tid == 0) { s_Tc = -1; s_ncand = 0; }
-        if (!s_flag) {
-            const int n_keys = end - base;
-            const int want = min(n_keys, (int)(((int64_t)keff * n_keys + L - 1) / L) * 2 + 64);
-            // smallest score whose inclusive count reaches `want`: thread t owns seg consecutive bins
-            const int seg = (a.NB + 255) / 256;
-            uint32_t loc = 0;
-            for (int j = 0; j < seg; ++j) loc += (tid * seg + j < a.NB) ? hist[tid * seg + j] : 0u;
-            const uint32_t incl = wave_incl_scan(loc);
-            if ((tid & 63) == 63) scan4[tid >> 6] = incl;
-            __syncthreads();
-            const int wv = tid >> 6;
-            uint32_t run = (wv > 0 ? scan4[0] : 0u) + (wv > 1 ? scan4[1] : 0u) + (wv > 2 ? scan4[2] : 0u) + incl - loc;
-            if (run < (uint32_t)want && run + loc >= (uint32_t)want) {
-                for (int j = 0; j < seg; ++j) {
-                    const uint32_t hv = (tid * seg + j < a.NB) ? hist[tid * seg + j] : 0u;
-                    if (run < (uint32_t)want && run + hv >= (uint32_t)want) { s_Tc = tid * seg + j; s_ncand = (int)(run + hv); }
-                    run += hv;
+    // While the other workgroups of the unit arrive: an ordered list of the chunk's CANDIDATES, the keys up to a
+    // score Tc chosen from the chunk's own histogram so that the list holds about twice the chunk's share of the
+    // budget.  If the unit's threshold turns out to be at most Tc -- the rule -- the selection is a filter over
+    // this short list instead of a pass over the whole chunk.
+    uint32_t* const s_cand = U.sel.cand;
+    const int Tc = s_Tc;
+    const bool listed = nc > 1 && Tc >= 0 && s_ncand <= CAND_MAX;
+    if (listed) {
+        const int wv = tid >> 6;
+        if constexpr (BIG) {
+            // (16 keys at a time, as the one-pass compaction of these chunks below)
+            const int kpt = a.chunk / 256;
+            const int n_first = tid * kpt;
+            uint32_t mc[8];
+            uint32_t cn = 0;
+#pragma unroll
+            for (int g = 0; g < 8; ++g) {
+                mc[g] = 0;
+                if (g * 16 < kpt) {
+                    const uint4 v0 = *reinterpret_cast<const uint4*>(&s_sc[n_first + g * 16]);
+                    const uint4 v1 = *reinterpret_cast<const uint4*>(&s_sc[n_first + g * 16 + 8]);
+                    const uint32_t w8[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+                    uint32_t m = 0;
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        const int sc = (int)((i & 1) ? (w8[i >> 1] >> 16) : (w8[i >> 1] & 0xffffu));
+                        m |= (sc <= Tc ? 1u : 0u) << i;
+                    }
+                    const int nlive = clampi(end - base - n_first - g * 16, 0, 16);
+                    mc[g] = m & ((1u << nlive) - 1u);
+                    cn += __popc(mc[g]);
                 }
             }
+            const uint32_t cincl = wave_incl_scan(cn);
+            __syncthreads();  // (scan4 is free again)
+            if ((tid & 63) == 63) scan4[tid >> 6] = cincl;
             __syncthreads();
-            const int Tc = s_Tc;
-            if (Tc >= 0 && s_ncand <= CAND_MAX) {
-                if constexpr (BIG) {
-                    // (16 keys at a time, as the one-pass compaction of these chunks below)
-                    const int kpt = a.chunk / 256;
-                    const int n_first = tid * kpt;
-                    uint32_t mc[8];
-                    uint32_t cn = 0;
+            uint32_t r = (wv > 0 ? scan4[0] : 0u) + (wv > 1 ? scan4[1] : 0u) + (wv > 2 ? scan4[2] : 0u) + cincl - cn;
 #pragma unroll
-                    for (int g = 0; g < 8; ++g) {
-                        mc[g] = 0;
-                        if (g * 16 < kpt) {
-                            const uint4 v0 = *reinterpret_cast<const uint4*>(&s_sc[n_first + g * 16]);
-                            const uint4 v1 = *reinterpret_cast<const uint4*>(&s_sc[n_first + g * 16 + 8]);
-                            const uint32_t w8[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
-                            uint32_t m = 0;
+            for (int g = 0; g < 8; ++g) {
+                uint32_t m = mc[g];
+                while (m) {
+                    const int n = n_first + g * 16 + __ffs(m) - 1;
+                    m &= m - 1;
+                    if (r < (uint32_t)CAND_MAX) s_cand[r] = (uint32_t)n | ((uint32_t)s_sc[n] << 16);
+                    ++r;
+                }
+            }
+        } else {
+            const int kpt = a.chunk / 256;
+            const int n_first = tid * kpt;
+            uint32_t sv[16];
 #pragma unroll
-                            for (int i = 0; i < 16; ++i) {
-                                const int sc = (int)((i & 1) ? (w8[i >> 1] >> 16) : (w8[i >> 1] & 0xffffu));
-                                m |= (sc <= Tc ? 1u : 0u) << i;
-                            }
-                            const int nlive = clampi(end - base - n_first - g * 16, 0, 16);
-                            mc[g] = m & ((1u << nlive) - 1u);
-                            cn += __popc(mc[g]);
-                        }
-                    }
-                    const uint32_t cincl = wave_incl_scan(cn);
-                    __syncthreads();  // (scan4 is free again)
-                    if ((tid & 63) == 63) scan4[tid >> 6] = cincl;
-                    __syncthreads();
-                    uint32_t r = (wv > 0 ? scan4[0] : 0u) + (wv > 1 ? scan4[1] : 0u) + (wv > 2 ? scan4[2] : 0u) + cincl - cn;
-#pragma unroll
-                    for (int g = 0; g < 8; ++g) {
-                        uint32_t m = mc[g];
-                        while (m) {
-                            const int n = n_first + g * 16 + __ffs(m) - 1;
-                            m &= m - 1;
-                            if (r < (uint32_t)CAND_MAX) s_cand[r] = (uint32_t)n | ((uint32_t)s_sc[n] << 16);
-                            ++r;
-                        }
-                    }
+            for (int i4 = 0; i4 < 4; ++i4) {
+                if (i4 * 4 < kpt) {
+                    const uint2 v = *reinterpret_cast<const uint2*>(&s_sc[n_first + i4 * 4]);
+                    sv[4 * i4 + 0] = v.x & 0xffffu; sv[4 * i4 + 1] = v.x >> 16;
+                    sv[4 * i4 + 2] = v.y & 0xffffu; sv[4 * i4 + 3] = v.y >> 16;
                 } else {
-                    const int kpt = a.chunk / 256;
-                    const int n_first = tid * kpt;
-                    uint32_t sv[16];
-#pragma unroll
-                    for (int i4 = 0; i4 < 4; ++i4) {
-                        if (i4 * 4 < kpt) {
-                            const uint2 v = *reinterpret_cast<const uint2*>(&s_sc[n_first + i4 * 4]);
-                            sv[4 * i4 + 0] = v.x & 0xffffu; sv[4 * i4 + 1] = v.x >> 16;
-                            sv[4 * i4 + 2] = v.y & 0xffffu; sv[4 * i4 + 3] = v.y >> 16;
-                        } else {
-                            sv[4 * i4 + 0] = sv[4 * i4 + 1] = sv[4 * i4 + 2] = sv[4 * i4 + 3] = 0xffffffffu;
-                        }
-                    }
-                    const int nlive = clampi(end - base - n_first, 0, kpt);
-                    uint32_t m_c = 0;
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) m_c |= ((int)sv[i] <= Tc ? 1u : 0u) << i;
-                    m_c &= (1u << nlive) - 1u;
-                    const uint32_t cn = __popc(m_c);
-                    const uint32_t cincl = wave_incl_scan(cn);
-                    __syncthreads();  // (scan4 is free again)
-                    if ((tid & 63) == 63) scan4[tid >> 6] = cincl;
-                    __syncthreads();
-                    uint32_t r = (wv > 0 ? scan4[0] : 0u) + (wv > 1 ? scan4[1] : 0u) + (wv > 2 ? scan4[2] : 0u) + cincl - cn;
-                    while (m_c) {
-                        const int i = __ffs(m_c) - 1;
-                        m_c &= m_c - 1;
-                        if (r < (uint32_t)CAND_MAX) s_cand[r] = (uint32_t)(n_first + i) | (sv[i] << 16);
-                        ++r;
-                    }
+                    sv[4 * i4 + 0] = sv[4 * i4 + 1] = sv[4 * i4 + 2] = sv[4 * i4 + 3] = 0xffffffffu;
                 }
-            } else if (tid == 0) {
-                s_Tc = -1;
+            }
+            const int nlive = clampi(end - base - n_first, 0, kpt);
+            uint32_t m_c = 0;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) m_c |= ((int)sv[i] <= Tc ? 1u : 0u) << i;
+            m_c &= (1u << nlive) - 1u;
+            const uint32_t cn = __popc(m_c);
+            const uint32_t cincl = wave_incl_scan(cn);
+            __syncthreads();  // (scan4 is free again)
+            if ((tid & 63) == 63) scan4[tid >> 6] = cincl;
+            __syncthreads();
+            uint32_t r = (wv > 0 ? scan4[0] : 0u) + (wv > 1 ? scan4[1] : 0u) + (wv > 2 ? scan4[2] : 0u) + cincl - cn;
+            // (straight-line: a loop over the set bits would pick its score out of sixteen registers at every turn)
+#pragma unroll
+            for (int i4 = 0; i4 < 4; ++i4) {
+                if (i4 * 4 < kpt) {
+#pragma unroll
+                    for (int i = 4 * i4; i < 4 * i4 + 4; ++i)
+                        if ((m_c >> i) & 1u) s_cand[r++] = (uint32_t)(n_first + i) | (sv[i] << 16);
+                }
             }
         }
-        __syncthreads();
     }
-    // every workgroup (the last arriver too) picks up its chunk's record: two words that carry
-    // this launch's epoch once the threshold of the unit has been published
-    if (tid == 0) {
-        int budget = a.spin_limit;
-        unsigned long long r0, r1;
-        for (;;) {
-            r0 = __hip_atomic_load(rec_u + HATA_REC_STRIDE * c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            r1 = __hip_atomic_load(rec_u + HATA_REC_STRIDE * c + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (((uint32_t)(r0 >> 32) == a.epoch && (uint32_t)(r1 >> 32) == a.epoch) || --budget <= 0) break;
-            __builtin_amdgcn_s_sleep(1);
+    TC(52);
+    int T = 0, take = 0, off = 0, cnt = 0;
+    if (nc == 1) {
+        if (keff > 0) {
+            T = s_est;
+            take = keff - (T > 0 ? (int)hist[T - 1] : 0);
+            cnt = keff;
         }
-        if (budget <= 0) { a.error_word[0] = 1u; s_bad = 1; r0 = 0; r1 = 0; }  // gave up: this launch's results are invalid
-        s_rec[0] = (uint32_t)r0;
-        s_rec[1] = (uint32_t)r1;
-        // this workgroup is the record's only reader: retired at once (see the query code words above)
-        rec_u[HATA_REC_STRIDE * c] = 0ull;
-        rec_u[HATA_REC_STRIDE * c + 1] = 0ull;
+    } else {
+        const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+        const unsigned long long* hu = a.cum + u * a.cum_pitch;
+        const uint32_t* marks = reinterpret_cast<const uint32_t*>(hu + a.cum_marks) + c * a.mark_pitch;
+        int budget = a.spin_limit, attempt = 0;
+        // The threshold T lies in [t_lo, t_hi].  A window of 64 columns shows it if the first of them counts fewer
+        // than keff keys (or is score 0) and the last one at least keff.  One window is enough unless the unit's chunks differ
+        // widely; the next one is beside it, the ones after that halve what is left.
+        const int w0_max = max(0, a.NBP - 64);
+        int t_lo = 0, t_hi = NB - 1, w0 = keff == 0 ? 0 : clampi((s_est - 32) & ~1, 0, w0_max);
+        bool found = false;  // (the same in all waves: every decision below is made from the same words of LDS)
+#pragma clang loop unroll(disable)
+        for (int it = 0; it < 32 && !found; ++it) {
+            // a wave reads two rows at a time, half a wave each, a lane two columns
+            const unsigned long long* hw = hu + min(w0 / 2 + (lane & 31), a.NBP / 2 - 1);
+            if (it) __syncthreads();  // (the last window has been read)
+            for (;;) {
+                // With many chunks the rows are too much to be read in vain; otherwise they are mostly there by now.
+                if (nc > 32 || attempt != it) {
+                    // One wave waits for the marks the chunks leave behind their rows, on lines that no other workgroup reads.
+                    // (Polling with the loads below kept a compute unit's memory pipe so busy that the youngest
+                    // workgroup on it -- the one everybody waited for -- never got to its own; all workgroups of a
+                    // unit polling the same marks made everything else that went to those lines' channel wait.)
+                    if (wv == 0) {
+                        for (;;) {
+                            bool absent = false;
+                            for (int m = lane; m < nc; m += 64) absent |= ld_dev(marks + m) != epoch;
+                            if (__builtin_amdgcn_ballot_w64(absent) == 0ull || --budget <= 0) break;
+                            __builtin_amdgcn_s_sleep(1);
+                        }
+                        if (--budget <= 0 && lane == 0) { a.error_word[0] = 1u; s_bad = 1; s_quit = attempt + 1; }  // gave up: this launch's results are invalid
+                    }
+                    __syncthreads();
+                    if (s_quit == attempt + 1) break;  // (all waves see the same: the next one to be written belongs to a later attempt)
+                }
+                ++attempt;
+                bool miss = false;
+                uint32_t sum[4] = {0, 0, 0, 0};  // columns 0 and 1 of all chunks, of those before this one
+                constexpr int UN = 8;
+                for (int r2 = 2 * wv; r2 < nc; r2 += 8 * UN) {
+                    const int r0 = r2 + (lane >> 5);
+                    unsigned long long x[UN];
+#pragma unroll
+                    for (int j = 0; j < UN; ++j) {
+                        x[j] = (unsigned long long)epoch << 32;
+                        if (r2 + 8 * j < nc)
+                            x[j] = __hip_atomic_load(hw + min(r0 + 8 * j, nc - 1) * (a.NBP / 2), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    }
+#pragma unroll
+                    for (int j = 0; j < UN; ++j) {
+                        const uint32_t lo = (uint32_t)x[j] & 0xffffu, hi = (uint32_t)x[j] >> 16;
+                        const bool in = r0 + 8 * j < nc, before = r0 + 8 * j < c;
+                        miss |= (uint32_t)(x[j] >> 32) != epoch;
+                        sum[0] += in ? lo : 0u;
+                        sum[1] += in ? hi : 0u;
+                        sum[2] += before ? lo : 0u;
+                        sum[3] += before ? hi : 0u;
+                    }
+                }
+                if (__builtin_amdgcn_ballot_w64(miss) != 0ull && lane == 0) s_miss = attempt;
+                U.sel.win[wv][lane] = make_uint4(sum[0], sum[1], sum[2], sum[3]);
+                __syncthreads();
+                if (s_miss != attempt) break;
+            }
+            uint32_t all0 = 0, all1 = 0, bef0 = 0, bef1 = 0;
+#pragma unroll
+            for (int w = 0; w < 8; ++w) {
+                const uint4 v = U.sel.win[w >> 1][(w & 1) * 32 + (lane & 31)];
+                all0 += v.x; all1 += v.y; bef0 += v.z; bef1 += v.w;
+            }
+            const unsigned long long hit = __builtin_amdgcn_ballot_w64(all1 >= (uint32_t)keff);
+            if (hit == 0ull) {
+                t_lo = w0 + 64;
+            } else {
+                const int l = __ffsll(hit) - 1, p = max(l - 1, 0);
+                const bool even = (uint32_t)__builtin_amdgcn_readlane((int)all0, l) >= (uint32_t)keff;
+                if (even && l == 0 && w0 > 0) {
+                    t_hi = w0;
+                } else {
+                    found = true;
+                    T = w0 + 2 * l + (even ? 0 : 1);
+                    // keys below T and up to T: in the whole unit, in the chunks before this one, in this one
+                    const int lt = even ? (l > 0 ? __builtin_amdgcn_readlane((int)all1, p) : 0) : __builtin_amdgcn_readlane((int)all0, l);
+                    const int lt_b = even ? (l > 0 ? __builtin_amdgcn_readlane((int)bef1, p) : 0) : __builtin_amdgcn_readlane((int)bef0, l);
+                    const int le_b = __builtin_amdgcn_readlane((int)(even ? bef0 : bef1), l);
+                    const int need = keff - lt;  // ties to grant, in cache order
+                    const int own_lt = T > 0 ? (int)hist[min(T, NBR) - 1] : 0, own_eq = (int)hist[min(T, NBR - 1)] - own_lt;
+                    take = clampi(need - (le_b - lt_b), 0, own_eq);
+                    cnt = own_lt + take;
+                    off = lt_b + min(le_b - lt_b, need);
+                }
+            }
+            // (every step leaves a shorter [t_lo, t_hi]: at most a dozen of them, unless a wait was given up)
+            if (!found) w0 = clampi((it == 0 ? (hit ? t_hi - 62 : t_lo - 2) : (t_lo + t_hi) / 2 - 32) & ~1, 0, w0_max);
+        }
+        TC(51);
+        off = clampi(off, 0, a.k_max);
+        cnt = clampi(cnt, 0, min(n_keys, a.k_max - off));
+        if (c == 0 && tid == 0)
+            st_dev(reinterpret_cast<unsigned long long*>(a.unit_epoch + u * HATA_COUNTER_STRIDE), ((unsigned long long)(s_bad ? a.epoch : 0u) << 32) | epoch);
     }
-    __syncthreads();
-    TC(45);
-    const int off = clampi((int)(s_rec[0] >> 16), 0, a.k_max);
-    const int cnt = clampi((int)(s_rec[0] & 0xffffu), 0, min(a.chunk, a.k_max - off));
-    const int take = (int)(s_rec[1] >> 13);
-    const int T = (int)(s_rec[1] & 0x1fffu);
 
     // ---- 3. ordered compaction of the own chunk from the LDS scores
     int32_t* io = a.idx + u * a.k_max;
     if (c == 0)
         for (int p = keff + tid; p < a.k_max; p += 256) io[p] = -1;
-    if (s_Tc >= 0 && (T <= s_Tc || cnt == 0)) {
+    if (listed && (T <= Tc || cnt == 0)) {
         // the candidate list covers the selection: a thread filters up to four consecutive candidates
         const int n_cand = s_ncand;
         const int cpt = (n_cand + 255) / 256;  // <= 4
@@ -728,14 +842,15 @@ void decode_step_coop_kernel(const CoopArgs a) {
         while ((uint32_t)__popc(keep) > avail) keep &= ~(0x80000000u >> __clz(keep));
         uint32_t sel = m_lt | keep;
         uint32_t r = lt_b + ties_before;
-        while (sel) {
-            const int i = __ffs(sel) - 1;
-            sel &= sel - 1;
-            if (r < (uint32_t)cnt) {
-                s_sc[r] = (uint16_t)(cw[i] & 0xffffu);
-                io[off + r] = base + (int)(cw[i] & 0xffffu);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if ((sel >> i) & 1u) {
+                if (r < (uint32_t)cnt) {
+                    s_sc[r] = (uint16_t)(cw[i] & 0xffffu);
+                    io[off + r] = base + (int)(cw[i] & 0xffffu);
+                }
+                ++r;
             }
-            ++r;
         }
     } else if constexpr (BIG) {
         // chunks of 8192 .. 32768 keys: a thread takes kpt = 32 .. 128 consecutive keys, 16 at a time
@@ -1007,10 +1122,10 @@ static const void* coop_kernel_for(int Wd, int G, bool paged, bool big) {
 
 // chunk sizes the kernel is built for, and the width of the {offset, count} record word
 static bool coop_shape_ok(const hata_ctx* c, bool paged, int chunk) {
-    return chunk >= 256 && chunk % 256 == 0 && chunk <= HATA_COOP_MAX_CHUNK &&
+    return chunk >= 1024 && (chunk & (chunk - 1)) == 0 && chunk <= HATA_COOP_MAX_CHUNK &&
            c->cfg.k_max <= 65535;
 }
-static size_t coop_dynamic_lds(const hata_ctx* c, int chunk) { return (size_t)chunk * 2 + (size_t)c->NB * 4; }
+static size_t coop_dynamic_lds(const hata_ctx* c, int chunk) { return (size_t)chunk * 2 + (size_t)((c->NB + 15) / 16 * 16) * 4; }
 
 // how many workgroups of this context's cooperative kernel fit on the device at once
 int coop_capacity(const hata_ctx* c, bool paged, int chunk) {
@@ -1065,17 +1180,20 @@ hipError_t launch_coop_step(hata_ctx* c, const void* q, const void* K, const voi
     a.prefetch = (c->cus > 0 && (int64_t)n_chunks * f.Hkv * B <= c->cus) ? 1 : 0;
     a.qcodes = c->qcodes + (int64_t)b0 * f.Hq * c->Wd; a.codes = codes; a.seq_len = seq_len; a.kbud = k;
     a.scores = c->scores + u0 * f.L_cap; a.idx = (idx_only ? idx_only : c->idx) + u0 * f.k_max;
-    a.chunk_hist = c->chunk_hist + u0 * n_chunks * c->NBP;
-    a.chunk_info = c->chunk_info + u0 * (n_chunks + 1) * 2; a.unit_info = c->unit_info + u0 * 2;
-    a.unit_counter = c->unit_counter + u0 * HATA_COUNTER_STRIDE;
-    a.unit_hist = c->unit_hist + u0 * c->NB; a.rec = c->coop_rec + u0 * n_chunks * HATA_REC_STRIDE;
+    a.cum_pitch = coop_cum_pitch(c->n_chunks, c->NBP);
+    a.cum_marks = c->n_chunks * (c->NBP / 2);
+    a.mark_pitch = coop_mark_pitch(c->n_chunks);
+    a.cum = c->coop_cum + u0 * a.cum_pitch;
+    a.unit_epoch = c->unit_epoch + u0 * HATA_COUNTER_STRIDE;
     a.qrec = c->coop_qrec + u0 * n_chunks * c->G * c->Wd;
     a.attn_counter = c->attn_counter + u0 * HATA_COUNTER_STRIDE;
     a.error_word = c->error_word;
     a.partials = c->partials + (int64_t)b0 * f.Hq * n_chunks * HATA_PSTRIDE;
     a.out = (uint16_t*)out; a.out_f32 = out_f32;
     a.Hq = f.Hq; a.Hkv = f.Hkv; a.L_cap = f.L_cap; a.k_max = f.k_max; a.chunk = chunk;
-    a.n_chunks = n_chunks; a.NB = c->NB; a.NBP = c->NBP; a.units = f.Hkv * B;
+    a.n_chunks = n_chunks; a.NBP = c->NBP; a.units = f.Hkv * B;
+    a.chunk_shift = 31 - __builtin_clz((unsigned)chunk);
+    a.by_groups = make_divisor(a.units >= 8 ? a.units / 8 : 1); a.by_chunks = make_divisor(n_chunks); a.by_heads = make_divisor(f.Hkv);
     a.sb = f.kv_stride_b; a.sh = f.kv_stride_h; a.sn = f.kv_stride_n;
     a.scale_log2 = sm_scale * 1.4426950408889634f;
     c->epoch += 1;

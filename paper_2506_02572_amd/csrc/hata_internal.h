@@ -12,9 +12,6 @@
 #define HATA_MAX_NB 4097
 // dense attention: at most this many rounds of one workgroup per CU, with a partial result each
 #define HATA_DENSE_ROUNDS 4
-// 64-bit words between the records of consecutive chunks (two are used): a cache line per chunk, so
-// that the workgroups polling for their records do not all read the same lines
-#define HATA_REC_STRIDE 8
 
 struct hata_ctx {
     hata_config cfg;
@@ -43,7 +40,8 @@ struct hata_ctx {
     uint32_t* unit_hist;     // [B_max*Hkv, NB] total histogram of a unit (self-clearing)
     uint32_t* attn_counter;  // [B_max*Hq (cooperative step: per unit), attn_counter_stride] finished attention slices (self-resetting)
     int attn_counter_stride; // HATA_COUNTER_STRIDE; 1 in the static scratch of hata_sparse_decode_static
-    unsigned long long* coop_rec;  // [B_max*Hkv, n_chunks, HATA_REC_STRIDE] epoch-stamped chunk records, two words used (cooperative step)
+    unsigned long long* coop_cum;  // [B_max*Hkv, coop_cum_pitch()] epoch-stamped cumulative chunk histograms, two scores a word, and marks (cooperative step)
+    uint32_t* unit_epoch;          // [B_max*Hkv, HATA_COUNTER_STRIDE] launches of the cooperative step on a unit, and the last one given up
     unsigned long long* coop_qrec; // [B_max*Hkv, n_chunks, G*Wd] epoch-stamped query code words, one copy per chunk (cooperative step)
     uint32_t* error_word;    // [1] set by a cooperative launch that gave up waiting
     uint32_t epoch;          // launch counter of the cooperative step
@@ -112,6 +110,10 @@ hipError_t launch_coop_step(hata_ctx* c, const void* q, const void* K, const voi
 // (chunk: keys per workgroup, one of the context's coop_opt_chunk; idx_only != nullptr: the launch
 // stops once the index lists are written, into idx_only [B, Hkv, k_max] instead of the workspace;
 // V, out and out_f32 are not touched)
+// marks of one reading chunk (whole cache lines; the step runs with at most 256 chunks per unit), and 64-bit words of a
+// unit's whole part of coop_cum: the chunks' rows, then the marks
+inline int coop_mark_pitch(int n_chunks) { return ((n_chunks < 256 ? n_chunks : 256) + 31) / 32 * 32; }
+inline int coop_cum_pitch(int n_chunks, int NBP) { return n_chunks * (NBP / 2) + (n_chunks < 256 ? n_chunks : 256) * coop_mark_pitch(n_chunks) / 2; }
 int coop_capacity(const hata_ctx* c, bool paged, int chunk);
 
 }  // namespace hata

@@ -60,8 +60,7 @@ template <int MAXSEG = 17>
 __device__ __forceinline__ void unit_threshold(
     const uint16_t* __restrict__ hp, uint32_t* __restrict__ unit_hist_u, int nc, int keff, int NB,
     int NBP, int32_t* __restrict__ chunk_info_u, int32_t* __restrict__ unit_info_u, uint32_t* tot,
-    ThresholdLds& S, unsigned long long* __restrict__ rec_u = nullptr, uint32_t epoch = 0,
-    int spec_bmin = -1) {
+    ThresholdLds& S, int spec_bmin) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (tid == 0) { S.T = (keff > 0) ? NB : 0; S.need = 0; }
     for (int c = tid; c < nc; c += 256) { S.c_lt[c] = 0; S.c_eq[c] = 0; }
@@ -208,26 +207,14 @@ __device__ __forceinline__ void unit_threshold(
         for (int c = c0; c < c1; ++c) {
             const uint32_t can = (uint32_t)need > eqb ? (uint32_t)need - eqb : 0u;
             const uint32_t take = min(can, S.c_eq[c]);
-            if (!rec_u) {  // (the single-launch step reads the records below instead)
-                st_dev(reinterpret_cast<uint32_t*>(chunk_info_u) + c * 2 + 0, off);
-                st_dev(reinterpret_cast<uint32_t*>(chunk_info_u) + c * 2 + 1, take);
-            } else {
-                // two self-validating words per chunk (each carries the launch epoch in its upper
-                // half, so a waiting workgroup needs no separate flag): {off, selected count}, 16 bits
-                // each (the caller runs this form only for budgets below 65536 rows), and
-                // {ties granted, T}, 19 and 13 bits
-                const uint32_t cnt_c = S.c_lt[c] + take;
-                __hip_atomic_store(rec_u + HATA_REC_STRIDE * c, ((unsigned long long)epoch << 32) | (off << 16) | cnt_c,
-                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(rec_u + HATA_REC_STRIDE * c + 1, ((unsigned long long)epoch << 32) | (take << 13) | (uint32_t)T,
-                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
+            st_dev(reinterpret_cast<uint32_t*>(chunk_info_u) + c * 2 + 0, off);
+            st_dev(reinterpret_cast<uint32_t*>(chunk_info_u) + c * 2 + 1, take);
             off += S.c_lt[c] + take;
             eqb += S.c_eq[c];
         }
     }
     HATA_TRACE_AT(29, true);
-    if (tid == 0 && !rec_u) {
+    if (tid == 0) {
         // (write-through: the next launch's workgroups read these)
         st_dev(reinterpret_cast<uint32_t*>(chunk_info_u) + nc * 2 + 0, (uint32_t)keff);
         st_dev(reinterpret_cast<uint32_t*>(chunk_info_u) + nc * 2 + 1, 0u);
@@ -276,7 +263,7 @@ __device__ __forceinline__ void finish_unit(
     HATA_TRACE_AT(5, u == 0);
     // the other workgroups' histograms are read with device-coherent loads
     unit_threshold(chunk_hist_u, unit_hist + u * NB, nc, keff, NB, NBP, chunk_info + u * (n_chunks + 1) * 2,
-                   unit_info + u * 2, hist, S, nullptr, 0, low);
+                   unit_info + u * 2, hist, S, low);
     HATA_TRACE_AT(6, u == 0);
 }
 
