@@ -11,25 +11,24 @@
 // bf16 already; fp32 operands (W, dZ) are split exactly into three bf16 planes, so every product is
 // exact and only the fp32 accumulation rounds.
 //
-// Launches of a step (three, four for batches of more than TR_FEW_WGS blocks):
-//   1. train_colsum_kernel   h(k) of every key -> per-workgroup column sums (the balance term couples
-//                            every row to the sum of h(k) over its query, so those sums come first);
-//                            extra workgroups: P = W^T W - I and its squared Frobenius norm, and the
-//                            three bf16 planes of W in operand order for the next launch
-//      (train_colreduce_kernel adds the column sums up per query when there are too many workgroups
-//      for every workgroup of the next launch to do so for its own query)
-//   2. train_grad_kernel     forward of q and k again, dL/dz elementwise in the MFMA result
-//                            registers, then X^T dZ with those registers as the B operand (the
-//                            contraction index -- the row -- may be enumerated in any order, so the
-//                            32x32 result layout is used as it stands; only X is read transposed,
-//                            from the LDS tile it was staged in) -> per-workgroup partial dW;
-//                            extra workgroups: W P
-//   3. train_update_kernel   dL/dW = sigma sum partials + 2 lam W P / ||P||_F, the loss terms, weight
-//                            decay, momentum, step
-// What does not depend on a launch's main work rides along in extra workgroups of it, so that the chain is
-// as short as the data flow allows: at r = 128 and 32768 triplets six launches took 63 us of kernel time a step, the
-// three take 37 us.
+// Launches of a step (two, three where the column sums have a launch of their own):
+//   1. train_grad_kernel     The balance term couples every row to the sum of h(k) over its query, but only through
+//                            a factor per hash column: dL/dz_k = (c_j - a_n) e_n with e = 1 - h(k)^2, so
+//                            K^T dZ_k = c_j K^T E - K^T (A E), and the two contractions need no sums.
+//                            So one pass over the triplets: forward of k and q, K^T E and K^T (A E) with the MFMA
+//                            result registers as the B operand (the contraction index -- the row -- may be
+//                            enumerated in any order, so the 32x32 result layout is used as it stands;
+//                            only X is read transposed, from the LDS tile it was staged in) -> partial sums of both
+//                            and column sums of h(k) per workgroup;
+//                            on the way: W W^T in fp64, half a row per workgroup, and a copy of W
+//      (train_colreduce_kernel adds the column sums up per query where the next launch's workgroups would have too
+//      many to do so themselves)
+//   2. train_update_kernel   dL/dW = sigma sum partials + 2 lam W P / ||P||_F with W P = (W W^T) W - W, the loss
+//                            terms, weight decay, momentum, step
+// At r = 128 and 32768 triplets of four queries a step takes 27 us; with the column sums in a launch in front of the
+// gradient's, h(k) twice and W P in extra workgroups behind it, it took 36.
 #include <new>
+#include <type_traits>
 
 #include "hata_device.h"
 #include "../../include/hata_train.h"
@@ -41,13 +40,11 @@ struct hata_train_ctx {
     int n_wgs_max;
     float* colsum_part;  // [n_wgs_max, r]
     float* colsum;       // [queries (<= n_wgs_max), r]  sum of h(k_n) over the triplets of a query
-    float* bal_part;     // [column groups (<= 2), n_wgs_max]  squared norms of those sums, a query's at its first workgroup
-    float* dw_part;      // [n_wgs_max, d, r]
-    float* loss_part;    // [column groups (<= 2), n_wgs_max]
-    float* P;            // [r, r]
-    float* fro_part;     // [r]
-    float* WP;           // [d, r]  W (W^T W - I)
-    uint4* planes;       // [r / 32, 3, 8, 64]  bf16 planes of W as operand fragments, 16 bytes a lane
+    float* dw_part;      // [pairs of blocks, 3, d, r]  K^T E, the rest of X^T dZ, K^T E of the second block if its query is another
+    float* loss_part;    // [column groups (<= 4), pairs of blocks]
+    double* gram;        // [d, d]  W W^T
+    double* fro_part;    // [2 d]  what its pieces add to ||W^T W - I||_F^2 - r
+    float* W_old;        // [d, r]  the weights the gradient was taken at (the update overwrites W as it goes)
     // label builder
     double* scores;      // [n_max] qk scores
     uint32_t* bins;      // [LB_COPIES, LB_BINS] how many scores fall into each bin, zero between calls
@@ -60,8 +57,11 @@ namespace hata {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 tr_bf16x8_t;
 typedef __attribute__((ext_vector_type(16))) float tr_f32x16_t;
-#define TR_ROWS 128   // triplets per workgroup (one LDS stage)
-#define TR_FEW_WGS 512  // up to here every workgroup of the gradient launch sums its query's column sums itself
+#define TR_ROWS 128   // triplets per block: those of one query
+#define TR_PAIR 256   // triplets per workgroup: two blocks (one LDS stage)
+#define TR_FEW_WGS 512    // up to so many blocks and queries every workgroup of the update adds the column sums up itself
+#define TR_FEW_QUERIES 16
+#define TR_UPDATE_WAVES 8  // waves of an update workgroup
 #define TR_PITCH 136  // LDS row pitch in bf16 elements (272 B: conflict-free 16-B and transposed reads)
 
 // Two fp32 values -> three bf16 terms each, whose sum carries all 24 mantissa bits (each term is the
@@ -83,45 +83,25 @@ __device__ __forceinline__ float relaxed_sign(float z, float nsl) {
 }
 #define TR_LOG2E 1.4426950408889634f
 
-// Weight fragments of hash column `col` as the B operand:
-// frag[plane][kk] holds W[16 kk + 8 half + e][col], e = 0..7
-template <int R>
-__device__ __forceinline__ void load_weight_planes(const float* __restrict__ W, int col, int half,
-                                                   tr_bf16x8_t (&frag)[3][8]) {
-    const float* wp = W + col;
-#pragma unroll
-    for (int kk = 0; kk < 8; ++kk) {
-        uint32_t hi[4], mid[4], lo[4];
-#pragma unroll
-        for (int e2 = 0; e2 < 4; ++e2) {
-            const float* w2 = wp + (int64_t)(kk * 16 + 8 * half + 2 * e2) * R;
-            split3_pair(w2[0], w2[R], hi[e2], mid[e2], lo[e2]);
-        }
-        frag[0][kk] = __builtin_bit_cast(tr_bf16x8_t, make_uint4(hi[0], hi[1], hi[2], hi[3]));
-        frag[1][kk] = __builtin_bit_cast(tr_bf16x8_t, make_uint4(mid[0], mid[1], mid[2], mid[3]));
-        frag[2][kk] = __builtin_bit_cast(tr_bf16x8_t, make_uint4(lo[0], lo[1], lo[2], lo[3]));
-    }
-}
-
-// How a workgroup's waves share its TR_ROWS rows and up to 128 hash columns: a wave owns 32 columns and
-// 1 / RS of the rows (RS = row split).  At least two waves per SIMD where the columns allow it: with one,
-// nothing covers the exponentials and LDS reads between its matrix instructions.
+// How a workgroup's eight waves share its TR_PAIR rows and up to 64 hash columns: a wave owns 32 columns and
+// 1 / RG of the rows.  Half the columns and twice the rows of a 128-column tile cost as many partial sums, two contractions
+// instead of one included.
 template <int R>
 struct TrainShape {
-    static constexpr int COLS = R < 128 ? R : 128;  // columns of a workgroup
+    static constexpr int COLS = R < 64 ? R : 64;  // columns of a workgroup
     static constexpr int CG = COLS / 32;
-    static constexpr int RS = CG == 4 ? 2 : 4;
-    static constexpr int THREADS = CG * RS * 64;
-    static constexpr int TILES = TR_ROWS / 32 / RS;  // 32-row tiles of a wave
-    static constexpr int WAVES = THREADS / 64;
-    static constexpr int SLICES = THREADS / COLS;  // threads per column (below 64 columns more than the waves)
+    static constexpr int WAVES = 8, THREADS = WAVES * 64;
+    static constexpr int RG = WAVES / CG;            // row groups
+    static constexpr int HB = RG / 2;                // of a block
+    static constexpr int TILES = TR_PAIR / 32 / RG;  // 32-row tiles of a wave
+    static constexpr int SLICES = THREADS / COLS;  // threads per column
     static constexpr int COL_ROWS = WAVES > SLICES ? WAVES : SLICES;  // rows of LDS that per-column sums of either kind need
 };
 
-// rows [row0, row0 + TR_ROWS) of X [n, 128] (zeros past n): fetched into registers, later put into an LDS tile
+// rows [row0, row0 + TR_PAIR) of X [n, 128] (zeros past n): fetched into registers, later put into an LDS tile
 template <int THREADS>
 struct StagedRows {
-    static constexpr int NV = TR_ROWS * 16 / THREADS;
+    static constexpr int NV = TR_PAIR * 16 / THREADS;
     uint4 v[NV];
     __device__ __forceinline__ void fetch(const uint16_t* __restrict__ X, int row0, int n) {
 #pragma unroll
@@ -140,108 +120,23 @@ struct StagedRows {
     }
 };
 
-// Z tile t (32 rows x the wave's 32 columns) = X_tile . W: result register ri of lane (m, half)
+// Z tiles t0 .. (32 rows x the wave's 32 columns each) = X_tile . W: result register ri of lane (m, half)
 // holds row 8 (ri / 4) + 4 half + ri % 4 of the tile, column 32 w + m
-__device__ __forceinline__ tr_f32x16_t project_tile(const uint16_t* tile, int t, int m, int half,
-                                                    const tr_bf16x8_t (&wfrag)[3][8]) {
-    tr_f32x16_t acc;
+template <int TILES>
+__device__ __forceinline__ void project_tiles(const uint16_t* tile, int t0, int m, int half, const tr_bf16x8_t (&wfrag)[3][8],
+                                              tr_f32x16_t (&z)[TILES]) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+    for (int t = 0; t < TILES; ++t)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) z[t][i] = 0.f;
 #pragma unroll
     for (int kk = 0; kk < 8; ++kk) {
-        const tr_bf16x8_t x = *reinterpret_cast<const tr_bf16x8_t*>(&tile[(t * 32 + m) * TR_PITCH + kk * 16 + 8 * half]);
 #pragma unroll
-        for (int p = 0; p < 3; ++p) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, wfrag[p][kk], acc, 0, 0, 0);
-    }
-    return acc;
-}
-
-// Channel step kk of the fragments of 32 hash columns into the workspace (one wave), and all of them back
-template <int R>
-__device__ __forceinline__ void store_weight_planes(const float* __restrict__ W, int cgroup, int kk, uint4* __restrict__ planes) {
-    const int lane = threadIdx.x & 63;
-    const float* wp = W + (int64_t)(kk * 16 + 8 * (lane >> 5)) * R + cgroup * 32 + (lane & 31);
-    uint32_t f[3][4];
+        for (int t = 0; t < TILES; ++t) {
+            const tr_bf16x8_t x = *reinterpret_cast<const tr_bf16x8_t*>(&tile[((t0 + t) * 32 + m) * TR_PITCH + kk * 16 + 8 * half]);
 #pragma unroll
-    for (int e2 = 0; e2 < 4; ++e2)
-        split3_pair(wp[(int64_t)(2 * e2) * R], wp[(int64_t)(2 * e2 + 1) * R], f[0][e2], f[1][e2], f[2][e2]);
-#pragma unroll
-    for (int p = 0; p < 3; ++p)
-        planes[((cgroup * 3 + p) * 8 + kk) * 64 + lane] = make_uint4(f[p][0], f[p][1], f[p][2], f[p][3]);
-}
-__device__ __forceinline__ void fetch_weight_planes(const uint4* __restrict__ planes, int cgroup, tr_bf16x8_t (&frag)[3][8]) {
-    const uint4* src = planes + cgroup * 3 * 8 * 64 + (threadIdx.x & 63);
-#pragma unroll
-    for (int kk = 0; kk < 8; ++kk)
-#pragma unroll
-        for (int p = 0; p < 3; ++p) frag[p][kk] = __builtin_bit_cast(tr_bf16x8_t, src[(p * 8 + kk) * 64]);
-}
-
-// P = W^T W - I (column j by one workgroup) and the squared Frobenius norm of that column; THREADS threads,
-// red: THREADS / 64 floats of LDS
-template <int THREADS>
-__device__ __forceinline__ void gram_column(const float* __restrict__ W, int r, int j, float* __restrict__ P,
-                                            float* __restrict__ fro_part, float* red) {
-    const int tid = threadIdx.x;
-    float sq = 0.f;
-    for (int i = tid; i < r; i += THREADS) {
-        float acc = 0.f;
-#pragma unroll 16
-        for (int c = 0; c < HATA_D; ++c) acc = fmaf(W[(int64_t)c * r + i], W[(int64_t)c * r + j], acc);
-        acc -= (i == j) ? 1.f : 0.f;
-        P[(int64_t)i * r + j] = acc;
-        sq = fmaf(acc, acc, sq);
-    }
-    sq = wave_sum64(sq);
-    if ((tid & 63) == 0) red[tid >> 6] = sq;
-    __syncthreads();
-    if (tid == 0) {
-        float t = 0.f;
-        for (int i = 0; i < THREADS / 64; ++i) t += red[i];
-        fro_part[j] = t;
-    }
-}
-
-// grid = (n_wgs workgroups of TR_ROWS triplets, then eight for the group's weight planes, then one for each of
-// its columns of the Gram matrix; groups of up to 128 hash columns)
-template <int R>
-__global__ __launch_bounds__(TrainShape<R>::THREADS) void train_colsum_kernel(
-    const uint16_t* __restrict__ K, const float* __restrict__ W, int n, int n_wgs, float sigma,
-    float* __restrict__ colsum_part, float* __restrict__ P, float* __restrict__ fro_part, uint4* __restrict__ planes) {
-    using S = TrainShape<R>;
-    __shared__ __attribute__((aligned(16))) uint16_t tile[TR_ROWS * TR_PITCH];
-    __shared__ float s_part[S::RS][S::COLS];
-    if ((int)blockIdx.x >= n_wgs) {
-        const int j = (int)blockIdx.x - n_wgs - 8;
-        if (j >= 0) gram_column<S::THREADS>(W, R, blockIdx.y * S::COLS + j, P, fro_part, &s_part[0][0]);
-        else if (threadIdx.x < S::CG * 64) store_weight_planes<R>(W, blockIdx.y * 4 + threadIdx.x / 64, j + 8, planes);
-        return;
-    }
-    const int tid = threadIdx.x, lane = tid & 63, w = (tid >> 6) % S::CG, rs = (tid >> 6) / S::CG;
-    const int m = lane & 31, half = lane >> 5;
-    const int col = blockIdx.y * 128 + w * 32 + m;
-    StagedRows<S::THREADS> xk;
-    xk.fetch(K, blockIdx.x * TR_ROWS, n);
-    tr_bf16x8_t wfrag[3][8];
-    load_weight_planes<R>(W, col, half, wfrag);
-    xk.put(tile);
-    __syncthreads();
-    const float nsl = -sigma * TR_LOG2E;
-    float cs = 0.f;
-#pragma unroll
-    for (int t = 0; t < S::TILES; ++t) {
-        const tr_f32x16_t z = project_tile(tile, rs * S::TILES + t, m, half, wfrag);
-#pragma unroll
-        for (int i = 0; i < 16; ++i) cs += relaxed_sign(z[i], nsl);  // (rows past n are zero: h = 0)
-    }
-    cs += __shfl_xor(cs, 32, 64);
-    if (half == 0) s_part[rs][w * 32 + m] = cs;
-    __syncthreads();
-    if (tid < S::COLS) {
-        float t = s_part[0][tid];
-#pragma unroll
-        for (int i = 1; i < S::RS; ++i) t += s_part[i][tid];
-        colsum_part[(int64_t)blockIdx.x * R + blockIdx.y * 128 + tid] = t;
+            for (int p = 0; p < 3; ++p) z[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, wfrag[p][kk], z[t], 0, 0, 0);
+        }
     }
 }
 
@@ -276,279 +171,530 @@ __device__ __forceinline__ uint2 lds_read_transposed(const uint16_t* p) {
     return __builtin_bit_cast(uint2, v);
 }
 
-// grid = (n_wgs blocks of TR_ROWS triplets and then 128 workgroups for the rows of W P, column groups).
-// colsum: per-query sums (train_colreduce_kernel), or nullptr: this workgroup adds its query's up itself
-// from colsum_part and leaves their squared norm in bal_part if it is the query's first.
+// eight consecutive values of a result (registers 8 ks .. 8 ks + 7), split for the B operand
+__device__ __forceinline__ void split_operand(const tr_f32x16_t& v, int ks, tr_bf16x8_t (&b)[3]) {
+    uint32_t pz[3][4];
+#pragma unroll
+    for (int e2 = 0; e2 < 4; ++e2) split3_pair(v[8 * ks + 2 * e2], v[8 * ks + 2 * e2 + 1], pz[0][e2], pz[1][e2], pz[2][e2]);
+#pragma unroll
+    for (int p = 0; p < 3; ++p) b[p] = __builtin_bit_cast(tr_bf16x8_t, make_uint4(pz[p][0], pz[p][1], pz[p][2], pz[p][3]));
+}
+
+// sum over a wave's lanes, in fp64
+__device__ __forceinline__ double wave_sum64_f64(double x) {
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) x += __shfl_xor(x, d, 64);
+    return x;
+}
+
+// Half rows of W W^T and rows of a copy of W, a piece of each per workgroup of 512 threads: what a thread needs of
+// it, requested ahead of its use
+template <int R>
+struct GramPiece {
+    static constexpr int PIECES = 2 * HATA_D;  // piece c: row c / 2, channels 64 (c % 2) ...
+    static constexpr int NV = R / 32;          // eight threads per element
+    float4 a[NV], b[NV];
+    float w;
+    __device__ __forceinline__ void fetch(const float* __restrict__ W, int c) {
+        const int tid = threadIdx.x, ch = (c & 1) * 64 + (tid >> 3), part = tid & 7;
+        const float4* ra = reinterpret_cast<const float4*>(W + (int64_t)ch * R) + part;
+        const float4* rb = reinterpret_cast<const float4*>(W + (int64_t)(c >> 1) * R) + part;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) { a[i] = ra[8 * i]; b[i] = rb[8 * i]; }
+        w = (c & 1) == 0 && tid < R ? W[(int64_t)(c >> 1) * R + tid] : 0.f;
+    }
+    // returns this wave's part of ||W W^T||^2 - 2 tr(W W^T)  (||W^T W - I||^2 = that + r)
+    __device__ __forceinline__ double finish(int c, double* __restrict__ gram, float* __restrict__ W_old) const {
+        const int tid = threadIdx.x, row = c >> 1, ch = (c & 1) * 64 + (tid >> 3);
+        double acc = 0.0;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            acc = fma((double)a[i].x, (double)b[i].x, acc);
+            acc = fma((double)a[i].y, (double)b[i].y, acc);
+            acc = fma((double)a[i].z, (double)b[i].z, acc);
+            acc = fma((double)a[i].w, (double)b[i].w, acc);
+        }
+        acc += __shfl_xor(acc, 1, 64);
+        acc += __shfl_xor(acc, 2, 64);
+        acc += __shfl_xor(acc, 4, 64);
+        if ((tid & 7) == 0) gram[row * HATA_D + ch] = acc;
+        if ((c & 1) == 0 && tid < R) W_old[(int64_t)row * R + tid] = w;
+        double f = acc * acc - (ch == row ? 2.0 * acc : 0.0);
+        f += __shfl_xor(f, 8, 64);
+        f += __shfl_xor(f, 16, 64);
+        return f + __shfl_xor(f, 32, 64);
+    }
+};
+
+// grid = (pairs of blocks of TR_ROWS triplets, groups of up to 64 hash columns).
 //
-// What bounds it: one round of workgroups, so the latency of what a workgroup reads (rows, weight planes,
-// column sums: 8 us until the first matrix instruction, 4 of them the column sums) and then, added up, the
-// matrix instructions (96 per 32-row tile and wave: two projections of three planes, two contractions of
-// three) and the exponentials (11 us).  Hence eight waves per workgroup, two per SIMD; the planes made once,
-// by the launch before, instead of split from W in every workgroup; transposing LDS reads instead of 2-byte
-// ones: 31 -> 25 us at r = 128 and 32768 triplets, the sums of the old reduction launch (4.4 us) included.
+// A block whose rows hold one query vector -- those of a sampled query against its keys do; rows of zeros with label 0
+// fill such a block up -- needs that vector projected once, and its part of Q^T dZ_q is that vector times a sum over
+// the rows.  Whether it does is looked up in the rows themselves; a workgroup with any other row takes the general way.
+//
+// What bounds it: one round of workgroups, one per CU, so the latency of what a workgroup reads (4.5 us to the first
+// product), then the matrix instructions (of a wave 48 for the projection of its keys, 24 for the query, 96 for
+// the two contractions; the general way has 72 more) with the exponentials and the splits between them.  21 us at r = 128 and
+// 256 blocks; a step 30 us with one query vector a block, 35 with others (38 both before); of 8 blocks 22 and 28 (25).  Batches
+// of several rounds of workgroups: 640 blocks 71 (74), but 960 of the general kind 120 (100): there the second staging of
+// the keys is in no latency's shadow.
 template <int R>
 __global__ __launch_bounds__(TrainShape<R>::THREADS) void train_grad_kernel(
-    const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const float* __restrict__ s,
-    const float* __restrict__ W, const uint4* __restrict__ planes, int n, int n_wgs, float sigma, float c_sim,
-    float c_bal, const float* __restrict__ colsum, const float* __restrict__ colsum_part, const int32_t* __restrict__ block_group,
-    int n_groups, const float* __restrict__ P, float* __restrict__ dw_part, float* __restrict__ loss_part,
-    float* __restrict__ bal_part, float* __restrict__ WP) {
+    const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const float* __restrict__ s, const float* __restrict__ W,
+    int n, int n_blocks, float sigma, float c_sim, const int32_t* __restrict__ block_group, int n_groups,
+    float* __restrict__ dw_part, float* __restrict__ colsum_part, float* __restrict__ loss_part, double* __restrict__ gram,
+    double* __restrict__ fro_part, float* __restrict__ W_old) {
     using S = TrainShape<R>;
-    constexpr int THREADS = S::THREADS, WAVES = S::WAVES, SLICES = S::SLICES;
-    __shared__ __attribute__((aligned(16))) uint16_t tile[2 * TR_ROWS * TR_PITCH];
-    __shared__ float s_lab[TR_ROWS];
-    __shared__ __attribute__((aligned(16))) float s_col[S::COL_ROWS][S::COLS];  // per hash column: sums of h(k_n) over this block's query, a wave's each; or of a row of W P, a slice's each
-    static_assert(sizeof(s_col) >= sizeof(float) * S::COLS * (WAVES > SLICES ? WAVES : SLICES), "a row per wave, and per slice");
-    __shared__ float s_bal[WAVES], s_loss[WAVES];
-    __shared__ int s_first;
+    constexpr int THREADS = S::THREADS, WAVES = S::WAVES, T = S::TILES;
+    __shared__ __attribute__((aligned(16))) uint16_t tile[TR_PAIR * TR_PITCH];
+    __shared__ __attribute__((aligned(16))) uint16_t s_q[2][HATA_D];  // first query row of each block
+    // operand fragments: the planes of the weights [CG][3][8], later those of a round's values [CG][RG][6]
+    __shared__ __attribute__((aligned(16))) uint4 s_frag[48][64];
+    static_assert(S::CG * 3 * 8 <= 48 && S::CG * S::RG * 6 <= 48, "fragments");
+    __shared__ float s_lab[TR_PAIR];
+    __shared__ float s_col[S::COL_ROWS][S::COLS];  // per hash column: sums of h(k_n) over a row group
+    static_assert(S::COL_ROWS >= WAVES && S::COL_ROWS >= S::SLICES, "a row per wave, and per slice");
+    __shared__ float s_dq[S::RG][S::COLS];  // sums of dZ_q
+    __shared__ float s_loss[WAVES];
+    __shared__ double s_red[WAVES];
+    __shared__ int s_mixed;
     const int tid = threadIdx.x, lane = tid & 63;
-    const int jc = tid % S::COLS, sl = tid / S::COLS;
-    if ((int)blockIdx.x >= n_wgs) {  // row c of W P
-        const int c = blockIdx.x - n_wgs, j = blockIdx.y * 128 + jc;
-        const int i0 = sl * (R / SLICES);
-        float wp = 0.f;
-#pragma unroll 16
-        for (int i = i0; i < i0 + R / SLICES; ++i) wp = fmaf(W[(int64_t)c * R + i], P[(int64_t)i * R + j], wp);
-        s_col[sl][jc] = wp;
-        __syncthreads();
-        if (sl == 0) {
-#pragma unroll
-            for (int i = 1; i < SLICES; ++i) wp += s_col[i][jc];
-            WP[(int64_t)c * R + j] = wp;
+    const int w = (tid >> 6) % S::CG, rg = (tid >> 6) / S::CG;
+    const int m = lane & 31, half = lane >> 5;
+    const int row0 = blockIdx.x * TR_PAIR, blk = rg / S::HB;
+    const int col = blockIdx.y * 64 + w * 32 + m;
+    StagedRows<THREADS> xk, xq;
+    xk.fetch(K, row0, n);
+    xq.fetch(Q, row0, n);
+    const int wg = blockIdx.y * gridDim.x + blockIdx.x;
+    GramPiece<R> piece;
+    if (wg < GramPiece<R>::PIECES) piece.fetch(W, wg);
+    const int first = 2 * blockIdx.x;
+    if (first >= n_blocks) {  // (small batches have workgroups for the pieces alone)
+        if (wg < GramPiece<R>::PIECES) {
+            const double f = piece.finish(wg, gram, W_old);
+            if (lane == 0) s_red[tid >> 6] = f;
+            __syncthreads();
+            if (tid == 0) {
+                double t = 0.0;
+                for (int i = 0; i < WAVES; ++i) t += s_red[i];
+                fro_part[wg] = t;
+            }
         }
         return;
     }
-    uint16_t* const tile_q = tile;
-    uint16_t* const tile_k = tile + TR_ROWS * TR_PITCH;
-    const int w = (tid >> 6) % S::CG, rs = (tid >> 6) / S::CG;
-    const int m = lane & 31, half = lane >> 5;
-    const int row0 = blockIdx.x * TR_ROWS;
-    const int col = blockIdx.y * 128 + w * 32 + m;
-    // everything the workgroup reads is requested before anything is waited for
-    StagedRows<THREADS> xq, xk;
-    xq.fetch(Q, row0, n);
-    xk.fetch(K, row0, n);
-    tr_bf16x8_t wfrag[3][8];
-    fetch_weight_planes(planes, blockIdx.y * 4 + w, wfrag);
-    if (tid == 0) s_first = 1;
-    for (int i = tid; i < TR_ROWS; i += THREADS) s_lab[i] = (row0 + i < n) ? s[row0 + i] : 0.f;
-    // the column sums of this block's query
-    const int query = block_query(block_group, blockIdx.x, n_groups);
-    if (colsum) {
-        if (sl == 0) s_col[0][jc] = colsum[(int64_t)query * R + blockIdx.y * 128 + jc];
-        xq.put(tile_q);
-        xk.put(tile_k);
-    } else {
-        // a wave takes a run of blocks, whole rows of column sums at a time: which of them are this
-        // query's is the same for all its lanes (scalar loads and branches)
-        constexpr int NV = S::COLS > 64 ? 2 : 1;
-        const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), per = (n_wgs + WAVES - 1) / WAVES;
-        const int g0 = wv * per, g1 = min(n_wgs, g0 + per), j0 = lane * NV;
-        const float* cp = colsum_part + blockIdx.y * 128 + min(j0, S::COLS - NV);
-        float sum[NV] = {};
-        bool earlier = false;
-        for (int g = g0; g < g1; g += 32) {
-            float x[32][NV];
+    const bool one_query = first + 1 >= n_blocks || block_query(block_group, first, n_groups) == block_query(block_group, first + 1, n_groups);
+    double fro = 0.0;
+    if (wg < GramPiece<R>::PIECES) fro = piece.finish(wg, gram, W_old);
+    if (lane == 0) s_red[tid >> 6] = fro;
+    // the planes of the column group's weights, a share of the channel steps by each of its row groups
+    constexpr int KS = 8 / S::RG;
+    float wv[KS][8];
 #pragma unroll
-            for (int u = 0; u < 32; ++u)
+    for (int k = 0; k < KS; ++k)
 #pragma unroll
-                for (int e = 0; e < NV; ++e) x[u][e] = cp[(int64_t)min(g + u, g1 - 1) * R + e];
+        for (int e = 0; e < 8; ++e) wv[k][e] = W[(int64_t)((rg * KS + k) * 16 + 8 * half + e) * R + col];
+    if (tid == 0) s_mixed = 0;
+    for (int i = tid; i < TR_PAIR; i += THREADS) s_lab[i] = (row0 + i < n) ? s[row0 + i] : 0.f;
+    xk.put(tile);
 #pragma unroll
-            for (int u = 0; u < 32; ++u) {
-                const bool own = g + u < g1 && block_query(block_group, min(g + u, g1 - 1), n_groups) == query;
-                earlier |= own && g + u < (int)blockIdx.x;
+    for (int k = 0; k < KS; ++k) {
+        uint32_t f[3][4];
 #pragma unroll
-                for (int e = 0; e < NV; ++e) sum[e] += own ? x[u][e] : 0.f;
-            }
-        }
-        xq.put(tile_q);
-        xk.put(tile_k);
-        if (j0 < S::COLS) {
+        for (int e2 = 0; e2 < 4; ++e2) split3_pair(wv[k][2 * e2], wv[k][2 * e2 + 1], f[0][e2], f[1][e2], f[2][e2]);
 #pragma unroll
-            for (int e = 0; e < NV; ++e) s_col[wv][j0 + e] = sum[e];
-        }
-        __syncthreads();
-        if (lane == 0 && earlier) s_first = 0;
-        float t = 0.f;
-        if (tid < S::COLS) {
-#pragma unroll
-            for (int i = 0; i < WAVES; ++i) t += s_col[i][tid];
-            s_col[0][tid] = t;  // (read by this thread alone before)
-        }
-        __syncthreads();
-        t = wave_sum64(s_first ? t * t : 0.f);
-        if (lane == 0) s_bal[tid >> 6] = t;
+        for (int p = 0; p < 3; ++p) s_frag[(w * 3 + p) * 8 + rg * KS + k][lane] = make_uint4(f[p][0], f[p][1], f[p][2], f[p][3]);
+    }
+    // thread: piece tid % 16 of rows tid / 16 + 32 j
+    if (tid < 16) {
+        *reinterpret_cast<uint4*>(&s_q[0][tid * 8]) = xq.v[0];
+        *reinterpret_cast<uint4*>(&s_q[1][tid * 8]) = xq.v[TR_ROWS * 16 / THREADS];
     }
     __syncthreads();
-    if (tid == 0 && !colsum) {
-        float t = 0.f;
+    {
+        uint32_t stray = 0;  // (no branches: every read is in flight at once)
+        uint4 f[2];
 #pragma unroll
-        for (int i = 0; i < WAVES; ++i) t += s_bal[i];
-        bal_part[blockIdx.y * n_wgs + blockIdx.x] = t;
+        for (int b = 0; b < 2; ++b) f[b] = *reinterpret_cast<const uint4*>(&s_q[b][(tid & 15) * 8]);
+#pragma unroll
+        for (int j = 0; j < StagedRows<THREADS>::NV; ++j) {
+            const int row = (tid >> 4) + j * (THREADS / 16), b = j / (StagedRows<THREADS>::NV / 2);
+            const uint4 x = xq.v[j];
+            const uint32_t differs = (x.x ^ f[b].x) | (x.y ^ f[b].y) | (x.z ^ f[b].z) | (x.w ^ f[b].w);
+            const uint32_t counts = x.x | x.y | x.z | x.w | (__float_as_uint(s_lab[row]) << 1);  // (a label of -0 is 0)
+            stray |= counts != 0u ? differs : 0u;
+        }
+        if (stray) s_mixed = 1;
     }
-    const float nsl = -sigma * TR_LOG2E, colk = c_bal * s_col[0][w * 32 + m];
-    tr_f32x16_t dw[4];  // dw[ct][ri]: channel 32 ct + 8 (ri / 4) + 4 half + ri % 4, this lane's column
+    tr_bf16x8_t wfrag[3][8];
 #pragma unroll
-    for (int ct = 0; ct < 4; ++ct)
+    for (int kk = 0; kk < 8; ++kk)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) dw[ct][i] = 0.f;
-    float lsim = 0.f;
+        for (int p = 0; p < 3; ++p) wfrag[p][kk] = __builtin_bit_cast(tr_bf16x8_t, s_frag[(w * 3 + p) * 8 + kk][lane]);
+    const float nsl = -sigma * TR_LOG2E;
+    const int t0 = rg * T;
+    tr_f32x16_t zk[T];  // then h(k)
+    project_tiles<T>(tile, t0, m, half, wfrag, zk);
+    __syncthreads();
+    const bool mixed = s_mixed != 0;
+    tr_f32x16_t zq[T];  // then h(q)
+    float hq0 = 0.f;
+    if (mixed) {
+        xq.put(tile);
+        xk.fetch(K, row0, n);  // (the tile's next content)
+        __syncthreads();
+        project_tiles<T>(tile, t0, m, half, wfrag, zq);
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) zq[t][i] = relaxed_sign(zq[t][i], nsl);
+    } else {
+        tr_f32x16_t z;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) z[i] = 0.f;
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk) {
+            const tr_bf16x8_t x = *reinterpret_cast<const tr_bf16x8_t*>(&s_q[blk][kk * 16 + 8 * half]);
+#pragma unroll
+            for (int p = 0; p < 3; ++p) z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, wfrag[p][kk], z, 0, 0, 0);
+        }
+        hq0 = relaxed_sign(z[0], nsl);
+    }
+    // Every wave has the values of its rows, and gets the sums over all of them (RG = 8: over one block's) for 32
+    // channels: a round hands 16 rows of each row group round through LDS, split into planes.  (With sums of its own rows over
+    // all channels instead, a wave held 128 of them, its products waited for one operand at a time, and the
+    // sums had to be added up through LDS: 14 us of that against 8.)
+    // accumulators: channel 32 ct + 8 (ri / 4) + 4 half + ri % 4, this lane's column
+    const int ct = rg & 3;
+    constexpr int G0 = S::RG == 8 ? 4 : S::RG;  // row groups a wave adds up
+    const int g0 = S::RG == 8 ? (rg & 4) : 0;
+    tr_f32x16_t ke[2], dw;  // K^T E, by block (RG = 8: the wave's block in both places);  Q^T dZ_q - K^T (A E)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) ke[0][i] = ke[1][i] = dw[i] = 0.f;
     // where this lane reads of a 4-row x 16-channel piece of a tile (lds_read_transposed), for row group
     // 4 half and channel group 16 (m / 16)
-    const int tr_off = (4 * half + (lane & 15) / 4) * TR_PITCH + 16 * (m >> 4) + 4 * (lane & 3);
-#pragma unroll 1
-    for (int tt = 0; tt < S::TILES; ++tt) {
-        const int t = rs * S::TILES + tt;
-        tr_f32x16_t zq = project_tile(tile_q, t, m, half, wfrag);  // then dL/dz of q
-        tr_f32x16_t zk = project_tile(tile_k, t, m, half, wfrag);  // then dL/dz of k
+    const uint16_t* const tr = tile + (4 * half + (lane & 15) / 4) * TR_PITCH + 16 * (m >> 4) + 4 * (lane & 3);
+    // X: 16 rows (slot (half, j) of the operand <-> row 8 (j / 4) + 4 half + j % 4), 32 channels
+    auto rows_transposed = [&](int t, int ks) {
+        const uint16_t* p = tr + (t * 32 + 16 * ks) * TR_PITCH + 32 * ct;
+        const uint2 lo = lds_read_transposed(p), hi = lds_read_transposed(p + 8 * TR_PITCH);
+        return __builtin_bit_cast(tr_bf16x8_t, make_uint4(lo.x, lo.y, hi.x, hi.y));
+    };
+    float lsim = 0.f, cs = 0.f, ssum = 0.f;  // similarity, sum of h(k), sum of s (h(q) - h(k))
+#pragma unroll
+    for (int t = 0; t < T; ++t)
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-            const int row = t * 32 + 8 * (i / 4) + 4 * half + (i % 4);
-            const float hq = relaxed_sign(zq[i], nsl), hk = relaxed_sign(zk[i], nsl);
-            const float diff = hq - hk, sd = s_lab[row] * diff;
-            const float dhq = c_sim * sd, dhk = colk - dhq;  // (half of dL/dh: h' = (1 - h^2) / 2)
-            zq[i] = dhq * fmaf(-hq, hq, 1.f);
-            zk[i] = dhk * fmaf(-hk, hk, 1.f);
-            lsim = fmaf(sd, diff, lsim);
+            const float hk = relaxed_sign(zk[t][i], nsl);
+            zk[t][i] = hk;
+            cs += hk;  // (rows past n are zero: h = 0)
         }
-        // X^T dZ over the tile's 32 rows, 16 per MFMA: the B operand is dZ as it sits in the
-        // registers (slot (half, j) of step ks <-> row 16 ks + 8 (j / 4) + 4 half + j % 4), the A
-        // operand X read from the LDS tile in that same row order
+    if (mixed) {
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-#pragma unroll
-            for (int qk = 0; qk < 2; ++qk) {
-                const uint16_t* tl = (qk ? tile_k : tile_q) + (t * 32 + 16 * ks) * TR_PITCH + tr_off;
-                tr_bf16x8_t bz[3];
-                {
-                    uint32_t pz[3][4];
-#pragma unroll
-                    for (int e2 = 0; e2 < 4; ++e2) {
-                        const int i = 8 * ks + 2 * e2;
-                        split3_pair(qk ? zk[i] : zq[i], qk ? zk[i + 1] : zq[i + 1], pz[0][e2], pz[1][e2], pz[2][e2]);
-                    }
-#pragma unroll
-                    for (int p = 0; p < 3; ++p)
-                        bz[p] = __builtin_bit_cast(tr_bf16x8_t, make_uint4(pz[p][0], pz[p][1], pz[p][2], pz[p][3]));
-                }
-#pragma unroll
-                for (int ct = 0; ct < 4; ++ct) {
-                    const uint2 lo = lds_read_transposed(tl + 32 * ct), hi = lds_read_transposed(tl + 32 * ct + 8 * TR_PITCH);
-                    const tr_bf16x8_t x = __builtin_bit_cast(tr_bf16x8_t, make_uint4(lo.x, lo.y, hi.x, hi.y));
-#pragma unroll
-                    for (int p = 0; p < 3; ++p) dw[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, bz[p], dw[ct], 0, 0, 0);
-                }
-            }
-        }
-    }
-    lsim = wave_sum64(lsim);
-    if (lane == 0) s_loss[tid >> 6] = lsim;
-    // the row groups' partial sums of a column group meet in the tiles' LDS, halving each time
-    float* const meet = reinterpret_cast<float*>(tile);
-#pragma unroll
-    for (int rows = S::RS / 2; rows >= 1; rows >>= 1) {
-        static_assert(S::RS / 2 * S::CG * 64 * 64 * 4 <= (int)sizeof(tile), "the sums of half the row groups fit");
-        __syncthreads();
-        float* mp = meet + (int64_t)((rs % rows) * S::CG + w) * 64 * 64 + lane;
-        if (rs >= rows && rs < 2 * rows) {
-#pragma unroll
-            for (int ct = 0; ct < 4; ++ct)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) mp[(ct * 16 + i) * 64] = dw[ct][i];
-        }
-        __syncthreads();
-        if (rs < rows) {
-#pragma unroll
-            for (int ct = 0; ct < 4; ++ct)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) dw[ct][i] += mp[(ct * 16 + i) * 64];
-        }
-    }
-    if (rs == 0) {
-        float* out = dw_part + (int64_t)blockIdx.x * HATA_D * R;
-#pragma unroll
-        for (int ct = 0; ct < 4; ++ct)
+        for (int t = 0; t < T; ++t) {
+            tr_f32x16_t gq;
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                const int ch = 32 * ct + 8 * (i / 4) + 4 * half + (i % 4);
-                out[(int64_t)ch * R + col] = dw[ct][i];
+                const float sd = s_lab[(t0 + t) * 32 + 8 * (i / 4) + 4 * half + (i % 4)] * (zq[t][i] - zk[t][i]);
+                gq[i] = c_sim * sd * fmaf(-zq[t][i], zq[t][i], 1.f);
             }
+            tr_bf16x8_t b[2][3];
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) split_operand(gq, ks, b[ks]);
+            __syncthreads();
+#pragma unroll
+            for (int p = 0; p < 6; ++p) s_frag[(w * S::RG + rg) * 6 + p][lane] = __builtin_bit_cast(uint4, b[p / 3][p % 3]);
+            __syncthreads();
+#pragma unroll
+            for (int g = 0; g < G0; ++g)
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks) {
+                    const tr_bf16x8_t x = rows_transposed((g0 + g) * T + t, ks);
+#pragma unroll
+                    for (int p = 0; p < 3; ++p)
+                        dw = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                            x, __builtin_bit_cast(tr_bf16x8_t, s_frag[(w * S::RG + g0 + g) * 6 + 3 * ks + p][lane]), dw, 0, 0, 0);
+                }
+        }
+        __syncthreads();  // (the tile of Q has been read)
+        xk.put(tile);
+        __syncthreads();
+    }
+    auto contract_keys = [&](auto one_vector) {
+        tr_bf16x8_t b[6];  // planes of E and of -A E for the next round
+        auto prepare = [&](int round) {
+            const int t = round / 2, ks = round % 2;
+            tr_f32x16_t e, ae;
+#pragma unroll
+            for (int i = 8 * ks; i < 8 * ks + 8; ++i) {
+                // (half of dL/dh: h' = (1 - h^2) / 2)
+                float hq = hq0;
+                if constexpr (!decltype(one_vector)::value) hq = zq[t][i];
+                const float hk = zk[t][i], diff = hq - hk, sd = s_lab[(t0 + t) * 32 + 8 * (i / 4) + 4 * half + (i % 4)] * diff;
+                e[i] = fmaf(-hk, hk, 1.f);
+                ae[i] = -c_sim * sd * e[i];
+                lsim = fmaf(sd, diff, lsim);
+                ssum += sd;
+            }
+            tr_bf16x8_t be[3], ba[3];
+            split_operand(e, ks, be);
+            split_operand(ae, ks, ba);
+#pragma unroll
+            for (int p = 0; p < 3; ++p) { b[p] = be[p]; b[3 + p] = ba[p]; }
+        };
+        prepare(0);
+#pragma unroll
+        for (int round = 0; round < 2 * T; ++round) {
+            __syncthreads();  // (what lay there has been read)
+#pragma unroll
+            for (int p = 0; p < 6; ++p) s_frag[(w * S::RG + rg) * 6 + p][lane] = __builtin_bit_cast(uint4, b[p]);
+            __syncthreads();
+            if (round + 1 < 2 * T) prepare(round + 1);
+#pragma unroll
+            for (int g = 0; g < G0; ++g) {
+                const tr_bf16x8_t x = rows_transposed((g0 + g) * T + round / 2, round % 2);
+                tr_f32x16_t& k = ke[g / S::HB];
+#pragma unroll
+                for (int p = 0; p < 3; ++p) {
+                    k = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, __builtin_bit_cast(tr_bf16x8_t, s_frag[(w * S::RG + g0 + g) * 6 + p][lane]), k, 0, 0, 0);
+                    dw = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, __builtin_bit_cast(tr_bf16x8_t, s_frag[(w * S::RG + g0 + g) * 6 + 3 + p][lane]), dw, 0, 0, 0);
+                }
+            }
+        }
+    };
+    if (mixed) contract_keys(std::false_type{});
+    else contract_keys(std::true_type{});
+    // (one query vector: its part of Q^T dZ_q is that vector times the sum over the rows, added behind the sums below)
+    ssum += __shfl_xor(ssum, 32, 64);
+    if (half == 0) s_dq[rg][w * 32 + m] = mixed ? 0.f : c_sim * ssum * fmaf(-hq0, hq0, 1.f);
+    cs += __shfl_xor(cs, 32, 64);
+    if (half == 0) s_col[rg][w * 32 + m] = cs;
+    lsim = wave_sum64(lsim);
+    if (lane == 0) s_loss[tid >> 6] = lsim;
+    __syncthreads();
+    if (S::RG == 8) {  // two waves have a part each: the second block's meets the first one's
+        float* const meet = reinterpret_cast<float*>(s_frag) + ct * 32 * 64 + lane;
+        if (rg >= 4) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) { meet[i * 64] = ke[0][i]; meet[(16 + i) * 64] = dw[i]; }
+        }
+        __syncthreads();
+        if (rg < 4) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) { ke[1][i] = meet[i * 64]; dw[i] += meet[(16 + i) * 64]; }
+        }
+    }
+    if (rg < 4) {
+        float g[2] = {0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < S::RG; ++i) g[i / S::HB] += s_dq[i][w * 32 + m];
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int i = 0; i < 16; i += 4) {
+                const uint2 x = *reinterpret_cast<const uint2*>(&s_q[b][32 * ct + 2 * i + 4 * half]);
+                dw[i] = fmaf(bf16_lo(x.x), g[b], dw[i]);
+                dw[i + 1] = fmaf(bf16_hi(x.x), g[b], dw[i + 1]);
+                dw[i + 2] = fmaf(bf16_lo(x.y), g[b], dw[i + 2]);
+                dw[i + 3] = fmaf(bf16_hi(x.y), g[b], dw[i + 3]);
+            }
+        float* const out = dw_part + (int64_t)blockIdx.x * 3 * HATA_D * R + (32 * ct + 4 * half) * R + col;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int at = (8 * (i / 4) + i % 4) * R;
+            out[at] = one_query ? ke[0][i] + ke[1][i] : ke[0][i];
+            out[HATA_D * R + at] = dw[i];
+            if (!one_query) out[2 * HATA_D * R + at] = ke[1][i];
+        }
+    }
+    // (everybody has written s_col and s_loss: the rounds above have barriers)
+    for (int i = tid; i < 2 * S::COLS; i += THREADS) {
+        const int b = i / S::COLS, jc = i % S::COLS;
+        float t = 0.f;
+#pragma unroll
+        for (int g = 0; g < S::HB; ++g) t += s_col[b * S::HB + g][jc];
+        if (first + b < n_blocks) colsum_part[(int64_t)(first + b) * R + blockIdx.y * 64 + jc] = t;
     }
     if (tid == 0) {  // (the similarity partial of column group y; the groups are summed later)
         float t = 0.f;
         for (int i = 0; i < WAVES; ++i) t += s_loss[i];
-        loss_part[blockIdx.y * n_wgs + blockIdx.x] = t;
+        loss_part[blockIdx.y * ((n_blocks + 1) / 2) + blockIdx.x] = t;
+        double f = 0.0;
+        for (int i = 0; i < WAVES; ++i) f += s_red[i];
+        if (wg < GramPiece<R>::PIECES) fro_part[wg] = f;
     }
 }
 
-// dL/dW = sigma * sum of the partials + 2 lam W P / ||P||_F, and the SGD update from it; the last block writes
+// dL/dW = sigma * (sum of the partials) + 2 lam W P / ||P||_F, and the SGD update from it; the last block writes
 // the loss terms.  64 elements per workgroup of 1024 threads: wave w sums a sixteenth of the partials of
-// each, the sixteen meet in LDS in a fixed order.  Bound by reading the partials once (16.8 MB at r = 128 and
-// 256 of them, in the caches): four waves with eight loads in flight each took 8 us, and a launch of its own for
-// the update 4.6 us on top; 4.9 us now.
-__global__ __launch_bounds__(1024) void train_update_kernel(
-    float* __restrict__ W, float* __restrict__ v, int r, int n_wgs, float sigma, float lam, float c_sim, float c_bal,
-    float lr, float momentum, float weight_decay, const float* __restrict__ dw_part, const float* __restrict__ WP,
-    const float* __restrict__ fro_part, const float* __restrict__ colsum, int n_groups,
-    const float* __restrict__ bal_part, const float* __restrict__ loss_part, float* __restrict__ grad,
-    float* __restrict__ loss) {
-    __shared__ float part[16][64];
-    __shared__ float s_fro;
-    const int tid = threadIdx.x, el = tid & 63, sl = tid >> 6;
-    const int count = HATA_D * r;
-    const int e = blockIdx.x * 64 + el;  // (count is a multiple of 64; the last block is past it)
-    float f = 0.f;
-    if (sl == 0) {
-        for (int j = el; j < r; j += 64) f += fro_part[j];
-        f = sqrtf(wave_sum64(f));
-        if (el == 0) s_fro = f;
-    }
-    if (e < count) {
-        float gp[4] = {0.f, 0.f, 0.f, 0.f};
-        int wg = (int)((int64_t)sl * n_wgs / 16);
-        const int wg_end = (int)((int64_t)(sl + 1) * n_wgs / 16);
-        const float* dp = dw_part + e;
-        for (; wg < wg_end; wg += 16) {
-            float x[16];
+// each -- K^T E times the column's factor, which it adds up first from the column sums of all blocks (colsum:
+// already added up per query) -- the sixteen meet in LDS in a fixed order.  Bound by reading the partials once (16.8 MB at
+// r = 128 and 256 blocks, in the caches).
+__global__ __launch_bounds__(TR_UPDATE_WAVES * 64) __attribute__((amdgpu_waves_per_eu(4, 4))) void train_update_kernel(
+    float* __restrict__ W, float* __restrict__ v, int log2_r, int n_blocks, float sigma, float lam, float c_sim, float c_bal,
+    float lr, float momentum, float weight_decay, const float* __restrict__ dw_part, const float* __restrict__ colsum_part,
+    const float* __restrict__ colsum, const int32_t* __restrict__ block_group, int n_groups, const double* __restrict__ gram,
+    const double* __restrict__ fro_part, const float* __restrict__ W_old, const float* __restrict__ loss_part,
+    float* __restrict__ grad, float* __restrict__ loss) {
+    constexpr int WAVES = TR_UPDATE_WAVES;
+    __shared__ float part[WAVES][64];
+    __shared__ double wp_part[WAVES][64];
+    __shared__ float s_slice[WAVES][TR_FEW_QUERIES][64], s_sum[TR_FEW_QUERIES][64];  // column sums: a slice's, a query's
+    const int tid = threadIdx.x, el = tid & 63, sl = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = 1 << log2_r, count = HATA_D * r, n_pairs = (n_blocks + 1) / 2;
+    // a wave's pairs of blocks, and the queries of its blocks, a lane each (where there are more than 64: looked up one by one)
+    const int p0 = sl * n_pairs / WAVES, p1 = (sl + 1) * n_pairs / WAVES, b0 = 2 * p0, b1 = min(2 * p1, n_blocks);
+    const int ids = block_query(block_group, min(b0 + el, n_blocks - 1), n_groups);
+    // (the rule: all of a wave's blocks are one query's)
+    const bool one = b1 - b0 <= 64 && __builtin_amdgcn_ballot_w64(ids != __builtin_amdgcn_readfirstlane(ids) && b0 + el < b1) == 0ull;
+    auto query_of = [&](int b) { return b - b0 < 64 ? __builtin_amdgcn_readlane(ids, b - b0) : block_query(block_group, b, n_groups); };
+    // sums of h(k) per query for column j, into s_sum[query][el]; two barriers
+    float cx[32];  // of up to 32 blocks: requested ahead of everything else
+    auto request_columns = [&](int j, int b) {
 #pragma unroll
-            for (int u = 0; u < 16; ++u) x[u] = dp[(int64_t)min(wg + u, wg_end - 1) * count];
+        for (int u = 0; u < 32; ++u) cx[u] = colsum_part[(int64_t)max(min(b + u, b1 - 1), 0) * r + j];
+    };
+    auto column_sums = [&](int j) {
+        for (int q = 0; q < n_groups; ++q) s_slice[sl][q][el] = 0.f;
+        int query = b0 < b1 ? query_of(b0) : 0;
+        float sum = 0.f;
+        for (int b = b0; b < b1; b += 32) {
+            if (b != b0) request_columns(j, b);
+            if (one) {
+                float x[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int u = 0; u < 16; ++u) gp[u & 3] += wg + u < wg_end ? x[u] : 0.f;
+                for (int u = 0; u < 32; ++u) x[u & 3] += b + u < b1 ? cx[u] : 0.f;
+                sum += (x[0] + x[1]) + (x[2] + x[3]);
+                continue;
+            }
+#pragma unroll
+            for (int u = 0; u < 32; ++u) {
+                if (b + u < b1) {
+                    const int of = query_of(b + u);  // (the same for the whole wave)
+                    if (of != query) {
+                        s_slice[sl][query][el] += sum;
+                        sum = 0.f;
+                        query = of;
+                    }
+                    sum += cx[u];
+                }
+            }
         }
+        s_slice[sl][query][el] += sum;
+        __syncthreads();
+        for (int q = sl; q < n_groups; q += WAVES) {
+            float t = 0.f;
+#pragma unroll
+            for (int i = 0; i < WAVES; ++i) t += s_slice[i][q][el];
+            s_sum[q][el] = t;
+        }
+        __syncthreads();
+    };
+    double f2 = 0.0;
+    if (sl == 0) {
+        for (int i = el; i < 2 * HATA_D; i += 64) f2 += fro_part[i];
+        f2 = fmax(wave_sum64_f64(f2) + (double)r, 0.0);
+    }
+    const float fro = (float)sqrt(f2);
+    if ((int)blockIdx.x * 64 < count) {  // (count is a multiple of 64; the last block is past it)
+        const int e = blockIdx.x * 64 + el, ch = e >> log2_r, j = e & (r - 1);
+        const float* dp = dw_part + e;
+        if (!colsum) request_columns(j, b0);
+        constexpr int UN = 16;
+        float ke[UN], dw[UN];
+        auto fetch = [&](int p) {
+#pragma unroll
+            for (int u = 0; u < UN; ++u) {
+                const float* at = dp + (int64_t)max(min(p + u, p1 - 1), 0) * 3 * count;
+                ke[u] = at[0];
+                dw[u] = at[count];
+            }
+        };
+        fetch(p0);
+        const float w0 = W[e], v0 = v[e];
+        if (!colsum) column_sums(j);
+        constexpr int NG = HATA_D / WAVES;
+        double gr[NG];
+        float wo[NG];
+#pragma unroll
+        for (int i = 0; i < NG; ++i) {
+            gr[i] = gram[ch * HATA_D + sl * NG + i];
+            wo[i] = W_old[(sl * NG + i) * r + j];
+        }
+        // a column's factor changes with the query only
+        int query = -1;
+        float factor = 0.f;
+        auto factor_of = [&](int q) {
+            if (q != query) {
+                query = q;
+                factor = c_bal * (colsum ? colsum[(int64_t)q * r + j] : s_sum[q][el]);
+            }
+            return factor;
+        };
+        float gp[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int p = p0; p < p1; p += UN) {
+            if (p != p0) fetch(p);
+            if (one) {
+                const float fc = factor_of(query_of(b0));
+#pragma unroll
+                for (int u = 0; u < UN; ++u) gp[u & 3] += p + u < p1 ? fmaf(fc, ke[u], dw[u]) : 0.f;
+                continue;
+            }
+#pragma unroll
+            for (int u = 0; u < UN; ++u) {
+                if (p + u < p1) {
+                    const int b = 2 * (p + u), q0 = query_of(b), q1 = b + 1 < n_blocks ? query_of(b + 1) : q0;
+                    gp[u & 3] += fmaf(factor_of(q0), ke[u], dw[u]);
+                    if (q1 != q0) gp[u & 3] = fmaf(factor_of(q1), dp[((int64_t)(p + u) * 3 + 2) * count], gp[u & 3]);
+                }
+            }
+        }
+        double wp = 0.0;
+#pragma unroll
+        for (int i = 0; i < NG; ++i) wp = fma(gr[i], (double)wo[i], wp);
         part[sl][el] = (gp[0] + gp[1]) + (gp[2] + gp[3]);
+        wp_part[sl][el] = wp;
         __syncthreads();
         if (sl == 0) {
             float g = 0.f;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) g += part[i][el];
+            for (int i = 0; i < WAVES; ++i) g += part[i][el];
+            wp = -(double)w0;
+#pragma unroll
+            for (int i = 0; i < WAVES; ++i) wp += wp_part[i][el];
             g *= sigma;
-            if (f > 0.f) g += lam * 2.f * WP[e] / f;
+            if (fro > 0.f) g += lam * 2.f * (float)wp / fro;
             if (grad) grad[e] = g;
-            const float w0 = W[e];
-            const float vn = fmaf(momentum, v[e], fmaf(weight_decay, w0, g));
+            const float vn = fmaf(momentum, v0, fmaf(weight_decay, w0, g));
             v[e] = vn;
             W[e] = fmaf(-lr, vn, w0);
         }
         return;
     }
     // similarity: sum of the workgroup partials; balance: squared norm of the column sums
-    const int parts = n_wgs * ((r + 127) / 128);
+    const int parts = n_pairs * ((r + 63) / 64);
     float ls = 0.f, lb = 0.f;
-    for (int i = tid; i < parts; i += 1024) ls += loss_part[i];
-    if (colsum)
-        for (int j = tid; j < r * n_groups; j += 1024) lb = fmaf(colsum[j], colsum[j], lb);
-    else
-        for (int i = tid; i < parts; i += 1024) lb += bal_part[i];
+    for (int i = tid; i < parts; i += WAVES * 64) ls += loss_part[i];
+    if (colsum) {
+        for (int j = tid; j < r * n_groups; j += WAVES * 64) lb = fmaf(colsum[j], colsum[j], lb);
+    } else {
+        for (int j0 = 0; j0 < r; j0 += 64) {
+            request_columns(min(j0 + el, r - 1), b0);
+            column_sums(min(j0 + el, r - 1));
+            for (int q = sl; q < n_groups; q += WAVES)
+                if (j0 + el < r) lb = fmaf(s_sum[q][el], s_sum[q][el], lb);
+        }
+    }
     ls = wave_sum64(ls);
     lb = wave_sum64(lb);
     if (el == 0) { part[0][sl] = ls; part[1][sl] = lb; }
     __syncthreads();
     if (tid == 0) {
         ls = lb = 0.f;
-        for (int i = 0; i < 16; ++i) { ls += part[0][i]; lb += part[1][i]; }
+        for (int i = 0; i < WAVES; ++i) { ls += part[0][i]; lb += part[1][i]; }
         loss[0] = c_sim * ls;
         loss[1] = c_bal * lb;
-        loss[2] = lam * s_fro;
+        loss[2] = lam * fro;
     }
 }
 
@@ -728,7 +874,7 @@ __global__ __launch_bounds__(1024) void train_labels_kernel(const LabelCand* __r
 namespace {
 constexpr size_t kAlignT = 256;
 inline size_t align_up_t(size_t x) { return (x + kAlignT - 1) / kAlignT * kAlignT; }
-struct TrainPlan { int n_wgs_max; size_t off_colsum, off_cs, off_bal, off_dw, off_loss, off_P, off_fro, off_WP, off_planes, off_scores, off_bins, off_ncand, off_cand, total; };
+struct TrainPlan { int n_wgs_max; size_t off_colsum, off_cs, off_dw, off_loss, off_gram, off_fro, off_old, off_scores, off_bins, off_ncand, off_cand, total; };
 int make_train_plan(const hata_train_config* f, TrainPlan* p) {
     if (!f) return HATA_EINVAL;
     if (f->n_max < 1) return HATA_EINVAL;
@@ -739,13 +885,12 @@ int make_train_plan(const hata_train_config* f, TrainPlan* p) {
     size_t o = 0;
     p->off_colsum = o; o = align_up_t(o + (size_t)p->n_wgs_max * f->r * 4);
     p->off_cs = o;     o = align_up_t(o + (size_t)p->n_wgs_max * f->r * 4);
-    p->off_dw = o;     o = align_up_t(o + (size_t)p->n_wgs_max * f->d * f->r * 4);
-    p->off_loss = o;   o = align_up_t(o + (size_t)p->n_wgs_max * 2 * 4);
-    p->off_P = o;      o = align_up_t(o + (size_t)f->r * f->r * 4);
-    p->off_fro = o;    o = align_up_t(o + (size_t)f->r * 4);
-    p->off_WP = o;     o = align_up_t(o + (size_t)f->d * f->r * 4);
-    p->off_planes = o; o = align_up_t(o + (size_t)f->r / 32 * 3 * 8 * 64 * 16);
-    p->off_bal = o;    o = align_up_t(o + (size_t)p->n_wgs_max * 2 * 4);
+    const size_t pairs = ((size_t)p->n_wgs_max + 1) / 2;
+    p->off_dw = o;     o = align_up_t(o + pairs * 3 * f->d * f->r * 4);
+    p->off_loss = o;   o = align_up_t(o + pairs * 4 * 4);
+    p->off_gram = o;   o = align_up_t(o + (size_t)f->d * f->d * 8);
+    p->off_fro = o;    o = align_up_t(o + (size_t)f->d * 2 * 8);
+    p->off_old = o;    o = align_up_t(o + (size_t)f->d * f->r * 4);
     p->off_scores = o; o = align_up_t(o + (size_t)f->n_max * 8);
     p->off_bins = o;   o = align_up_t(o + (size_t)LB_COPIES * LB_BINS * 4);
     p->off_ncand = o;  o = align_up_t(o + 4);
@@ -783,11 +928,9 @@ int hata_train_create(hata_train_ctx** ctx_out, const hata_train_config* cfg, vo
     c->colsum = (float*)(w + p.off_cs);
     c->dw_part = (float*)(w + p.off_dw);
     c->loss_part = (float*)(w + p.off_loss);
-    c->P = (float*)(w + p.off_P);
-    c->fro_part = (float*)(w + p.off_fro);
-    c->WP = (float*)(w + p.off_WP);
-    c->planes = (uint4*)(w + p.off_planes);
-    c->bal_part = (float*)(w + p.off_bal);
+    c->gram = (double*)(w + p.off_gram);
+    c->fro_part = (double*)(w + p.off_fro);
+    c->W_old = (float*)(w + p.off_old);
     c->scores = (double*)(w + p.off_scores);
     c->bins = (uint32_t*)(w + p.off_bins);
     c->n_cand = (uint32_t*)(w + p.off_ncand);
@@ -817,21 +960,21 @@ int hata_train_step(hata_train_ctx* ctx, const void* Q, const void* K, const flo
     const float c_sim = hp->eps * hp->scale_sim, c_bal = hp->eta * hp->scale_bal;
     const uint16_t* q = (const uint16_t*)Q;
     const uint16_t* k = (const uint16_t*)K;
-    const bool few = n_wgs <= TR_FEW_WGS;
+    const bool few = n_wgs <= TR_FEW_WGS && n_queries <= TR_FEW_QUERIES;
     const float* colsum = few ? nullptr : ctx->colsum;
+    // workgroups of the gradient launch in a column group: a pair of blocks each, and at least a piece of W W^T each
+    const int col_groups = r < 64 ? 1 : r / 64, pairs = (n_wgs + 1) / 2;
+    const int n_grad = pairs * col_groups < 2 * HATA_D ? 2 * HATA_D / col_groups : pairs;
 #define HATA_TRAIN_LAUNCH(RR)                                                                          \
     do {                                                                                               \
         using S = hata::TrainShape<RR>;                                                                \
-        hipLaunchKernelGGL((hata::train_colsum_kernel<RR>), dim3(n_wgs + 8 + S::COLS, RR / S::COLS),   \
-                           dim3(S::THREADS), 0, st, k, W, n, n_wgs, hp->sigma, ctx->colsum_part,       \
-                           ctx->P, ctx->fro_part, ctx->planes);                                        \
+        hipLaunchKernelGGL((hata::train_grad_kernel<RR>), dim3(n_grad, RR / S::COLS),                  \
+                           dim3(S::THREADS), 0, st, q, k, s, W, n, n_wgs, hp->sigma, c_sim,            \
+                           block_query, n_queries, ctx->dw_part, ctx->colsum_part, ctx->loss_part,     \
+                           ctx->gram, ctx->fro_part, ctx->W_old);                                      \
         if (!few)                                                                                      \
             hipLaunchKernelGGL(hata::train_colreduce_kernel, dim3(RR, n_queries), dim3(256), 0, st,    \
                                ctx->colsum_part, RR, n_wgs, block_query, n_queries, ctx->colsum);      \
-        hipLaunchKernelGGL((hata::train_grad_kernel<RR>), dim3(n_wgs + HATA_D, RR / S::COLS),          \
-                           dim3(S::THREADS), 0, st, q, k, s, W, ctx->planes, n, n_wgs, hp->sigma,      \
-                           c_sim, c_bal, colsum, ctx->colsum_part, block_query, n_queries, ctx->P,     \
-                           ctx->dw_part, ctx->loss_part, ctx->bal_part, ctx->WP);                      \
     } while (0)
     switch (r) {
         case 32: HATA_TRAIN_LAUNCH(32); break;
@@ -840,9 +983,10 @@ int hata_train_step(hata_train_ctx* ctx, const void* Q, const void* K, const flo
         default: HATA_TRAIN_LAUNCH(256); break;
     }
 #undef HATA_TRAIN_LAUNCH
-    hipLaunchKernelGGL(hata::train_update_kernel, dim3(HATA_D * r / 64 + (loss ? 1 : 0)), dim3(1024), 0, st, W, v, r, n_wgs,
-                       hp->sigma, hp->lam, c_sim, c_bal, hp->lr, hp->momentum, hp->weight_decay, ctx->dw_part, ctx->WP,
-                       ctx->fro_part, colsum, n_queries, ctx->bal_part, ctx->loss_part, grad, loss);
+    hipLaunchKernelGGL(hata::train_update_kernel, dim3(HATA_D * r / 64 + (loss ? 1 : 0)), dim3(TR_UPDATE_WAVES * 64), 0, st, W, v, __builtin_ctz(r), n_wgs,
+                       hp->sigma, hp->lam, c_sim, c_bal, hp->lr, hp->momentum, hp->weight_decay, ctx->dw_part,
+                       ctx->colsum_part, colsum, block_query, n_queries, ctx->gram, ctx->fro_part, ctx->W_old,
+                       ctx->loss_part, grad, loss);
     return hipGetLastError() == hipSuccess ? HATA_OK : HATA_EHIP;
 }
 
