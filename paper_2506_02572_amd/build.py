@@ -9,7 +9,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libhata.so")
 OBJ = os.path.join(HERE, "_build")
-SOURCES = ["hata_api.hip", "hata_encode.hip", "hata_score.hip", "hata_topk.hip", "hata_attn.hip", "hata_dense.hip", "hata_gather.hip", "hata_coop.hip",
+SOURCES = ["hata_api.hip", "hata_encode.hip", "hata_score.hip", "hata_topk.hip", "hata_attn.hip", "hata_dense.hip", "hata_gather.hip", "hata_coop.hip", "hata_unit.hip",
            "hata_train.hip", "hata_probe.hip"]
 HEADERS = ["hata_device.h", "hata_internal.h", "hata_select.h", "hata_trace.h", "hata_attn_core.h", "hata_hash.h", os.path.join("..", "..", "include", "hata.h"),
            os.path.join("..", "..", "include", "hata_train.h")]

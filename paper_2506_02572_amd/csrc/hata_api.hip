@@ -183,6 +183,20 @@ inline int coop_sub_batches(const hata_ctx* c, int B, bool paged, int* chunk_out
     if (chunk_out) *chunk_out = best_chunk;
     return best;
 }
+// Whether the step's own choice is a workgroup per unit.  Nothing waits in that form, so a shared device (step mode 3 unless the
+// caller asks for that) takes it too.  Beyond 4096 keys it needs many units, as a compute unit alone streams slowly, but not so
+// many that they go in several rounds.  us a layer, workgroups that share units / one per unit, r = 128, groups of four unless
+// noted: 64 units of 6000 keys 15.0 / 14.9; 128 of 8192 18.5 / 17.1 (r = 256 23.1 / 22.7, ragged 17.6 / 16.8, one head a unit
+// 14.6 / 12.9), of 16384 23.4 / 26.5; 256 of 16384 37.5 / 30.9 (r = 256 51.3 / 44.8); 512 of 8192 31.4 / 29.2, 1024 of 8192
+// 44.3 / 55.9.  On a shared device, three launches / one per unit: 8 units of 8192 keys 20.5 / 15.7 (r = 256 22.0 / 21.0), of
+// 12000 20.7 / 20.0 (22.3 / 24.7); 64 units of 12000 25.1 / 20.9 (27.7 / 26.1); 128 of 16384 31.3 / 26.6 (42.4 / 36.7).
+inline bool takes_unit_step(const hata_ctx* c, int B) {
+    if (!c->unit_keys || (c->step_mode != 0 && c->mode_asked)) return false;
+    const int64_t units = (int64_t)B * c->cfg.Hkv;
+    if (c->cfg.L_cap <= HATA_UNIT_KEYS) return true;
+    if (c->step_mode != 0) return c->cfg.L_cap <= 8192 || (c->cfg.L_cap <= 128 * units && units <= 512);
+    return c->cfg.L_cap <= 64 * units && units <= 512;
+}
 inline bool aligned(const void* p, size_t a) { return ((uintptr_t)p % a) == 0; }
 
 // Validates a block-table description and fills the view the launchers take.
@@ -298,6 +312,12 @@ int hata_create_tuned(hata_ctx** ctx_out, const hata_config* cfg, const hata_tun
     }
     // a device shared with other work cannot promise that a whole grid is resident: three launches
     c->step_mode = (tuning && tuning->shared_device) ? 3 : 0;
+    c->mode_asked = 0;
+    if (hata::prepare_unit_step(c) != hipSuccess) {
+        delete c;
+        return HATA_EHIP;
+    }
+    if (tuning && tuning->chunk != 0) c->unit_keys = 0;
     c->spin_limit = 0;
     c->keep_scores = 0;
     // with more than one query head per KV head the merge is spread over the unit's workgroups,
@@ -499,6 +519,8 @@ int hata_decode_step(hata_ctx* ctx, const void* q, const void* K, const void* V,
         !aligned(W_H, 16) || !aligned(out, 2))
         return HATA_EINVAL;
     hipStream_t s = (hipStream_t)stream;
+    if (takes_unit_step(ctx, B))
+        return hip_rc(hata::launch_unit_step(ctx, q, K, V, W_H, codes, append, seq_len, k, B, sm_scale, out, out_f32, s));
     // Cooperative path: encoding, scoring, selection and attention in ONE launch (workgroups of a
     // unit wait for the unit's threshold inside the kernel), when every workgroup can be resident
     // at once.
@@ -568,6 +590,9 @@ int hata_decode_step_paged(hata_ctx* ctx, const void* q, const void* K_pool, con
     const int ns = coop_sub_batches(ctx, B, true, &step_chunk);
     ctx->step_mode = mode;
     if (ns == 0) return HATA_EUNSUPPORTED;
+    if (takes_unit_step(ctx, B))
+        return hip_rc(hata::launch_unit_step(ctx, q, K_pool, V_pool, W_H, codes_pool, append, seq_len, k, B, sm_scale, out, out_f32,
+                                             (hipStream_t)stream, &pv));
     hipError_t e = hipSuccess;
     for (int i = 0; i < ns && e == hipSuccess; ++i) {
         const int b0 = (int)((int64_t)i * B / ns), b1 = (int)((int64_t)(i + 1) * B / ns);
@@ -582,8 +607,9 @@ int hata_step_plan(const hata_ctx* ctx, int32_t B, int32_t* n_launches, int32_t*
     int rc = check_call(ctx, B);
     if (rc != HATA_OK) return rc;
     int step_chunk = 0;
-    const bool single = coop_sub_batches(ctx, B, false, &step_chunk) != 0;
+    const bool unit = takes_unit_step(ctx, B), single = unit || coop_sub_batches(ctx, B, false, &step_chunk) != 0;
     if (!single) step_chunk = ctx->chunk;
+    if (unit) step_chunk = ctx->unit_keys;
     if (n_launches) *n_launches = single ? 1 : 3;
     if (chunk) *chunk = step_chunk;
     if (n_chunks) *n_chunks = (ctx->cfg.L_cap + step_chunk - 1) / step_chunk;
@@ -594,13 +620,14 @@ int hata_step_sub_batches(const hata_ctx* ctx, int32_t B, int32_t* n_sub) {
     int rc = check_call(ctx, B);
     if (rc != HATA_OK) return rc;
     if (!n_sub) return HATA_EINVAL;
-    *n_sub = coop_sub_batches(ctx, B, false);
+    *n_sub = takes_unit_step(ctx, B) ? 1 : coop_sub_batches(ctx, B, false);
     return HATA_OK;
 }
 
 int hata_set_step_mode(hata_ctx* ctx, int32_t mode) {
     if (!ctx || (mode != 0 && mode != 1 && mode != 3)) return HATA_EINVAL;
     ctx->step_mode = mode;
+    ctx->mode_asked = 1;
     return HATA_OK;
 }
 

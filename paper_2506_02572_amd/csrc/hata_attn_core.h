@@ -30,11 +30,12 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 
 // (the accumulator rows are padded by 4 floats so that the 128-bit stores of the matrix-core path,
 // one head per lane, spread over the LDS banks)
-template <int HT>
+// (NW: waves of the workgroup, four unless the caller has more)
+template <int HT, int NW = 4>
 struct AttnLds {
-    float m[4][HT];
-    float l[4][HT];
-    float acc[4][HT][HATA_D + 4];  // reused by the merge for the slice weights
+    float m[NW][HT];
+    float l[NW][HT];
+    float acc[NW][HT][HATA_D + 4];  // reused by the merge for the slice weights
 };
 
 // this lane's 8 query elements of each of the HT heads starting at q0 (packed bf16 pairs)
@@ -50,13 +51,13 @@ __device__ __forceinline__ void attn_load_q(const uint16_t* __restrict__ q0, uin
 
 // Attention of the HT heads over rows [row_begin, row_end): row_of(row) gives the cache row (< 0 or
 // >= L_cap: skipped).  On return (after a workgroup barrier) S holds the four waves' states.
-// Must be called by all 256 threads.
-// IT: 16-row load iterations per tile (a tile of 16 IT rows is in flight per workgroup).
-template <int HT, int IT, typename RowOf>
+// Must be called by all threads (64 NW).
+// IT: load iterations per tile, four rows of a wave each (a tile of 4 NW IT rows is in flight per workgroup).
+template <int HT, int IT, int NW = 4, typename RowOf>
 __device__ __forceinline__ void attn_rows(
     const uint32_t (&qr)[HT][4], const uint16_t* __restrict__ Kb, const uint16_t* __restrict__ Vb,
     int64_t sn, int L_cap, int row_begin, int row_end, float scale_log2, RowOf row_of,
-    AttnLds<HT>& S) {
+    AttnLds<HT, NW>& S) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int sub = lane & 15, rg = lane >> 4;
     float m_run[HT], l_run[HT], acc[HT][8];
@@ -66,12 +67,12 @@ __device__ __forceinline__ void attn_rows(
 #pragma unroll
         for (int e = 0; e < 8; ++e) acc[g][e] = 0.f;
     }
-    for (int tile = row_begin; tile < row_end; tile += 16 * IT) {
+    for (int tile = row_begin; tile < row_end; tile += 4 * NW * IT) {
         uint4 kv[IT], vv[IT];
         bool ok[IT];
 #pragma unroll
         for (int it = 0; it < IT; ++it) {
-            const int row = tile + it * 16 + wave * 4 + rg;
+            const int row = tile + it * 4 * NW + wave * 4 + rg;
             ok[it] = row < row_end;
             int n = 0;
             if (ok[it]) n = row_of(row);
@@ -169,7 +170,7 @@ typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 
 #define HATA_VT_PITCH 144                    // uint16 per staged V row (288 B)
 #define HATA_VT_WAVE (16 * HATA_VT_PITCH)    // uint16 per wave
-#define HATA_VT_ELEMS (4 * HATA_VT_WAVE)     // uint16 of LDS a workgroup needs for attn_rows_mfma
+#define HATA_VT_ELEMS (4 * HATA_VT_WAVE)     // uint16 of LDS a workgroup of four waves needs for attn_rows_mfma
 
 // Q as the B operand: lane (n, kg) holds q[head n][32 s + 8 kg, + 8) for s < 4; heads >= HT are zero
 template <int HT>
@@ -182,12 +183,13 @@ __device__ __forceinline__ void attn_load_q_mfma(const uint16_t* __restrict__ q0
     }
 }
 
-// Same contract as attn_rows (state of the four waves in S after a workgroup barrier).
-// vt: HATA_VT_ELEMS uint16 of LDS.
-template <int HT, typename RowOf>
+// Same contract as attn_rows (states of the waves in S after a workgroup barrier).
+// vt: HATA_VT_WAVE uint16 of LDS per wave.
+// ALIAS: S and vt share their LDS (the waves meet before the first state is written).
+template <int HT, int NW = 4, bool ALIAS = false, typename RowOf>
 __device__ __forceinline__ void attn_rows_mfma(
     const uint4 (&qb)[4], const uint16_t* __restrict__ Kb, const uint16_t* __restrict__ Vb, int64_t sn,
-    int L_cap, int row_begin, int row_end, float scale_log2, RowOf row_of, AttnLds<HT>& S,
+    int L_cap, int row_begin, int row_end, float scale_log2, RowOf row_of, AttnLds<HT, NW>& S,
     uint16_t* vt_all) {
     static_assert(HT >= 1 && HT <= 16, "heads are padded to one 16-wide MFMA tile");
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -261,7 +263,7 @@ __device__ __forceinline__ void attn_rows_mfma(
         }
         __builtin_amdgcn_wave_barrier();
     };
-    for (int tile0 = row_begin + wave * 16; tile0 < row_end; tile0 += 64) {
+    for (int tile0 = row_begin + wave * 16; tile0 < row_end; tile0 += 16 * NW) {
         Tile st;
         bool ok = tile0 + n < row_end;
         int idx = 0;
@@ -274,6 +276,7 @@ __device__ __forceinline__ void attn_rows_mfma(
     }
     // lanes of the 4 row groups hold partial sums of the same head
     l_run = rows_sum4(l_run);
+    if (ALIAS) __syncthreads();
     if (n < HT) {
         if (kg == 0) { S.m[wave][n] = m_run; S.l[wave][n] = l_run; }
 #pragma unroll

@@ -73,4 +73,53 @@ __device__ __forceinline__ void hash_pass(const HashWeights<COLS>& W, const uint
     if (lane < 4 && v < last && wave < COLS / 16) reinterpret_cast<uint16_t*>(s_codes)[v * pitch * 2 + wave] = (uint16_t)bits;
 }
 
+// ---- the same by 16 waves, each 16 columns and a part of the channels (r = 32 .. 256: 8, 4, 2 or 1 parts) ----
+template <int R>
+struct UnitHash {
+    static constexpr int GROUPS = R / 16, PARTS = 16 / GROUPS;  // groups of 16 columns; waves of a group
+    static constexpr int CH = HATA_D / PARTS / 4;               // channels of a lane
+    float w[CH];
+    // the wave's first channel, and this lane's
+    static __device__ __forceinline__ int channel() {
+        return (threadIdx.x >> 6) / GROUPS * (HATA_D / PARTS) + CH * ((threadIdx.x & 63) >> 4);
+    }
+    __device__ __forceinline__ void fetch(const float* __restrict__ W) {
+        const float* p = W + (int64_t)channel() * R + (threadIdx.x >> 6) % GROUPS * 16 + (threadIdx.x & 15);
+#pragma unroll
+        for (int s = 0; s < CH; ++s) w[s] = p[s * R];
+    }
+    struct Vector { uint32_t x[CH / 2]; };
+    static __device__ __forceinline__ Vector fetch_x(const uint16_t* __restrict__ x) {
+        Vector v;
+        const uint16_t* p = x + channel();
+        if constexpr (CH == 4) {
+            const uint2 a = *reinterpret_cast<const uint2*>(p);
+            v.x[0] = a.x; v.x[1] = a.y;
+        } else {
+#pragma unroll
+            for (int i = 0; i < CH / 8; ++i) {
+                const uint4 a = reinterpret_cast<const uint4*>(p)[i];
+                v.x[4 * i] = a.x; v.x[4 * i + 1] = a.y; v.x[4 * i + 2] = a.z; v.x[4 * i + 3] = a.w;
+            }
+        }
+        return v;
+    }
+    // this wave's part of four projections (result: vector lane % 4, column lane / 16 + 4 (lane / 4 % 4) of the group)
+    __device__ __forceinline__ double project(const Vector& v) const {
+        double acc = 0.0;
+#pragma unroll
+        for (int s = 0; s < CH; ++s) {
+            const double xd = (double)((s & 1) ? bf16_hi(v.x[s >> 1]) : bf16_lo(v.x[s >> 1]));
+            acc = __builtin_amdgcn_mfma_f64_4x4x4f64((double)w[s], xd, acc, 0, 0, 0);
+        }
+        return acc;
+    }
+    // sign bits of a whole projection: 16 bits of vector first + lane % 4 (below `last`), into s_codes[vector][R / 32]
+    static __device__ __forceinline__ void store_bits(double acc, uint32_t* s_codes, int group, int first, int last) {
+        const int lane = threadIdx.x & 63, v = first + lane;
+        const uint32_t bits = or_columns((acc >= 0.0 ? 1u : 0u) << ((lane >> 4) + (lane & 12)));
+        if (lane < 4 && v < last) reinterpret_cast<uint16_t*>(s_codes)[v * (R / 16) + group] = (uint16_t)bits;
+    }
+};
+
 }  // namespace hata

@@ -49,6 +49,8 @@ struct hata_ctx {
     int keep_scores;         // single-launch step also writes the score array
     int par_merge;           // single-launch step merges the heads of a unit in several workgroups
     int step_mode;           // 0 = single launch when it fits, 3 = always three launches
+    int unit_keys;           // keys a workgroup per unit handles (0: that form is not available, or the caller asked for a launch shape)
+    int mode_asked;          // step_mode was set by the caller (and is not just that of a shared device)
     int cus;                 // compute units of the device that was current in hata_create
     int coop_opt_cap_paged[4];  // the same for the block-table variant of the kernel
     float* partials;       // [B_max*Hq, max(sparse_splits, n_chunks), d + 2], at least 256 * HATA_DENSE_ROUNDS * G rows
@@ -114,6 +116,14 @@ hipError_t launch_coop_step(hata_ctx* c, const void* q, const void* K, const voi
 // unit's whole part of coop_cum: the chunks' rows, then the marks
 inline int coop_mark_pitch(int n_chunks) { return ((n_chunks < 256 ? n_chunks : 256) + 31) / 32 * 32; }
 inline int coop_cum_pitch(int n_chunks, int NBP) { return n_chunks * (NBP / 2) + (n_chunks < 256 ? n_chunks : 256) * coop_mark_pitch(n_chunks) / 2; }
+// the step with a workgroup per (sequence, KV head) unit: caches of up to HATA_UNIT_KEYS_LONG rows, of up to HATA_UNIT_KEYS by
+// a form of its own
+#define HATA_UNIT_KEYS 4096
+#define HATA_UNIT_KEYS_LONG 16384
+hipError_t prepare_unit_step(hata_ctx* c);  // once per context
+hipError_t launch_unit_step(const hata_ctx* c, const void* q, const void* K, const void* V, const float* W_H, uint32_t* codes,
+                            int append, const int32_t* seq_len, const int32_t* k, int B, float sm_scale, void* out,
+                            float* out_f32, hipStream_t s, const PageView* pages = nullptr);
 int coop_capacity(const hata_ctx* c, bool paged, int chunk);
 
 }  // namespace hata
