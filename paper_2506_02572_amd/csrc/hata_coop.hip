@@ -335,8 +335,6 @@ void decode_step_coop_kernel(const CoopArgs a) {
     // this launch's number in the unit's count of launches (0 is the cleared state of the published words); the second
     // word names a launch that chunk 0 gave up before all had read it: such a latecomer would take the next launch's number
     const uint2 launches = ld_dev_u2(a.unit_epoch + u * HATA_COUNTER_STRIDE);
-    const uint32_t epoch = max(launches.x + 1u, 1u);
-    const bool publishes = launches.y != a.epoch;
     const int L = clampi(a.seq_len[b], 0, PAGED ? min(a.L_cap, a.pv.max_blocks << a.pv.shift) : a.L_cap);
     // Row n of the unit (a row of this chunk when PAGED) -> its row in the code array, in rows of
     // one (sequence or page, head): the contiguous cache is [B, Hkv, L_cap], the pools are
@@ -553,6 +551,8 @@ void decode_step_coop_kernel(const CoopArgs a) {
     // freezes kernel arguments, has one of its own too; chunk 0 moves it on once it has seen every chunk's words (all
     // have read it by then).
     const int n_keys = end - base;
+    const uint32_t epoch = max((uint32_t)__builtin_amdgcn_readfirstlane((int)launches.x) + 1u, 1u);
+    const bool publishes = nc > 1 && (uint32_t)__builtin_amdgcn_readfirstlane((int)launches.y) != a.epoch;
     {
         constexpr int SEG = ((NB + 255) / 256 + 3) / 4 * 4;  // consecutive scores of a thread
         // keys of this chunk if the unit's selection were spread evenly over its chunks
@@ -599,14 +599,14 @@ void decode_step_coop_kernel(const CoopArgs a) {
 #pragma unroll
         for (int j4 = 0; j4 < SEG; j4 += 4) {
             if (s0 + j4 < NBR) *reinterpret_cast<uint4*>(&hist[s0 + j4]) = make_uint4(cm[j4], cm[j4 + 1], cm[j4 + 2], cm[j4 + 3]);
-            if (nc > 1 && publishes && s0 + j4 < a.NBP) {
+            if (publishes && s0 + j4 < a.NBP) {
 #pragma unroll
                 for (int j = j4; j < j4 + 4; j += 2)
                     st_dev(hp + (s0 + j) / 2, ((unsigned long long)epoch << 32) | (cm[j] | (cm[j + 1] << 16)));
             }
         }
     }
-    if (nc > 1 && publishes && tid < nc)  // (at most 256 chunks)
+    if (publishes && tid < nc)  // (at most 256 chunks)
         st_dev(reinterpret_cast<uint32_t*>(a.cum + u * a.cum_pitch + a.cum_marks) + tid * a.mark_pitch + c, epoch);
     TC(42);
     __syncthreads();
