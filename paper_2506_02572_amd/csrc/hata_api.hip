@@ -421,8 +421,7 @@ int hata_hamming_score(hata_ctx* ctx, const uint32_t* qcodes, const uint32_t* co
     if (rc != HATA_OK) return rc;
     if (!qcodes || !codes || !seq_len || !scores) return HATA_EINVAL;
     if (!aligned(qcodes, 4) || !aligned(codes, 16) || !aligned(scores, 2)) return HATA_EINVAL;
-    return hip_rc(hata::launch_score(ctx, qcodes, codes, seq_len, B, scores, nullptr,
-                                     (hipStream_t)stream));
+    return hip_rc(hata::launch_score(ctx, qcodes, codes, seq_len, B, scores, (hipStream_t)stream));
 }
 
 int hata_topk(hata_ctx* ctx, const uint16_t* scores, const int32_t* seq_len, const int32_t* k,
@@ -539,9 +538,9 @@ int hata_decode_step(hata_ctx* ctx, const void* q, const void* K, const void* V,
     hipError_t e = hata::launch_encode_vectors(ctx, q, ctx->qcodes, append ? K : nullptr, seq_len,
                                                nullptr, 1, 1, codes, W_H, B, s);
     if (e != hipSuccess) return HATA_EHIP;
-    // Three-launch path.  Hamming distances of every cached code (the new one included), chunk
-    // histograms, and -- by the last workgroup of each unit -- the selection threshold and offsets
-    e = hata::launch_score(ctx, ctx->qcodes, codes, seq_len, B, ctx->scores, k, s);
+    // Three-launch path.  Hamming distances of every cached code (the new one included) and the chunks' cumulative
+    // histograms
+    e = hata::launch_score_select(ctx, codes, seq_len, k, B, s);
     if (e != hipSuccess) return HATA_EHIP;
     // TopK(S, N) compaction fused with the attention over the selected rows (gather fused too)
     e = hata::launch_attention(ctx, 2, q, K, V, ctx->idx, k, seq_len, B, sm_scale, out, out_f32, s);

@@ -28,12 +28,12 @@ struct AttnArgs {
     const uint16_t* V;
     const int32_t* idx_in;      // ROWS_IDX
     int32_t* idx_out;           // ROWS_SELECT
-    const int32_t* count_src;   // ROWS_IDX: k[B]
+    const int32_t* count_src;   // k[B]
     const uint16_t* scores;     // ROWS_SELECT ...
     const int32_t* seq_len;
-    const int32_t* chunk_info;
-    const int32_t* unit_info;
-    int chunk, n_chunks, chunks_per_split, owners, piece_rows, B;  // (chunk, chunks_per_split: powers of two)
+    const uint16_t* cum;        // [units, n_chunks, NBP] cumulative histograms of the chunks' scores
+    const int32_t* estimate;    // [units, n_chunks] the chunks' estimates of the threshold
+    int NBP, chunk, n_chunks, chunks_per_split, owners, piece_rows, B;  // (chunk, chunks_per_split: powers of two)
     float* partials;
     uint32_t* counter;
     int counter_stride;
@@ -46,8 +46,11 @@ struct AttnArgs {
 
 // grid = (splits, Hkv * (G / HT), B), in ROWS_SELECT (owners, .., B + layers for the further pieces); 256 threads.
 // ROWS_SELECT: the first `owners` splits are a chunk each (or as many as leave at most 256 splits to merge), so that
-// everything the selection needs -- the chunk's scores, its offset and ties, the threshold -- is at addresses known from
-// the start, and on the XCD that scored the chunk.  Slices of the index list instead, which had to find their chunks first,
+// what the selection needs of a chunk -- its scores, its cumulative histogram -- is at addresses known from
+// the start, and on the XCD that scored the chunk.  The unit's threshold and the chunk's place in the index list come from
+// 64 columns of all the chunks' cumulative histograms around the chunk's own estimate (as in hata_coop.hip); the scoring launch's
+// last workgroup of a unit used to find them, behind everybody else: 2 x 20011 keys, a group of five, 24.6 -> 22.2 us a step
+// (the scoring launch 9.8 -> 4.8, this one 10.8 -> 13.8), one sequence of 32768 22.6 -> 20.0, 32 of them 84.4 -> 82.4.  Slices of the index list instead, which had to find their chunks first,
 // took 18.4 us per launch at 16 units of 20011 keys, this takes 10.4.  A prompt's selected rows may all lie in a chunk or
 // two, though: an owner attends over the first piece_rows rows of its chunk only, and the further pieces go to the splits
 // behind the owners, which compact that chunk again: 8 units of 131072 keys, 2048 rows all in one place, 64.5 -> 35.0 us a step
@@ -60,6 +63,7 @@ __global__ __launch_bounds__(256) void attn_kernel(const AttnArgs a) {
     extern __shared__ __attribute__((aligned(16))) uint16_t s_sc[];  // ROWS_SELECT: the chunk's scores, then its selected rows
     __shared__ uint32_t scan4[4];
     __shared__ int s_last;
+    __shared__ uint4 s_win[MODE == ROWS_SELECT ? 4 : 1][64][2];  // {columns 0 and 1 of all chunks, of those before this owner's}, {of this owner's}
     const int tid = threadIdx.x;
     const int tiles = a.G / HT;
     const int h = blockIdx.y / tiles;
@@ -96,21 +100,12 @@ __global__ __launch_bounds__(256) void attn_kernel(const AttnArgs a) {
             attn_rows<HT, 4>(qr, Kb, Vb, a.sn, a.L_cap, row_begin, row_end, a.scale_log2, row_of, S);
     };
     if constexpr (MODE == ROWS_SELECT) {
-        // what an owner reads is requested together: no address depends on the sequence's length
-        const int per = a.chunks_per_split, span = per * a.chunk;
-        const int32_t* ci_unit = a.chunk_info + u * (a.n_chunks + 1) * 2;
-        auto entry = [&](int s) { return ci_unit + 2 * min(s * per, a.n_chunks); };
-        const int seq = a.seq_len[b], T = a.unit_info[u * 2 + 0], budget = a.unit_info[u * 2 + 1];
-        int off = 0, take = 0, next = 0;
-        if (split < a.owners) {
-            off = entry(split)[0];
-            take = entry(split)[1];
-            next = entry(split + 1)[0];
-        }
-        const int lane = tid & 63;
-        const int first0 = *entry(lane), next0 = *entry(lane + 1);
-        const int L = clampi(seq, 0, a.L_cap), keff = clampi(budget, 0, a.k_max);
-        const int nc = (L + a.chunk - 1) >> __builtin_ctz(a.chunk);  // (entry nc closes the list: keff)
+        const int per = a.chunks_per_split, span = per * a.chunk, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+        const uint16_t* hu = a.cum + u * a.n_chunks * a.NBP;
+        const bool owner = split < a.owners;
+        const int estimate = a.estimate[u * a.n_chunks + (owner ? min(split * per, a.n_chunks - 1) : 0)];
+        const int L = clampi(a.seq_len[b], 0, a.L_cap), keff = min(clampi(a.count_src[b], 0, a.k_max), L);
+        const int nc = (L + a.chunk - 1) >> __builtin_ctz(a.chunk);
         const int live = (L + span - 1) >> __builtin_ctz(span);      // owners with keys
         int32_t* io = a.idx_out + u * a.k_max;
         if (split == 0) {
@@ -118,60 +113,144 @@ __global__ __launch_bounds__(256) void attn_kernel(const AttnArgs a) {
                 for (int p = keff + tid; p < a.k_max; p += 256) io[p] = -1;
             if (L == 0) zero_output();
         }
-        auto selected = [&](int s, int first, int next) {
-            return clampi(next - first, 0, min(min(span, L - s * span), a.k_max - clampi(first, 0, a.k_max)));
+        if (owner ? split >= live : live == 0) return;
+        const int c0 = owner ? split * per : 0, c1 = min(c0 + per, nc);  // the owner's chunks (a further piece looks from chunk 0)
+        auto stage_scores = [&](int base, int n_keys) {
+            const uint16_t* sp = a.scores + u * a.L_cap + base;
+            const bool whole = (reinterpret_cast<uintptr_t>(sp) & 15) == 0;
+            for (int i = tid * 8; i < n_keys; i += 256 * 8) {
+                if (whole && i + 8 <= n_keys) {
+                    *reinterpret_cast<uint4*>(&s_sc[i]) = *reinterpret_cast<const uint4*>(sp + i);
+                } else {
+                    for (int e = i; e < min(i + 8, n_keys); ++e) s_sc[e] = sp[e];
+                }
+            }
         };
-        // pieces beyond an owner's first: lane l looks at owners l, l + 64, ... (the first of them are requested above);
-        // returns how many there are, and where number `nth` of them is
+        // The threshold T lies in [t_lo, t_hi]; a window of 64 columns shows it if the first of them counts fewer than keff keys (or
+        // is score 0) and the last one at least keff.  The next window is beside it, the ones after that halve what is left.
+        const int w0_max = max(0, a.NBP - 64);
+        int t_lo = 0, t_hi = a.NBP - 1, w0 = keff == 0 ? 0 : clampi((estimate - 32) & ~1, 0, w0_max);
+        int T = 0, need = 0, off = 0, take = 0, cnt = 0;
+        bool found = false;
+#pragma clang loop unroll(disable)
+        for (int it = 0; it < 32 && !found; ++it) {
+            // a wave reads two rows at a time, half a wave each, a lane two columns
+            const uint16_t* hw = hu + min(w0 + 2 * (lane & 31), a.NBP - 2);
+            uint32_t sum[6] = {0, 0, 0, 0, 0, 0};
+            constexpr int UN = 8;
+            for (int r2 = 2 * wv; r2 < nc; r2 += 8 * UN) {
+                const int r0 = r2 + (lane >> 5);
+                uint32_t x[UN];
+#pragma unroll
+                for (int j = 0; j < UN; ++j) {
+                    x[j] = 0;
+                    if (r2 + 8 * j < nc) x[j] = *reinterpret_cast<const uint32_t*>(hw + (int64_t)min(r0 + 8 * j, nc - 1) * a.NBP);
+                }
+#pragma unroll
+                for (int j = 0; j < UN; ++j) {
+                    const int c = r0 + 8 * j;
+                    const uint32_t lo = x[j] & 0xffffu, hi = x[j] >> 16;
+                    sum[0] += c < nc ? lo : 0u;
+                    sum[1] += c < nc ? hi : 0u;
+                    sum[2] += c < c0 ? lo : 0u;
+                    sum[3] += c < c0 ? hi : 0u;
+                    sum[4] += c >= c0 && c < c1 ? lo : 0u;
+                    sum[5] += c >= c0 && c < c1 ? hi : 0u;
+                }
+            }
+            if (it == 0 && owner) stage_scores(split * span, min(span, L - split * span));  // (behind the first window's loads)
+            if (it) __syncthreads();  // (the last window has been read)
+            s_win[wv][lane][0] = make_uint4(sum[0], sum[1], sum[2], sum[3]);
+            s_win[wv][lane][1] = make_uint4(sum[4], sum[5], 0, 0);
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < 6; ++i) sum[i] = 0;
+#pragma unroll
+            for (int w = 0; w < 8; ++w) {
+                const uint4 v = s_win[w >> 1][(w & 1) * 32 + (lane & 31)][0], o = s_win[w >> 1][(w & 1) * 32 + (lane & 31)][1];
+                sum[0] += v.x; sum[1] += v.y; sum[2] += v.z; sum[3] += v.w;
+                sum[4] += o.x; sum[5] += o.y;
+            }
+            const unsigned long long hit = __builtin_amdgcn_ballot_w64(sum[1] >= (uint32_t)keff);
+            if (hit == 0ull) {
+                t_lo = w0 + 64;
+            } else {
+                const int l = __ffsll(hit) - 1, p = max(l - 1, 0);
+                const bool even = (uint32_t)__builtin_amdgcn_readlane((int)sum[0], l) >= (uint32_t)keff;
+                if (even && l == 0 && w0 > 0) {
+                    t_hi = w0;
+                } else {
+                    found = true;
+                    T = w0 + 2 * l + (even ? 0 : 1);
+                    // keys below T and up to T: in the whole unit, in the chunks before the owner's, in the owner's
+                    auto below = [&](uint32_t e, uint32_t o) {
+                        return even ? (l > 0 ? __builtin_amdgcn_readlane((int)o, p) : 0) : __builtin_amdgcn_readlane((int)e, l);
+                    };
+                    auto up_to = [&](uint32_t e, uint32_t o) { return __builtin_amdgcn_readlane((int)(even ? e : o), l); };
+                    need = keff - below(sum[0], sum[1]);  // ties to grant, in cache order
+                    const int lt_b = below(sum[2], sum[3]), eq_b = up_to(sum[2], sum[3]) - lt_b;
+                    const int lt = below(sum[4], sum[5]), eq = up_to(sum[4], sum[5]) - lt;
+                    take = clampi(need - eq_b, 0, eq);
+                    cnt = lt + take;
+                    off = lt_b + min(eq_b, need);
+                }
+            }
+            if (!found) w0 = clampi((it == 0 ? (hit ? t_hi - 62 : t_lo - 2) : (t_lo + t_hi) / 2 - 32) & ~1, 0, w0_max);
+        }
+        // Rows each owner selects, lane l looking at owners l, l + 64, ...: pieces beyond an owner's first; returns how many there
+        // are, and finds number `nth` of them: its owner, its place there, and what that owner selects.
         const float half_inv = 0.5f * __builtin_amdgcn_rcpf((float)a.piece_rows);  // (rows - 1) / piece_rows, exact below 2^20
-        auto further_pieces = [&](int nth, int& own, int& piece) {
-            int extra = 0;
+        auto columns = [&](int s, int& lt, int& le) {
+            lt = le = 0;
+            for (int i = 0; i < per; ++i) {
+                const int c = s * per + i;
+                if (c < nc) {
+                    const uint16_t* row = hu + (int64_t)c * a.NBP;
+                    lt += T > 0 ? row[T - 1] : 0;
+                    le += row[min(T, a.NBP - 1)];
+                }
+            }
+        };
+        int lt0, le0;  // requested here, used behind the attention
+        columns(lane, lt0, le0);
+        auto further_pieces = [&](int nth, int& own, int& piece, int& off, int& take, int& cnt) {
+            int extra = 0, ties = 0, rows_before = 0;  // of the owners before these 64
             for (int s0 = 0; s0 < live; s0 += 64) {
                 const int s = s0 + lane;
-                const int first = s0 == 0 ? first0 : *entry(s);
-                const int next = (s + 1) * per > nc ? keff : s0 == 0 ? next0 : *entry(s + 1);
-                const int rows = s < live ? selected(s, first, next) : 0;
+                int lt = lt0, le = le0;
+                if (s0) columns(s, lt, le);
+                const int eq = le - lt, eq_incl = (int)wave_incl_scan((uint32_t)eq);
+                const int granted = clampi(need - ties - (eq_incl - eq), 0, eq);
+                const int rows = keff > 0 ? lt + granted : 0;
                 const int more = rows > 0 ? (int)((float)(2 * rows - 1) * half_inv) : 0;
-                if (__builtin_amdgcn_ballot_w64(more > 0) == 0) continue;
+                const int rows_incl = (int)wave_incl_scan((uint32_t)rows);
                 const int upto = extra + (int)wave_incl_scan((uint32_t)more);
-                const unsigned long long past = __builtin_amdgcn_ballot_w64(extra <= nth && upto > nth);
+                const unsigned long long past = __builtin_amdgcn_ballot_w64(upto - more <= nth && upto > nth);
                 if (past) {
                     const int l = __ffsll(past) - 1;
                     own = s0 + l;
                     piece = nth - __builtin_amdgcn_readlane(upto - more, l) + 1;
+                    off = rows_before + __builtin_amdgcn_readlane(rows_incl - rows, l);
+                    take = __builtin_amdgcn_readlane(granted, l);
+                    cnt = __builtin_amdgcn_readlane(rows, l);
                 }
                 extra = __builtin_amdgcn_readlane(upto, 63);
+                ties += __builtin_amdgcn_readlane(eq_incl, 63);
+                rows_before += __builtin_amdgcn_readlane(rows_incl, 63);
             }
             return min(extra, a.n_splits - a.owners);
         };
         int own = split, piece = 0, extra = 0;
-        if (split >= a.owners) {
-            extra = further_pieces(split - a.owners, own, piece);
+        if (!owner) {
+            extra = further_pieces(split - a.owners, own, piece, off, take, cnt);
             if (split - a.owners >= extra) return;
-            own = __builtin_amdgcn_readfirstlane(own);
-            piece = __builtin_amdgcn_readfirstlane(piece);
             slot = live + split - a.owners;
-            off = entry(own)[0];
-            take = entry(own)[1];
-            next = entry(own + 1)[0];
-        } else if (split >= live) {
-            return;
         }
-        const int c0 = own * per, base = own * span, n_keys = min(span, L - base);
-        if (c0 + per > nc) next = keff;
-        // ties are granted in cache order, so those of consecutive chunks add up
-        for (int i = 1; i < min(per, nc - c0); ++i) take += ci_unit[2 * (c0 + i) + 1];
-        const uint16_t* sp = a.scores + u * a.L_cap + base;
-        const bool whole = (reinterpret_cast<uintptr_t>(sp) & 15) == 0;
-        for (int i = tid * 8; i < n_keys; i += 256 * 8) {
-            if (whole && i + 8 <= n_keys) {
-                *reinterpret_cast<uint4*>(&s_sc[i]) = *reinterpret_cast<const uint4*>(sp + i);
-            } else {
-                for (int e = i; e < min(i + 8, n_keys); ++e) s_sc[e] = sp[e];
-            }
-        }
+        const int base = own * span, n_keys = min(span, L - base);
+        off = clampi(off, 0, a.k_max);
+        cnt = clampi(cnt, 0, min(n_keys, a.k_max - off));
+        if (!owner) stage_scores(base, n_keys);
         __syncthreads();
-        const int cnt = selected(own, off, next);
         if (cnt > 0)  // (the same for the whole workgroup)
             compact_lds(s_sc, n_keys, span / 256, T, take, cnt, scan4, [&](int r, int n) {
                 s_sc[r] = (uint16_t)n;
@@ -179,7 +258,10 @@ __global__ __launch_bounds__(256) void attn_kernel(const AttnArgs a) {
             });
         __syncthreads();
         attend(piece * a.piece_rows, min(cnt, (piece + 1) * a.piece_rows), [&](int row) { return base + (int)s_sc[row]; });
-        if (piece == 0) extra = further_pieces(-1, own, piece);
+        if (owner) {
+            int o, p, f, t, n;
+            extra = further_pieces(-1, o, p, f, t, n);
+        }
         ns = live + extra;
     } else {
         const int count = clampi(a.count_src[b], 0, a.k_max);
@@ -242,8 +324,8 @@ hipError_t launch_attention(const hata_ctx* c, int mode, const void* q, const vo
     AttnArgs a;
     a.q = (const uint16_t*)q; a.K = (const uint16_t*)K; a.V = (const uint16_t*)V;
     a.idx_in = idx; a.idx_out = idx; a.count_src = count_src;
-    a.scores = c->scores; a.seq_len = seq_len; a.chunk_info = c->chunk_info;
-    a.unit_info = c->unit_info; a.chunk = c->chunk; a.n_chunks = c->n_chunks;
+    a.scores = c->scores; a.seq_len = seq_len; a.cum = c->chunk_hist; a.estimate = c->chunk_info; a.NBP = c->NBP;
+    a.chunk = c->chunk; a.n_chunks = c->n_chunks;
     // splits of a selected step: single chunks, paired up while at least 16 splits and 256 workgroups remain (a
     // long cache's many small slices cost more in the merge than they gain; 131072 keys, 8 units, k = 512, 64 / 32 /
     // 16 splits: 29.1 / 25.0 / 26.2 us a step) and to at most 256 splits (n_chunks <= 1024, chunk <= 8192)

@@ -33,8 +33,8 @@ struct hata_ctx {
     uint32_t* qcodes;      // [B_max, Hq, Wd]
     uint16_t* scores;      // [B_max, Hkv, L_cap]
     int32_t* idx;          // [B_max, Hkv, k_max]
-    uint16_t* chunk_hist;  // [B_max*Hkv, n_chunks, NBP]
-    int32_t* chunk_info;   // [B_max*Hkv, n_chunks + 1, 2] = {output offset, ties taken}
+    uint16_t* chunk_hist;  // [B_max*Hkv, n_chunks, NBP] histograms of the chunks (top-k), cumulative ones (step without waits)
+    int32_t* chunk_info;   // [B_max*Hkv, n_chunks + 1, 2] = {output offset, ties taken} (top-k); estimates of the threshold [B_max*Hkv, n_chunks] (step without waits)
     int32_t* unit_info;    // [B_max*Hkv, 2] = {threshold, selected count}
     uint32_t* unit_counter;  // [B_max*Hkv, HATA_COUNTER_STRIDE] scored chunks of a unit (self-resetting)
     uint32_t* unit_hist;     // [B_max*Hkv, NB] total histogram of a unit (self-clearing)
@@ -83,9 +83,9 @@ hipError_t launch_encode_bulk(const hata_ctx* c, const void* K, const float* W_H
                               const void* V_new = nullptr, void* K_out = nullptr, void* V_out = nullptr,
                               const PageView* pages = nullptr);
 hipError_t launch_split_weights(const hata_ctx* c, const float* W_H, hipStream_t s);
-hipError_t launch_score(const hata_ctx* c, const uint32_t* qcodes, const uint32_t* codes,
-                        const int32_t* seq_len, int B, uint16_t* scores, const int32_t* kbud,
-                        hipStream_t s);
+hipError_t launch_score(const hata_ctx* c, const uint32_t* qcodes, const uint32_t* codes, const int32_t* seq_len, int B,
+                        uint16_t* scores, hipStream_t s);
+hipError_t launch_score_select(const hata_ctx* c, const uint32_t* codes, const int32_t* seq_len, const int32_t* k, int B, hipStream_t s);
 hipError_t prepare_dense();  // once per context
 hipError_t launch_dense(const hata_ctx* c, const void* q, const void* K, const void* V, const int32_t* seq_len, int B,
                         float sm_scale, void* out, float* out_f32, hipStream_t s);
