@@ -20,8 +20,8 @@
 // merge.  What bounds a small batch is the chain of exchanges between the workgroups, about 0.5 us each, and the short
 // serial stages between them.  The threshold used to be found by the unit's last arriver from a total histogram
 // (an atomic per occupied bin, an arrival, the search, a record per chunk to wait for); found by every workgroup, the
-// step of one sequence of 32768 keys went from 16.9 to 14.5 us, that of 131072 keys at r = 256 from 28.1 to 27.3,
-// sixteen sequences of up to 32768 from 33.9 to 31.9.
+// step of one sequence of 32768 keys went from 16.9 to 14.5 us, that of 131072 keys at r = 256 from 28.1 to 26.0,
+// sixteen sequences of up to 32768 from 33.9 to 32.1.
 // What workgroups poll or bump lives on cache lines of its own per unit / per chunk (counters,
 // marks, one copy of the query code words per chunk): polls and arrivals that share lines across
 // units queue behind each other at the memory side.
@@ -552,6 +552,13 @@ void decode_step_coop_kernel(const CoopArgs a) {
     // have read it by then).
     const int n_keys = end - base;
     const uint32_t epoch = max((uint32_t)__builtin_amdgcn_readfirstlane((int)launches.x) + 1u, 1u);
+    // Where a thread has more than four scores its own words are 32 to 96 bytes from its neighbour's, and each store of a
+    // wave writes parts of as many lines as it has lanes, through to memory: such rows (4 to 16 KB) are written from LDS, consecutive
+    // lanes consecutive words, behind a barrier (group of eight, 8 layers of 32768 keys at r = 256 164 -> 151 us, 2 layers of
+    // 3 x 117252 at r = 128 58.2 -> 55.2).  Narrow rows go straight from the registers (one sequence of 32768, 32 heads of
+    // their own, two layers: 29.9 us, 30.1 from LDS).
+    constexpr bool WIDE = NB > 1024;
+    unsigned long long* const cum_row = a.cum + u * a.cum_pitch + c * (a.NBP / 2);
     const bool publishes = nc > 1 && (uint32_t)__builtin_amdgcn_readfirstlane((int)launches.y) != a.epoch;
     {
         constexpr int SEG = ((NB + 255) / 256 + 3) / 4 * 4;  // consecutive scores of a thread
@@ -595,21 +602,29 @@ void decode_step_coop_kernel(const CoopArgs a) {
             s_Tc = at;
             s_ncand = (int)n;
         }
-        unsigned long long* hp = a.cum + u * a.cum_pitch + c * (a.NBP / 2);
 #pragma unroll
         for (int j4 = 0; j4 < SEG; j4 += 4) {
             if (s0 + j4 < NBR) *reinterpret_cast<uint4*>(&hist[s0 + j4]) = make_uint4(cm[j4], cm[j4 + 1], cm[j4 + 2], cm[j4 + 3]);
-            if (publishes && s0 + j4 < a.NBP) {
+            if (!WIDE && publishes && s0 + j4 < a.NBP) {
 #pragma unroll
                 for (int j = j4; j < j4 + 4; j += 2)
-                    st_dev(hp + (s0 + j) / 2, ((unsigned long long)epoch << 32) | (cm[j] | (cm[j + 1] << 16)));
+                    st_dev(cum_row + (s0 + j) / 2, ((unsigned long long)epoch << 32) | (cm[j] | (cm[j + 1] << 16)));
+            }
+        }
+    }
+    if constexpr (WIDE) {
+        __syncthreads();
+        if (publishes) {
+            for (int i = tid; i < a.NBP / 2; i += 256) {  // (NBP <= NBR)
+                const uint2 v = *reinterpret_cast<const uint2*>(&hist[2 * i]);
+                st_dev(cum_row + i, ((unsigned long long)epoch << 32) | (v.x | (v.y << 16)));
             }
         }
     }
     if (publishes && tid < nc)  // (at most 256 chunks)
         st_dev(reinterpret_cast<uint32_t*>(a.cum + u * a.cum_pitch + a.cum_marks) + tid * a.mark_pitch + c, epoch);
     TC(42);
-    __syncthreads();
+    if constexpr (!WIDE) __syncthreads();
     // query fragments for the attention: in flight across the wait below
     uint32_t qr[MFMA ? 1 : G][4];
     uint4 qb[4];
@@ -724,8 +739,14 @@ void decode_step_coop_kernel(const CoopArgs a) {
             const unsigned long long* hw = hu + min(w0 / 2 + (lane & 31), a.NBP / 2 - 1);
             if (it) __syncthreads();  // (the last window has been read)
             for (;;) {
-                // With many chunks the rows are too much to be read in vain; otherwise they are mostly there by now.
-                if (nc > 32 || attempt != it) {
+                // With many chunks the rows are too much to be read in vain; otherwise they are mostly there by now.  At most
+                // one workgroup per CU: they start together, and up to 32 rows are tried at once (8 layers of 32768 keys 108.4 us,
+                // with the marks first 112; beyond, the marks).  More of them start one after the other, and what they read in
+                // vain is in the way of the last: wide rows are tried up to 12 chunks (group of eight, 2 layers of 3 x 117252
+                // keys, 29 chunks: tried 61.7, marks 58.2; 3 x 40000, 20 chunks: 41.8 and 38.4; the search before it was 58.6 and
+                // 42.3), narrow ones up to 24 (32 heads of their own, 131072 keys, 32 chunks: 60.5 and 58.4;
+                // 100000, 25 chunks: the same; 16384, 16 chunks, four layers: 51.8 and 53.3).
+                if (nc > (a.prefetch ? 32 : WIDE ? 12 : 24) || attempt != it) {
                     // One wave waits for the marks the chunks leave behind their rows, on lines that no other workgroup reads.
                     // (Polling with the loads below kept a compute unit's memory pipe so busy that the youngest
                     // workgroup on it -- the one everybody waited for -- never got to its own; all workgroups of a

@@ -16,6 +16,23 @@ from tests import harness as H
 @pytest.mark.parametrize("kind", ["one_near", "one_far", "staircase", "two_values"])
 def test_threshold_of_unequal_chunks(r, heads, L, chunk, kind):
     """Every chunk estimates the threshold from its own keys: here the estimates are off by up to the whole range of scores."""
+    compare_steps(r, heads, L, chunk, kind)
+
+
+@pytest.mark.parametrize("r,heads,chunks", [(128, (64, 8), 12), (128, (64, 8), 13), (64, (8, 8), 24), (64, (8, 8), 25)])
+def test_rows_tried_or_waited_for(r, heads, chunks):
+    """More than one workgroup per CU, on both sides of the chunk counts from which the rows are not tried unannounced."""
+    compare_steps(r, heads, chunks * 1024 - 3, 1024, "staircase")
+
+
+@pytest.mark.parametrize("r,heads,L", [(128, (5, 1), 20011), (256, (8, 1), 9000), (64, (1, 1), 40000), (32, (2, 1), 8449)])
+@pytest.mark.parametrize("kind", ["one_near", "one_far", "staircase", "two_values"])
+def test_threshold_found_by_the_attention_launch(r, heads, L, kind):
+    """The step without waits inside a kernel: the scoring launch's rows, read by the attention launch."""
+    compare_steps(r, heads, L, 1024, kind, waits=False)
+
+
+def compare_steps(r, heads, L, chunk, kind, waits=True):
     import torch
     from paper_2506_02572_amd import hata
     (Hq, Hkv), B = heads, 3
@@ -40,8 +57,11 @@ def test_threshold_of_unequal_chunks(r, heads, L, chunk, kind):
     mask = np.packbits(bits.reshape(L, W, 32), axis=-1, bitorder="little").view(np.uint32).reshape(L, W)
     codes = qcodes.reshape(B, Hkv, G, W)[:, :, :1, :] ^ mask[None, None]
     ref = O.decode_step(q, K, V, WH, codes.copy(), seq, k, k_max, 1 / math.sqrt(128), append=False)
-    ctx = hata.Context(B, Hq, Hkv, 128, r, L, k_max, chunk=chunk)
-    assert ctx.hata_step_plan(B)[:2] == (1, chunk)
+    ctx = hata.Context(B, Hq, Hkv, 128, r, L, k_max, chunk=chunk, shared_device=not waits)
+    if waits:
+        assert ctx.hata_step_plan(B)[:2] == (1, chunk)
+    else:
+        assert ctx.hata_step_plan(B)[0] == 3
     out = torch.zeros((B, Hq, 128), dtype=torch.int16, device="cuda")
     out32 = torch.zeros((B, Hq, 128), dtype=torch.float32, device="cuda")
     Kd, Vd, Wd, cd, qd, sd, kd = (H.to_dev(x) for x in (K, V, WH, codes, q, seq, k))
