@@ -1,6 +1,6 @@
-// Device-side pieces of the selection stage (Alg. 3 of the paper: Idx = TopK(S, N)), shared by
-// the stand-alone top-k kernels, the scoring kernel (which finishes a unit's threshold as soon
-// as its last chunk is scored) and the fused select-and-attend kernel.
+// Device-side pieces of the selection stage (Alg. 3 of the paper: Idx = TopK(S, N)): the threshold of the
+// stand-alone top-k (found by the last workgroup of a unit to publish its histogram), and the ordered
+// compaction.
 //
 // Selection is a counting select over the <= G*r + 1 possible score values:
 //   chunk histograms -> unit threshold T, ties still needed -> per-chunk output offsets,
@@ -31,7 +31,7 @@ struct ThresholdLds {
 //                        c = 0 .. nc (entry nc = {keff, 0} closes the list)
 // from the nc chunk histograms of the unit (`hp`, pitch NBP, uint16 counts) and the unit's total
 // histogram `unit_hist` (NB words) that the workgroups of this launch accumulated with atomics; it
-// is read with device-coherent loads and cleared for the next launch.  `tot` is unused.
+// is read with device-coherent loads and cleared for the next launch. 
 // Must be called by all 256 threads.
 //
 // Only the few 8-bin columns between the lowest occupied score and T matter for the per-chunk
@@ -39,28 +39,19 @@ struct ThresholdLds {
 // just those columns of every chunk row.
 struct Bins8 { uint32_t w[4]; };  // 8 uint16 counts
 
-template <bool COHERENT>
 __device__ __forceinline__ Bins8 load_bins8(const uint16_t* p) {
-    Bins8 r;
-    if constexpr (COHERENT) {
-        const uint2 a = ld_dev_u2(p), b = ld_dev_u2(p + 4);
-        r.w[0] = a.x; r.w[1] = a.y; r.w[2] = b.x; r.w[3] = b.y;
-    } else {
-        const uint4 v = *reinterpret_cast<const uint4*>(p);
-        r.w[0] = v.x; r.w[1] = v.y; r.w[2] = v.z; r.w[3] = v.w;
-    }
-    return r;
+    const uint2 a = ld_dev_u2(p), b = ld_dev_u2(p + 4);
+    return Bins8{{a.x, a.y, b.x, b.y}};
 }
 __device__ __forceinline__ uint32_t bin_of(const Bins8& v, int e) {
     const uint32_t w = v.w[e >> 1];
     return (e & 1) ? (w >> 16) : (w & 0xffffu);
 }
 
-template <int MAXSEG = 17>
 __device__ __forceinline__ void unit_threshold(
     const uint16_t* __restrict__ hp, uint32_t* __restrict__ unit_hist_u, int nc, int keff, int NB,
-    int NBP, int32_t* __restrict__ chunk_info_u, int32_t* __restrict__ unit_info_u, uint32_t* tot,
-    ThresholdLds& S, int spec_bmin) {
+    int NBP, int32_t* __restrict__ chunk_info_u, int32_t* __restrict__ unit_info_u, ThresholdLds& S) {
+    constexpr int MAXSEG = 17;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (tid == 0) { S.T = (keff > 0) ? NB : 0; S.need = 0; }
     for (int c = tid; c < nc; c += 256) { S.c_lt[c] = 0; S.c_eq[c] = 0; }
@@ -69,31 +60,12 @@ __device__ __forceinline__ void unit_threshold(
     const int seg = (NB + 255) / 256;
     const int s0 = tid * seg;
     uint32_t x[MAXSEG];
-    // Speculation (spec_bmin = lowest score of the caller's own chunk, or -1): the per-chunk counts
-    // below need columns [bmin / 8, T / 8] of every chunk row, which are only known after T -- a
-    // second dependent round trip.  T sits in the low tail, a few columns above the lowest score
-    // of any chunk, so SPEC_COLS columns starting a little below the caller's own lowest score are
-    // fetched together with the unit histogram and used if they turn out to cover the range
-    // (3 columns below: the unit's lowest score is a little lower than one chunk's).
-    constexpr int SPEC_COLS = 8, SPEC_IT = 4;
-    const bool spec = spec_bmin >= 0 && nc * SPEC_COLS <= 256 * SPEC_IT && NBP / 8 >= SPEC_COLS;
-    const int colA = spec ? min(max(spec_bmin / 8 - 3, 0), NBP / 8 - SPEC_COLS) : 0;
-    Bins8 sx[SPEC_IT];
     {
 #pragma unroll
         for (int j = 0; j < MAXSEG; ++j)  // clamped index: unconditional loads
             if (j < seg)
                 x[j] = __hip_atomic_load(unit_hist_u + min(s0 + j, NB - 1), __ATOMIC_RELAXED,
                                          __HIP_MEMORY_SCOPE_AGENT);
-        if (spec) {
-#pragma unroll
-            for (int j = 0; j < SPEC_IT; ++j) {
-                if (j * 256 < nc * SPEC_COLS) {
-                    const int i = min(tid + j * 256, nc * SPEC_COLS - 1);
-                    sx[j] = load_bins8<true>(hp + (int64_t)(i / SPEC_COLS) * NBP + (colA + i % SPEC_COLS) * 8);
-                }
-            }
-        }
 #pragma unroll
         for (int j = 0; j < MAXSEG; ++j) {
             if (j < seg && s0 + j < NB) {
@@ -150,18 +122,7 @@ __device__ __forceinline__ void unit_threshold(
         }
         if (lt) atomicAdd(&S.c_lt[c], lt);
     };
-    if (T < NB && spec && min(S.bmin, T) / 8 >= colA && T / 8 < colA + SPEC_COLS) {
-        // the speculative columns cover [bmin / 8, T / 8]: no second round trip
-        const int col0 = min(S.bmin, T) / 8, col1 = T / 8;
-#pragma unroll
-        for (int j = 0; j < SPEC_IT; ++j) {
-            const int i = tid + j * 256;
-            if (i < nc * SPEC_COLS) {
-                const int c = i / SPEC_COLS, col = colA + i % SPEC_COLS;
-                if (col >= col0 && col <= col1) count_item(sx[j], c, col);
-            }
-        }
-    } else if (T < NB) {
+    if (T < NB) {
         const int col0 = min(S.bmin, T) / 8;
         const int ncols = T / 8 - col0 + 1;
         const int items = nc * ncols;
@@ -171,7 +132,7 @@ __device__ __forceinline__ void unit_threshold(
             for (int j = 0; j < 4; ++j) {
                 const int i = min(i0 + j * 256, items - 1);
                 const int c = i / ncols, col = col0 + (i - c * ncols);
-                x[j] = load_bins8<true>(hp + (int64_t)c * NBP + col * 8);
+                x[j] = load_bins8(hp + (int64_t)c * NBP + col * 8);
             }
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
@@ -233,13 +194,12 @@ __device__ __forceinline__ void write_chunk_hist(uint16_t* hp, const uint32_t* h
     }
 }
 
-// Tail of a scoring workgroup in the fused step: publish the chunk histogram, count the unit's
-// finished chunks, and let the last one compute the unit's threshold.  `hist` (NB words of LDS)
-// is reused as the total histogram.  low: the chunk's lowest score, or -1 (unit_threshold's spec_bmin).
+// Tail of a histogram workgroup of the top-k: add the chunk's histogram (NB words of LDS) to the unit's total,
+// count the unit's finished chunks, and let the last one compute the unit's threshold.
 __device__ __forceinline__ void finish_unit(
     int64_t u, int nc, int keff, const uint16_t* __restrict__ chunk_hist_u, int NB, int NBP,
     int n_chunks, int32_t* __restrict__ chunk_info, int32_t* __restrict__ unit_info,
-    uint32_t* __restrict__ unit_counter, uint32_t* __restrict__ unit_hist, uint32_t* hist, int low,
+    uint32_t* __restrict__ unit_counter, uint32_t* __restrict__ unit_hist, const uint32_t* hist,
     ThresholdLds& S, int* flag) {
     HATA_TRACE_AT(2, u == 0);
     // add this chunk's histogram to the unit's total (only occupied bins)
@@ -263,7 +223,7 @@ __device__ __forceinline__ void finish_unit(
     HATA_TRACE_AT(5, u == 0);
     // the other workgroups' histograms are read with device-coherent loads
     unit_threshold(chunk_hist_u, unit_hist + u * NB, nc, keff, NB, NBP, chunk_info + u * (n_chunks + 1) * 2,
-                   unit_info + u * 2, hist, S, low);
+                   unit_info + u * 2, S);
     HATA_TRACE_AT(6, u == 0);
 }
 

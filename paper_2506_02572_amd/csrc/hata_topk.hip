@@ -11,8 +11,7 @@
 namespace hata {
 
 // grid = (n_chunks, Hkv, B), 256 threads: histogram of one chunk of stored scores; the last workgroup
-// of a unit to finish goes on to the unit's threshold and chunk offsets (finish_unit), as the scoring
-// kernel of the three-launch step does.
+// of a unit to finish goes on to the unit's threshold and chunk offsets (finish_unit).
 __global__ __launch_bounds__(256) void hist_kernel(
     const uint16_t* __restrict__ scores, const int32_t* __restrict__ seq_len,
     const int32_t* __restrict__ kbud, uint16_t* __restrict__ chunk_hist, int Hkv, int L_cap, int k_max,
@@ -44,7 +43,7 @@ __global__ __launch_bounds__(256) void hist_kernel(
     write_chunk_hist(chunk_hist + (u * n_chunks + c) * NBP, hist, NB, NBP);
     const int keff = min(clampi(kbud[b], 0, k_max), L);
     finish_unit(u, (L + chunk - 1) / chunk, keff, chunk_hist + u * n_chunks * NBP, NB, NBP, n_chunks, chunk_info,
-                unit_info, unit_counter, unit_hist, hist, -1, S, &last_flag);
+                unit_info, unit_counter, unit_hist, hist, S, &last_flag);
 }
 
 // grid = (n_chunks, Hkv, B), 256 threads: ordered compaction of one chunk into the index list.
