@@ -185,17 +185,19 @@ inline int coop_sub_batches(const hata_ctx* c, int B, bool paged, int* chunk_out
 }
 // Whether the step's own choice is a workgroup per unit.  Nothing waits in that form, so a shared device (step mode 3 unless the
 // caller asks for that) takes it too.  Beyond 4096 keys it needs many units, as a compute unit alone streams slowly, but not so
-// many that they go in several rounds.  us a layer, workgroups that share units / one per unit, r = 128, groups of four unless
-// noted: 64 units of 6000 keys 15.0 / 14.9; 128 of 8192 18.5 / 17.1 (r = 256 23.1 / 22.7, ragged 17.6 / 16.8, one head a unit
-// 14.6 / 12.9), of 16384 23.4 / 26.5; 256 of 16384 37.5 / 30.9 (r = 256 51.3 / 44.8); 512 of 8192 31.4 / 29.2, 1024 of 8192
-// 44.3 / 55.9.  On a shared device, three launches / one per unit: 8 units of 8192 keys 20.5 / 15.7 (r = 256 22.0 / 21.0), of
-// 12000 20.7 / 20.0 (22.3 / 24.7); 64 units of 12000 25.1 / 20.9 (27.7 / 26.1); 128 of 16384 31.3 / 26.6 (42.4 / 36.7).
+// many that they go in several rounds, unless a code is so wide (r = 256) that a unit's time is its stream.  us a layer,
+// workgroups that share units / one per unit, r = 128, groups of four unless noted: 64 units of 6000 keys 15.0 / 14.9; 128 of
+// 8192 18.5 / 17.1 (r = 256 23.1 / 22.7, ragged 17.6 / 16.8, one head a unit 14.6 / 12.9), of 16384 23.4 / 26.5; 256 of 16384
+// 37.5 / 30.9 (r = 256 51.3 / 44.8); 264 of 10000 30.6 / 37.5; 384 of 12000, one head a unit, 28.9 / 32.9; 512 of 8000, one
+// head a unit, 24.1 / 27.5; 448 of up to 12000 at r = 256, one head a unit, 40.0 / 37.1.  On a shared device, three launches /
+// one per unit: 8 units of 8192 keys 20.5 / 15.7 (r = 256 22.0 / 21.0), of 12000 20.7 / 20.0 (22.3 / 24.7); 64 units of 12000
+// 25.1 / 20.9 (27.7 / 26.1); 128 of 16384 31.3 / 26.6 (42.4 / 36.7).
 inline bool takes_unit_step(const hata_ctx* c, int B) {
     if (!c->unit_keys || (c->step_mode != 0 && c->mode_asked)) return false;
     const int64_t units = (int64_t)B * c->cfg.Hkv;
     if (c->cfg.L_cap <= HATA_UNIT_KEYS) return true;
     if (c->step_mode != 0) return c->cfg.L_cap <= 8192 || (c->cfg.L_cap <= 128 * units && units <= 512);
-    return c->cfg.L_cap <= 64 * units && units <= 512;
+    return c->cfg.L_cap <= 64 * units && units <= (c->Wd >= 8 ? 512 : 256);
 }
 inline bool aligned(const void* p, size_t a) { return ((uintptr_t)p % a) == 0; }
 
