@@ -244,7 +244,8 @@ int hata_dense_decode(hata_ctx* ctx, const void* q, const void* K, const void* V
  * hata_tuning.shared_device set (or call hata_set_step_mode(ctx, 3)), or watch hata_check().
  * Both forms select the same rows and agree on the output to rounding.  Either form may be
  * recorded into a HIP graph and replayed (no memset nodes, no host-side state a replay depends
- * on: the single-launch kernel retires the words its workgroups publish before it ends);
+ * on: what the workgroups of a unit publish carries the number of the unit's launch, counted in the workspace, so
+ * that nothing an earlier launch or replay left there, not even one that gave up, is taken for a later one's);
  * hata_check() is a synchronising call and stays outside the capture. */
 int hata_decode_step(hata_ctx* ctx, const void* q, const void* K, const void* V, const float* W_H,
                      uint32_t* codes, const int32_t* seq_len, const int32_t* k, int32_t B,

@@ -289,7 +289,6 @@ int hata_create_tuned(hata_ctx** ctx_out, const hata_config* cfg, const hata_tun
     c->unit_epoch = (uint32_t*)(w + p.off_epoch);
     c->coop_qrec = (unsigned long long*)(w + p.off_qrec);
     c->error_word = (uint32_t*)(w + p.off_err);
-    c->epoch = 0;
     c->coop_opts = 0;
     c->partials = (float*)(w + p.off_partials);
     c->wplanes = (f_has_mfma_width(cfg->r)) ? (void*)(w + p.off_wplanes) : nullptr;

@@ -67,9 +67,9 @@ struct CoopArgs {
     int32_t* idx;
     unsigned long long* cum;  // [units, cum_pitch], a chunk's row NBP / 2 words: cumulative chunk histograms, two scores and the unit's epoch a word
     int cum_marks, mark_pitch;  // where a unit's marks begin, a row of them per reading chunk: the epoch too, stored behind a chunk's row for every other chunk (they tell when to look)
-    int cum_pitch;            // (the same for every chunk size: what a unit's words hold was stamped with that unit's epoch)
     uint32_t* unit_epoch;
-    unsigned long long* qrec;
+    unsigned long long* qrec;   // [units, qrec_pitch], a chunk's copy G * WD words: the unit's query code words, its epoch in the upper half
+    int cum_pitch, qrec_pitch;  // (the same for every chunk size: what a unit's words hold was stamped with that unit's epoch)
     uint32_t* attn_counter;
     uint32_t* error_word;
     float* partials;
@@ -78,7 +78,6 @@ struct CoopArgs {
     int Hq, Hkv, L_cap, k_max, chunk, n_chunks, NBP, units;
     int64_t sb, sh, sn;
     float scale_log2;
-    uint32_t epoch;
     int append;
     int chunk_shift;  // chunk = 1 << chunk_shift
     Divisor by_groups, by_chunks, by_heads;  // units / 8, n_chunks, Hkv
@@ -332,9 +331,14 @@ void decode_step_coop_kernel(const CoopArgs a) {
         nblk = min(((base + a.chunk - 1) >> a.pv.shift) + 1, a.pv.max_blocks) - blk0;
         if (threadIdx.x < nblk) my_page = a.pv.table[(int64_t)b * a.pv.max_blocks + blk0 + threadIdx.x];
     }
-    // this launch's number in the unit's count of launches (0 is the cleared state of the published words); the second
-    // word names a launch that chunk 0 gave up before all had read it: such a latecomer would take the next launch's number
-    const uint2 launches = ld_dev_u2(a.unit_epoch + u * HATA_COUNTER_STRIDE);
+    // The unit's count of launches in device memory (a replay of a captured HIP graph, which freezes kernel arguments, has a
+    // number of its own too), and a flag: the last one was given up by chunk 0, which had to count it although a
+    // workgroup may not have read the count yet.  (What the launch before left, or what chunk 0 of this one has
+    // made of that; either will do, so where the weights are on their way already an ordinary scalar load beside the
+    // sequence length's: a device-scope load comes back behind the weights, 0.3 to 2 % of a step.  At r = 256 the weights would
+    // wait for the scalar one: 1 to 2 % too.)
+    const uint32_t* const launches_at = a.unit_epoch + u * HATA_COUNTER_STRIDE;
+    const uint2 launches = EARLY ? *reinterpret_cast<const uint2*>(launches_at) : ld_dev_u2(launches_at);
     const int L = clampi(a.seq_len[b], 0, PAGED ? min(a.L_cap, a.pv.max_blocks << a.pv.shift) : a.L_cap);
     // Row n of the unit (a row of this chunk when PAGED) -> its row in the code array, in rows of
     // one (sequence or page, head): the contiguous cache is [B, Hkv, L_cap], the pools are
@@ -356,6 +360,31 @@ void decode_step_coop_kernel(const CoopArgs a) {
 #define TU(i) HATA_TRACE_AT(i, true)
     TC(40);
     const int end = min(base + a.chunk, L);
+    // This launch's number among the unit's, never 0 (the cleared state of the published words).  Everything that workgroups
+    // hand to each other carries it, so what an earlier launch left behind, whole or given up half-way, is nobody's.
+    // After a launch that was given up: its own latecomers and all workgroups of the next one read the same count and flag.  Only chunk 0
+    // can tell -- it wrote the flag at the end of its work, so where it finds the flag at the start, the launch is another one -- and
+    // takes the flag back; the others wait for that, and a latecomer, for whom nobody does it, gives up and publishes nothing.
+    // (The same in all lanes of a wave.  A wave that reads late finds the flag gone and the same count.)
+    uint32_t epoch = 0;
+    bool late = false;
+    auto number_launch = [&]() {  // (behind the encoding's first loads: the count is on its way meanwhile)
+        if (epoch != 0) return;
+        epoch = max((uint32_t)__builtin_amdgcn_readfirstlane((int)launches.x) + 1u, 1u);
+        if (__builtin_amdgcn_readfirstlane((int)launches.y) != 0) {
+            uint32_t* const at = a.unit_epoch + u * HATA_COUNTER_STRIDE;
+            if (c == 0) {
+                if (tid == 0) st_dev(reinterpret_cast<unsigned long long*>(at), (unsigned long long)launches.x);
+            } else {
+                int budget = a.spin_limit;
+                while (__builtin_amdgcn_readfirstlane((int)ld_dev_u2(at).y) != 0) {
+                    if (--budget <= 0) { late = true; break; }
+                    __builtin_amdgcn_s_sleep(1);
+                }
+                if (late && (tid & 63) == 0) { a.error_word[0] = 1u; s_bad = 1; }
+            }
+        }
+    };
     // ---- 0. HashEncode(Q) and HashEncode(K_new).  The G query vectors of the unit are dealt out
     // to its nc workgroups (vector v to chunk v mod nc), each published as epoch-stamped words
     // that every workgroup of the unit then picks up; the workgroup whose chunk holds the
@@ -389,8 +418,8 @@ void decode_step_coop_kernel(const CoopArgs a) {
     };
     {
         // every chunk of the unit has its own copy of the G * WD published words (the encoders write
-        // all copies, a workgroup polls -- and afterwards clears -- only its own)
-        unsigned long long* qrec_u = a.qrec + u * a.n_chunks * (G * WD);
+        // all copies, a workgroup polls only its own)
+        unsigned long long* qrec_u = a.qrec + u * a.qrec_pitch;
         unsigned long long* qrec = qrec_u + c * (G * WD);
         if (tid < (G + 1) * WD) s_codes[tid] = 0;
         if (tid == 0) { s_bad = 0; s_miss = 0; s_quit = 0; s_est = 0; s_Tc = -1; s_ncand = 0; }
@@ -404,10 +433,10 @@ void decode_step_coop_kernel(const CoopArgs a) {
         __syncthreads();
         auto publish = [&](int v) {
             __syncthreads();
-            for (int i = tid; i < WD * max(nc, 1); i += 256)
-                __hip_atomic_store(qrec_u + (i / WD) * (G * WD) + v * WD + i % WD,
-                                   ((unsigned long long)a.epoch << 32) | s_codes[v * WD + i % WD],
-                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            number_launch();
+            if (!late)
+                for (int i = tid; i < WD * max(nc, 1); i += 256)
+                    st_dev(qrec_u + (i / WD) * (G * WD) + v * WD + i % WD, ((unsigned long long)epoch << 32) | s_codes[v * WD + i % WD]);
         };
         const uint16_t* kx = !own ? nullptr
                              : PAGED ? a.K + cache_row(L - 1) * HATA_D
@@ -457,29 +486,31 @@ void decode_step_coop_kernel(const CoopArgs a) {
             __builtin_amdgcn_sched_barrier(0);
             load_codes(base + tid, end_main);
         }
+        number_launch();
         if (tid < 64) {  // one wave collects the G * WD (<= 64) query code words of the unit
             const int i = min(tid, G * WD - 1);
             int budget = a.spin_limit;
             unsigned long long r;
             for (;;) {
                 r = __hip_atomic_load(qrec + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                const bool miss = (uint32_t)(r >> 32) != a.epoch;
+                const bool miss = (uint32_t)(r >> 32) != epoch;
                 if (__builtin_amdgcn_ballot_w64(miss) == 0ull) break;
                 if (--budget <= 0) { if (tid == 0) { a.error_word[0] = 1u; s_bad = 1; } break; }  // gave up: results invalid
                 __builtin_amdgcn_s_sleep(1);
             }
-            if (tid < G * WD) {
-                s_codes[tid] = (uint32_t)r;
-                // retired at once: a later launch that carries the SAME epoch (a replay of a captured
-                // HIP graph freezes the kernel arguments) must not mistake these words for its own
-                qrec[tid] = 0ull;
-            }
+            if (tid < G * WD) s_codes[tid] = (uint32_t)r;
         }
         __syncthreads();
     }
     if (c == 0)
         for (int i = tid; i < G * WD; i += 256) a.qcodes[((int64_t)b * a.Hq + hq0) * WD + i] = s_codes[i];
     if (own && tid < WD) a.codes[cache_row(L - 1) * WD + tid] = s_codes[G * WD + tid];
+    // chunk 0 counts this launch (where the unit has other chunks, once it knows that they have read the count)
+    auto count_launch = [&](bool given_up) {
+        if (c == 0 && tid == 0)
+            st_dev(reinterpret_cast<unsigned long long*>(a.unit_epoch + u * HATA_COUNTER_STRIDE), ((unsigned long long)(given_up ? 1u : 0u) << 32) | epoch);
+    };
+    if (nc <= 1) count_launch(false);
     if (base >= L) {  // empty sequence: nothing selected, zero output
         for (int i = tid; i < (a.select_only ? 0 : G * HATA_D); i += 256) {
             outp[i] = 0;
@@ -547,11 +578,7 @@ void decode_step_coop_kernel(const CoopArgs a) {
     // threshold -- those of all chunks, and those of the chunks before its own -- which gives it the threshold
     // and its own place in the index list without a further exchange.  A published word holds two counts and the unit's
     // epoch, so the words themselves tell when they are there: no arrival counter, no wait for the stores.
-    // The epoch counts the unit's launches in device memory, so that a replay of a captured HIP graph, which
-    // freezes kernel arguments, has one of its own too; chunk 0 moves it on once it has seen every chunk's words (all
-    // have read it by then).
     const int n_keys = end - base;
-    const uint32_t epoch = max((uint32_t)__builtin_amdgcn_readfirstlane((int)launches.x) + 1u, 1u);
     // Where a thread has more than four scores its own words are 32 to 96 bytes from its neighbour's, and each store of a
     // wave writes parts of as many lines as it has lanes, through to memory: such rows (4 to 16 KB) are written from LDS, consecutive
     // lanes consecutive words, behind a barrier (group of eight, 8 layers of 32768 keys at r = 256 164 -> 151 us, 2 layers of
@@ -559,7 +586,7 @@ void decode_step_coop_kernel(const CoopArgs a) {
     // their own, two layers: 29.9 us, 30.1 from LDS).
     constexpr bool WIDE = NB > 1024;
     unsigned long long* const cum_row = a.cum + u * a.cum_pitch + c * (a.NBP / 2);
-    const bool publishes = nc > 1 && (uint32_t)__builtin_amdgcn_readfirstlane((int)launches.y) != a.epoch;
+    const bool publishes = nc > 1 && !late;
     {
         constexpr int SEG = ((NB + 255) / 256 + 3) / 4 * 4;  // consecutive scores of a thread
         // keys of this chunk if the unit's selection were spread evenly over its chunks
@@ -826,8 +853,7 @@ void decode_step_coop_kernel(const CoopArgs a) {
         TC(51);
         off = clampi(off, 0, a.k_max);
         cnt = clampi(cnt, 0, min(n_keys, a.k_max - off));
-        if (c == 0 && tid == 0)
-            st_dev(reinterpret_cast<unsigned long long*>(a.unit_epoch + u * HATA_COUNTER_STRIDE), ((unsigned long long)(s_bad ? a.epoch : 0u) << 32) | epoch);
+        count_launch(s_quit != 0);
     }
 
     // ---- 3. ordered compaction of the own chunk from the LDS scores
@@ -1161,7 +1187,7 @@ int coop_capacity(const hata_ctx* c, bool paged, int chunk) {
     return per_cu * c->cus;
 }
 
-hipError_t launch_coop_step(hata_ctx* c, const void* q, const void* K, const void* V,
+hipError_t launch_coop_step(const hata_ctx* c, const void* q, const void* K, const void* V,
                             const float* W_H, uint32_t* codes, int append, const int32_t* seq_len,
                             const int32_t* k, int B, float sm_scale, void* out, float* out_f32, hipStream_t s,
                             int chunk, const PageView* pages, int b0, int32_t* idx_only) {
@@ -1202,11 +1228,12 @@ hipError_t launch_coop_step(hata_ctx* c, const void* q, const void* K, const voi
     a.qcodes = c->qcodes + (int64_t)b0 * f.Hq * c->Wd; a.codes = codes; a.seq_len = seq_len; a.kbud = k;
     a.scores = c->scores + u0 * f.L_cap; a.idx = (idx_only ? idx_only : c->idx) + u0 * f.k_max;
     a.cum_pitch = coop_cum_pitch(c->n_chunks, c->NBP);
+    a.qrec_pitch = c->n_chunks * c->G * c->Wd;
     a.cum_marks = c->n_chunks * (c->NBP / 2);
     a.mark_pitch = coop_mark_pitch(c->n_chunks);
     a.cum = c->coop_cum + u0 * a.cum_pitch;
     a.unit_epoch = c->unit_epoch + u0 * HATA_COUNTER_STRIDE;
-    a.qrec = c->coop_qrec + u0 * n_chunks * c->G * c->Wd;
+    a.qrec = c->coop_qrec + u0 * a.qrec_pitch;
     a.attn_counter = c->attn_counter + u0 * HATA_COUNTER_STRIDE;
     a.error_word = c->error_word;
     a.partials = c->partials + (int64_t)b0 * f.Hq * n_chunks * HATA_PSTRIDE;
@@ -1217,9 +1244,6 @@ hipError_t launch_coop_step(hata_ctx* c, const void* q, const void* K, const voi
     a.by_groups = make_divisor(a.units >= 8 ? a.units / 8 : 1); a.by_chunks = make_divisor(n_chunks); a.by_heads = make_divisor(f.Hkv);
     a.sb = f.kv_stride_b; a.sh = f.kv_stride_h; a.sn = f.kv_stride_n;
     a.scale_log2 = sm_scale * 1.4426950408889634f;
-    c->epoch += 1;
-    if (c->epoch == 0) c->epoch = 1;  // 0 is the cleared state of the flags
-    a.epoch = c->epoch;
     void* args[] = {(void*)&a};
     return hipLaunchKernel(fn, dim3((unsigned)(n_chunks * f.Hkv * B)), dim3(256), args, coop_dynamic_lds(c, chunk), s);
 }

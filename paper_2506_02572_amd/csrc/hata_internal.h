@@ -40,11 +40,10 @@ struct hata_ctx {
     uint32_t* unit_hist;     // [B_max*Hkv, NB] total histogram of a unit (self-clearing)
     uint32_t* attn_counter;  // [B_max*Hq (cooperative step: per unit), attn_counter_stride] finished attention slices (self-resetting)
     int attn_counter_stride; // HATA_COUNTER_STRIDE; 1 in the static scratch of hata_sparse_decode_static
-    unsigned long long* coop_cum;  // [B_max*Hkv, coop_cum_pitch()] epoch-stamped cumulative chunk histograms, two scores a word, and marks (cooperative step)
-    uint32_t* unit_epoch;          // [B_max*Hkv, HATA_COUNTER_STRIDE] launches of the cooperative step on a unit, and the last one given up
-    unsigned long long* coop_qrec; // [B_max*Hkv, n_chunks, G*Wd] epoch-stamped query code words, one copy per chunk (cooperative step)
+    unsigned long long* coop_cum;  // [B_max*Hkv, coop_cum_pitch()] cumulative chunk histograms, two scores and the unit's launch a word, and marks (cooperative step)
+    uint32_t* unit_epoch;          // [B_max*Hkv, HATA_COUNTER_STRIDE] launches of the cooperative step on a unit, and whether chunk 0 gave the last one up
+    unsigned long long* coop_qrec; // [B_max*Hkv, n_chunks, G*Wd] query code words, one copy per chunk, stamped with the unit's launch (cooperative step)
     uint32_t* error_word;    // [1] set by a cooperative launch that gave up waiting
-    uint32_t epoch;          // launch counter of the cooperative step
     int spin_limit;          // polls an in-kernel wait makes before it gives up (0 = the default)
     int keep_scores;         // single-launch step also writes the score array
     int par_merge;           // single-launch step merges the heads of a unit in several workgroups
@@ -105,7 +104,7 @@ hipError_t launch_gather_rows(const hata_ctx* c, const void* K, const void* V, c
 
 // encode + score + select + attend in one cooperative launch; returns hipErrorNotSupported if
 // this shape has no cooperative kernel
-hipError_t launch_coop_step(hata_ctx* c, const void* q, const void* K, const void* V,
+hipError_t launch_coop_step(const hata_ctx* c, const void* q, const void* K, const void* V,
                             const float* W_H, uint32_t* codes, int append, const int32_t* seq_len,
                             const int32_t* k, int B, float sm_scale, void* out, float* out_f32, hipStream_t s,
                             int chunk, const PageView* pages = nullptr, int b0 = 0, int32_t* idx_only = nullptr);

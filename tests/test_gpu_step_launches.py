@@ -1,0 +1,126 @@
+"""What the single-launch step keeps between launches: after one that gave up a wait, and between captured and eager ones."""
+import ctypes
+import math
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+from oracle import hata_oracle as O
+from paper_2506_02572_amd import synth
+from tests import harness as H
+
+SCALE = 1.0 / math.sqrt(128)
+
+
+def make_case(r, heads, seq, k_max):
+    (Hq, Hkv), B, L = heads, len(seq), max(seq)
+    rng = np.random.default_rng(L + r)
+    seq, k = np.array(seq, np.int32), np.array([max(1, k_max >> b) for b in range(B)], np.int32)
+    K, V = (synth.round_to_bf16_bits(rng.standard_normal((B, Hkv, L, 128))) for _ in range(2))
+    W = rng.standard_normal((Hkv, 128, r)).astype(np.float32)
+    codes = rng.integers(0, 2**32, (B, Hkv, L, r // 32), dtype=np.uint32)
+    queries = [synth.round_to_bf16_bits(rng.standard_normal((B, Hq, 128))) for _ in range(4)]
+    refs = [O.decode_step(q, K, V, W, codes.copy(), seq, k, k_max, SCALE, append=False) for q in queries]
+    return seq, k, K, V, W, codes, queries, refs
+
+
+@pytest.mark.parametrize("r,heads,seq,k_max,chunk", [(128, (8, 2), (9000, 5000, 1000), 200, 1024), (256, (8, 1), (70000, 3000), 500, 1024),
+                                                     (64, (16, 2), (30000, 9000), 90, 1024), (128, (16, 4), (40000, 17000), 300, 16384)])
+def test_step_after_one_that_gave_up(r, heads, seq, k_max, chunk):
+    """No call of hata_check between them.  Two contexts over one workspace, so that host-side counts are the same in both
+    launches, as in replays of one graph: the second launch is right, with queries of its own."""
+    import torch
+    from paper_2506_02572_amd import hata
+    print(f"[launches] r={r} heads={heads} seq={seq} chunk={chunk}", flush=True)
+    (Hq, Hkv), B, L = heads, len(seq), max(seq)
+    seq, k, K, V, W, codes, queries, refs = make_case(r, heads, seq, k_max)
+    Kd, Vd, Wd, cd, sd, kd = (H.to_dev(x) for x in (K, V, W, codes, seq, k))
+    out = torch.zeros((B, Hq, 128), dtype=torch.int16, device="cuda")
+    out32 = torch.zeros((B, Hq, 128), dtype=torch.float32, device="cuda")
+    for turn in range(4):
+        ctx = hata.Context(B, Hq, Hkv, 128, r, L, k_max, chunk=chunk)
+        second = ctypes.c_void_p(None)
+        rc = ctx._lib.hata_create_tuned(ctypes.byref(second), ctypes.byref(ctx.cfg), ctypes.byref(ctx.tuning),
+                                        ctypes.c_void_p(ctx._ws_ptr), ctx.workspace_bytes)
+        assert rc == 0 and ctx.hata_step_plan(B)[:2] == (1, chunk)
+        first = ctx._h
+        ctx.hata_set_wait_limit(1)
+        for _ in range(1 + turn // 2):
+            ctx.hata_decode_step(H.to_dev(queries[turn]), Kd, Vd, Wd, cd, sd, kd, B, False, SCALE, out, out32)
+        assert np.any(np.isnan(H.to_host(out32))), "a wait bound of one poll was expected to be given up"
+        ctx._h = second
+        try:
+            if turn % 2:  # the selection alone first
+                idx = torch.zeros((B, Hkv, k_max), dtype=torch.int32, device="cuda")
+                ctx.hata_select_step(H.to_dev(queries[3 - turn]), None, Wd, cd, sd, kd, B, False, idx)
+                assert np.array_equal(H.to_host(idx), refs[3 - turn]["idx"])
+            for j in (1, 2):
+                n = (turn + j) % 4
+                ctx.hata_decode_step(H.to_dev(queries[n]), Kd, Vd, Wd, cd, sd, kd, B, False, SCALE, out, out32)
+                torch.cuda.synchronize()
+                assert np.array_equal(H.to_host(ctx.hata_step_buffers()[2]), refs[n]["idx"])
+                H.check_attention(H.to_host(out32), H.to_host(out, np.uint16), refs[n]["out"], "behind a give-up")
+            with pytest.raises(hata.HataError, match="gave up"):
+                ctx.hata_check()
+        finally:
+            ctx._lib.hata_destroy(first)
+            ctx.close()
+
+
+def test_replays_beside_eager_steps_of_other_batches():
+    """A graph of a step for two of three sequences, replayed between eager steps of one, two and three sequences and one that
+    gives up: units that sit launches out keep a count of their own."""
+    import torch
+    from paper_2506_02572_amd import hata
+    r, heads, k_max, chunk, B = 128, (8, 2), 150, 1024, 3
+    seq, k, K, V, W, codes, queries, refs = make_case(r, heads, (9000, 7000, 3000), k_max)
+    ctx = hata.Context(B, heads[0], heads[1], 128, r, int(seq.max()), k_max, chunk=chunk)
+    Kd, Vd, Wd, cd, sd, kd = (H.to_dev(x) for x in (K, V, W, codes, seq, k))
+    qd = H.to_dev(queries[0])
+    out = torch.zeros((B, heads[0], 128), dtype=torch.int16, device="cuda")
+    out32 = torch.zeros((B, heads[0], 128), dtype=torch.float32, device="cuda")
+
+    def step(n):
+        ctx.hata_decode_step(qd, Kd, Vd, Wd, cd, sd, kd, n, False, SCALE, out, out32)
+
+    def check(n, query):
+        torch.cuda.synchronize()
+        assert np.array_equal(H.to_host(ctx.hata_step_buffers()[2])[:n], refs[query]["idx"][:n])
+        H.check_attention(H.to_host(out32)[:n], H.to_host(out, np.uint16)[:n], refs[query]["out"][:n], "replay")
+
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        step(2)
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        step(2)
+    for turn, (eager, gives_up) in enumerate([(3, False), (1, False), (3, True), (2, True), (1, True), (3, False)]):
+        query = turn % 4
+        qd.copy_(H.to_dev(queries[query]))
+        torch.cuda.synchronize()
+        ctx.hata_set_wait_limit(1 if gives_up else 0)
+        step(eager)
+        if not gives_up:
+            check(eager, query)
+        ctx.hata_set_wait_limit(0)
+        for again in (1, 2):
+            query = (turn + again) % 4
+            qd.copy_(H.to_dev(queries[query]))
+            torch.cuda.synchronize()
+            out32.fill_(7.0)
+            g.replay()
+            check(2, query)
+            assert torch.all(out32[2] == 7.0)
+    step(3)
+    check(3, query)
+    with pytest.raises(hata.HataError, match="gave up"):
+        ctx.hata_check()
+    step(3)
+    check(3, query)
+    ctx.hata_check()
+    ctx.close()
