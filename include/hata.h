@@ -323,10 +323,11 @@ int hata_step_sub_batches(const hata_ctx* ctx, int32_t B, int32_t* n_sub);
  * mode 3: always the three-launch form (no in-kernel waits). */
 int hata_set_step_mode(hata_ctx* ctx, int32_t mode);
 
-/* The Hamming scores of a step are an intermediate: the single-launch form keeps them on chip and
- * writes the score region of the workspace only if asked to (keep != 0; default off, which saves
- * 2 bytes of HBM writes per cached key).  The three-launch form always writes it (its second
- * launch reads it back). */
+/* The Hamming scores of a step are an intermediate: the single-launch forms keep them on chip and
+ * write the score region of the workspace only if asked to (keep != 0; default off, which saves
+ * 2 bytes of HBM writes per cached key).  The three-launch form always writes it (its last
+ * launch reads it back), and so does every hata_decode_step of a context made for a shared device, whatever
+ * form it takes (unless hata_set_step_mode asked for mode 0 or 1). */
 int hata_keep_step_scores(hata_ctx* ctx, int32_t keep);
 
 /* Bound of every in-kernel wait of the single-launch form, in polls (0 restores the default, 2^18:

@@ -90,3 +90,34 @@ def test_unit_step_of_many_units(units, L_cap, page_rows):
     assert np.array_equal(got[0][0], got[1][0])
     # (fp32 sums in another order, weights of 16 bits or more: hata_attn_core.h)
     assert torch.allclose(got[0][1], got[1][1], rtol=1e-3, atol=1e-4)
+
+
+@pytest.mark.parametrize("L_cap", [700, 5000])
+def test_scores_of_a_shared_device(L_cap):
+    """A context of a shared device leaves the scores in the workspace without being asked, whatever form its steps take."""
+    import torch
+    from paper_2506_02572_amd import hata
+    B, Hq, Hkv, r, k_max = 2, 4, 1, 64, 40
+    print(f"[unit] scores of a shared device, L_cap={L_cap}", flush=True)
+    rng = np.random.default_rng(L_cap)
+    seq, k = np.array([L_cap, L_cap // 2], np.int32), np.array([k_max, 9], np.int32)
+    K, V = (synth.round_to_bf16_bits(rng.standard_normal((B, Hkv, L_cap, 128))) for _ in range(2))
+    q = synth.round_to_bf16_bits(rng.standard_normal((B, Hq, 128)))
+    W = rng.standard_normal((Hkv, 128, r)).astype(np.float32)
+    codes = rng.integers(0, 2**32, (B, Hkv, L_cap, r // 32), dtype=np.uint32)
+    ref = O.decode_step(q, K, V, W, codes.copy(), seq, k, k_max, SCALE, append=False)
+    out = torch.zeros((B, Hq, 128), dtype=torch.int16, device="cuda")
+    dev = [H.to_dev(x) for x in (q, K, V, W, codes, seq, k)]
+    for launches in (1, 3):
+        ctx = hata.Context(B, Hq, Hkv, 128, r, L_cap, k_max, shared_device=True)
+        if launches == 3:
+            ctx.hata_set_step_mode(3)
+        assert ctx.hata_step_plan(B)[0] == launches
+        scores = ctx.hata_step_buffers()[1]
+        scores.fill_(-1)
+        ctx.hata_decode_step(*dev, B, False, SCALE, out)
+        torch.cuda.synchronize()
+        for b in range(B):
+            assert np.array_equal(H.to_host(scores, np.uint16)[b, :, :seq[b]].astype(np.int32), ref["scores"][b, :, :seq[b]])
+            assert np.all(H.to_host(scores, np.uint16)[b, :, seq[b]:] == 0xffff)
+        ctx.close()
