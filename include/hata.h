@@ -280,8 +280,9 @@ int hata_select_step(hata_ctx* ctx, const void* q, const void* K, const float* W
  * may share pages for reading; the page that holds an appended row must belong to one sequence.
  *
  * hata_decode_step_paged: hata_decode_step on that layout, same outputs (Idx holds LOGICAL row
- * numbers).  It exists in the single-launch form only: HATA_EUNSUPPORTED when the shape does not
- * fit it (see hata_decode_step; hata_set_step_mode does not apply).
+ * numbers).  It exists in the single-launch forms only -- a workgroup per unit under the same rule, which for
+ * a shared device is that of hata_tuning.shared_device, else the form with in-kernel waits -- and hata_set_step_mode
+ * does not apply to it.  HATA_EUNSUPPORTED when the shape does not fit the form with waits (see hata_decode_step).
  */
 int hata_decode_step_paged(hata_ctx* ctx, const void* q, const void* K_pool, const void* V_pool,
                            const float* W_H, uint32_t* codes_pool, const int32_t* block_table,

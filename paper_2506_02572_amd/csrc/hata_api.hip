@@ -206,11 +206,13 @@ inline int coop_sub_batches(const hata_ctx* c, int B, bool paged, int* chunk_out
 // head a unit, 24.1 / 27.5; 448 of up to 12000 at r = 256, one head a unit, 40.0 / 37.1.  On a shared device, three launches /
 // one per unit: 8 units of 8192 keys 20.5 / 15.7 (r = 256 22.0 / 21.0), of 12000 20.7 / 20.0 (22.3 / 24.7); 64 units of 12000
 // 25.1 / 20.9 (27.7 / 26.1); 128 of 16384 31.3 / 26.6 (42.4 / 36.7).
-inline bool takes_unit_step(const hata_ctx* c, int B) {
-    if (!c->unit_keys || (c->step_mode != 0 && c->mode_asked)) return false;
+inline bool takes_unit_step(const hata_ctx* c, int B, bool paged = false) {
+    // (the block-table step knows no modes: what a caller set for the other layout changes nothing)
+    if (!c->unit_keys || (!paged && c->step_mode != 0 && c->mode_asked)) return false;
+    const bool shared = paged ? c->shared != 0 : c->step_mode != 0;
     const int64_t units = (int64_t)B * c->cfg.Hkv;
     if (c->cfg.L_cap <= HATA_UNIT_KEYS) return true;
-    if (c->step_mode != 0) return c->cfg.L_cap <= 8192 || (c->cfg.L_cap <= 128 * units && units <= 512);
+    if (shared) return c->cfg.L_cap <= 8192 || (c->cfg.L_cap <= 128 * units && units <= 512);
     return c->cfg.L_cap <= 64 * units && units <= (c->Wd >= 8 ? 512 : 256);
 }
 inline bool aligned(const void* p, size_t a) { return ((uintptr_t)p % a) == 0; }
@@ -326,7 +328,8 @@ int hata_create_tuned(hata_ctx** ctx_out, const hata_config* cfg, const hata_tun
         c->coop_opt_cap_paged[o] = hata::coop_capacity(c, true, c->coop_opt_chunk[o]);
     }
     // a device shared with other work cannot promise that a whole grid is resident: three launches
-    c->step_mode = (tuning && tuning->shared_device) ? 3 : 0;
+    c->shared = tuning && tuning->shared_device;
+    c->step_mode = c->shared ? 3 : 0;
     c->mode_asked = 0;
     if (hata::prepare_unit_step(c) != hipSuccess) {
         delete c;
@@ -604,7 +607,7 @@ int hata_decode_step_paged(hata_ctx* ctx, const void* q, const void* K_pool, con
     const int ns = coop_sub_batches(ctx, B, true, &step_chunk);
     ctx->step_mode = mode;
     if (ns == 0) return HATA_EUNSUPPORTED;
-    if (takes_unit_step(ctx, B))
+    if (takes_unit_step(ctx, B, true))
         return hip_rc(hata::launch_unit_step(ctx, q, K_pool, V_pool, W_H, codes_pool, append, seq_len, k, B, sm_scale, out, out_f32,
                                              (hipStream_t)stream, &pv));
     hipError_t e = hipSuccess;

@@ -49,6 +49,7 @@ struct hata_ctx {
     int par_merge;           // single-launch step merges the heads of a unit in several workgroups
     int step_mode;           // 0 = single launch when it fits, 3 = always three launches
     int unit_keys;           // keys a workgroup per unit handles (0: that form is not available, or the caller asked for a launch shape)
+    int shared;              // hata_tuning.shared_device
     int mode_asked;          // step_mode was set by the caller (and is not just that of a shared device)
     int cus;                 // compute units of the device that was current in hata_create
     int coop_opt_cap_paged[4];  // the same for the block-table variant of the kernel

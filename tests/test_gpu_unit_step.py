@@ -121,3 +121,38 @@ def test_scores_of_a_shared_device(L_cap):
             assert np.array_equal(H.to_host(scores, np.uint16)[b, :, :seq[b]].astype(np.int32), ref["scores"][b, :, :seq[b]])
             assert np.all(H.to_host(scores, np.uint16)[b, :, seq[b]:] == 0xffff)
         ctx.close()
+
+
+@pytest.mark.parametrize("mode", [0, 1, 3])
+@pytest.mark.parametrize("L_cap", [3000, 7000])
+def test_paged_step_knows_no_modes(mode, L_cap):
+    """The block-table step of a short cache takes a workgroup per unit, whatever mode the other layout was given: nothing in
+    it waits, so one poll is enough (the form with waits would give up)."""
+    import torch
+    from paper_2506_02572_amd import hata
+    B, Hq, Hkv, r, k_max, page_rows = 2, 8, 2, 128, 96, 64
+    print(f"[unit] paged, mode={mode} L_cap={L_cap}", flush=True)
+    rng = np.random.default_rng(L_cap)
+    seq, k = np.array([L_cap, L_cap - 100], np.int32), np.array([k_max, 50], np.int32)
+    K, V = (synth.round_to_bf16_bits(rng.standard_normal((B, Hkv, L_cap, 128))) for _ in range(2))
+    q = synth.round_to_bf16_bits(rng.standard_normal((B, Hq, 128)))
+    W = rng.standard_normal((Hkv, 128, r)).astype(np.float32)
+    codes = rng.integers(0, 2**32, (B, Hkv, L_cap, r // 32), dtype=np.uint32)
+    ref = O.decode_step(q, K, V, W, codes.copy(), seq, k, k_max, SCALE, append=False)
+    table, max_blocks, n_pages, blocks = make_table(rng, seq, page_rows)
+    pools = []
+    for x in (K, V, codes):
+        pool = np.zeros((n_pages, Hkv, page_rows, x.shape[-1]), x.dtype)
+        scatter(pool, x, table, blocks, page_rows, seq)
+        pools.append(H.to_dev(pool))
+    ctx = hata.Context(B, Hq, Hkv, 128, r, L_cap, k_max, shared_device=True)
+    ctx.hata_set_step_mode(mode)
+    ctx.hata_set_wait_limit(1)
+    out = torch.zeros((B, Hq, 128), dtype=torch.int16, device="cuda")
+    out32 = torch.zeros((B, Hq, 128), dtype=torch.float32, device="cuda")
+    ctx.hata_decode_step_paged(H.to_dev(q), pools[0], pools[1], H.to_dev(W), pools[2], H.to_dev(table), max_blocks, page_rows,
+                               n_pages, H.to_dev(seq), H.to_dev(k), B, False, SCALE, out, out32)
+    ctx.hata_check()
+    assert np.array_equal(H.to_host(ctx.hata_step_buffers()[2]), ref["idx"])
+    H.check_attention(H.to_host(out32), H.to_host(out, np.uint16), ref["out"], "paged unit step")
+    ctx.close()
