@@ -162,7 +162,6 @@ inline int coop_sub_batches(const hata_ctx* c, int B, bool paged, int* chunk_out
     // the oversubscribed grid of mode 1 uses the first size only
     const int n_opts = c->step_mode == 1 ? 1 : c->coop_opts;
     int best = 0, best_chunk = 0;
-    bool best_fits_well = false;
     for (int o = 0; o < n_opts; ++o) {
         const int chunk = c->coop_opt_chunk[o];
         const int n_chunks = (c->cfg.L_cap + chunk - 1) / chunk;
@@ -179,20 +178,13 @@ inline int coop_sub_batches(const hata_ctx* c, int B, bool paged, int* chunk_out
             const int per_launch = (int)(cap / per_seq);
             ns = (B + per_launch - 1) / per_launch;
         }
-        // Fewest launches first.  Then the smallest chunk, but at r = 128 not one with more than three and a half workgroups per CU
-        // if a larger chunk goes in one launch too: the fourth one per CU shares what bounds the other three, and twice as many
-        // partials and rows are exchanged (us, two layers unless noted, 4 per CU -> the next chunk: one sequence of 131072
-        // keys, 32 heads of their own 65.2 -> 55.1; 4 x 131072 72.4 -> 63.2, unequal ones 62.7 -> 57.9; 16 x 32768, four layers
-        // 143 -> 133, unequal ones 123.6 -> 122.4; 8 x 60000 67.8 -> 61.7, unequal ones 59.3 -> 57.3; the other way where one
-        // layer is all that is run: unequal 16 x 32768 27.7 -> 30.0).  Up to there sequences of equal length gain too (20 x 20000,
-        // 800 workgroups, 66.8 -> 62.2), but unequal ones, whose lengths only the device knows, leave too few of the
-        // halved number at work (53.1 -> 58.5; 5 x 79430 51.5 -> 55.6).  At r = 64 nothing is gained (56.8 and 57.1).
-        const bool fits_well = ns == 1 && (c->Wd != 4 || 2 * per_seq * B <= (int64_t)7 * c->cus);
-        if (best == 0 || ns < best || (ns == best && fits_well && !best_fits_well)) {
-            best = ns;
-            best_chunk = chunk;
-            best_fits_well = fits_well;
-        }
+        // Fewest launches first, then the smallest chunk: the capacity is all that is known here, and where the caches are not full,
+        // workgroups of twice the keys are half of what the device could hold.  us, four per CU at 4096 keys / 8192 keys a workgroup,
+        // r = 128, groups of four, two layers (16 sequences: four): 8 caches of 60000 rows holding as many 58.8 / 60.6, 32768 42.5 / 51.3;
+        // 4 of 131072 rows 61.7 / 62.3, holding 65536 43.0 / 51.4; 16 of 32768 rows holding up to as many 113.7 / 118.6, 16384
+        // 90.7 / 106.0, and the other way round where all are full, 140.3 / 125.2 (268 MB of codes in four layers, which the larger
+        // chunks' loads do not keep: coop_load_code).
+        if (best == 0 || ns < best) { best = ns; best_chunk = chunk; }
     }
     if (chunk_out) *chunk_out = best_chunk;
     return best;

@@ -124,3 +124,13 @@ def test_replays_beside_eager_steps_of_other_batches():
     check(3, query)
     ctx.hata_check()
     ctx.close()
+
+
+@pytest.mark.parametrize("B,Hkv,L_cap", [(16, 8, 32768), (8, 8, 65536), (4, 8, 131072), (1, 32, 131072)])
+def test_chunk_goes_by_residency_alone(B, Hkv, L_cap):
+    """A batch that is resident at 4096 keys a workgroup stays at that: how full its caches are only the device knows."""
+    from paper_2506_02572_amd import hata
+    print(f"[launches] chunk of {B} caches of {L_cap} rows", flush=True)
+    ctx = hata.Context(B, 32, Hkv, 128, 128, L_cap, 512)
+    assert ctx.hata_step_plan(B) == (1, 4096, L_cap // 4096) and ctx.hata_step_sub_batches(B) == 1
+    ctx.close()
