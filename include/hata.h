@@ -223,8 +223,8 @@ int hata_dense_decode(hata_ctx* ctx, const void* q, const void* K, const void* V
  *
  * Launches (see hata_step_plan): for r in {32, 64, 128, 256} and Hq/Hkv in {1, 2, 4, 5, 8}, a cache of at most
  * 4096 rows, or of up to 16384 where a call has (sequence, KV head) units enough, takes ONE launch with a workgroup
- * per unit and no in-kernel wait, on a shared device too (unless hata_tuning.chunk or hata_set_step_mode ask for
- * another form).  Otherwise, for r in {32, 64, 128, 256} and Hq/Hkv in {1, 2, 4, 5, 8}, or 16
+ * per unit and no in-kernel wait, on a shared device too (unless k_max is large for so few units, or hata_tuning.chunk or
+ * hata_set_step_mode ask for another form).  Otherwise, for r in {32, 64, 128, 256} and Hq/Hkv in {1, 2, 4, 5, 8}, or 16
  * with r <= 128, a budget k_max of at most 65535 rows, and when the workgroups of at least one sequence
  * can be resident on the device at once,
  * the step is ONE kernel launch whose workgroups each take a chunk of 1024 to 32768 cached keys of

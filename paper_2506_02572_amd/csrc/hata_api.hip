@@ -190,22 +190,37 @@ inline int coop_sub_batches(const hata_ctx* c, int B, bool paged, int* chunk_out
     return best;
 }
 // Whether the step's own choice is a workgroup per unit.  Nothing waits in that form, so a shared device (step mode 3 unless the
-// caller asks for that) takes it too.  Beyond 4096 keys it needs many units, as a compute unit alone streams slowly, but not so
-// many that they go in several rounds, unless a code is so wide (r = 256) that a unit's time is its stream.  us a layer,
-// workgroups that share units / one per unit, r = 128, groups of four unless noted: 64 units of 6000 keys 15.0 / 14.9; 128 of
-// 8192 18.5 / 17.1 (r = 256 23.1 / 22.7, ragged 17.6 / 16.8, one head a unit 14.6 / 12.9), of 16384 23.4 / 26.5; 256 of 16384
-// 37.5 / 30.9 (r = 256 51.3 / 44.8); 264 of 10000 30.6 / 37.5; 384 of 12000, one head a unit, 28.9 / 32.9; 512 of 8000, one
-// head a unit, 24.1 / 27.5; 448 of up to 12000 at r = 256, one head a unit, 40.0 / 37.1.  On a shared device, three launches /
-// one per unit: 8 units of 8192 keys 20.5 / 15.7 (r = 256 22.0 / 21.0), of 12000 20.7 / 20.0 (22.3 / 24.7); 64 units of 12000
-// 25.1 / 20.9 (27.7 / 26.1); 128 of 16384 31.3 / 26.6 (42.4 / 36.7).
+// caller asks for that) takes it too.  Two things bound it, the rates at which a compute unit alone streams codes and gathers
+// rows (a row of a group of four 6.9 ns a layer, 2.1 ns where four workgroups share the unit).
+//
+// Codes: up to 4096 keys always; beyond, the units must be many, but not so many that they go in several rounds, unless a code is so
+// wide (r = 256) that a unit's time is its stream.  us a layer, workgroups that share units / one per unit, r = 128, groups of
+// four unless noted: 64 units of 6000 keys 15.0 / 14.9; 128 of 8192 18.5 / 17.1 (r = 256 23.1 / 22.7, ragged 17.6 / 16.8, one head a
+// unit 14.6 / 12.9), of 16384 23.4 / 26.5; 256 of 16384 37.5 / 30.9 (r = 256 51.3 / 44.8); 264 of 10000 30.6 / 37.5; 384 of 12000, one
+// head a unit, 28.9 / 32.9; 512 of 8000, one head a unit, 24.1 / 27.5; 448 of up to 12000 at r = 256, one head a unit,
+// 40.0 / 37.1.  On a shared device, three launches / one per unit: 8 units of 8192 keys 18.3 / 17.5 (r = 256 18.8 / 20.6), 96 of
+// 12000 26.3 / 21.4, 128 of 16384 28.2 / 25.6 (r = 256 34.3 / 30.9), one of them that long and the others of 500 21.9 / 23.6.
+//
+// Rows: the other forms gather a unit's rows by several workgroups, the more the longer the cache, unless the units are as many as
+// three quarters of the compute units (192 units of 4096 and of 8192 keys, k = 2000: 55.8 / 48.8, 60.0 / 54.1).  Below, both forms
+// take as long at these budgets: 8 to 64 units of 2048 / 3000 / 4096 keys 900 / 600 / 400 to 530, 128 of 4096 and of 8192 keys 900 and
+// 400; with two heads a unit half as many again, with one head three times, at r = 256 three quarters.  On a shared device 8 to 32 units
+// of 4096 / 6000 / 8192 keys 900 / 510 / 350 to 450, 64 of 8192 690, 128 of 12000 and of 16384 1900 and 700.  (k_max is what the host
+// knows of the budgets; at k = 2048 8 units of 4096 keys took 38.0 for 22.0, on a shared device 8 of 8192 keys 42.0 for 23.8.)
 inline bool takes_unit_step(const hata_ctx* c, int B, bool paged = false) {
     // (the block-table step knows no modes: what a caller set for the other layout changes nothing)
     if (!c->unit_keys || (!paged && c->step_mode != 0 && c->mode_asked)) return false;
-    const bool shared = paged ? c->shared != 0 : c->step_mode != 0;
-    const int64_t units = (int64_t)B * c->cfg.Hkv;
-    if (c->cfg.L_cap <= HATA_UNIT_KEYS) return true;
-    if (shared) return c->cfg.L_cap <= 8192 || (c->cfg.L_cap <= 128 * units && units <= 512);
-    return c->cfg.L_cap <= 64 * units && units <= (c->Wd >= 8 ? 512 : 256);
+    const bool shared = paged ? c->shared != 0 : c->step_mode != 0, wide = c->Wd >= 8;
+    const int64_t units = (int64_t)B * c->cfg.Hkv, L_cap = c->cfg.L_cap;
+    if (L_cap > HATA_UNIT_KEYS) {
+        if (shared ? L_cap > 8192 && (L_cap > 128 * units || units > 512) : L_cap > 64 * units || units > (wide ? 512 : 256))
+            return false;
+    }
+    if (units >= 192) return true;
+    int64_t rows_keys = (units > 64 ? units : 64) * 25000;
+    if (shared) rows_keys = units <= 48 ? 3000000 : units < 100 ? units * units * 1300 : 13000000;
+    if (wide) rows_keys = rows_keys / 4 * 3;
+    return 2 * c->cfg.k_max * L_cap <= rows_keys * (c->G == 1 ? 6 : c->G == 2 ? 3 : 2);
 }
 inline bool aligned(const void* p, size_t a) { return ((uintptr_t)p % a) == 0; }
 

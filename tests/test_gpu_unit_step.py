@@ -24,8 +24,8 @@ def test_unit_step(L_cap, heads, r, ties):
     print(f"[unit] L_cap={L_cap} heads={heads} r={r} ties={ties}", flush=True)
     rng = np.random.default_rng(L_cap + r + Hq)
     seq = np.array([L_cap, max(1, L_cap - 5), max(1, L_cap // 2)], np.int32)  # (an empty sequence has no row to append)
-    k_max = max(1, L_cap // 3)
-    k = np.array([max(1, L_cap // 50), k_max, 0 if L_cap < 100 else 40], np.int32)
+    k_max = max(1, min(L_cap // 3, 2_200_000 // L_cap))  # (larger budgets of so few units go to several workgroups a unit)
+    k = np.array([max(1, min(L_cap // 50, k_max)), k_max, 0 if L_cap < 100 else 40], np.int32)
     K, V = (synth.round_to_bf16_bits(rng.standard_normal((B, Hkv, L_cap, 128))) for _ in range(2))
     q = synth.round_to_bf16_bits(rng.standard_normal((B, Hq, 128)))
     W = rng.standard_normal((Hkv, 128, r)).astype(np.float32)
@@ -90,6 +90,21 @@ def test_unit_step_of_many_units(units, L_cap, page_rows):
     assert np.array_equal(got[0][0], got[1][0])
     # (fp32 sums in another order, weights of 16 bits or more: hata_attn_core.h)
     assert torch.allclose(got[0][1], got[1][1], rtol=1e-3, atol=1e-4)
+
+
+@pytest.mark.parametrize("L_cap,Hkv,G,r,k_max,B,shared,unit", [
+    (4096, 8, 4, 128, 64, 1, False, True), (4096, 8, 4, 128, 2048, 1, False, False), (4096, 8, 1, 128, 1024, 1, False, True),
+    (4096, 8, 4, 128, 2048, 24, False, True), (8192, 8, 4, 128, 256, 16, False, True), (8192, 8, 4, 128, 2048, 16, False, False),
+    (8192, 8, 4, 128, 200, 1, True, True), (8192, 8, 4, 128, 2048, 1, True, False), (8192, 8, 4, 256, 384, 1, True, False),
+    (16384, 8, 4, 128, 2048, 32, False, True), (16384, 8, 4, 128, 512, 16, True, True)])
+def test_budgets_a_unit_workgroup_takes(L_cap, Hkv, G, r, k_max, B, shared, unit):
+    """A compute unit alone gathers rows slowly: budgets that are large for so few units go to several workgroups a unit."""
+    from paper_2506_02572_amd import hata
+    print(f"[unit] rule L_cap={L_cap} units={B * Hkv} G={G} r={r} k_max={k_max} shared={shared}", flush=True)
+    ctx = hata.Context(B, Hkv * G, Hkv, 128, r, L_cap, k_max, shared_device=shared)
+    launches, _, chunks = ctx.hata_step_plan(B)
+    assert ((launches, chunks) == (1, 1)) == unit
+    ctx.close()
 
 
 @pytest.mark.parametrize("L_cap", [700, 5000])
