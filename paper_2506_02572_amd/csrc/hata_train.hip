@@ -526,10 +526,13 @@ __global__ __launch_bounds__(TrainShape<R>::THREADS) void train_grad_kernel(
 }
 
 // dL/dW = sigma * (sum of the partials) + 2 lam W P / ||P||_F, and the SGD update from it; the last block writes
-// the loss terms.  64 elements per workgroup of 1024 threads: wave w sums a sixteenth of the partials of
-// each -- K^T E times the column's factor, which it adds up first from the column sums of all blocks (colsum:
-// already added up per query) -- the sixteen meet in LDS in a fixed order.  Bound by reading the partials once (16.8 MB at
-// r = 128 and 256 blocks, in the caches).
+// the loss terms.  64 elements per workgroup of 512 threads: a wave sums an eighth of the partials of each -- K^T E
+// times the column's factor, which the workgroup adds up first from the column sums of all blocks (colsum: already added up per
+// query) -- and the eighths meet in LDS in a fixed order.  Large batches are bound by reading the partials once (16.8 MB at r = 128
+// and 256 blocks, in the caches), small ones by the round trips to what a wave reads: hence everything of the first 32 blocks
+// is requested at once, queries are looked up by 32 blocks (a lane each), and the loss workgroup's waves have 64 columns of a
+// share of the blocks each instead of all columns one after the other (one block 6.5 -> 5.8 us, at r = 256 12.7 -> 8.7;
+// 960 blocks of four queries, r = 32 15.6 -> 9.4, r = 128 17.1 -> 13.1).
 __global__ __launch_bounds__(TR_UPDATE_WAVES * 64) __attribute__((amdgpu_waves_per_eu(4, 4))) void train_update_kernel(
     float* __restrict__ W, float* __restrict__ v, int log2_r, int n_blocks, float sigma, float lam, float c_sim, float c_bal,
     float lr, float momentum, float weight_decay, const float* __restrict__ dw_part, const float* __restrict__ colsum_part,
@@ -542,65 +545,65 @@ __global__ __launch_bounds__(TR_UPDATE_WAVES * 64) __attribute__((amdgpu_waves_p
     __shared__ float s_slice[WAVES][TR_FEW_QUERIES][64], s_sum[TR_FEW_QUERIES][64];  // column sums: a slice's, a query's
     const int tid = threadIdx.x, el = tid & 63, sl = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = 1 << log2_r, count = HATA_D * r, n_pairs = (n_blocks + 1) / 2;
-    // a wave's pairs of blocks, and the queries of its blocks, a lane each (where there are more than 64: looked up one by one)
+    constexpr int UN = 16;  // pairs of blocks whose sums are in flight together
     const int p0 = sl * n_pairs / WAVES, p1 = (sl + 1) * n_pairs / WAVES, b0 = 2 * p0, b1 = min(2 * p1, n_blocks);
-    const int ids = block_query(block_group, min(b0 + el, n_blocks - 1), n_groups);
-    // (the rule: all of a wave's blocks are one query's)
-    const bool one = b1 - b0 <= 64 && __builtin_amdgcn_ballot_w64(ids != __builtin_amdgcn_readfirstlane(ids) && b0 + el < b1) == 0ull;
-    auto query_of = [&](int b) { return b - b0 < 64 ? __builtin_amdgcn_readlane(ids, b - b0) : block_query(block_group, b, n_groups); };
-    // sums of h(k) per query for column j, into s_sum[query][el]; two barriers
-    float cx[32];  // of up to 32 blocks: requested ahead of everything else
-    auto request_columns = [&](int j, int b) {
+    // the queries of blocks b .. below e, a lane each (the lanes behind them: the last one's); the rule: all are one query's
+    auto queries_from = [&](int b, int e) { return block_query(block_group, max(min(b + el, e - 1), 0), n_groups); };
+    auto uniform = [](int ids) { return __builtin_amdgcn_ballot_w64(ids != __builtin_amdgcn_readfirstlane(ids)) == 0ull; };
+    // sums of h(k) per query for column j over blocks [b, e), into s_slice[sl][query][el]; the first 32 blocks and their
+    // queries requested ahead
+    float cx[2 * UN];
+    auto request_columns = [&](int j, int b, int e) {
 #pragma unroll
-        for (int u = 0; u < 32; ++u) cx[u] = colsum_part[(int64_t)max(min(b + u, b1 - 1), 0) * r + j];
+        for (int u = 0; u < 2 * UN; ++u) cx[u] = colsum_part[(int64_t)max(min(b + u, e - 1), 0) * r + j];
     };
-    auto column_sums = [&](int j) {
+    auto add_columns = [&](int j, int b, int e, int ids) {
         for (int q = 0; q < n_groups; ++q) s_slice[sl][q][el] = 0.f;
-        int query = b0 < b1 ? query_of(b0) : 0;
-        float sum = 0.f;
-        for (int b = b0; b < b1; b += 32) {
-            if (b != b0) request_columns(j, b);
-            if (one) {
+        for (; b < e; b += 2 * UN) {
+            if (uniform(ids)) {
                 float x[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int u = 0; u < 32; ++u) x[u & 3] += b + u < b1 ? cx[u] : 0.f;
-                sum += (x[0] + x[1]) + (x[2] + x[3]);
-                continue;
-            }
+                for (int u = 0; u < 2 * UN; ++u) x[u & 3] += b + u < e ? cx[u] : 0.f;
+                s_slice[sl][__builtin_amdgcn_readfirstlane(ids)][el] += (x[0] + x[1]) + (x[2] + x[3]);
+            } else {
+                int query = __builtin_amdgcn_readfirstlane(ids);
+                float sum = 0.f;
 #pragma unroll
-            for (int u = 0; u < 32; ++u) {
-                if (b + u < b1) {
-                    const int of = query_of(b + u);  // (the same for the whole wave)
-                    if (of != query) {
-                        s_slice[sl][query][el] += sum;
-                        sum = 0.f;
-                        query = of;
+                for (int u = 0; u < 2 * UN; ++u) {
+                    if (b + u < e) {
+                        const int of = __builtin_amdgcn_readlane(ids, u);
+                        if (of != query) {
+                            s_slice[sl][query][el] += sum;
+                            sum = 0.f;
+                            query = of;
+                        }
+                        sum += cx[u];
                     }
-                    sum += cx[u];
                 }
+                s_slice[sl][query][el] += sum;
+            }
+            if (b + 2 * UN < e) {
+                request_columns(j, b + 2 * UN, e);
+                ids = queries_from(b + 2 * UN, min(b + 4 * UN, e));
             }
         }
-        s_slice[sl][query][el] += sum;
-        __syncthreads();
-        for (int q = sl; q < n_groups; q += WAVES) {
-            float t = 0.f;
-#pragma unroll
-            for (int i = 0; i < WAVES; ++i) t += s_slice[i][q][el];
-            s_sum[q][el] = t;
-        }
-        __syncthreads();
     };
-    double f2 = 0.0;
+    // (everything a wave reads first is requested before any of it is waited for)
+    double f2 = 0.0, fp[2 * HATA_D / 64];
     if (sl == 0) {
-        for (int i = el; i < 2 * HATA_D; i += 64) f2 += fro_part[i];
-        f2 = fmax(wave_sum64_f64(f2) + (double)r, 0.0);
+#pragma unroll
+        for (int i = 0; i < 2 * HATA_D / 64; ++i) fp[i] = fro_part[el + 64 * i];
     }
-    const float fro = (float)sqrt(f2);
+    auto fro_norm = [&]() {  // (wave 0)
+#pragma unroll
+        for (int i = 0; i < 2 * HATA_D / 64; ++i) f2 += fp[i];
+        return (float)sqrt(fmax(wave_sum64_f64(f2) + (double)r, 0.0));
+    };
     if ((int)blockIdx.x * 64 < count) {  // (count is a multiple of 64; the last block is past it)
-        const int e = blockIdx.x * 64 + el, ch = e >> log2_r, j = e & (r - 1);
+        const int e0 = blockIdx.x * 64, e = e0 + el, j = e & (r - 1);
         const float* dp = dw_part + e;
-        if (!colsum) request_columns(j, b0);
-        constexpr int UN = 16;
+        int ids = queries_from(b0, min(b0 + 2 * UN, b1));
+        if (!colsum) request_columns(j, b0, b1);
         float ke[UN], dw[UN];
         auto fetch = [&](int p) {
 #pragma unroll
@@ -611,51 +614,61 @@ __global__ __launch_bounds__(TR_UPDATE_WAVES * 64) __attribute__((amdgpu_waves_p
             }
         };
         fetch(p0);
-        const float w0 = W[e], v0 = v[e];
-        if (!colsum) column_sums(j);
         constexpr int NG = HATA_D / WAVES;
-        double gr[NG];
         float wo[NG];
 #pragma unroll
-        for (int i = 0; i < NG; ++i) {
-            gr[i] = gram[ch * HATA_D + sl * NG + i];
-            wo[i] = W_old[(sl * NG + i) * r + j];
-        }
-        // a column's factor changes with the query only
-        int query = -1;
-        float factor = 0.f;
-        auto factor_of = [&](int q) {
-            if (q != query) {
-                query = q;
-                factor = c_bal * (colsum ? colsum[(int64_t)q * r + j] : s_sum[q][el]);
+        for (int i = 0; i < NG; ++i) wo[i] = W_old[(sl * NG + i) * r + j];
+        const float w0 = W[e], v0 = v[e];
+        // (the workgroup's elements are one channel's, or at r = 32 two channels')
+        const double* const g_lo = gram + (e0 >> log2_r) * HATA_D + sl * NG;
+        const double* const g_hi = gram + ((e0 + 63) >> log2_r) * HATA_D + sl * NG;
+        const bool hi = (e >> log2_r) != (e0 >> log2_r);
+        if (!colsum) {
+            add_columns(j, b0, b1, ids);
+            __syncthreads();
+            for (int q = sl; q < n_groups; q += WAVES) {
+                float t = 0.f;
+#pragma unroll
+                for (int i = 0; i < WAVES; ++i) t += s_slice[i][q][el];
+                s_sum[q][el] = t;
             }
-            return factor;
-        };
+            __syncthreads();
+        }
+        auto factor_of = [&](int q) { return c_bal * (colsum ? colsum[(int64_t)q * r + j] : s_sum[q][el]); };
         float gp[4] = {0.f, 0.f, 0.f, 0.f};
         for (int p = p0; p < p1; p += UN) {
-            if (p != p0) fetch(p);
-            if (one) {
-                const float fc = factor_of(query_of(b0));
+            if (p != p0) {
+                ids = queries_from(2 * p, min(2 * (p + UN), b1));
+                fetch(p);
+            }
+            if (uniform(ids)) {
+                const float fc = factor_of(__builtin_amdgcn_readfirstlane(ids));
 #pragma unroll
                 for (int u = 0; u < UN; ++u) gp[u & 3] += p + u < p1 ? fmaf(fc, ke[u], dw[u]) : 0.f;
-                continue;
-            }
+            } else {
+                float f0[UN], f1[UN], k1[UN];
 #pragma unroll
-            for (int u = 0; u < UN; ++u) {
-                if (p + u < p1) {
-                    const int b = 2 * (p + u), q0 = query_of(b), q1 = b + 1 < n_blocks ? query_of(b + 1) : q0;
-                    gp[u & 3] += fmaf(factor_of(q0), ke[u], dw[u]);
-                    if (q1 != q0) gp[u & 3] = fmaf(factor_of(q1), dp[((int64_t)(p + u) * 3 + 2) * count], gp[u & 3]);
+                for (int u = 0; u < UN; ++u) {
+                    const int q0 = __builtin_amdgcn_readlane(ids, 2 * u), q1 = __builtin_amdgcn_readlane(ids, 2 * u + 1);
+                    f0[u] = factor_of(q0);
+                    f1[u] = k1[u] = 0.f;
+                    if (q1 != q0) {
+                        f1[u] = factor_of(q1);
+                        k1[u] = dp[((int64_t)(p + u) * 3 + 2) * count];
+                    }
                 }
+#pragma unroll
+                for (int u = 0; u < UN; ++u) gp[u & 3] += p + u < p1 ? fmaf(f1[u], k1[u], fmaf(f0[u], ke[u], dw[u])) : 0.f;
             }
         }
         double wp = 0.0;
 #pragma unroll
-        for (int i = 0; i < NG; ++i) wp = fma(gr[i], (double)wo[i], wp);
+        for (int i = 0; i < NG; ++i) wp = fma(hi ? g_hi[i] : g_lo[i], (double)wo[i], wp);
         part[sl][el] = (gp[0] + gp[1]) + (gp[2] + gp[3]);
         wp_part[sl][el] = wp;
         __syncthreads();
         if (sl == 0) {
+            const float fro = fro_norm();
             float g = 0.f;
 #pragma unroll
             for (int i = 0; i < WAVES; ++i) g += part[i][el];
@@ -678,16 +691,24 @@ __global__ __launch_bounds__(TR_UPDATE_WAVES * 64) __attribute__((amdgpu_waves_p
     if (colsum) {
         for (int j = tid; j < r * n_groups; j += WAVES * 64) lb = fmaf(colsum[j], colsum[j], lb);
     } else {
-        for (int j0 = 0; j0 < r; j0 += 64) {
-            request_columns(min(j0 + el, r - 1), b0);
-            column_sums(min(j0 + el, r - 1));
-            for (int q = sl; q < n_groups; q += WAVES)
-                if (j0 + el < r) lb = fmaf(s_sum[q][el], s_sum[q][el], lb);
+        // a wave: 64 columns of a share of the blocks
+        const int cols = (r + 63) / 64, share = WAVES / cols, grp = sl % cols, at = sl / cols;
+        const int first = at * n_blocks / share, last = (at + 1) * n_blocks / share, j = min(grp * 64 + el, r - 1);
+        const int ids = queries_from(first, min(first + 2 * UN, last));
+        request_columns(j, first, last);
+        add_columns(j, first, last, ids);
+        __syncthreads();
+        for (int i = sl; i < n_groups * cols; i += WAVES) {
+            const int q = i / cols, g = i % cols;
+            float t = 0.f;
+            for (int k = 0; k < share; ++k) t += s_slice[k * cols + g][q][el];
+            if (g * 64 + el < r) lb = fmaf(t, t, lb);
         }
     }
     ls = wave_sum64(ls);
     lb = wave_sum64(lb);
     if (el == 0) { part[0][sl] = ls; part[1][sl] = lb; }
+    const float fro = sl == 0 ? fro_norm() : 0.f;
     __syncthreads();
     if (tid == 0) {
         ls = lb = 0.f;

@@ -36,6 +36,33 @@ def test_step_on_both_sides_of_the_column_sum_rule(blocks, r):
     ctx.close()
 
 
+@pytest.mark.parametrize("r", [32, 64, 256])
+@pytest.mark.parametrize("runs", [(1,), (33, 31), (64, 1, 447), (1,) * 17, (1,) * 600, (600,), (70, 33, 1, 1, 1095)])
+def test_step_on_runs_of_blocks(r, runs):
+    """The update looks at 32 blocks at a time: all one query's, a few queries', a query each; any number of such pieces."""
+    import torch
+    blocks, n_q = sum(runs), len(runs)
+    n = blocks * train.BLOCK - 3
+    print(f"[train] runs={runs if n_q < 9 else n_q} r={r}", flush=True)
+    Qb, Kb, Q, K, s, W = make_problem(n, r, seed=blocks)
+    names = np.repeat(np.arange(n_q, dtype=np.int32), runs)
+    hp = train.default_hparams(n)
+    hp.lr = 0.0
+    kw = dict(sigma=hp.sigma, eps=hp.eps, eta=hp.eta, lam=hp.lam, scale_sim=hp.scale_sim, scale_bal=hp.scale_bal,
+              group=np.repeat(names, train.BLOCK)[:n])
+    terms = T.loss_terms(Q, K, s, W, **kw)
+    _, g_ref = T.loss_and_grad(Q, K, s, W, **kw)
+    ctx = train.TrainContext(128, r, n)
+    Wd = H.to_dev(W.copy())
+    gd, ld = torch.empty_like(Wd), torch.empty(3, dtype=torch.float32, device="cuda")
+    ctx.hata_train_step(H.to_dev(Qb), H.to_dev(Kb), H.to_dev(s), n, Wd, torch.zeros_like(Wd), hp, gd, ld,
+                        block_query=H.to_dev(names), n_queries=n_q)
+    torch.cuda.synchronize()
+    assert np.max(np.abs(H.to_host(gd) - g_ref)) <= GRAD_TOL * np.max(np.abs(g_ref))
+    np.testing.assert_allclose(H.to_host(ld), terms, rtol=2e-5)
+    ctx.close()
+
+
 @pytest.mark.parametrize("m", [256, 257, 20000])
 @pytest.mark.parametrize("kind", ["equal", "one_bin", "octaves", "negative"])
 def test_labels_of_awkward_scores(kind, m):
