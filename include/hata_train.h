@@ -72,7 +72,7 @@ int hata_train_destroy(hata_train_ctx* ctx);
  * block_query (device, may be NULL = one query) and n_queries (1 <= n_queries <= number of blocks;
  * ignored when block_query is NULL) select the per-query balance term; ids outside [0, n_queries)
  * count as the nearest valid id.  hp: host pointer.  grad and loss may be NULL.  Two launches
- * (three above 65536 triplets or 16 queries) on `stream`; the projections and the weight-gradient contraction run on the matrix
+ * (three above 65536 triplets or 32 queries) on `stream`; the projections and the weight-gradient contraction run on the matrix
  * cores (bf16 MFMA over exact three-way bf16 splits of the fp32 operands, fp32 accumulation). */
 int hata_train_step(hata_train_ctx* ctx, const void* Q, const void* K, const float* s, int32_t n,
                     const int32_t* block_query, int32_t n_queries, float* W, float* v,

@@ -60,7 +60,7 @@ typedef __attribute__((ext_vector_type(16))) float tr_f32x16_t;
 #define TR_ROWS 128   // triplets per block: those of one query
 #define TR_PAIR 256   // triplets per workgroup: two blocks (one LDS stage)
 #define TR_FEW_WGS 512    // up to so many blocks and queries every workgroup of the update adds the column sums up itself
-#define TR_FEW_QUERIES 16
+#define TR_FEW_QUERIES 32
 #define TR_UPDATE_WAVES 8  // waves of an update workgroup
 #define TR_PITCH 136  // LDS row pitch in bf16 elements (272 B: conflict-free 16-B and transposed reads)
 
@@ -146,19 +146,55 @@ __device__ __forceinline__ int block_query(const int32_t* __restrict__ block_gro
     return block_group ? clampi(block_group[wg], 0, n_groups - 1) : 0;
 }
 
-// sum of the per-workgroup column sums of one query: one workgroup per (hash column, query)
-__global__ __launch_bounds__(256) void train_colreduce_kernel(const float* __restrict__ colsum_part, int r,
-                                                              int n_wgs, const int32_t* __restrict__ block_group,
-                                                              int n_groups, float* __restrict__ colsum) {
-    __shared__ float red[4];
-    const int j = blockIdx.x, q = blockIdx.y, tid = threadIdx.x;
+// The blocks' column sums added up per query: a workgroup per (64 hash columns, query), a wave a sixteenth of the blocks.  It
+// looks up 64 blocks' queries at a time, a lane each, and reads whole rows of its own query's blocks, so that many queries
+// are many short workgroups (with a workgroup per column and query, a thread per block, a step of 960 blocks of as many queries,
+// r = 128, took 224 us, 158 so, 122 with the loss term's sums read sixteen at a time too).
+#define TR_REDUCE_WAVES 16
+__global__ __launch_bounds__(TR_REDUCE_WAVES * 64) void train_colreduce_kernel(const float* __restrict__ colsum_part, int r,
+                                                                               int n_blocks, const int32_t* __restrict__ block_group,
+                                                                               int n_groups, float* __restrict__ colsum) {
+    __shared__ float part[TR_REDUCE_WAVES][64];
+    const int tid = threadIdx.x, el = tid & 63, sl = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int q = blockIdx.y, j = min((int)blockIdx.x * 64 + el, r - 1);
     float acc = 0.f;
-    for (int g = tid; g < n_wgs; g += 256)
-        if (block_query(block_group, g, n_groups) == q) acc += colsum_part[(int64_t)g * r + j];
-    acc = wave_sum64(acc);
-    if ((tid & 63) == 0) red[tid >> 6] = acc;
+    for (int b = 64 * sl; b < n_blocks; b += 64 * TR_REDUCE_WAVES) {
+        const int id = block_query(block_group, min(b + el, n_blocks - 1), n_groups);
+        unsigned long long own = __builtin_amdgcn_ballot_w64(id == q && b + el < n_blocks);
+        if (own == 0) continue;
+        const float* const rows = colsum_part + (int64_t)b * r + j;
+        if (__popcll(own) > 8) {
+            const int last = 63 - __builtin_clzll(own);
+#pragma unroll
+            for (int h = 0; h < 64; h += 32) {
+                float x[32];
+#pragma unroll
+                for (int u = 0; u < 32; ++u) x[u] = rows[(int64_t)min(h + u, last) * r];
+#pragma unroll
+                for (int u = 0; u < 32; ++u) acc += (own >> (h + u)) & 1 ? x[u] : 0.f;
+            }
+        } else {
+            float x[8];
+            int at = 0;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const bool more = own != 0;
+                if (more) at = __builtin_ctzll(own);
+                own &= own - 1;
+                const float y = rows[(int64_t)at * r];
+                x[u] = more ? y : 0.f;
+            }
+            acc += ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
+        }
+    }
+    part[sl][el] = acc;
     __syncthreads();
-    if (tid == 0) colsum[(int64_t)q * r + j] = red[0] + red[1] + red[2] + red[3];
+    if (sl == 0) {
+        float t = 0.f;
+#pragma unroll
+        for (int i = 0; i < TR_REDUCE_WAVES; ++i) t += part[i][el];
+        if ((int)blockIdx.x * 64 + el < r) colsum[(int64_t)q * r + j] = t;
+    }
 }
 
 // Four rows of one channel per lane, from an LDS tile of rows: every group of 16 lanes reads 4 rows x 16
@@ -689,7 +725,13 @@ __global__ __launch_bounds__(TR_UPDATE_WAVES * 64) __attribute__((amdgpu_waves_p
     float ls = 0.f, lb = 0.f;
     for (int i = tid; i < parts; i += WAVES * 64) ls += loss_part[i];
     if (colsum) {
-        for (int j = tid; j < r * n_groups; j += WAVES * 64) lb = fmaf(colsum[j], colsum[j], lb);
+        for (int j = tid; j < r * n_groups; j += 16 * WAVES * 64) {
+            float x[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) x[u] = colsum[min(j + u * WAVES * 64, r * n_groups - 1)];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) lb = j + u * WAVES * 64 < r * n_groups ? fmaf(x[u], x[u], lb) : lb;
+        }
     } else {
         // a wave: 64 columns of a share of the blocks
         const int cols = (r + 63) / 64, share = WAVES / cols, grp = sl % cols, at = sl / cols;
@@ -994,7 +1036,7 @@ int hata_train_step(hata_train_ctx* ctx, const void* Q, const void* K, const flo
                            block_query, n_queries, ctx->dw_part, ctx->colsum_part, ctx->loss_part,     \
                            ctx->gram, ctx->fro_part, ctx->W_old);                                      \
         if (!few)                                                                                      \
-            hipLaunchKernelGGL(hata::train_colreduce_kernel, dim3(RR, n_queries), dim3(256), 0, st,    \
+            hipLaunchKernelGGL(hata::train_colreduce_kernel, dim3((RR + 63) / 64, n_queries), dim3(TR_REDUCE_WAVES * 64), 0, st,    \
                                ctx->colsum_part, RR, n_wgs, block_query, n_queries, ctx->colsum);      \
     } while (0)
     switch (r) {

@@ -37,7 +37,7 @@ def test_step_on_both_sides_of_the_column_sum_rule(blocks, r):
 
 
 @pytest.mark.parametrize("r", [32, 64, 256])
-@pytest.mark.parametrize("runs", [(1,), (33, 31), (64, 1, 447), (1,) * 17, (1,) * 600, (600,), (70, 33, 1, 1, 1095)])
+@pytest.mark.parametrize("runs", [(1,), (33, 31), (64, 1, 447), (1,) * 17, (1,) * 32, (1,) * 33, (1, 9) * 30, (1,) * 600, (600,), (70, 33, 1, 1, 1095)])
 def test_step_on_runs_of_blocks(r, runs):
     """The update looks at 32 blocks at a time: all one query's, a few queries', a query each; any number of such pieces."""
     import torch
