@@ -25,8 +25,8 @@
 //      many to do so themselves)
 //   2. train_update_kernel   dL/dW = sigma sum partials + 2 lam W P / ||P||_F with W P = (W W^T) W - W, the loss
 //                            terms, weight decay, momentum, step
-// At r = 128 and 32768 triplets of four queries a step takes 27 us; with the column sums in a launch in front of the
-// gradient's, h(k) twice and W P in extra workgroups behind it, it took 36.
+// At r = 128 and 32768 triplets of four queries a step takes 28 us; with the column sums in a launch in front of the
+// gradient's, h(k) twice and W P in extra workgroups behind it, it took 37.
 #include <new>
 #include <type_traits>
 
@@ -41,7 +41,7 @@ struct hata_train_ctx {
     float* colsum_part;  // [n_wgs_max, r]
     float* colsum;       // [queries (<= n_wgs_max), r]  sum of h(k_n) over the triplets of a query
     float* dw_part;      // [pairs of blocks, 3, d, r]  K^T E, the rest of X^T dZ, K^T E of the second block if its query is another
-    float* loss_part;    // [column groups (<= 4), pairs of blocks]
+    float* loss_part;    // [column groups, pairs of blocks]
     double* gram;        // [d, d]  W W^T
     double* fro_part;    // [2 d]  what its pieces add to ||W^T W - I||_F^2 - r
     float* W_old;        // [d, r]  the weights the gradient was taken at (the update overwrites W as it goes)
@@ -59,6 +59,7 @@ typedef __attribute__((ext_vector_type(8))) __bf16 tr_bf16x8_t;
 typedef __attribute__((ext_vector_type(16))) float tr_f32x16_t;
 #define TR_ROWS 128   // triplets per block: those of one query
 #define TR_PAIR 256   // triplets per workgroup: two blocks (one LDS stage)
+#define TR_ONE_ROUND 256  // workgroups of the gradient launch that run side by side, one per CU
 #define TR_FEW_WGS 512    // up to so many blocks and queries every workgroup of the update adds the column sums up itself
 #define TR_FEW_QUERIES 32
 #define TR_UPDATE_WAVES 8  // waves of an update workgroup
@@ -83,22 +84,21 @@ __device__ __forceinline__ float relaxed_sign(float z, float nsl) {
 }
 #define TR_LOG2E 1.4426950408889634f
 
-// How a workgroup's eight waves share its TR_PAIR rows and up to 64 hash columns: a wave owns 32 columns and
+// How a workgroup's eight waves share its TR_PAIR rows and COLS = 32 or 64 hash columns: a wave owns 32 columns and
 // 1 / RG of the rows.  Half the columns and twice the rows of a 128-column tile cost as many partial sums, two contractions
 // instead of one included.
-template <int R>
+template <int COLS_>
 struct TrainShape {
-    static constexpr int COLS = R < 64 ? R : 64;  // columns of a workgroup
+    static constexpr int COLS = COLS_;
     static constexpr int CG = COLS / 32;
     static constexpr int WAVES = 8, THREADS = WAVES * 64;
     static constexpr int RG = WAVES / CG;            // row groups
     static constexpr int HB = RG / 2;                // of a block
     static constexpr int TILES = TR_PAIR / 32 / RG;  // 32-row tiles of a wave
-    static constexpr int SLICES = THREADS / COLS;  // threads per column
-    static constexpr int COL_ROWS = WAVES > SLICES ? WAVES : SLICES;  // rows of LDS that per-column sums of either kind need
 };
 
-// rows [row0, row0 + TR_PAIR) of X [n, 128] (zeros past n): fetched into registers, later put into an LDS tile
+// rows [row0, row0 + TR_PAIR) of X [n, 128] (row0 < n): fetched into registers -- past n the last row, so that no load
+// is behind a branch -- and, once they are zeroed there, put into an LDS tile
 template <int THREADS>
 struct StagedRows {
     static constexpr int NV = TR_PAIR * 16 / THREADS;
@@ -106,10 +106,14 @@ struct StagedRows {
     __device__ __forceinline__ void fetch(const uint16_t* __restrict__ X, int row0, int n) {
 #pragma unroll
         for (int j = 0; j < NV; ++j) {
-            const int i = threadIdx.x + j * THREADS, row = i >> 4, sub = i & 15;
-            v[j] = make_uint4(0, 0, 0, 0);
-            if (row0 + row < n) v[j] = *reinterpret_cast<const uint4*>(X + (int64_t)(row0 + row) * HATA_D + sub * 8);
+            const int i = threadIdx.x + j * THREADS, row = min(row0 + (i >> 4), n - 1), sub = i & 15;
+            v[j] = *reinterpret_cast<const uint4*>(X + (int64_t)row * HATA_D + sub * 8);
         }
+    }
+    __device__ __forceinline__ void zero_past(int row0, int n) {
+#pragma unroll
+        for (int j = 0; j < NV; ++j)
+            if (row0 + (int)((threadIdx.x + j * THREADS) >> 4) >= n) v[j] = make_uint4(0, 0, 0, 0);
     }
     __device__ __forceinline__ void put(uint16_t* tile) const {
 #pragma unroll
@@ -262,25 +266,27 @@ struct GramPiece {
     }
 };
 
-// grid = (pairs of blocks of TR_ROWS triplets, groups of up to 64 hash columns).
+// grid = (pairs of blocks of TR_ROWS triplets, groups of COLS hash columns).
 //
 // A block whose rows hold one query vector -- those of a sampled query against its keys do; rows of zeros with label 0
 // fill such a block up -- needs that vector projected once, and its part of Q^T dZ_q is that vector times a sum over
 // the rows.  Whether it does is looked up in the rows themselves; a workgroup with any other row takes the general way.
 //
-// What bounds it: one round of workgroups, one per CU, so the latency of what a workgroup reads (4.5 us to the first
-// product), then the matrix instructions (of a wave 48 for the projection of its keys, 24 for the query, 96 for
-// the two contractions; the general way has 72 more) with the exponentials and the splits between them.  21 us at r = 128 and
-// 256 blocks; a step 30 us with one query vector a block, 35 with others (38 both before); of 8 blocks 22 and 28 (25).  Batches
-// of several rounds of workgroups: 640 blocks 71 (74), but 960 of the general kind 120 (100): there the second staging of
-// the keys is in no latency's shadow.
-template <int R>
-__global__ __launch_bounds__(TrainShape<R>::THREADS) void train_grad_kernel(
+// What bounds it: the way of a workgroup, one per CU and in step throughout, from what it reads (4 us to the first product)
+// over the matrix instructions (of a wave 48 for the projection of its keys, 24 for the query, 96 for the two contractions; the
+// general way has 72 more, and stages the keys twice) with the exponentials and the splits, to its sums.  So the reads are
+// requested together, behind no branch, and small batches have workgroups of 32 columns, half the way.  Kernel time at r = 128, us,
+// one query vector a block / others: one block 11.0 / 13.6 (64 columns 14.5 / 20.1), 256 blocks 20.0 / 25.4 (21.1 / 26.9 with
+// the reads one after the other), 960 blocks, four rounds, 74 / 97 (79 / 100).  A step of 960 blocks 87 / 107; with a launch for the
+// column sums, two workgroups a CU and both tiles side by side it was 95 of either kind: there the general way is behind, and in
+// the smallest batches of r = 32 (one block 19.1 for 16.7).
+template <int R, int COLS>
+__global__ __launch_bounds__(TrainShape<COLS>::THREADS) void train_grad_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const float* __restrict__ s, const float* __restrict__ W,
     int n, int n_blocks, float sigma, float c_sim, const int32_t* __restrict__ block_group, int n_groups,
     float* __restrict__ dw_part, float* __restrict__ colsum_part, float* __restrict__ loss_part, double* __restrict__ gram,
     double* __restrict__ fro_part, float* __restrict__ W_old) {
-    using S = TrainShape<R>;
+    using S = TrainShape<COLS>;
     constexpr int THREADS = S::THREADS, WAVES = S::WAVES, T = S::TILES;
     __shared__ __attribute__((aligned(16))) uint16_t tile[TR_PAIR * TR_PITCH];
     __shared__ __attribute__((aligned(16))) uint16_t s_q[2][HATA_D];  // first query row of each block
@@ -288,9 +294,8 @@ __global__ __launch_bounds__(TrainShape<R>::THREADS) void train_grad_kernel(
     __shared__ __attribute__((aligned(16))) uint4 s_frag[48][64];
     static_assert(S::CG * 3 * 8 <= 48 && S::CG * S::RG * 6 <= 48, "fragments");
     __shared__ float s_lab[TR_PAIR];
-    __shared__ float s_col[S::COL_ROWS][S::COLS];  // per hash column: sums of h(k_n) over a row group
-    static_assert(S::COL_ROWS >= WAVES && S::COL_ROWS >= S::SLICES, "a row per wave, and per slice");
-    __shared__ float s_dq[S::RG][S::COLS];  // sums of dZ_q
+    __shared__ float s_col[S::RG][COLS];  // per hash column: sums of h(k_n) over a row group
+    __shared__ float s_dq[S::RG][COLS];  // sums of dZ_q
     __shared__ float s_loss[WAVES];
     __shared__ double s_red[WAVES];
     __shared__ int s_mixed;
@@ -298,16 +303,12 @@ __global__ __launch_bounds__(TrainShape<R>::THREADS) void train_grad_kernel(
     const int w = (tid >> 6) % S::CG, rg = (tid >> 6) / S::CG;
     const int m = lane & 31, half = lane >> 5;
     const int row0 = blockIdx.x * TR_PAIR, blk = rg / S::HB;
-    const int col = blockIdx.y * 64 + w * 32 + m;
-    StagedRows<THREADS> xk, xq;
-    xk.fetch(K, row0, n);
-    xq.fetch(Q, row0, n);
-    const int wg = blockIdx.y * gridDim.x + blockIdx.x;
+    const int col = blockIdx.y * COLS + w * 32 + m;
+    const int wg = blockIdx.y * gridDim.x + blockIdx.x, first = 2 * blockIdx.x;
     GramPiece<R> piece;
-    if (wg < GramPiece<R>::PIECES) piece.fetch(W, wg);
-    const int first = 2 * blockIdx.x;
     if (first >= n_blocks) {  // (small batches have workgroups for the pieces alone)
         if (wg < GramPiece<R>::PIECES) {
+            piece.fetch(W, wg);
             const double f = piece.finish(wg, gram, W_old);
             if (lane == 0) s_red[tid >> 6] = f;
             __syncthreads();
@@ -319,10 +320,9 @@ __global__ __launch_bounds__(TrainShape<R>::THREADS) void train_grad_kernel(
         }
         return;
     }
-    const bool one_query = first + 1 >= n_blocks || block_query(block_group, first, n_groups) == block_query(block_group, first + 1, n_groups);
-    double fro = 0.0;
-    if (wg < GramPiece<R>::PIECES) fro = piece.finish(wg, gram, W_old);
-    if (lane == 0) s_red[tid >> 6] = fro;
+    // everything the workgroup reads is requested before any of it is waited for; what it needs last, last
+    StagedRows<THREADS> xk, xq;
+    xk.fetch(K, row0, n);
     // the planes of the column group's weights, a share of the channel steps by each of its row groups
     constexpr int KS = 8 / S::RG;
     float wv[KS][8];
@@ -330,8 +330,13 @@ __global__ __launch_bounds__(TrainShape<R>::THREADS) void train_grad_kernel(
     for (int k = 0; k < KS; ++k)
 #pragma unroll
         for (int e = 0; e < 8; ++e) wv[k][e] = W[(int64_t)((rg * KS + k) * 16 + 8 * half + e) * R + col];
+    xq.fetch(Q, row0, n);
+    const int lab_row = row0 + (tid & (TR_PAIR - 1));
+    const float lab = s[min(lab_row, n - 1)];
+    if (wg < GramPiece<R>::PIECES) piece.fetch(W, wg);
+    const bool one_query = first + 1 >= n_blocks || block_query(block_group, first, n_groups) == block_query(block_group, first + 1, n_groups);
     if (tid == 0) s_mixed = 0;
-    for (int i = tid; i < TR_PAIR; i += THREADS) s_lab[i] = (row0 + i < n) ? s[row0 + i] : 0.f;
+    xk.zero_past(row0, n);
     xk.put(tile);
 #pragma unroll
     for (int k = 0; k < KS; ++k) {
@@ -341,10 +346,17 @@ __global__ __launch_bounds__(TrainShape<R>::THREADS) void train_grad_kernel(
 #pragma unroll
         for (int p = 0; p < 3; ++p) s_frag[(w * 3 + p) * 8 + rg * KS + k][lane] = make_uint4(f[p][0], f[p][1], f[p][2], f[p][3]);
     }
+    if (tid < TR_PAIR) s_lab[tid] = lab_row < n ? lab : 0.f;
     // thread: piece tid % 16 of rows tid / 16 + 32 j
+    xq.zero_past(row0, n);
     if (tid < 16) {
         *reinterpret_cast<uint4*>(&s_q[0][tid * 8]) = xq.v[0];
         *reinterpret_cast<uint4*>(&s_q[1][tid * 8]) = xq.v[TR_ROWS * 16 / THREADS];
+    }
+    {
+        double fro = 0.0;
+        if (wg < GramPiece<R>::PIECES) fro = piece.finish(wg, gram, W_old);
+        if (lane == 0) s_red[tid >> 6] = fro;
     }
     __syncthreads();
     {
@@ -373,11 +385,11 @@ __global__ __launch_bounds__(TrainShape<R>::THREADS) void train_grad_kernel(
     project_tiles<T>(tile, t0, m, half, wfrag, zk);
     __syncthreads();
     const bool mixed = s_mixed != 0;
+    float lsim = 0.f, cs = 0.f, ssum = 0.f;  // similarity, sum of h(k), sum of s (h(q) - h(k))
     tr_f32x16_t zq[T];  // then h(q)
     float hq0 = 0.f;
     if (mixed) {
         xq.put(tile);
-        xk.fetch(K, row0, n);  // (the tile's next content)
         __syncthreads();
         project_tiles<T>(tile, t0, m, half, wfrag, zq);
 #pragma unroll
@@ -396,6 +408,14 @@ __global__ __launch_bounds__(TrainShape<R>::THREADS) void train_grad_kernel(
         }
         hq0 = relaxed_sign(z[0], nsl);
     }
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const float hk = relaxed_sign(zk[t][i], nsl);
+            zk[t][i] = hk;
+            cs += hk;  // (rows past n are zero: h = 0)
+        }
     // Every wave has the values of its rows, and gets the sums over all of them (RG = 8: over one block's) for 32
     // channels: a round hands 16 rows of each row group round through LDS, split into planes.  (With sums of its own rows over
     // all channels instead, a wave held 128 of them, its products waited for one operand at a time, and the
@@ -416,90 +436,96 @@ __global__ __launch_bounds__(TrainShape<R>::THREADS) void train_grad_kernel(
         const uint2 lo = lds_read_transposed(p), hi = lds_read_transposed(p + 8 * TR_PITCH);
         return __builtin_bit_cast(tr_bf16x8_t, make_uint4(lo.x, lo.y, hi.x, hi.y));
     };
-    float lsim = 0.f, cs = 0.f, ssum = 0.f;  // similarity, sum of h(k), sum of s (h(q) - h(k))
+    tr_bf16x8_t b[6];  // planes of the next round's values
+    auto hand_round = [&]() {
 #pragma unroll
-    for (int t = 0; t < T; ++t)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const float hk = relaxed_sign(zk[t][i], nsl);
-            zk[t][i] = hk;
-            cs += hk;  // (rows past n are zero: h = 0)
-        }
-    if (mixed) {
-#pragma unroll
-        for (int t = 0; t < T; ++t) {
-            tr_f32x16_t gq;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const float sd = s_lab[(t0 + t) * 32 + 8 * (i / 4) + 4 * half + (i % 4)] * (zq[t][i] - zk[t][i]);
-                gq[i] = c_sim * sd * fmaf(-zq[t][i], zq[t][i], 1.f);
-            }
-            tr_bf16x8_t b[2][3];
-#pragma unroll
-            for (int ks = 0; ks < 2; ++ks) split_operand(gq, ks, b[ks]);
-            __syncthreads();
-#pragma unroll
-            for (int p = 0; p < 6; ++p) s_frag[(w * S::RG + rg) * 6 + p][lane] = __builtin_bit_cast(uint4, b[p / 3][p % 3]);
-            __syncthreads();
-#pragma unroll
-            for (int g = 0; g < G0; ++g)
-#pragma unroll
-                for (int ks = 0; ks < 2; ++ks) {
-                    const tr_bf16x8_t x = rows_transposed((g0 + g) * T + t, ks);
-#pragma unroll
-                    for (int p = 0; p < 3; ++p)
-                        dw = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                            x, __builtin_bit_cast(tr_bf16x8_t, s_frag[(w * S::RG + g0 + g) * 6 + 3 * ks + p][lane]), dw, 0, 0, 0);
-                }
-        }
-        __syncthreads();  // (the tile of Q has been read)
-        xk.put(tile);
+        for (int p = 0; p < 6; ++p) s_frag[(w * S::RG + rg) * 6 + p][lane] = __builtin_bit_cast(uint4, b[p]);
         __syncthreads();
-    }
+    };
+    auto handed = [&](int g, int p) { return __builtin_bit_cast(tr_bf16x8_t, s_frag[(w * S::RG + g0 + g) * 6 + p][lane]); };
+    // 16 rows' E and -A E
+    auto prepare_keys = [&](int round, auto one_vector) {
+        const int t = round / 2, ks = round % 2;
+        tr_f32x16_t e, ae;
+#pragma unroll
+        for (int i = 8 * ks; i < 8 * ks + 8; ++i) {
+            // (half of dL/dh: h' = (1 - h^2) / 2)
+            float hq = hq0;
+            if constexpr (!decltype(one_vector)::value) hq = zq[t][i];
+            const float hk = zk[t][i], diff = hq - hk, sd = s_lab[(t0 + t) * 32 + 8 * (i / 4) + 4 * half + (i % 4)] * diff;
+            e[i] = fmaf(-hk, hk, 1.f);
+            ae[i] = -c_sim * sd * e[i];
+            lsim = fmaf(sd, diff, lsim);
+            ssum += sd;
+        }
+        tr_bf16x8_t be[3], ba[3];
+        split_operand(e, ks, be);
+        split_operand(ae, ks, ba);
+#pragma unroll
+        for (int p = 0; p < 3; ++p) { b[p] = be[p]; b[3 + p] = ba[p]; }
+    };
     auto contract_keys = [&](auto one_vector) {
-        tr_bf16x8_t b[6];  // planes of E and of -A E for the next round
-        auto prepare = [&](int round) {
-            const int t = round / 2, ks = round % 2;
-            tr_f32x16_t e, ae;
-#pragma unroll
-            for (int i = 8 * ks; i < 8 * ks + 8; ++i) {
-                // (half of dL/dh: h' = (1 - h^2) / 2)
-                float hq = hq0;
-                if constexpr (!decltype(one_vector)::value) hq = zq[t][i];
-                const float hk = zk[t][i], diff = hq - hk, sd = s_lab[(t0 + t) * 32 + 8 * (i / 4) + 4 * half + (i % 4)] * diff;
-                e[i] = fmaf(-hk, hk, 1.f);
-                ae[i] = -c_sim * sd * e[i];
-                lsim = fmaf(sd, diff, lsim);
-                ssum += sd;
-            }
-            tr_bf16x8_t be[3], ba[3];
-            split_operand(e, ks, be);
-            split_operand(ae, ks, ba);
-#pragma unroll
-            for (int p = 0; p < 3; ++p) { b[p] = be[p]; b[3 + p] = ba[p]; }
-        };
-        prepare(0);
 #pragma unroll
         for (int round = 0; round < 2 * T; ++round) {
             __syncthreads();  // (what lay there has been read)
-#pragma unroll
-            for (int p = 0; p < 6; ++p) s_frag[(w * S::RG + rg) * 6 + p][lane] = __builtin_bit_cast(uint4, b[p]);
-            __syncthreads();
-            if (round + 1 < 2 * T) prepare(round + 1);
+            if constexpr (!decltype(one_vector)::value) {
+                if (round == 0) {
+                    xk.zero_past(row0, n);
+                    xk.put(tile);
+                }
+            }
+            hand_round();
+            if (round + 1 < 2 * T) prepare_keys(round + 1, one_vector);
 #pragma unroll
             for (int g = 0; g < G0; ++g) {
                 const tr_bf16x8_t x = rows_transposed((g0 + g) * T + round / 2, round % 2);
                 tr_f32x16_t& k = ke[g / S::HB];
 #pragma unroll
                 for (int p = 0; p < 3; ++p) {
-                    k = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, __builtin_bit_cast(tr_bf16x8_t, s_frag[(w * S::RG + g0 + g) * 6 + p][lane]), k, 0, 0, 0);
-                    dw = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, __builtin_bit_cast(tr_bf16x8_t, s_frag[(w * S::RG + g0 + g) * 6 + 3 + p][lane]), dw, 0, 0, 0);
+                    k = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, handed(g, p), k, 0, 0, 0);
+                    dw = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, handed(g, 3 + p), dw, 0, 0, 0);
                 }
             }
         }
     };
-    if (mixed) contract_keys(std::false_type{});
-    else contract_keys(std::true_type{});
+    if (mixed) {
+        auto prepare_queries = [&](int t) {  // 32 rows' dZ_q
+            tr_f32x16_t gq;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const float sd = s_lab[(t0 + t) * 32 + 8 * (i / 4) + 4 * half + (i % 4)] * (zq[t][i] - zk[t][i]);
+                gq[i] = c_sim * sd * fmaf(-zq[t][i], zq[t][i], 1.f);
+            }
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) {
+                tr_bf16x8_t bq[3];
+                split_operand(gq, ks, bq);
+#pragma unroll
+                for (int p = 0; p < 3; ++p) b[3 * ks + p] = bq[p];
+            }
+        };
+        xk.fetch(K, row0, n);  // (the tile's next content)
+        prepare_queries(0);
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            __syncthreads();
+            hand_round();
+            if (t + 1 < T) prepare_queries(t + 1);
+            else prepare_keys(0, std::false_type{});
+#pragma unroll
+            for (int g = 0; g < G0; ++g)
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks) {
+                    const tr_bf16x8_t x = rows_transposed((g0 + g) * T + t, ks);
+#pragma unroll
+                    for (int p = 0; p < 3; ++p) dw = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, handed(g, 3 * ks + p), dw, 0, 0, 0);
+                }
+        }
+        contract_keys(std::false_type{});
+    } else {
+        prepare_keys(0, std::true_type{});
+        contract_keys(std::true_type{});
+    }
     // (one query vector: its part of Q^T dZ_q is that vector times the sum over the rows, added behind the sums below)
     ssum += __shfl_xor(ssum, 32, 64);
     if (half == 0) s_dq[rg][w * 32 + m] = mixed ? 0.f : c_sim * ssum * fmaf(-hq0, hq0, 1.f);
@@ -544,12 +570,12 @@ __global__ __launch_bounds__(TrainShape<R>::THREADS) void train_grad_kernel(
         }
     }
     // (everybody has written s_col and s_loss: the rounds above have barriers)
-    for (int i = tid; i < 2 * S::COLS; i += THREADS) {
-        const int b = i / S::COLS, jc = i % S::COLS;
+    for (int i = tid; i < 2 * COLS; i += THREADS) {
+        const int b = i / COLS, jc = i % COLS;
         float t = 0.f;
 #pragma unroll
         for (int g = 0; g < S::HB; ++g) t += s_col[b * S::HB + g][jc];
-        if (first + b < n_blocks) colsum_part[(int64_t)(first + b) * R + blockIdx.y * 64 + jc] = t;
+        if (first + b < n_blocks) colsum_part[(int64_t)(first + b) * R + blockIdx.y * COLS + jc] = t;
     }
     if (tid == 0) {  // (the similarity partial of column group y; the groups are summed later)
         float t = 0.f;
@@ -570,7 +596,7 @@ __global__ __launch_bounds__(TrainShape<R>::THREADS) void train_grad_kernel(
 // share of the blocks each instead of all columns one after the other (one block 6.5 -> 5.8 us, at r = 256 12.7 -> 8.7;
 // 960 blocks of four queries, r = 32 15.6 -> 9.4, r = 128 17.1 -> 13.1).
 __global__ __launch_bounds__(TR_UPDATE_WAVES * 64) __attribute__((amdgpu_waves_per_eu(4, 4))) void train_update_kernel(
-    float* __restrict__ W, float* __restrict__ v, int log2_r, int n_blocks, float sigma, float lam, float c_sim, float c_bal,
+    float* __restrict__ W, float* __restrict__ v, int log2_r, int n_blocks, int n_loss, float sigma, float lam, float c_sim, float c_bal,
     float lr, float momentum, float weight_decay, const float* __restrict__ dw_part, const float* __restrict__ colsum_part,
     const float* __restrict__ colsum, const int32_t* __restrict__ block_group, int n_groups, const double* __restrict__ gram,
     const double* __restrict__ fro_part, const float* __restrict__ W_old, const float* __restrict__ loss_part,
@@ -721,9 +747,8 @@ __global__ __launch_bounds__(TR_UPDATE_WAVES * 64) __attribute__((amdgpu_waves_p
         return;
     }
     // similarity: sum of the workgroup partials; balance: squared norm of the column sums
-    const int parts = n_pairs * ((r + 63) / 64);
     float ls = 0.f, lb = 0.f;
-    for (int i = tid; i < parts; i += WAVES * 64) ls += loss_part[i];
+    for (int i = tid; i < n_loss; i += WAVES * 64) ls += loss_part[i];
     if (colsum) {
         for (int j = tid; j < r * n_groups; j += 16 * WAVES * 64) {
             float x[16];
@@ -950,7 +975,7 @@ int make_train_plan(const hata_train_config* f, TrainPlan* p) {
     p->off_cs = o;     o = align_up_t(o + (size_t)p->n_wgs_max * f->r * 4);
     const size_t pairs = ((size_t)p->n_wgs_max + 1) / 2;
     p->off_dw = o;     o = align_up_t(o + pairs * 3 * f->d * f->r * 4);
-    p->off_loss = o;   o = align_up_t(o + pairs * 4 * 4);
+    p->off_loss = o;   o = align_up_t(o + (pairs * 4 > TR_ONE_ROUND ? pairs * 4 : TR_ONE_ROUND) * 4);
     p->off_gram = o;   o = align_up_t(o + (size_t)f->d * f->d * 8);
     p->off_fro = o;    o = align_up_t(o + (size_t)f->d * 2 * 8);
     p->off_old = o;    o = align_up_t(o + (size_t)f->d * f->r * 4);
@@ -1025,28 +1050,33 @@ int hata_train_step(hata_train_ctx* ctx, const void* Q, const void* K, const flo
     const uint16_t* k = (const uint16_t*)K;
     const bool few = n_wgs <= TR_FEW_WGS && n_queries <= TR_FEW_QUERIES;
     const float* colsum = few ? nullptr : ctx->colsum;
-    // workgroups of the gradient launch in a column group: a pair of blocks each, and at least a piece of W W^T each
-    const int col_groups = r < 64 ? 1 : r / 64, pairs = (n_wgs + 1) / 2;
+    // The gradient launch: a workgroup per pair of blocks and 64 hash columns, or 32 where it all goes in one round of the chip
+    // then, which a narrower workgroup is through sooner (us a step, one query vector a block / others: one block r = 64 20.3 / 26.4 ->
+    // 16.6 / 19.5, r = 256 24.3 / 30.1 -> 20.2 / 23.0; 64 blocks r = 128 23.5 / 29.1 -> 19.9 / 22.6; 256 blocks r = 64 24.1 / 29.9 -> 20.8 / 24.3).  At least a piece of W W^T each: workgroups behind the pairs have
+    // nothing else.
+    const int pairs = (n_wgs + 1) / 2, cols = r == 32 || pairs * (r / 32) <= TR_ONE_ROUND ? 32 : 64, col_groups = r / cols;
     const int n_grad = pairs * col_groups < 2 * HATA_D ? 2 * HATA_D / col_groups : pairs;
-#define HATA_TRAIN_LAUNCH(RR)                                                                          \
-    do {                                                                                               \
-        using S = hata::TrainShape<RR>;                                                                \
-        hipLaunchKernelGGL((hata::train_grad_kernel<RR>), dim3(n_grad, RR / S::COLS),                  \
-                           dim3(S::THREADS), 0, st, q, k, s, W, n, n_wgs, hp->sigma, c_sim,            \
-                           block_query, n_queries, ctx->dw_part, ctx->colsum_part, ctx->loss_part,     \
-                           ctx->gram, ctx->fro_part, ctx->W_old);                                      \
-        if (!few)                                                                                      \
-            hipLaunchKernelGGL(hata::train_colreduce_kernel, dim3((RR + 63) / 64, n_queries), dim3(TR_REDUCE_WAVES * 64), 0, st,    \
-                               ctx->colsum_part, RR, n_wgs, block_query, n_queries, ctx->colsum);      \
-    } while (0)
+#define HATA_TRAIN_GRAD(RR, CC)                                                                                          \
+    hipLaunchKernelGGL((hata::train_grad_kernel<RR, CC>), dim3(n_grad, RR / CC), dim3(hata::TrainShape<CC>::THREADS), 0, \
+                       st, q, k, s, W, n, n_wgs, hp->sigma, c_sim, block_query, n_queries, ctx->dw_part,                 \
+                       ctx->colsum_part, ctx->loss_part, ctx->gram, ctx->fro_part, ctx->W_old)
+#define HATA_TRAIN_CASE(RR)                          \
+    case RR:                                         \
+        if (cols == 32) HATA_TRAIN_GRAD(RR, 32);     \
+        else HATA_TRAIN_GRAD(RR, 64);                \
+        break
     switch (r) {
-        case 32: HATA_TRAIN_LAUNCH(32); break;
-        case 64: HATA_TRAIN_LAUNCH(64); break;
-        case 128: HATA_TRAIN_LAUNCH(128); break;
-        default: HATA_TRAIN_LAUNCH(256); break;
+        case 32: HATA_TRAIN_GRAD(32, 32); break;
+        HATA_TRAIN_CASE(64);
+        HATA_TRAIN_CASE(128);
+        HATA_TRAIN_CASE(256);
     }
-#undef HATA_TRAIN_LAUNCH
-    hipLaunchKernelGGL(hata::train_update_kernel, dim3(HATA_D * r / 64 + (loss ? 1 : 0)), dim3(TR_UPDATE_WAVES * 64), 0, st, W, v, __builtin_ctz(r), n_wgs,
+#undef HATA_TRAIN_CASE
+#undef HATA_TRAIN_GRAD
+    if (!few)
+        hipLaunchKernelGGL(hata::train_colreduce_kernel, dim3((r + 63) / 64, n_queries), dim3(TR_REDUCE_WAVES * 64), 0, st,
+                           ctx->colsum_part, r, n_wgs, block_query, n_queries, ctx->colsum);
+    hipLaunchKernelGGL(hata::train_update_kernel, dim3(HATA_D * r / 64 + (loss ? 1 : 0)), dim3(TR_UPDATE_WAVES * 64), 0, st, W, v, __builtin_ctz(r), n_wgs, pairs * col_groups,
                        hp->sigma, hp->lam, c_sim, c_bal, hp->lr, hp->momentum, hp->weight_decay, ctx->dw_part,
                        ctx->colsum_part, colsum, block_query, n_queries, ctx->gram, ctx->fro_part, ctx->W_old,
                        ctx->loss_part, grad, loss);
