@@ -95,6 +95,7 @@ struct TrainShape {
     static constexpr int RG = WAVES / CG;            // row groups
     static constexpr int HB = RG / 2;                // of a block
     static constexpr int TILES = TR_PAIR / 32 / RG;  // 32-row tiles of a wave
+    static constexpr int COL_ROWS = WAVES > THREADS / COLS ? WAVES : THREADS / COLS;  // rows of per-column sums: for any split over waves or threads (the row groups have one each)
 };
 
 // rows [row0, row0 + TR_PAIR) of X [n, 128] (row0 < n): fetched into registers -- past n the last row, so that no load
@@ -294,7 +295,7 @@ __global__ __launch_bounds__(TrainShape<COLS>::THREADS) void train_grad_kernel(
     __shared__ __attribute__((aligned(16))) uint4 s_frag[48][64];
     static_assert(S::CG * 3 * 8 <= 48 && S::CG * S::RG * 6 <= 48, "fragments");
     __shared__ float s_lab[TR_PAIR];
-    __shared__ float s_col[S::RG][COLS];  // per hash column: sums of h(k_n) over a row group
+    __shared__ float s_col[S::COL_ROWS][COLS];  // per hash column: sums of h(k_n) over a row group
     __shared__ float s_dq[S::RG][COLS];  // sums of dZ_q
     __shared__ float s_loss[WAVES];
     __shared__ double s_red[WAVES];
