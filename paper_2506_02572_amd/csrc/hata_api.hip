@@ -167,7 +167,7 @@ inline int coop_sub_batches(const hata_ctx* c, int B, bool paged, int* chunk_out
         const int n_chunks = (c->cfg.L_cap + chunk - 1) / chunk;
         const int cap = paged ? c->coop_opt_cap_paged[o] : c->coop_opt_cap[o];
         const int64_t per_seq = (int64_t)n_chunks * c->cfg.Hkv;
-        if (n_chunks > 256 || cap <= 0 || per_seq > cap) continue;
+        if (n_chunks > HATA_COOP_CHUNKS || cap <= 0 || per_seq > cap) continue;
         int ns;
         // mode 1: the whole batch in one grid, whatever its size, if the workgroups of the units that
         // are at work together -- eight units interleaved when their number is a multiple of eight,

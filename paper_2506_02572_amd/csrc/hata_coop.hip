@@ -1195,6 +1195,7 @@ hipError_t launch_coop_step(const hata_ctx* c, const void* q, const void* K, con
     const void* fn = coop_kernel_for(c->Wd, c->G, pages != nullptr, chunk > HATA_COOP_SUB);
     if (!fn || !coop_shape_ok(c, pages != nullptr, chunk) || chunk < c->chunk) return hipErrorNotSupported;
     const int n_chunks = (f.L_cap + chunk - 1) / chunk;  // (the workspace regions are sized for c->n_chunks >= n_chunks)
+    if (n_chunks > HATA_COOP_CHUNKS) return hipErrorNotSupported;  // (and what the workgroups hand each other for so many)
     CoopArgs a;
     a.q = (const uint16_t*)q; a.K = (const uint16_t*)K; a.V = (const uint16_t*)V;
     a.W_H = W_H; a.append = append;
@@ -1229,7 +1230,7 @@ hipError_t launch_coop_step(const hata_ctx* c, const void* q, const void* K, con
     a.scores = c->scores + u0 * f.L_cap; a.idx = (idx_only ? idx_only : c->idx) + u0 * f.k_max;
     a.cum_pitch = coop_cum_pitch(c->n_chunks, c->NBP);
     a.qrec_pitch = c->n_chunks * c->G * c->Wd;
-    a.cum_marks = c->n_chunks * (c->NBP / 2);
+    a.cum_marks = coop_rows(c->n_chunks) * (c->NBP / 2);
     a.mark_pitch = coop_mark_pitch(c->n_chunks);
     a.cum = c->coop_cum + u0 * a.cum_pitch;
     a.unit_epoch = c->unit_epoch + u0 * HATA_COUNTER_STRIDE;

@@ -112,10 +112,13 @@ hipError_t launch_coop_step(const hata_ctx* c, const void* q, const void* K, con
 // (chunk: keys per workgroup, one of the context's coop_opt_chunk; idx_only != nullptr: the launch
 // stops once the index lists are written, into idx_only [B, Hkv, k_max] instead of the workspace;
 // V, out and out_f32 are not touched)
-// marks of one reading chunk (whole cache lines; the step runs with at most 256 chunks per unit), and 64-bit words of a
-// unit's whole part of coop_cum: the chunks' rows, then the marks
-inline int coop_mark_pitch(int n_chunks) { return ((n_chunks < 256 ? n_chunks : 256) + 31) / 32 * 32; }
-inline int coop_cum_pitch(int n_chunks, int NBP) { return n_chunks * (NBP / 2) + (n_chunks < 256 ? n_chunks : 256) * coop_mark_pitch(n_chunks) / 2; }
+// The single-launch step runs with at most HATA_COOP_CHUNKS chunks per unit, whatever the plan's chunk (on which the other kernels have
+// up to 1024): marks of one reading chunk (whole cache lines), and 64-bit words of a unit's whole part of coop_cum: the chunks' rows,
+// then the marks
+#define HATA_COOP_CHUNKS 256
+inline int coop_rows(int n_chunks) { return n_chunks < HATA_COOP_CHUNKS ? n_chunks : HATA_COOP_CHUNKS; }
+inline int coop_mark_pitch(int n_chunks) { return (coop_rows(n_chunks) + 31) / 32 * 32; }
+inline int coop_cum_pitch(int n_chunks, int NBP) { return coop_rows(n_chunks) * (NBP / 2 + coop_mark_pitch(n_chunks) / 2); }
 // the step with a workgroup per (sequence, KV head) unit: caches of up to HATA_UNIT_KEYS_LONG rows, of up to HATA_UNIT_KEYS by
 // a form of its own
 #define HATA_UNIT_KEYS 4096

@@ -134,3 +134,33 @@ def test_chunk_goes_by_residency_alone(B, Hkv, L_cap):
     ctx = hata.Context(B, 32, Hkv, 128, 128, L_cap, 512)
     assert ctx.hata_step_plan(B) == (1, 4096, L_cap // 4096) and ctx.hata_step_sub_batches(B) == 1
     ctx.close()
+
+
+def test_plan_with_more_chunks_than_the_step_runs_with():
+    """1.1M rows are 269 chunks of the plan and fewer of the single-launch step: the same rows as three launches select."""
+    import torch
+    from paper_2506_02572_amd import hata
+    L, Hkv, G, r, k_max = 1_100_000, 2, 4, 64, 700
+    print(f"[launches] {L} rows", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    K = torch.randn((1, Hkv, L, 128), dtype=torch.bfloat16, device="cuda", generator=g)
+    q = torch.randn((1, Hkv * G, 128), dtype=torch.bfloat16, device="cuda", generator=g)
+    W = torch.randn((Hkv, 128, r), device="cuda", generator=g)
+    codes = torch.randint(-2**31, 2**31 - 1, (1, Hkv, L, r // 32), dtype=torch.int32, device="cuda", generator=g)
+    k = H.to_dev(np.array([k_max], np.int32))
+    ctx = hata.Context(1, Hkv * G, Hkv, 128, r, L, k_max)
+    assert -(-L // 4096) > 256 >= ctx.hata_step_plan(1)[2] > 1 and ctx.hata_step_plan(1)[0] == 1
+    for rows in (L, L - 70_001, 5):
+        seq = H.to_dev(np.array([rows], np.int32))
+        got = []
+        for mode in (0, 3):
+            ctx.hata_set_step_mode(mode)
+            out = torch.zeros((1, Hkv * G, 128), dtype=torch.float32, device="cuda")
+            for _ in range(2):
+                ctx.hata_decode_step(q, K, K, W, codes, seq, k, 1, False, SCALE, torch.empty_like(q), out)
+            ctx.hata_check()
+            got.append((H.to_host(ctx.hata_step_buffers()[2]).copy(), out))
+        assert np.array_equal(got[0][0], got[1][0])
+        # (fp32 sums in another order, weights of 16 bits or more: hata_attn_core.h)
+        assert torch.allclose(got[0][1], got[1][1], rtol=1e-3, atol=1e-4)
+    ctx.close()

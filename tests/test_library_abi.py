@@ -47,6 +47,19 @@ def test_trainer_symbols_are_exported_and_bound():
     assert lib.hata_train_destroy(None) == 0
 
 
+def test_workspace_of_long_caches():
+    """What the single-launch step exchanges is laid out for the 256 chunks it runs with, however many the plan has: from 1M to
+    4M rows the workspace grows by scores, histograms, partial results and query codes alone (104 MB here, 155 with it)."""
+    lib = hata.load_library()
+    n = []
+    for rows in (1 << 20, 1 << 22):
+        b = ctypes.c_size_t(0)
+        cfg = hata.hata_config(1, 64, 8, 128, 256, rows, 2048, 8 * rows * 128, rows * 128, 128)
+        assert lib.hata_workspace_bytes(ctypes.byref(cfg), ctypes.byref(b)) == 0
+        n.append(b.value)
+    assert n[1] - n[0] < 120e6
+
+
 def test_strerror_and_workspace_validation():
     lib = hata.load_library()
     assert hata.strerror(0) == "ok"
