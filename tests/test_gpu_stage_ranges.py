@@ -88,6 +88,8 @@ def test_chunk_owned_attention(L, k_max, chunk, heads):
     w = synth.Workload("chunks", B, Hq, Hkv, 128, 64, (L, max(1, L // 3)), (k_max, max(1, k_max // 2)), k_max=k_max)
     print(f"[stages] attention L={L} k={k_max} chunk={chunk} heads={heads}", flush=True)
     c = H.Case(w, shared_device=True, chunk=chunk)
+    c.ctx.hata_set_step_mode(3)
+    assert c.ctx.hata_step_plan(B)[0] == 3
     q = c.inp.q()
     for clustered in (False, True):
         codes = c.codes_ref.copy()
@@ -330,6 +332,8 @@ def test_selected_rows_of_one_chunk_in_pieces(L, k_max, chunk, heads):
     w = synth.Workload("pieces", B, Hq, Hkv, 128, 64, (L, max(1, L // 3), 5), (k_max, max(1, k_max // 2), 3), k_max=k_max)
     print(f"[stages] pieces L={L} k={k_max} chunk={chunk} heads={heads}", flush=True)
     c = H.Case(w, shared_device=True, chunk=chunk)
+    c.ctx.hata_set_step_mode(3)
+    assert c.ctx.hata_step_plan(B)[0] == 3
     q = c.inp.q()
     qc, _ = O.encode_query_batch(q, c.inp.W_H)
     near = qc.reshape(B, Hkv, Hq // Hkv, -1)[:, :, :1]

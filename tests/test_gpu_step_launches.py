@@ -164,3 +164,51 @@ def test_plan_with_more_chunks_than_the_step_runs_with():
         # (fp32 sums in another order, weights of 16 bits or more: hata_attn_core.h)
         assert torch.allclose(got[0][1], got[1][1], rtol=1e-3, atol=1e-4)
     ctx.close()
+
+
+@pytest.mark.parametrize("form,heads,r", [
+    (f, h, r) for f in ("waits", "waits_large_chunks", "waits_one_grid", "paged", "three_launches", "unit")
+    for h, r in (((4, 4), 128), ((10, 2), 64), ((16, 2), 256), ((16, 1), 128))
+    if f != "unit" or h != (16, 1)])  # (no workgroup per unit for groups of sixteen)
+def test_empty_sequences_and_budgets_in_every_form(form, heads, r):
+    """Sequences without rows and budgets of none beside others, twice over: the second step finds what the first one left."""
+    import torch
+    from paper_2506_02572_amd import hata
+    from tests.test_gpu_paged import make_table, scatter
+    (Hq, Hkv), k_max, page_rows = heads, 90, 64
+    print(f"[launches] empty, {form} heads={heads} r={r}", flush=True)
+    seq, k = np.array([0, 3900, 1, 2050, 0, 1024], np.int32), np.array([5, 0, 7, 90, 0, 3], np.int32)
+    B, L = len(seq), 3900
+    rng = np.random.default_rng(r + Hq)
+    K, V = (synth.round_to_bf16_bits(rng.standard_normal((B, Hkv, L, 128))) for _ in range(2))
+    W = rng.standard_normal((Hkv, 128, r)).astype(np.float32)
+    codes = rng.integers(0, 2**32, (B, Hkv, L, r // 32), dtype=np.uint32)
+    ctx = hata.Context(B, Hq, Hkv, 128, r, L, k_max, chunk={"waits_large_chunks": 16384, "unit": 0, "three_launches": 0}.get(form, 1024))
+    ctx.hata_set_step_mode({"waits_one_grid": 1, "three_launches": 3}.get(form, 0))
+    launches, _, chunks = ctx.hata_step_plan(B)
+    assert launches == (3 if form == "three_launches" else 1) and (chunks == 1) == (form in ("unit", "waits_large_chunks"))
+    cache = [H.to_dev(x) for x in (K, V, W, codes)]
+    call = ctx.hata_decode_step
+    if form == "paged":
+        table, max_blocks, n_pages, blocks = make_table(rng, seq, page_rows)
+        pools = []
+        for x in (K, V, codes):
+            pool = np.zeros((n_pages, Hkv, page_rows, x.shape[-1]), x.dtype)
+            scatter(pool, x, table, blocks, page_rows, seq)
+            pools.append(H.to_dev(pool))
+        cache = [pools[0], pools[1], cache[2], pools[2], H.to_dev(table), max_blocks, page_rows, n_pages]
+        call = ctx.hata_decode_step_paged
+    out = torch.zeros((B, Hq, 128), dtype=torch.int16, device="cuda")
+    out32 = torch.zeros((B, Hq, 128), dtype=torch.float32, device="cuda")
+    for turn, order in enumerate((np.arange(B), np.arange(B), np.arange(B)[::-1])):
+        # (the lengths change places in the last turn: units that had rows have none, and the other way round)
+        s2, k2 = (seq, k) if form == "paged" else (seq[order], k[order])
+        q = synth.round_to_bf16_bits(rng.standard_normal((B, Hq, 128)))
+        ref = O.decode_step(q, K, V, W, codes.copy(), s2, k2, k_max, SCALE, append=False)
+        out32.fill_(float("nan"))
+        call(H.to_dev(q), *cache, H.to_dev(s2), H.to_dev(k2), B, False, SCALE, out, out32)
+        ctx.hata_check()
+        assert np.array_equal(H.to_host(ctx.hata_step_buffers()[0], np.uint32), ref["qcodes"])
+        assert np.array_equal(H.to_host(ctx.hata_step_buffers()[2]), ref["idx"])
+        H.check_attention(H.to_host(out32), H.to_host(out, np.uint16), ref["out"], form)
+    ctx.close()

@@ -171,3 +171,52 @@ def test_paged_step_knows_no_modes(mode, L_cap):
     assert np.array_equal(H.to_host(ctx.hata_step_buffers()[2]), ref["idx"])
     H.check_attention(H.to_host(out32), H.to_host(out, np.uint16), ref["out"], "paged unit step")
     ctx.close()
+
+
+@pytest.mark.parametrize("L_cap", [8193, 12000, 16384])
+@pytest.mark.parametrize("G,r", [(1, 128), (4, 256), (5, 128), (8, 256), (8, 128), (4, 128)])
+@pytest.mark.parametrize("ties", [False, True])
+@pytest.mark.parametrize("page_rows", [0, 64])
+def test_unit_step_of_long_caches(L_cap, G, r, ties, page_rows):
+    """Sixteen keys a thread, in both layouts: 128 sequences over the rows of one cache, two of them against the oracle."""
+    import torch
+    from paper_2506_02572_amd import hata
+    B, k_max, look = 128, 500, [0, 127]
+    print(f"[unit] long L_cap={L_cap} G={G} r={r} ties={ties} page_rows={page_rows}", flush=True)
+    rng = np.random.default_rng(L_cap + G + r)
+    seq, k = rng.integers(1, L_cap + 1, B).astype(np.int32), rng.integers(0, k_max + 1, B).astype(np.int32)
+    seq[look], k[look] = (L_cap, L_cap - 1030), (k_max, 77)
+    K, V = (synth.round_to_bf16_bits(rng.standard_normal((1, 1, L_cap, 128))) for _ in range(2))
+    q = synth.round_to_bf16_bits(rng.standard_normal((B, G, 128)))
+    W = rng.standard_normal((1, 128, r)).astype(np.float32)
+    codes = rng.integers(0, 2**32, (1, 1, L_cap, r // 32), dtype=np.uint32)
+    if ties:
+        codes = codes[:, :, rng.integers(0, 2, L_cap)]
+    ctx = hata.Context(B, G, 1, 128, r, L_cap, k_max, kv_strides=(0, 0, 128), shared_device=True)
+    assert ctx.hata_step_plan(B)[0] == 1 and ctx.hata_step_plan(B)[2] == 1
+    ctx.hata_keep_step_scores(True)
+    out = torch.zeros((B, G, 128), dtype=torch.int16, device="cuda")
+    out32 = torch.full((B, G, 128), float("nan"), dtype=torch.float32, device="cuda")
+    if page_rows:
+        table, max_blocks, n_pages, blocks = make_table(rng, [L_cap], page_rows)
+        pools = []
+        for x in (K, V, codes):
+            pool = np.zeros((n_pages, 1, page_rows, x.shape[-1]), x.dtype)
+            scatter(pool, x, table, blocks, page_rows, [L_cap])
+            pools.append(H.to_dev(pool))
+        ctx.hata_decode_step_paged(H.to_dev(q), pools[0], pools[1], H.to_dev(W), pools[2], H.to_dev(np.repeat(table, B, 0)), max_blocks,
+                                   page_rows, n_pages, H.to_dev(seq), H.to_dev(k), B, False, SCALE, out, out32)
+    else:
+        ctx.hata_decode_step(H.to_dev(q), H.to_dev(K), H.to_dev(V), H.to_dev(W), H.to_dev(np.repeat(codes, B, 0)), H.to_dev(seq),
+                             H.to_dev(k), B, False, SCALE, out, out32)
+    torch.cuda.synchronize()
+    two = [np.repeat(x, 2, 0) for x in (K, V, codes)]
+    ref = O.decode_step(q[look], two[0], two[1], W, two[2], seq[look], k[look], k_max, SCALE, append=False)
+    qc, sc, ix = ctx.hata_step_buffers()
+    assert np.array_equal(H.to_host(qc, np.uint32)[look], ref["qcodes"])
+    for i, b in enumerate(look):
+        assert np.array_equal(H.to_host(sc[b], np.uint16)[:, :seq[b]].astype(np.int32), ref["scores"][i, :, :seq[b]])
+    assert np.array_equal(H.to_host(ix)[look], ref["idx"])
+    H.check_attention(H.to_host(out32)[look], H.to_host(out, np.uint16)[look], ref["out"], "long unit step")
+    assert not torch.isnan(out32).any()
+    ctx.close()
