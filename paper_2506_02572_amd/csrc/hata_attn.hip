@@ -138,17 +138,17 @@ __global__ __launch_bounds__(256) void attn_kernel(const AttnArgs a) {
             const uint16_t* hw = hu + min(w0 + 2 * (lane & 31), a.NBP - 2);
             uint32_t sum[6] = {0, 0, 0, 0, 0, 0};
             constexpr int UN = 8;
-            for (int r2 = 2 * wv; r2 < nc; r2 += 8 * UN) {
-                const int r0 = r2 + (lane >> 5);
-                uint32_t x[UN];
+            auto request = [&](uint32_t (&x)[UN], int r2) {
 #pragma unroll
                 for (int j = 0; j < UN; ++j) {
                     x[j] = 0;
-                    if (r2 + 8 * j < nc) x[j] = *reinterpret_cast<const uint32_t*>(hw + (int64_t)min(r0 + 8 * j, nc - 1) * a.NBP);
+                    if (r2 + 8 * j < nc) x[j] = *reinterpret_cast<const uint32_t*>(hw + (int64_t)min(r2 + (lane >> 5) + 8 * j, nc - 1) * a.NBP);
                 }
+            };
+            auto add = [&](const uint32_t (&x)[UN], int r2) {
 #pragma unroll
                 for (int j = 0; j < UN; ++j) {
-                    const int c = r0 + 8 * j;
+                    const int c = r2 + (lane >> 5) + 8 * j;
                     const uint32_t lo = x[j] & 0xffffu, hi = x[j] >> 16;
                     sum[0] += c < nc ? lo : 0u;
                     sum[1] += c < nc ? hi : 0u;
@@ -157,6 +157,14 @@ __global__ __launch_bounds__(256) void attn_kernel(const AttnArgs a) {
                     sum[4] += c >= c0 && c < c1 ? lo : 0u;
                     sum[5] += c >= c0 && c < c1 ? hi : 0u;
                 }
+            };
+            for (int r2 = 2 * wv; r2 < nc; r2 += 16 * UN) {  // (the 65th row is no round trip of its own)
+                uint32_t x[UN], y[UN];
+                request(x, r2);
+                const bool more = r2 + 8 * UN < nc;
+                if (more) request(y, r2 + 8 * UN);
+                add(x, r2);
+                if (more) add(y, r2 + 8 * UN);
             }
             if (it == 0 && owner) stage_scores(split * span, min(span, L - split * span));  // (behind the first window's loads)
             if (it) __syncthreads();  // (the last window has been read)

@@ -780,8 +780,15 @@ void decode_step_coop_kernel(const CoopArgs a) {
                     // unit polling the same marks made everything else that went to those lines' channel wait.)
                     if (wv == 0) {
                         for (;;) {
+                            uint32_t mk[HATA_COOP_CHUNKS / 64];  // (requested together)
+#pragma unroll
+                            for (int j = 0; j < HATA_COOP_CHUNKS / 64; ++j) {
+                                mk[j] = epoch;
+                                if (64 * j < nc) mk[j] = ld_dev(marks + min(lane + 64 * j, nc - 1));
+                            }
                             bool absent = false;
-                            for (int m = lane; m < nc; m += 64) absent |= ld_dev(marks + m) != epoch;
+#pragma unroll
+                            for (int j = 0; j < HATA_COOP_CHUNKS / 64; ++j) absent |= mk[j] != epoch;
                             if (__builtin_amdgcn_ballot_w64(absent) == 0ull || --budget <= 0) break;
                             __builtin_amdgcn_s_sleep(1);
                         }
@@ -794,15 +801,16 @@ void decode_step_coop_kernel(const CoopArgs a) {
                 bool miss = false;
                 uint32_t sum[4] = {0, 0, 0, 0};  // columns 0 and 1 of all chunks, of those before this one
                 constexpr int UN = 8;
-                for (int r2 = 2 * wv; r2 < nc; r2 += 8 * UN) {
-                    const int r0 = r2 + (lane >> 5);
-                    unsigned long long x[UN];
+                auto request = [&](unsigned long long (&x)[UN], int r2) {
 #pragma unroll
                     for (int j = 0; j < UN; ++j) {
                         x[j] = (unsigned long long)epoch << 32;
                         if (r2 + 8 * j < nc)
-                            x[j] = __hip_atomic_load(hw + min(r0 + 8 * j, nc - 1) * (a.NBP / 2), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            x[j] = __hip_atomic_load(hw + min(r2 + (lane >> 5) + 8 * j, nc - 1) * (a.NBP / 2), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     }
+                };
+                auto add = [&](const unsigned long long (&x)[UN], int r2) {
+                    const int r0 = r2 + (lane >> 5);
 #pragma unroll
                     for (int j = 0; j < UN; ++j) {
                         const uint32_t lo = (uint32_t)x[j] & 0xffffu, hi = (uint32_t)x[j] >> 16;
@@ -813,6 +821,14 @@ void decode_step_coop_kernel(const CoopArgs a) {
                         sum[2] += before ? lo : 0u;
                         sum[3] += before ? hi : 0u;
                     }
+                };
+                for (int r2 = 2 * wv; r2 < nc; r2 += 16 * UN) {  // (the 65th row is no round trip of its own)
+                    unsigned long long x[UN], y[UN];
+                    request(x, r2);
+                    const bool more = r2 + 8 * UN < nc;
+                    if (more) request(y, r2 + 8 * UN);
+                    add(x, r2);
+                    if (more) add(y, r2 + 8 * UN);
                 }
                 if (__builtin_amdgcn_ballot_w64(miss) != 0ull && lane == 0) s_miss = attempt;
                 U.sel.win[wv][lane] = make_uint4(sum[0], sum[1], sum[2], sum[3]);
