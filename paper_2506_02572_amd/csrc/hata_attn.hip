@@ -103,7 +103,9 @@ __global__ __launch_bounds__(256) void attn_kernel(const AttnArgs a) {
         const int per = a.chunks_per_split, span = per * a.chunk, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
         const uint16_t* hu = a.cum + u * a.n_chunks * a.NBP;
         const bool owner = split < a.owners;
-        const int estimate = a.estimate[u * a.n_chunks + (owner ? min(split * per, a.n_chunks - 1) : 0)];
+        const int c0 = owner ? split * per : 0;  // the owner's first chunk (a further piece looks from chunk 0)
+        const int32_t* estimates = a.estimate + u * a.n_chunks + min(c0, a.n_chunks - 1);
+        const int estimate_own = estimates[0], estimate_before = estimates[c0 > 0 && a.n_chunks > 1 ? -1 : 0];
         const int L = clampi(a.seq_len[b], 0, a.L_cap), keff = min(clampi(a.count_src[b], 0, a.k_max), L);
         const int nc = (L + a.chunk - 1) >> __builtin_ctz(a.chunk);
         const int live = (L + span - 1) >> __builtin_ctz(span);      // owners with keys
@@ -114,7 +116,7 @@ __global__ __launch_bounds__(256) void attn_kernel(const AttnArgs a) {
             if (L == 0) zero_output();
         }
         if (owner ? split >= live : live == 0) return;
-        const int c0 = owner ? split * per : 0, c1 = min(c0 + per, nc);  // the owner's chunks (a further piece looks from chunk 0)
+        const int c1 = min(c0 + per, nc);  // past the owner's last chunk
         auto stage_scores = [&](int base, int n_keys) {
             const uint16_t* sp = a.scores + u * a.L_cap + base;
             const bool whole = (reinterpret_cast<uintptr_t>(sp) & 15) == 0;
@@ -129,6 +131,8 @@ __global__ __launch_bounds__(256) void attn_kernel(const AttnArgs a) {
         // The threshold T lies in [t_lo, t_hi]; a window of 64 columns shows it if the first of them counts fewer than keff keys (or
         // is score 0) and the last one at least keff.  The next window is beside it, the ones after that halve what is left.
         const int w0_max = max(0, a.NBP - 64);
+        // (a last chunk of a few keys knows nothing of the unit: the chunk before does)
+        const int estimate = 8 * (L - c0 * a.chunk) < a.chunk ? estimate_before : estimate_own;
         int t_lo = 0, t_hi = a.NBP - 1, w0 = keff == 0 ? 0 : clampi((estimate - 32) & ~1, 0, w0_max);
         int T = 0, need = 0, off = 0, take = 0, cnt = 0;
         bool found = false;

@@ -29,6 +29,8 @@
 // The waits need every workgroup of a unit to be running; the host launches this kernel
 // only when the whole grid can be resident at once.  The wait is bounded anyway: a workgroup that
 // gives up sets the context's error word and runs to its end, so every wave always terminates.
+#include <type_traits>
+
 #include "hata_attn_core.h"
 #include "hata_device.h"
 #include "hata_internal.h"
@@ -54,6 +56,10 @@ __device__ __forceinline__ uint32_t divide(uint32_t x, Divisor by, uint32_t& res
     return q;
 }
 
+// A mark: the low bits of the launch's number above the chunk's estimate of the threshold.  (It only tells when to look -- the rows carry
+// the whole number -- so that one of 2^20 launches before is looked at in vain.)
+constexpr int MARK_BITS = 12;
+
 struct CoopArgs {
     const uint16_t* q;
     const uint16_t* K;
@@ -66,7 +72,7 @@ struct CoopArgs {
     uint16_t* scores;
     int32_t* idx;
     unsigned long long* cum;  // [units, cum_pitch], a chunk's row NBP / 2 words: cumulative chunk histograms, two scores and the unit's epoch a word
-    int cum_marks, mark_pitch;  // where a unit's marks begin, a row of them per reading chunk: the epoch too, stored behind a chunk's row for every other chunk (they tell when to look)
+    int cum_marks, mark_pitch;  // where a unit's marks begin, a row of them per reading chunk: a word stored behind a chunk's row for every other chunk (MARK_BITS)
     uint32_t* unit_epoch;
     unsigned long long* qrec;   // [units, qrec_pitch], a chunk's copy G * WD words: the unit's query code words, its epoch in the upper half
     int cum_pitch, qrec_pitch;  // (the same for every chunk size: what a unit's words hold was stamped with that unit's epoch)
@@ -648,10 +654,11 @@ void decode_step_coop_kernel(const CoopArgs a) {
             }
         }
     }
-    if (publishes && tid < nc)  // (at most 256 chunks)
-        st_dev(reinterpret_cast<uint32_t*>(a.cum + u * a.cum_pitch + a.cum_marks) + tid * a.mark_pitch + c, epoch);
     TC(42);
     if constexpr (!WIDE) __syncthreads();
+    static_assert(NB <= 1 << MARK_BITS, "a mark carries an estimate");
+    if (publishes && tid < nc)  // (at most 256 chunks)
+        st_dev(reinterpret_cast<uint32_t*>(a.cum + u * a.cum_pitch + a.cum_marks) + tid * a.mark_pitch + c, epoch << MARK_BITS | (uint32_t)s_est);
     // query fragments for the attention: in flight across the wait below
     uint32_t qr[MFMA ? 1 : G][4];
     uint4 qb[4];
@@ -759,6 +766,51 @@ void decode_step_coop_kernel(const CoopArgs a) {
         // widely; the next one is beside it, the ones after that halve what is left.
         const int w0_max = max(0, a.NBP - 64);
         int t_lo = 0, t_hi = NB - 1, w0 = keff == 0 ? 0 : clampi((s_est - 32) & ~1, 0, w0_max);
+        // With many chunks the rows are too much to be read in vain; otherwise they are mostly there by now.  At most
+        // one workgroup per CU: they start together, and up to 32 rows are tried at once (8 layers of 32768 keys 108.4 us,
+        // with the marks first 112; beyond, the marks).  More of them start one after the other, and what they read in
+        // vain is in the way of the last: wide rows are tried up to 12 chunks (group of eight, 2 layers of 3 x 117252
+        // keys, 29 chunks: tried 61.7, marks 58.2; 3 x 40000, 20 chunks: 41.8 and 38.4; the search before it was 58.6 and
+        // 42.3), narrow ones up to 24 (32 heads of their own, 131072 keys, 32 chunks: 60.5 and 58.4;
+        // 100000, 25 chunks: the same; 16384, 16 chunks, four layers: 51.8 and 53.3).
+        int tried = a.prefetch ? 32 : WIDE ? 12 : 24;
+        // One wave waits for the marks the chunks leave behind their rows, on lines that no other workgroup reads.
+        // (Polling with the loads of the rows kept a compute unit's memory pipe so busy that the youngest
+        // workgroup on it -- the one everybody waited for -- never got to its own; all workgroups of a
+        // unit polling the same marks made everything else that went to those lines' channel wait.)
+        auto wait_for_marks = [&](auto with_estimate) {
+            if (wv == 0) {
+                for (;;) {
+                    uint32_t mk[HATA_COOP_CHUNKS / 64];  // (requested together)
+                    int n = nc;
+                    asm volatile("" : "+s"(n));  // (the comparisons here, not in front of the search in two scalar registers each)
+#pragma unroll
+                    for (int j = 0; j < HATA_COOP_CHUNKS / 64; ++j) {
+                        mk[j] = epoch << MARK_BITS;
+                        if (64 * j < n) mk[j] = ld_dev(marks + min(lane + 64 * j, n - 1));
+                    }
+                    bool absent = false;
+#pragma unroll
+                    for (int j = 0; j < HATA_COOP_CHUNKS / 64; ++j) absent |= (mk[j] ^ epoch << MARK_BITS) >> MARK_BITS != 0;
+                    if constexpr (decltype(with_estimate)::value) {
+                        const uint32_t m = c <= 64 ? mk[0] : c <= 128 ? mk[1] : c <= 192 ? mk[2] : mk[3];
+                        if (lane == ((c - 1) & 63)) s_est = (int)(m & ((1u << MARK_BITS) - 1));
+                    }
+                    if (__builtin_amdgcn_ballot_w64(absent) == 0ull || --budget <= 0) break;
+                    __builtin_amdgcn_s_sleep(1);
+                }
+                if (--budget <= 0 && lane == 0) { a.error_word[0] = 1u; s_bad = 1; s_quit = attempt + 1; }  // gave up: this launch's results are invalid
+            }
+            __syncthreads();
+        };
+        // A last chunk of a few keys knows nothing of the unit: it takes the estimate of the chunk before, which comes
+        // with that one's mark (beginning around its own, it needed several windows and everyone waited for it: 131074 keys, 1025 score
+        // values 22.9 us a layer, now 20.0; 262146 keys, 2049 score values, 41.8 and 33.5).
+        if (4 * n_keys < a.chunk && keff > 0) {
+            wait_for_marks(std::true_type());
+            w0 = clampi((s_est - 32) & ~1, 0, w0_max);
+            tried = HATA_COOP_CHUNKS;
+        }
         bool found = false;  // (the same in all waves: every decision below is made from the same words of LDS)
 #pragma clang loop unroll(disable)
         for (int it = 0; it < 32 && !found; ++it) {
@@ -766,35 +818,8 @@ void decode_step_coop_kernel(const CoopArgs a) {
             const unsigned long long* hw = hu + min(w0 / 2 + (lane & 31), a.NBP / 2 - 1);
             if (it) __syncthreads();  // (the last window has been read)
             for (;;) {
-                // With many chunks the rows are too much to be read in vain; otherwise they are mostly there by now.  At most
-                // one workgroup per CU: they start together, and up to 32 rows are tried at once (8 layers of 32768 keys 108.4 us,
-                // with the marks first 112; beyond, the marks).  More of them start one after the other, and what they read in
-                // vain is in the way of the last: wide rows are tried up to 12 chunks (group of eight, 2 layers of 3 x 117252
-                // keys, 29 chunks: tried 61.7, marks 58.2; 3 x 40000, 20 chunks: 41.8 and 38.4; the search before it was 58.6 and
-                // 42.3), narrow ones up to 24 (32 heads of their own, 131072 keys, 32 chunks: 60.5 and 58.4;
-                // 100000, 25 chunks: the same; 16384, 16 chunks, four layers: 51.8 and 53.3).
-                if (nc > (a.prefetch ? 32 : WIDE ? 12 : 24) || attempt != it) {
-                    // One wave waits for the marks the chunks leave behind their rows, on lines that no other workgroup reads.
-                    // (Polling with the loads below kept a compute unit's memory pipe so busy that the youngest
-                    // workgroup on it -- the one everybody waited for -- never got to its own; all workgroups of a
-                    // unit polling the same marks made everything else that went to those lines' channel wait.)
-                    if (wv == 0) {
-                        for (;;) {
-                            uint32_t mk[HATA_COOP_CHUNKS / 64];  // (requested together)
-#pragma unroll
-                            for (int j = 0; j < HATA_COOP_CHUNKS / 64; ++j) {
-                                mk[j] = epoch;
-                                if (64 * j < nc) mk[j] = ld_dev(marks + min(lane + 64 * j, nc - 1));
-                            }
-                            bool absent = false;
-#pragma unroll
-                            for (int j = 0; j < HATA_COOP_CHUNKS / 64; ++j) absent |= mk[j] != epoch;
-                            if (__builtin_amdgcn_ballot_w64(absent) == 0ull || --budget <= 0) break;
-                            __builtin_amdgcn_s_sleep(1);
-                        }
-                        if (--budget <= 0 && lane == 0) { a.error_word[0] = 1u; s_bad = 1; s_quit = attempt + 1; }  // gave up: this launch's results are invalid
-                    }
-                    __syncthreads();
+                if (nc > tried || attempt != it) {
+                    wait_for_marks(std::false_type());
                     if (s_quit == attempt + 1) break;  // (all waves see the same: the next one to be written belongs to a later attempt)
                 }
                 ++attempt;
@@ -802,15 +827,18 @@ void decode_step_coop_kernel(const CoopArgs a) {
                 uint32_t sum[4] = {0, 0, 0, 0};  // columns 0 and 1 of all chunks, of those before this one
                 constexpr int UN = 8;
                 auto request = [&](unsigned long long (&x)[UN], int r2) {
+                    int n = nc;
+                    asm volatile("" : "+s"(n));
 #pragma unroll
                     for (int j = 0; j < UN; ++j) {
                         x[j] = (unsigned long long)epoch << 32;
-                        if (r2 + 8 * j < nc)
-                            x[j] = __hip_atomic_load(hw + min(r2 + (lane >> 5) + 8 * j, nc - 1) * (a.NBP / 2), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        if (r2 + 8 * j < n)
+                            x[j] = __hip_atomic_load(hw + min(r2 + (lane >> 5) + 8 * j, n - 1) * (a.NBP / 2), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     }
                 };
                 auto add = [&](const unsigned long long (&x)[UN], int r2) {
-                    const int r0 = r2 + (lane >> 5);
+                    int r0 = r2 + (lane >> 5);
+                    asm volatile("" : "+v"(r0));
 #pragma unroll
                     for (int j = 0; j < UN; ++j) {
                         const uint32_t lo = (uint32_t)x[j] & 0xffffu, hi = (uint32_t)x[j] >> 16;

@@ -1,5 +1,6 @@
 """What the single-launch step keeps between launches: after one that gave up a wait, and between captured and eager ones."""
 import ctypes
+import functools
 import math
 
 import numpy as np
@@ -209,6 +210,68 @@ def test_empty_sequences_and_budgets_in_every_form(form, heads, r):
         call(H.to_dev(q), *cache, H.to_dev(s2), H.to_dev(k2), B, False, SCALE, out, out32)
         ctx.hata_check()
         assert np.array_equal(H.to_host(ctx.hata_step_buffers()[0], np.uint32), ref["qcodes"])
+        assert np.array_equal(H.to_host(ctx.hata_step_buffers()[2]), ref["idx"])
+        H.check_attention(H.to_host(out32), H.to_host(out, np.uint16), ref["out"], form)
+    ctx.close()
+
+
+@functools.lru_cache(maxsize=1)
+def make_unlike_chunks(heads, r, seq, k_max, budgets):
+    """Codes whose chunks of 1024 keys have a share of the query's bits of their own, so that the distributions hardly
+    overlap (every third sequence: the same share everywhere)."""
+    (Hq, Hkv), B, L = heads, len(seq), max(seq)
+    rng = np.random.default_rng(L + r)
+    K = synth.round_to_bf16_bits(rng.standard_normal((B, Hkv, L, 128), dtype=np.float32))
+    V = np.roll(K, 1, axis=3)
+    W = rng.standard_normal((Hkv, 128, r)).astype(np.float32)
+    q = synth.round_to_bf16_bits(np.repeat(rng.standard_normal((B, Hkv, 1, 128)), Hq // Hkv, 2).reshape(B, Hq, 128))
+    one = np.ones(B, np.int32)
+    qc = O.decode_step(q, K[:, :, :1], V[:, :, :1], W, np.zeros((B, Hkv, 1, r // 32), np.uint32), one, one, 1, SCALE,
+                       append=False)["qcodes"].reshape(B, Hkv, Hq // Hkv, r // 32)[:, :, :1]
+    share = rng.integers(0, 9, (B, -(-L // 1024)))
+    share[::3] = 4
+    share = np.repeat(share, 1024, 1)[:, None, :L, None]
+    flips = rng.integers(0, 2**32, (B, Hkv, L, r // 32), dtype=np.uint32)
+    for i in range(3):  # a bit flipped with probability 1/2, 1/4 .. 1/16, or kept with it
+        flips &= np.where(share % 4 > i, rng.integers(0, 2**32, flips.shape, dtype=np.uint32), np.uint32(0xffffffff))
+    codes = qc ^ np.where(share >= 5, ~flips, flips)
+    n = np.array(seq, np.int32)
+    refs = [O.decode_step(q, K, V, W, codes.copy(), n, np.full(B, k, np.int32), k_max, SCALE, append=False) for k in budgets]
+    return rng, q, K, V, W, codes, refs
+
+
+@pytest.mark.parametrize("heads,r", [((4, 1), 128), ((8, 1), 256), ((2, 2), 64)])
+@pytest.mark.parametrize("seq", [(1025, 1024 + 255, 1024 + 256, 2049), (13 * 1024 + 2, 25 * 1024 + 1, 33 * 1024 + 3), (64 * 1024 + 2, 65 * 1024 + 200, 64 * 1024)])
+@pytest.mark.parametrize("form", ["waits", "waits_large_chunks", "paged", "three_launches", "three_launches_pieces"])
+def test_last_chunk_of_a_few_keys(form, heads, r, seq):
+    """It goes by the estimate of the chunk before; that one's keys are like the others' or nothing like them."""
+    import torch
+    from paper_2506_02572_amd import hata
+    from tests.test_gpu_paged import make_table, scatter
+    (Hq, Hkv), B, L, k_max, page_rows, budgets = heads, len(seq), max(seq), 700, 64, (1, 150, 700)
+    print(f"[launches] few keys, {form} heads={heads} r={r} seq={seq}", flush=True)
+    rng, q, K, V, W, codes, refs = make_unlike_chunks(heads, r, seq, k_max, budgets)
+    seq = np.array(seq, np.int32)
+    ctx = hata.Context(B, Hq, Hkv, 128, r, L, k_max, chunk=16384 if form == "waits_large_chunks" else 1024,
+                       attn_rows=16 if form == "three_launches_pieces" else 0)
+    ctx.hata_set_step_mode(3 if form.startswith("three") else 0)
+    assert ctx.hata_step_plan(B)[0] == (3 if form.startswith("three") else 1)
+    cache = [H.to_dev(x) for x in (K, V, W, codes)]
+    call = ctx.hata_decode_step
+    if form == "paged":
+        table, max_blocks, n_pages, blocks = make_table(rng, seq, page_rows)
+        pools = []
+        for x in (K, V, codes):
+            pool = np.zeros((n_pages, Hkv, page_rows, x.shape[-1]), x.dtype)
+            scatter(pool, x, table, blocks, page_rows, seq)
+            pools.append(H.to_dev(pool))
+        cache = [pools[0], pools[1], cache[2], pools[2], H.to_dev(table), max_blocks, page_rows, n_pages]
+        call = ctx.hata_decode_step_paged
+    out = torch.zeros((B, Hq, 128), dtype=torch.int16, device="cuda")
+    out32 = torch.zeros((B, Hq, 128), dtype=torch.float32, device="cuda")
+    for budget, ref in zip(budgets, refs):
+        call(H.to_dev(q), *cache, H.to_dev(seq), H.to_dev(np.full(B, budget, np.int32)), B, False, SCALE, out, out32)
+        ctx.hata_check()
         assert np.array_equal(H.to_host(ctx.hata_step_buffers()[2]), ref["idx"])
         H.check_attention(H.to_host(out32), H.to_host(out, np.uint16), ref["out"], form)
     ctx.close()
