@@ -269,7 +269,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((G >= 16 ? 
 void decode_step_coop_kernel(const CoopArgs a) {
     static_assert(G * WD <= 64, "query code words of a unit are collected by one wave");
     // dynamic LDS: the chunk's scores (2 bytes per key; later the selected rows as offsets in the
-    // chunk) at a fixed address, then NB words of histogram (the chunk's, later the unit's total)
+    // chunk) at a fixed address, then NB words of histogram (the chunk's, then cumulative)
     extern __shared__ __attribute__((aligned(16))) uint16_t s_sc[];
     uint32_t* const hist = reinterpret_cast<uint32_t*>(s_sc + a.chunk);
     constexpr bool MFMA = G >= 4;  // matrix-core form of the attention core
@@ -805,8 +805,11 @@ void decode_step_coop_kernel(const CoopArgs a) {
         };
         // A last chunk of a few keys knows nothing of the unit: it takes the estimate of the chunk before, which comes
         // with that one's mark (beginning around its own, it needed several windows and everyone waited for it: 131074 keys, 1025 score
-        // values 22.9 us a layer, now 20.0; 262146 keys, 2049 score values, 41.8 and 33.5).
-        if (4 * n_keys < a.chunk && keff > 0) {
+        // values 22.9 us a layer, now 20.0; 262146 keys, 2049 score values, 41.8 and 33.5).  Where the rows would be tried at once that
+        // is a round trip more, and its own estimate will do as long as it comes from keys enough for the width of the
+        // scores: three of 1025, ten of 2049 (2 x 4262 keys, k = 64, 166 keys in the last chunk, 513 values: 13.5 us, by the marks 14.0).
+        const float own_rows = (float)n_keys * (float)keff, rows_wanted = (float)L * (float)(NB * NB) * (1.f / (640 * 640));
+        if (keff > 0 && 4 * n_keys < a.chunk && (nc > tried || own_rows < rows_wanted)) {
             wait_for_marks(std::true_type());
             w0 = clampi((s_est - 32) & ~1, 0, w0_max);
             tried = HATA_COOP_CHUNKS;
@@ -1211,7 +1214,7 @@ static const void* coop_kernel_for(int Wd, int G, bool paged, bool big) {
     }
 }
 
-// chunk sizes the kernel is built for, and the width of the {offset, count} record word
+// chunk sizes the kernel is built for; larger budgets than 65535 rows take three launches (not measured in this form)
 static bool coop_shape_ok(const hata_ctx* c, bool paged, int chunk) {
     return chunk >= 1024 && (chunk & (chunk - 1)) == 0 && chunk <= HATA_COOP_MAX_CHUNK &&
            c->cfg.k_max <= 65535;
