@@ -342,9 +342,11 @@ void decode_step_coop_kernel(const CoopArgs a) {
     // workgroup may not have read the count yet.  (What the launch before left, or what chunk 0 of this one has
     // made of that; either will do, so where the weights are on their way already an ordinary scalar load beside the
     // sequence length's: a device-scope load comes back behind the weights, 0.3 to 2 % of a step.  At r = 256 the weights would
-    // wait for the scalar one: 1 to 2 % too.)
+    // wait for the scalar one, 1 to 2 % too, and a vector load's two registers are more than the encoding leaves: the
+    // scalar load goes out behind the weights' requests there.)
     const uint32_t* const launches_at = a.unit_epoch + u * HATA_COUNTER_STRIDE;
-    const uint2 launches = EARLY ? *reinterpret_cast<const uint2*>(launches_at) : ld_dev_u2(launches_at);
+    uint2 launches = make_uint2(0, 0);
+    if (EARLY) launches = *reinterpret_cast<const uint2*>(launches_at);
     const int L = clampi(a.seq_len[b], 0, PAGED ? min(a.L_cap, a.pv.max_blocks << a.pv.shift) : a.L_cap);
     // Row n of the unit (a row of this chunk when PAGED) -> its row in the code array, in rows of
     // one (sequence or page, head): the contiguous cache is [B, Hkv, L_cap], the pools are
@@ -376,6 +378,11 @@ void decode_step_coop_kernel(const CoopArgs a) {
     bool late = false;
     auto number_launch = [&]() {  // (behind the encoding's first loads: the count is on its way meanwhile)
         if (epoch != 0) return;
+        if constexpr (!EARLY) {
+            unsigned long long x;
+            asm volatile("s_load_dwordx2 %0, %1, 0x0\n\ts_waitcnt lgkmcnt(0)" : "=&s"(x) : "s"(launches_at) : "memory");
+            launches = make_uint2((uint32_t)x, (uint32_t)(x >> 32));
+        }
         epoch = max((uint32_t)__builtin_amdgcn_readfirstlane((int)launches.x) + 1u, 1u);
         if (__builtin_amdgcn_readfirstlane((int)launches.y) != 0) {
             uint32_t* const at = a.unit_epoch + u * HATA_COUNTER_STRIDE;
@@ -477,6 +484,7 @@ void decode_step_coop_kernel(const CoopArgs a) {
         } else {
             for (int v = c; v < G; v += max(nc, 1)) {
                 if (!EARLY || v != c) coop_encode_load<WD>(Wh, qv + v * HATA_D, el);
+                if (!EARLY) number_launch();
                 coop_encode_vec<WD>(Wh, el, &s_codes[v * WD]);
                 publish(v);
             }
