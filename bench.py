@@ -41,13 +41,13 @@ PER_CONFIG_WARMUP = 40
 # constant of the build the profile names, not a value measured by the run that prints it: the
 # "traffic_source" field of the output says so.  "step": the single-launch decode step
 # (decode_step_coop_kernel); "score": the scoring kernel alone (hata_hamming_score).
-HBM_TRAFFIC_SOURCE = "profiles/hbm_traffic_pmc.md (library of commit 27b79d8; b32_32k: e4b3f88)"
+HBM_TRAFFIC_SOURCE = "profiles/hbm_traffic_pmc.md (library of commit 2cf71d0)"
 HBM_TRAFFIC_BYTES = {
-    "cfg2_llama3_8b_32k": {"step": 9348096, "score": 5082317},
-    "cfg3_batched_ragged": {"step": 73044890, "score": 45608141},
-    "cfg4_long_128k_r256": {"step": 48791552, "score": 36881203},
-    "cfg5_gqa8_append": {"step": 59498394, "score": 39123354},
-    "b32_32k": {"step": 209088922, "score": 153628262},
+    "cfg2_llama3_8b_32k": {"step": 10071962, "score": 4779110},
+    "cfg3_batched_ragged": {"step": 74342965, "score": 44855142},
+    "cfg4_long_128k_r256": {"step": 50044049, "score": 35735654},
+    "cfg5_gqa8_append": {"step": 60189345, "score": 37911654},
+    "b32_32k": {"step": 209143906, "score": 151323811},
 }
 
 
@@ -619,7 +619,7 @@ def train_leg(torch, dev, w, W_H, stream):
     flop = 4 * 2.0 * n_tr * w.d * w.r  # two projections + two weight-gradient contractions
     leg = {"triplets": n_tr, "r": w.r, "us_per_step": round(ms_tr * 1e3, 1),
            "TFLOPs": round(flop / (ms_tr * 1e-3) / 1e12, 1),
-           "mfma_issue_TFLOPs": round((3 * 3 + 2 * 3) / 4 * flop / (ms_tr * 1e-3) / 1e12, 1), "launches": 3}
+           "mfma_issue_TFLOPs": round(5 * 3 / 4 * flop / (ms_tr * 1e-3) / 1e12, 1), "launches": 2}
     tctx.close()
     return leg
 

@@ -97,7 +97,8 @@ typedef struct {
                             * (the other kernels keep their default) */
     int32_t attn_rows;     /* selected rows per attention workgroup of the three-launch form: 0 = default, else a power of two in 16..256 */
     int32_t par_merge;     /* single-launch form, merge of a unit's partials: -1 = default, 0 = by the last workgroup to arrive, 1 = a query head per workgroup (taken for launches with more than four chunks per unit; the default when a group has two heads or more) */
-    int32_t shared_device; /* != 0: other work may run on the device beside the step, so the context starts in step mode 3 (see hata_set_step_mode) */
+    int32_t shared_device; /* != 0: other work may run on the device beside the step: no in-kernel waits unless hata_set_step_mode asks for them
+                            * (three launches, short caches a workgroup per unit: see hata_decode_step) */
 } hata_tuning;
 
 /* hata_workspace_bytes / hata_create with the launch shapes of `tuning` (host pointer, may be
@@ -237,7 +238,7 @@ int hata_dense_decode(hata_ctx* ctx, const void* q, const void* K, const void* V
  * with NaN (out: bf16 0x7fc0, out_f32: NaN), so the failure shows in the data itself (the idx
  * rows of such a step are unspecified: -1 where the unit could still be marked, else whatever its
  * workgroups wrote), and the next hata_check() returns HATA_ETIMEOUT.  Otherwise
- * the step is three launches (encode; score + threshold; select + attend) with no in-kernel wait.
+ * the step is three launches (encode; score; threshold + select + attend) with no in-kernel wait.
  * The residency test assumes the device runs nothing else at that moment and that the context is
  * used on the device that was current in hata_create(): a process that overlaps other kernels
  * with the step (other streams, other processes) should create the context with
@@ -321,7 +322,9 @@ int hata_step_sub_batches(const hata_ctx* ctx, int32_t B, int32_t* n_sub);
  *   and finish -- which is how the hardware dispatches a grid, not a guarantee of the
  *   programming model: should a wait ever give up, hata_check() reports it (HATA_ETIMEOUT) and
  *   the step must be repeated in mode 0 or 3;
- * mode 3: always the three-launch form (no in-kernel waits). */
+ * mode 3: always the three-launch form (no in-kernel waits).
+ * (Modes 1 and 3, once asked for, rule out the workgroup per unit of short caches too; a context made for a shared device
+ * starts without waits but with that form.) */
 int hata_set_step_mode(hata_ctx* ctx, int32_t mode);
 
 /* The Hamming scores of a step are an intermediate: the single-launch forms keep them on chip and

@@ -7,8 +7,8 @@
 // apart.  No workgroup waits for another one either, so the grid need not be resident and the device may be shared.
 // us a layer, workgroups that share units / this: one sequence, eight KV heads, r = 128, 2048 keys 16.0 / 10.7, 4096 keys
 // 15.7 / 11.7, a group of eight 19.6 / 14.2, r = 256 18.2 / 15.4; 32 sequences of 4096 keys 22.8 / 13.5.
-// A compute unit alone streams codes at little more than 20 GB/s (its misses in flight bound it), so longer caches take
-// this form only where the units are many: takes_unit_step in hata_api.hip.
+// Beyond that the unit's time is what one compute unit streams and gathers, so longer caches and large budgets take this
+// form only where the units are many: takes_unit_step in hata_api.hip, with both sides measured.
 #include "hata_attn_core.h"
 #include "hata_device.h"
 #include "hata_hash.h"
