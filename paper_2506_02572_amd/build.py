@@ -17,6 +17,9 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # the first arguments of a kernel (all a user SGPR block holds) are in registers when a wave starts, instead of a cold scalar
+    # load in front of its first request: 0.15 us a launch where they are plain values (the five stage calls 26.7 -> 26.0 us)
+    "-mllvm", "-amdgpu-kernarg-preload-count=14",
     "-Wall", "-Wno-unused-function",
 ]
 
