@@ -12,7 +12,8 @@
 // exact and only the fp32 accumulation rounds.
 //
 // Launches of a step (two, three where the column sums have a launch of their own):
-//   1. train_grad_kernel     The balance term couples every row to the sum of h(k) over its query, but only through
+//   1. train_grad_kernel, train_grad_runs_kernel (batches of more than a round of workgroups)
+//                            The balance term couples every row to the sum of h(k) over its query, but only through
 //                            a factor per hash column: dL/dz_k = (c_j - a_n) e_n with e = 1 - h(k)^2, so
 //                            K^T dZ_k = c_j K^T E - K^T (A E), and the two contractions need no sums.
 //                            So one pass over the triplets: forward of k and q, K^T E and K^T (A E) with the MFMA
@@ -25,8 +26,7 @@
 //      many to do so themselves)
 //   2. train_update_kernel   dL/dW = sigma sum partials + 2 lam W P / ||P||_F with W P = (W W^T) W - W, the loss
 //                            terms, weight decay, momentum, step
-// At r = 128 and 32768 triplets of four queries a step takes 28 us; with the column sums in a launch in front of the
-// gradient's, h(k) twice and W P in extra workgroups behind it, it took 37.
+// At r = 128 and 32768 triplets of four queries a step takes 27 us (29 with a workgroup per pair of blocks), at 122880 triplets 64 (86).
 #include <new>
 #include <type_traits>
 
@@ -40,7 +40,7 @@ struct hata_train_ctx {
     int n_wgs_max;
     float* colsum_part;  // [n_wgs_max, r]
     float* colsum;       // [queries (<= n_wgs_max), r]  sum of h(k_n) over the triplets of a query
-    float* dw_part;      // [pairs of blocks, 3, d, r]  K^T E, the rest of X^T dZ, K^T E of the second block if its query is another
+    float* dw_part;      // [pairs of blocks, 3, d, r]  K^T E, the rest of X^T dZ, K^T E of the second block if its query is another; of a run: in its last pair's place
     float* loss_part;    // [column groups, pairs of blocks]
     double* gram;        // [d, d]  W W^T
     double* fro_part;    // [2 d]  what its pieces add to ||W^T W - I||_F^2 - r
@@ -64,6 +64,7 @@ typedef __attribute__((ext_vector_type(16))) float tr_f32x16_t;
 #define TR_FEW_QUERIES 32
 #define TR_UPDATE_WAVES 8  // waves of an update workgroup
 #define TR_PITCH 136  // LDS row pitch in bf16 elements (272 B: conflict-free 16-B and transposed reads)
+#define TR_KEPT 4      // stages of a workgroup whose column sums are kept until they are written
 
 // Two fp32 values -> three bf16 terms each, whose sum carries all 24 mantissa bits (each term is the
 // remainder truncated to its upper 8 significant bits, so both subtractions are exact); the pair's terms are packed
@@ -266,6 +267,40 @@ struct GramPiece {
         return f + __shfl_xor(f, 32, 64);
     }
 };
+
+// The same without the registers of requests made ahead: four loads of either row at a time
+template <int R>
+__device__ __forceinline__ double gram_piece(const float* __restrict__ W, int c, int tid, double* __restrict__ gram, float* __restrict__ W_old) {
+    constexpr int NV = R / 32 < 4 ? R / 32 : 4;  // eight threads per element, NV loads of either row in flight (registers)
+    const int row = c >> 1, ch = (c & 1) * 64 + (tid >> 3), part = tid & 7;
+    const float4* ra = reinterpret_cast<const float4*>(W + ch * R) + part;
+    const float4* rb = reinterpret_cast<const float4*>(W + row * R) + part;
+    const bool copies = (c & 1) == 0 && tid < R;
+    const float w = copies ? W[row * R + tid] : 0.f;
+    double acc = 0.0;
+#pragma clang loop unroll(disable)
+    for (int i0 = 0; i0 < R / 32; i0 += NV) {
+        float4 a[NV], b[NV];
+#pragma unroll
+        for (int i = 0; i < NV; ++i) { a[i] = ra[8 * (i0 + i)]; b[i] = rb[8 * (i0 + i)]; }
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            acc = fma((double)a[i].x, (double)b[i].x, acc);
+            acc = fma((double)a[i].y, (double)b[i].y, acc);
+            acc = fma((double)a[i].z, (double)b[i].z, acc);
+            acc = fma((double)a[i].w, (double)b[i].w, acc);
+        }
+    }
+    acc += __shfl_xor(acc, 1, 64);
+    acc += __shfl_xor(acc, 2, 64);
+    acc += __shfl_xor(acc, 4, 64);
+    if (part == 0) gram[row * HATA_D + ch] = acc;
+    if (copies) W_old[row * R + tid] = w;
+    double f = acc * acc - (ch == row ? 2.0 * acc : 0.0);
+    f += __shfl_xor(f, 8, 64);
+    f += __shfl_xor(f, 16, 64);
+    return f + __shfl_xor(f, 32, 64);
+}
 
 // grid = (pairs of blocks of TR_ROWS triplets, groups of COLS hash columns).
 //
@@ -588,28 +623,422 @@ __global__ __launch_bounds__(TrainShape<COLS>::THREADS) void train_grad_kernel(
     }
 }
 
+// The same for batches of more than a round of workgroups: grid = (pairs / stages, groups of 32 hash columns), a workgroup goes through
+// `stages` pairs of blocks one after the other, a wave through a tile of 32 rows of each, and keeps the sums in registers for a run: up
+// to run_len pairs (a share of `stages`, at most TR_KEPT) of one query.  The partial of a run lies in its last pair's place.
+//
+// Whether a tile holds one query vector is a wave's own matter here; where one does not, the wave takes the run again the general way.
+//
+// What bounds it: a tile is 72 matrix instructions (48 of them the contractions, at the rate these sustain), 500 of the vector ALU
+// and 40 KB through LDS, 5 us for the eight waves together.  So the waves have nothing to wait for each other for until a run's sums are
+// complete: a wave stages its rows itself, the next tile's under this one's products, makes half of its values under the other half's
+// products, and holds the sums for all 128 channels, which meet in LDS at the end (3 us, which is why small batches take the form
+// above).  In step with each other, handing the values round through LDS, the waves took 7 us a tile.  us a step, one query vector a
+// block / others, the form above with 64 columns / this: r = 128 256 blocks 28.5 / 35.5 -> 27.2 / 34.7, 960 blocks 86 / 108 -> 64 / 83; r = 256
+// 256 blocks 52 -> 46, 960 153 / 195 -> 112 / 151; r = 32 960 blocks 42 -> 34.
+template <int R>
+__global__ __launch_bounds__(TrainShape<32>::THREADS) void train_grad_runs_kernel(
+    const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const float* __restrict__ s, const float* __restrict__ W,
+    int n, int n_blocks, int stages, int run_len, float sigma, float c_sim, const int32_t* __restrict__ block_group, int n_groups,
+    float* __restrict__ dw_part, float* __restrict__ colsum_part, float* __restrict__ loss_part, double* __restrict__ gram,
+    double* __restrict__ fro_part, float* __restrict__ W_old) {
+    using S = TrainShape<32>;
+    constexpr int WAVES = S::WAVES;
+    // the waves' tiles, K's and Q's in rotation (the next K's, once Q's has been looked at); piece j of row i lies in the place of piece j ^ (i & 15), so that 16 lanes that
+    // read a piece of a row each meet in no bank
+    __shared__ __attribute__((aligned(16))) uint4 s_tile[WAVES][2][32 * 16];
+    __shared__ __attribute__((aligned(16))) uint4 s_weights[8][3][64];  // operand fragments: the planes of the weights, by channel step
+    __shared__ __attribute__((aligned(16))) uint16_t s_q[WAVES][HATA_D];  // the tile's query
+    __shared__ __attribute__((aligned(16))) float s_lab[WAVES][32];
+    __shared__ float s_col[TR_KEPT][WAVES][32];  // per hash column: sums of h(k_n) over a tile
+    static_assert(TR_KEPT >= 2, "the first queries' projections in parts, before that");
+    __shared__ float s_loss[WAVES];
+    __shared__ double s_red[WAVES];
+    const int tid = threadIdx.x, lane = tid & 63, rg = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int m = lane & 31, half = lane >> 5;
+    const int n_pairs = (n_blocks + 1) / 2, p0 = blockIdx.x * stages, p1 = min(p0 + stages, n_pairs);
+    const int col = blockIdx.y * 32 + m;
+    const int wg = blockIdx.y * gridDim.x + blockIdx.x;
+    const bool has_piece = wg < GramPiece<R>::PIECES;
+    auto piece_sum = [&]() {
+        double f = 0.0;
+        for (int i = 0; i < WAVES; ++i) f += s_red[i];
+        return f;
+    };
+    if (p0 >= n_pairs) {  // (small batches have workgroups for the pieces alone)
+        if (has_piece) {
+            const double f = gram_piece<R>(W, wg, tid, gram, W_old);
+            if (lane == 0) s_red[rg] = f;
+            __syncthreads();
+            if (tid == 0) fro_part[wg] = piece_sum();
+        }
+        return;
+    }
+    // (addresses made from it are made where they are used, not in front of the loops and kept in registers)
+    auto fresh_lane = [&]() {
+        int l = lane;
+        asm volatile("" : "+v"(l));
+        return l;
+    };
+    // Rows of X into a tile, past n the last row: eight instructions of four rows, a lane 16 bytes, which land at the
+    // instruction's base + 16 lane.  (Instructions rather than the compiler's builtin, which would make every later
+    // read of LDS wait for all of them; landed() does.)
+    auto request_tile = [&](const uint16_t* X, int row0, uint4* dst) {
+        const int l = fresh_lane();
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int row = 4 * j + (l >> 4);
+            const uint16_t* const g = X + (int64_t)min(row0 + row, n - 1) * HATA_D + ((l & 15) ^ (row & 15)) * 8;
+            const uint32_t base = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)(dst + j * 64));
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(base), "v"(g) : "memory", "m0");
+        }
+    };
+    auto landed = []() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
+    auto read_done = []() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); };  // (what is requested next may take the place of what was read)
+    auto row_of = [&](int p) { return p * TR_PAIR + 32 * rg; };
+    auto tile_of = [&](int p) { return &s_tile[rg][p & 1][0]; };
+    auto zero_past_n = [&](int row0, uint4* t) {  // rows past n count as zeros
+        const int l = fresh_lane();
+#pragma clang loop unroll(disable)
+        for (int j = 0; j < 8; ++j)
+            if (row0 + 4 * j + (l >> 4) >= n) t[j * 64 + l] = make_uint4(0, 0, 0, 0);
+    };
+    request_tile(K, row_of(p0), tile_of(p0));
+    request_tile(Q, row_of(p0), tile_of(p0 + 1));
+    // the blocks of the next stages with another query than the stage's first block has, a bit each (those past the last block: none)
+    auto other_queries = [&](int p) {
+        const int own = block_query(block_group, 2 * p, n_groups), b = 2 * p + (lane & (2 * TR_KEPT - 1));
+        const int id = block_query(block_group, min(b, n_blocks - 1), n_groups);
+        return (uint32_t)__builtin_amdgcn_ballot_w64(b < n_blocks && id != own && lane < 2 * TR_KEPT);
+    };
+    uint32_t others = other_queries(p0);
+    const float nsl = -sigma * TR_LOG2E;
+    // The last tile's query, its piece lane % 16 (in s_q too), and its hash values: of the first stage it mostly is the one of the block's first row.
+    // A channel step of the planes of the column group's weights by each wave, and of the projections of the two blocks' first rows
+    uint4 query = *reinterpret_cast<const uint4*>(Q + (int64_t)min(p0 * TR_PAIR + (rg >> 2) * TR_ROWS, n - 1) * HATA_D + (lane & 15) * 8);
+    float hq0;
+    {
+        const uint4 x = *reinterpret_cast<const uint4*>(Q + (int64_t)min(p0 * TR_PAIR + (m & 1) * TR_ROWS, n - 1) * HATA_D + rg * 16 + 8 * half);
+        float wv[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) wv[e] = W[(int64_t)(rg * 16 + 8 * half + e) * R + col];
+        uint32_t f[3][4];
+#pragma unroll
+        for (int e2 = 0; e2 < 4; ++e2) split3_pair(wv[2 * e2], wv[2 * e2 + 1], f[0][e2], f[1][e2], f[2][e2]);
+#pragma unroll
+        for (int p = 0; p < 3; ++p) s_weights[rg][p][lane] = make_uint4(f[p][0], f[p][1], f[p][2], f[p][3]);
+        tr_f32x16_t z;  // row 0: the first block's, row 1: the second one's
+#pragma unroll
+        for (int i = 0; i < 16; ++i) z[i] = 0.f;
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+            z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(tr_bf16x8_t, x), __builtin_bit_cast(tr_bf16x8_t, make_uint4(f[p][0], f[p][1], f[p][2], f[p][3])), z, 0, 0, 0);
+        if (half == 0) {
+            s_col[0][rg][m] = z[0];
+            s_col[1][rg][m] = z[1];
+        }
+        __syncthreads();
+        float part[WAVES];
+#pragma unroll
+        for (int i = 0; i < WAVES; ++i) part[i] = s_col[rg >> 2][i][m];
+        hq0 = relaxed_sign(((part[0] + part[1]) + (part[2] + part[3])) + ((part[4] + part[5]) + (part[6] + part[7])), nsl);
+        if (lane < 16) *reinterpret_cast<uint4*>(&s_q[rg][8 * lane]) = query;
+    }
+    float lsim = 0.f;  // similarity
+    auto product = [](tr_bf16x8_t x, tr_bf16x8_t y, tr_f32x16_t& sum) { sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, y, sum, 0, 0, 0); };
+    // Z (32 rows x 32 columns) = X . W: result register ri of lane (m, half) holds row 8 (ri / 4) + 4 half + ri % 4, column m.
+    // x(kk): channels 16 kk + 8 half ... of row m
+    auto project = [&](auto x) {
+        const int l = fresh_lane();
+        tr_f32x16_t z;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) z[i] = 0.f;
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk) {
+            if (kk == 4) __builtin_amdgcn_sched_barrier(0);  // (sixteen operands at a time, not all of them: registers)
+            const tr_bf16x8_t a = x(l, kk);
+#pragma unroll
+            for (int p = 0; p < 3; ++p) product(a, __builtin_bit_cast(tr_bf16x8_t, s_weights[kk][p][l]), z);
+        }
+        return z;
+    };
+    auto project_tile = [&](const uint4* t) {
+        return project([&](int l, int kk) { return __builtin_bit_cast(tr_bf16x8_t, t[(l & 31) * 16 + ((2 * kk + (l >> 5)) ^ (l & 15))]); });
+    };
+    // X transposed: 16 rows (slot (half, j) of the operand <-> row 8 (j / 4) + 4 half + j % 4), 32 channels.  This lane
+    // reads channels 32 ct + 16 (m / 16) + 4 (lane % 4) ... of row 16 ks + 4 half + lane % 16 / 4, and of 8 rows on (lds_read_transposed)
+    auto rows_transposed = [](const uint4* t, int l, int ks, int ct) {
+        const int row = 4 * (l >> 5) + (l & 15) / 4, piece = 2 * (l >> 4 & 1) + (l & 3) / 2;
+        const uint16_t* const p = reinterpret_cast<const uint16_t*>(t) + 4 * (l & 1);
+        const uint2 lo = lds_read_transposed(p + ((16 * ks + row) * 16 + ((4 * ct + piece) ^ row)) * 8);
+        const uint2 hi = lds_read_transposed(p + ((16 * ks + row + 8) * 16 + ((4 * ct + piece) ^ (row + 8))) * 8);
+        return __builtin_bit_cast(tr_bf16x8_t, make_uint4(lo.x, lo.y, hi.x, hi.y));
+    };
+    auto label_of = [&](int l, int i) { return s_lab[rg][8 * (i / 4) + 4 * (l >> 5) + i % 4]; };
+    // What both ways have in common: the tile's K and Q there, its labels, K's projection (then h(k)); whether it takes the general way
+    auto begin_tile = [&](int p, bool requested, tr_f32x16_t& zk) {
+        const int row0 = row_of(p);
+        uint4 *const t = tile_of(p), *const tq = tile_of(p + 1);
+        landed();
+        const float lab = s[min(row0 + m, n - 1)];
+        if (!requested) request_tile(Q, row0, tq);
+        if (row0 + 32 > n) zero_past_n(row0, t);
+        zk = project_tile(t);
+        if (requested && p == p0 && has_piece) {
+            const double f = gram_piece<R>(W, wg, 64 * rg + fresh_lane(), gram, W_old);
+            if (lane == 0) s_red[rg] = f;
+        }
+        if (half == 0) s_lab[rg][m] = row0 + m < n ? lab : 0.f;
+        landed();
+        if (row0 + 32 > n) zero_past_n(row0, tq);
+        __builtin_amdgcn_wave_barrier();  // (LDS serves a wave's accesses in order)
+    };
+    auto squash = [&](tr_f32x16_t& z) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) z[i] = relaxed_sign(z[i], nsl);
+    };
+    __syncthreads();
+#pragma clang loop unroll(disable)
+    for (int p = p0, limit = p0; p < p1;) {
+        if (p == limit) limit = min(limit + run_len, p1);
+        const bool one_query = (others & 2u) == 0;
+        const int pe = one_query ? min(limit, others ? p + (__builtin_ctz(others) >> 1) : limit) : p + 1;  // past the run
+        // accumulators: channel 32 ct + 8 (ri / 4) + 4 half + ri % 4, this lane's column
+        tr_f32x16_t ke[4], dw[4];  // K^T E;  Q^T dZ_q - K^T (A E)
+        auto clear_sums = [&]() {
+#pragma unroll
+            for (int ct = 0; ct < 4; ++ct)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) ke[ct][i] = dw[ct][i] = 0.f;
+        };
+        float lsim_run = 0.f;
+        // h(k) of the tile (zk: its projection) and the contractions with it.  Half of the rows' values are made under the products of the
+        // other half: a wave issues a product and then what fits beside it.
+        auto contract_keys = [&](const uint4* t, const tr_f32x16_t& zk, auto hash_of_key, auto hash_of_query, float& ssum, float& cs) {
+            const int l = fresh_lane();
+            uint32_t be[2][3][4], ba[2][3][4];  // the planes of 16 rows' E and -A E
+            auto prepare = [&](int ks, int e2) {  // two values
+                float e[2], ae[2];
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const int i = 8 * ks + 2 * e2 + j;
+                    // (half of dL/dh: h' = (1 - h^2) / 2)
+                    const float hk = hash_of_key(zk[i]), diff = hash_of_query(i) - hk, sd = label_of(l, i) * diff;
+                    cs += hk;  // (rows past n are zero: h = 0)
+                    e[j] = fmaf(-hk, hk, 1.f);
+                    ae[j] = -c_sim * sd * e[j];
+                    lsim_run = fmaf(sd, diff, lsim_run);
+                    ssum += sd;
+                }
+                split3_pair(e[0], e[1], be[ks][0][e2], be[ks][1][e2], be[ks][2][e2]);
+                split3_pair(ae[0], ae[1], ba[ks][0][e2], ba[ks][1][e2], ba[ks][2][e2]);
+            };
+            auto plane = [](const uint32_t (&x)[4]) { return __builtin_bit_cast(tr_bf16x8_t, make_uint4(x[0], x[1], x[2], x[3])); };
+#pragma unroll
+            for (int e2 = 0; e2 < 4; ++e2) prepare(0, e2);
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+                for (int ct = 0; ct < 4; ++ct) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    const tr_bf16x8_t x = rows_transposed(t, l, ks, ct);
+                    if (ks == 0) prepare(1, ct);
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) {
+                        product(x, plane(be[ks][i]), ke[ct]);
+                        product(x, plane(ba[ks][i]), dw[ct]);
+                    }
+                    if (ks == 0) {
+#pragma unroll
+                        for (int i = 0; i < 6; ++i) {
+                            __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);  // a product
+                            __builtin_amdgcn_sched_group_barrier(0x2, 8, 0);  // vector instructions
+                        }
+                    }
+                }
+            }
+        };
+        bool general = false;
+        {
+            clear_sums();
+            float sum_q = 0.f;  // of dZ_q, which the query has yet to be multiplied with
+            // one product for 32 channels: the query in the first three places of the contraction, the planes of the sums
+            auto add_query = [&]() {
+                const int l = fresh_lane();
+                uint32_t hi, mid, lo;
+                split3_pair(l < 32 ? sum_q : 0.f, 0.f, hi, mid, lo);
+                const tr_bf16x8_t y = __builtin_bit_cast(tr_bf16x8_t, make_uint4(hi | mid << 16, lo, 0, 0));
+#pragma unroll
+                for (int ct = 0; ct < 4; ++ct) {
+                    const uint32_t x = s_q[rg][32 * ct + (l & 31)];
+                    product(__builtin_bit_cast(tr_bf16x8_t, make_uint4(x | x << 16, x, 0, 0)), y, dw[ct]);
+                }
+                sum_q = 0.f;
+            };
+#pragma clang loop unroll(disable)
+            for (int i = p; i < pe; ++i) {
+                tr_f32x16_t zk;
+                begin_tile(i, i == p, zk);
+                const uint4* const tq = tile_of(i + 1);
+                const uint4 f = tq[lane & 15];  // the first row's piece lane % 16
+                uint32_t stray = 0;
+                const int l = fresh_lane();
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const int row = 4 * j + (l >> 4);
+                    const uint4 x = tq[row * 16 + ((l & 15) ^ (row & 15))];
+                    const uint32_t differs = (x.x ^ f.x) | (x.y ^ f.y) | (x.z ^ f.z) | (x.w ^ f.w);
+                    const uint32_t counts = x.x | x.y | x.z | x.w | (__float_as_uint(s_lab[rg][row]) << 1);  // (a label of -0 is 0)
+                    stray |= counts != 0u ? differs : 0u;
+                }
+                if (__builtin_amdgcn_ballot_w64(stray != 0u) != 0ull) { general = true; break; }
+                if (i + 1 < pe) {
+                    read_done();
+                    request_tile(K, row_of(i + 1), tile_of(i + 1));
+                }
+                const uint32_t differs = (f.x ^ query.x) | (f.y ^ query.y) | (f.z ^ query.z) | (f.w ^ query.w);
+                if (__builtin_amdgcn_ballot_w64(differs != 0u) != 0ull) {
+                    add_query();
+                    query = f;
+                    if (lane < 16) *reinterpret_cast<uint4*>(&s_q[rg][8 * lane]) = f;
+                    __builtin_amdgcn_wave_barrier();
+                    hq0 = relaxed_sign(project([&](int l, int kk) { return *reinterpret_cast<const tr_bf16x8_t*>(&s_q[rg][16 * kk + 8 * (l >> 5)]); })[0], nsl);
+                }
+                float ssum = 0.f, cs = 0.f;  // sums of s (h(q) - h(k)) and of h(k)
+                contract_keys(tile_of(i), zk, [&](float z) { return relaxed_sign(z, nsl); }, [&](int) { return hq0; }, ssum, cs);
+                sum_q += c_sim * (ssum + __shfl_xor(ssum, 32, 64)) * fmaf(-hq0, hq0, 1.f);
+                cs += __shfl_xor(cs, 32, 64);
+                if (half == 0) s_col[i - p][rg][m] = cs;
+            }
+            if (!general) add_query();
+        }
+        if (general) {  // the run again, from its start
+            clear_sums();
+            lsim_run = 0.f;
+            read_done();
+            request_tile(K, row_of(p), tile_of(p));
+#pragma clang loop unroll(disable)
+            for (int i = p; i < pe; ++i) {
+                tr_f32x16_t zk;
+                begin_tile(i, false, zk);
+                squash(zk);
+                const uint4* const tq = tile_of(i + 1);
+                tr_f32x16_t zq = project_tile(tq), gq;  // then h(q);  the rows' dZ_q
+                squash(zq);
+                const int l = fresh_lane();
+#pragma unroll
+                for (int j = 0; j < 16; ++j) gq[j] = c_sim * label_of(l, j) * (zq[j] - zk[j]) * fmaf(-zq[j], zq[j], 1.f);
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks) {
+                    tr_bf16x8_t bq[3];
+                    split_operand(gq, ks, bq);
+#pragma unroll
+                    for (int ct = 0; ct < 4; ++ct) {
+                        const tr_bf16x8_t x = rows_transposed(tq, l, ks, ct);
+#pragma unroll
+                        for (int j = 0; j < 3; ++j) product(x, bq[j], dw[ct]);
+                    }
+                }
+                if (i + 1 < pe) {
+                    read_done();
+                    request_tile(K, row_of(i + 1), tile_of(i + 1));
+                }
+                float ssum = 0.f, cs = 0.f;
+                contract_keys(tile_of(i), zk, [](float h) { return h; }, [&](int j) { return zq[j]; }, ssum, cs);
+                cs += __shfl_xor(cs, 32, 64);
+                if (half == 0) s_col[i - p][rg][m] = cs;
+            }
+        }
+        lsim += lsim_run;
+        // The waves' sums, the first four the first block's, meet in the tiles' place; a wave adds up 16 channels
+        __syncthreads();
+        const int l = fresh_lane();
+        {  // the column sums, by block
+            const int block = 2 * (p + rg) + (l >> 5);
+            if (p + rg < pe && block < n_blocks) {
+                float sum = 0.f;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) sum += s_col[rg][4 * (l >> 5) + i][l & 31];
+                colsum_part[(int64_t)block * R + col] = sum;
+            }
+        }
+        float4* const meet = reinterpret_cast<float4*>(&s_tile[0][0][0]) + l;
+        static_assert(sizeof(s_tile) == WAVES * 64 * 64 * 4, "a wave's sums in its tiles' place");
+        float* const out = dw_part + (int64_t)(pe - 1) * 3 * HATA_D * R + 16 * rg * R + blockIdx.y * 32;
+        auto store = [&](float* to, int i4, float4 x) {  // channels 8 i4 + 4 half ... of the wave's
+            float* const at = to + (uint32_t)((8 * i4 + 4 * (l >> 5)) * R + (l & 31));
+            at[0] = x.x; at[R] = x.y; at[2 * R] = x.z; at[3 * R] = x.w;
+        };
+        auto plus = [](float4 x, float4 y) { return make_float4(x.x + y.x, x.y + y.y, x.z + y.z, x.w + y.w); };
+        auto hand_over = [&](const tr_f32x16_t (&x)[4]) {
+#pragma unroll
+            for (int ct = 0; ct < 4; ++ct)
+#pragma unroll
+                for (int i4 = 0; i4 < 4; ++i4)
+                    meet[(rg * 16 + ct * 4 + i4) * 64] = make_float4(x[ct][4 * i4], x[ct][4 * i4 + 1], x[ct][4 * i4 + 2], x[ct][4 * i4 + 3]);
+            __syncthreads();
+        };
+        auto block_sum = [&](int w0, int i4) {  // over the waves of a block
+            const float4* const at = meet + (w0 * 16 + 2 * rg + i4) * 64;
+            return plus(plus(at[0], at[16 * 64]), plus(at[32 * 64], at[48 * 64]));
+        };
+        hand_over(ke);
+#pragma unroll
+        for (int i4 = 0; i4 < 2; ++i4) {
+            const float4 x = block_sum(0, i4), y = block_sum(4, i4);
+            if (one_query) {
+                store(out, i4, plus(x, y));
+            } else {
+                store(out, i4, x);
+                store(out + 2 * HATA_D * R, i4, y);
+            }
+        }
+        __syncthreads();
+        hand_over(dw);
+#pragma unroll
+        for (int i4 = 0; i4 < 2; ++i4) store(out + HATA_D * R, i4, plus(block_sum(0, i4), block_sum(4, i4)));
+        p = pe;
+        if (p == p1) break;
+        __syncthreads();  // (the tiles' places are free again)
+        request_tile(K, row_of(p), tile_of(p));
+        request_tile(Q, row_of(p), tile_of(p + 1));
+        others = other_queries(p);
+    }
+    lsim = wave_sum64(lsim);
+    if (lane == 0) s_loss[rg] = lsim;
+    __syncthreads();
+    if (tid == 0) {  // (the similarity partial of column group y; the groups are summed later)
+        float t = 0.f;
+        for (int i = 0; i < WAVES; ++i) t += s_loss[i];
+        loss_part[blockIdx.y * ((n_pairs + stages - 1) / stages) + blockIdx.x] = t;
+        if (has_piece) fro_part[wg] = piece_sum();
+    }
+}
+
 // dL/dW = sigma * (sum of the partials) + 2 lam W P / ||P||_F, and the SGD update from it; the last block writes
 // the loss terms.  64 elements per workgroup of 512 threads: a wave sums an eighth of the partials of each -- K^T E
 // times the column's factor, which the workgroup adds up first from the column sums of all blocks (colsum: already added up per
-// query) -- and the eighths meet in LDS in a fixed order.  Large batches are bound by reading the partials once (16.8 MB at r = 128
-// and 256 blocks, in the caches), small ones by the round trips to what a wave reads: hence everything of the first 32 blocks
+// query) -- and the eighths meet in LDS in a fixed order.  Large batches are bound by reading the partials once (8.4 MB at r = 128
+// from 256 blocks on, in the caches) and the column sums by every workgroup, small ones by the round trips to what a wave reads: hence everything of the first 32 blocks
 // is requested at once, queries are looked up by 32 blocks (a lane each), and the loss workgroup's waves have 64 columns of a
 // share of the blocks each instead of all columns one after the other (one block 6.5 -> 5.8 us, at r = 256 12.7 -> 8.7;
 // 960 blocks of four queries, r = 32 15.6 -> 9.4, r = 128 17.1 -> 13.1).
+template <bool RUNS>
 __global__ __launch_bounds__(TR_UPDATE_WAVES * 64) __attribute__((amdgpu_waves_per_eu(4, 4))) void train_update_kernel(
     float* __restrict__ W, float* __restrict__ v, int log2_r, int n_blocks, int n_loss, float sigma, float lam, float c_sim, float c_bal,
     float lr, float momentum, float weight_decay, const float* __restrict__ dw_part, const float* __restrict__ colsum_part,
     const float* __restrict__ colsum, const int32_t* __restrict__ block_group, int n_groups, const double* __restrict__ gram,
     const double* __restrict__ fro_part, const float* __restrict__ W_old, const float* __restrict__ loss_part,
-    float* __restrict__ grad, float* __restrict__ loss) {
+    float* __restrict__ grad, float* __restrict__ loss, int run_len, int runs) {
     constexpr int WAVES = TR_UPDATE_WAVES;
     __shared__ float part[WAVES][64];
     __shared__ double wp_part[WAVES][64];
     __shared__ float s_slice[WAVES][TR_FEW_QUERIES][64], s_sum[TR_FEW_QUERIES][64];  // column sums: a slice's, a query's
     const int tid = threadIdx.x, el = tid & 63, sl = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = 1 << log2_r, count = HATA_D * r, n_pairs = (n_blocks + 1) / 2;
-    constexpr int UN = 16;  // pairs of blocks whose sums are in flight together
-    const int p0 = sl * n_pairs / WAVES, p1 = (sl + 1) * n_pairs / WAVES, b0 = 2 * p0, b1 = min(2 * p1, n_blocks);
+    constexpr int UN = 16;  // runs of pairs of blocks whose sums are in flight together
+    const int n_runs = RUNS ? runs : n_pairs, r0 = sl * n_runs / WAVES, r1 = (sl + 1) * n_runs / WAVES;
+    const int b0 = 2 * (RUNS ? run_len : 1) * r0, b1 = min(2 * (RUNS ? run_len : 1) * r1, n_blocks);
     // the queries of blocks b .. below e, a lane each (the lanes behind them: the last one's); the rule: all are one query's
     auto queries_from = [&](int b, int e) { return block_query(block_group, max(min(b + el, e - 1), 0), n_groups); };
     auto uniform = [](int ids) { return __builtin_amdgcn_ballot_w64(ids != __builtin_amdgcn_readfirstlane(ids)) == 0ull; };
@@ -664,19 +1093,35 @@ __global__ __launch_bounds__(TR_UPDATE_WAVES * 64) __attribute__((amdgpu_waves_p
     };
     if ((int)blockIdx.x * 64 < count) {  // (count is a multiple of 64; the last block is past it)
         const int e0 = blockIdx.x * 64, e = e0 + el, j = e & (r - 1);
-        const float* dp = dw_part + e;
+        const float* const dp = dw_part + e;
         int ids = queries_from(b0, min(b0 + 2 * UN, b1));
         if (!colsum) request_columns(j, b0, b1);
         float ke[UN], dw[UN];
-        auto fetch = [&](int p) {
+        // what the last pairs of runs i, i + 1, ... hold: the whole run's sums where its query stays the same
+        auto fetch = [&](int i) {
 #pragma unroll
             for (int u = 0; u < UN; ++u) {
-                const float* at = dp + (int64_t)max(min(p + u, p1 - 1), 0) * 3 * count;
+                const int run = max(min(i + u, r1 - 1), 0);
+                const float* at = dp + (int64_t)(RUNS ? min((run + 1) * run_len, n_pairs) - 1 : run) * 3 * count;
                 ke[u] = at[0];
                 dw[u] = at[count];
             }
         };
-        fetch(p0);
+        // the query of run i + lane % 16's first block; whether others follow in that run
+        auto queries_of = [&](int i, int& first, bool& broken) {
+            const int b = 2 * run_len * max(min(i + (el & (UN - 1)), r1 - 1), 0);
+            int id[2 * TR_KEPT];
+#pragma unroll
+            for (int k = 0; k < 2 * TR_KEPT; ++k) id[k] = block_query(block_group, min(b + min(k, 2 * run_len - 1), n_blocks - 1), n_groups);
+            first = id[0];
+            broken = false;
+#pragma unroll
+            for (int k = 1; k < 2 * TR_KEPT; ++k) broken |= id[k] != first;
+        };
+        int run_query = 0;
+        bool run_broken = false;
+        if constexpr (RUNS) queries_of(r0, run_query, run_broken);
+        fetch(r0);
         constexpr int NG = HATA_D / WAVES;
         float wo[NG];
 #pragma unroll
@@ -699,15 +1144,15 @@ __global__ __launch_bounds__(TR_UPDATE_WAVES * 64) __attribute__((amdgpu_waves_p
         }
         auto factor_of = [&](int q) { return c_bal * (colsum ? colsum[(int64_t)q * r + j] : s_sum[q][el]); };
         float gp[4] = {0.f, 0.f, 0.f, 0.f};
-        for (int p = p0; p < p1; p += UN) {
-            if (p != p0) {
+        for (int p = r0; p < (RUNS ? r0 : r1); p += UN) {  // (a run: a pair of blocks)
+            if (p != r0) {
                 ids = queries_from(2 * p, min(2 * (p + UN), b1));
                 fetch(p);
             }
             if (uniform(ids)) {
                 const float fc = factor_of(__builtin_amdgcn_readfirstlane(ids));
 #pragma unroll
-                for (int u = 0; u < UN; ++u) gp[u & 3] += p + u < p1 ? fmaf(fc, ke[u], dw[u]) : 0.f;
+                for (int u = 0; u < UN; ++u) gp[u & 3] += p + u < r1 ? fmaf(fc, ke[u], dw[u]) : 0.f;
             } else {
                 float f0[UN], f1[UN], k1[UN];
 #pragma unroll
@@ -721,7 +1166,43 @@ __global__ __launch_bounds__(TR_UPDATE_WAVES * 64) __attribute__((amdgpu_waves_p
                     }
                 }
 #pragma unroll
-                for (int u = 0; u < UN; ++u) gp[u & 3] += p + u < p1 ? fmaf(f1[u], k1[u], fmaf(f0[u], ke[u], dw[u])) : 0.f;
+                for (int u = 0; u < UN; ++u) gp[u & 3] += p + u < r1 ? fmaf(f1[u], k1[u], fmaf(f0[u], ke[u], dw[u])) : 0.f;
+            }
+        }
+        for (int i = r0; i < (RUNS ? r1 : r0); i += UN) {
+            if (i != r0) {
+                queries_of(i, run_query, run_broken);
+                fetch(i);
+            }
+            const uint32_t broken = (uint32_t)__builtin_amdgcn_ballot_w64(run_broken) & ((1u << UN) - 1u);
+            if (broken == 0 && uniform(run_query)) {
+                const float fc = factor_of(__builtin_amdgcn_readfirstlane(run_query));
+#pragma unroll
+                for (int u = 0; u < UN; ++u) gp[u & 3] += i + u < r1 ? fmaf(fc, ke[u], dw[u]) : 0.f;
+                continue;
+            }
+            float f[UN];
+#pragma unroll
+            for (int u = 0; u < UN; ++u) f[u] = factor_of(__builtin_amdgcn_readlane(run_query, u));
+#pragma unroll
+            for (int u = 0; u < UN; ++u) gp[u & 3] += i + u < r1 && !(broken >> u & 1u) ? fmaf(f[u], ke[u], dw[u]) : 0.f;
+            // a run with several queries: a pair has a place of its own where its query does not go on
+#pragma clang loop unroll(disable)
+            for (uint32_t left = broken; left; left &= left - 1) {
+                const int run = i + __builtin_ctz(left);
+                if (run >= r1) break;
+                const int p_last = min((run + 1) * run_len, n_pairs);
+#pragma clang loop unroll(disable)
+                for (int p = run * run_len; p < p_last; ++p) {
+                    const int id = queries_from(2 * p, n_blocks);
+                    const int q0 = __builtin_amdgcn_readlane(id, 0), q1 = __builtin_amdgcn_readlane(id, 1);
+                    const bool goes_on = q1 == q0 && __builtin_amdgcn_readlane(id, 2) == q0 && __builtin_amdgcn_readlane(id, 3) == q0;
+                    if (goes_on && p + 1 < p_last) continue;
+                    const float* const at = dp + (int64_t)p * 3 * count;
+                    const float k0 = at[0], d0 = at[count], k1 = at[q1 != q0 ? 2 * count : 0];
+                    gp[0] += fmaf(factor_of(q0), k0, d0);
+                    if (q1 != q0) gp[0] = fmaf(factor_of(q1), k1, gp[0]);
+                }
             }
         }
         double wp = 0.0;
@@ -1051,36 +1532,51 @@ int hata_train_step(hata_train_ctx* ctx, const void* Q, const void* K, const flo
     const uint16_t* k = (const uint16_t*)K;
     const bool few = n_wgs <= TR_FEW_WGS && n_queries <= TR_FEW_QUERIES;
     const float* colsum = few ? nullptr : ctx->colsum;
-    // The gradient launch: a workgroup per pair of blocks and 64 hash columns, or 32 where it all goes in one round of the chip
-    // then, which a narrower workgroup is through sooner (us a step, one query vector a block / others: one block r = 64 20.3 / 26.4 ->
-    // 16.6 / 19.5, r = 256 24.3 / 30.1 -> 20.2 / 23.0; 64 blocks r = 128 23.5 / 29.1 -> 19.9 / 22.6; 256 blocks r = 64 24.1 / 29.9 -> 20.8 / 24.3).  At least a piece of W W^T each: workgroups behind the pairs have
-    // nothing else.
-    const int pairs = (n_wgs + 1) / 2, cols = r == 32 || pairs * (r / 32) <= TR_ONE_ROUND ? 32 : 64, col_groups = r / cols;
-    const int n_grad = pairs * col_groups < 2 * HATA_D ? 2 * HATA_D / col_groups : pairs;
-#define HATA_TRAIN_GRAD(RR, CC)                                                                                          \
+    // The gradient launch.  A workgroup per pair of blocks and 32 hash columns where that is at most one round of the chip, which is through
+    // sooner than one of 64 (us a step, one query vector a block / others: one block r = 64 20.3 / 26.4 -> 16.6 / 19.5, r = 256 24.3 / 30.1 ->
+    // 20.2 / 23.0; 64 blocks r = 128 23.5 / 29.1 -> 19.9 / 22.6).  Beyond, a workgroup goes through as many pairs as one round takes, in
+    // runs of at most TR_KEPT -- but where two would do and a query need not end with a run, a pair and 64 columns: a second query in a
+    // workgroup's pairs costs it 5 us (r = 128, all runs whole / not, 64 columns / two pairs: 192 blocks 28.1 / 27.0, 202 29.5 / 32.5, 256
+    // 28.5 / 27.2, 250 31.5 / 33.8; r = 256 128 blocks 33.9 / 32.9; r = 64 512 blocks 32.8 / 30.6; whole runs are what the host
+    // can tell, queries of equal shares).  At least a piece of W W^T each: workgroups behind the pairs have nothing else.
+    const int pairs = (n_wgs + 1) / 2, pairs_32 = pairs * (r / 32);
+    const bool one_stage = pairs_32 <= TR_ONE_ROUND || (r > 32 && pairs_32 <= 2 * TR_ONE_ROUND && n_wgs % (4 * n_queries) != 0);
+    const int cols = one_stage && pairs_32 > TR_ONE_ROUND ? 64 : 32, col_groups = r / cols;
+    const int least = one_stage ? 1 : (pairs * col_groups + TR_ONE_ROUND - 1) / TR_ONE_ROUND;
+    const int runs_each = (least + TR_KEPT - 1) / TR_KEPT, run_len = (least + runs_each - 1) / runs_each, stages = runs_each * run_len;
+    const int n_runs = (pairs + run_len - 1) / run_len, n_grad_wgs = (pairs + stages - 1) / stages;
+    const int n_grad = n_grad_wgs * col_groups < 2 * HATA_D ? 2 * HATA_D / col_groups : n_grad_wgs;
+#define HATA_TRAIN_ONE(RR, CC)                                                                                           \
     hipLaunchKernelGGL((hata::train_grad_kernel<RR, CC>), dim3(n_grad, RR / CC), dim3(hata::TrainShape<CC>::THREADS), 0, \
                        st, q, k, s, W, n, n_wgs, hp->sigma, c_sim, block_query, n_queries, ctx->dw_part,                 \
                        ctx->colsum_part, ctx->loss_part, ctx->gram, ctx->fro_part, ctx->W_old)
-#define HATA_TRAIN_CASE(RR)                          \
-    case RR:                                         \
-        if (cols == 32) HATA_TRAIN_GRAD(RR, 32);     \
-        else HATA_TRAIN_GRAD(RR, 64);                \
+#define HATA_TRAIN_CASE(RR)                                                                                                         \
+    case RR:                                                                                                                        \
+        if (!one_stage)                                                                                                             \
+            hipLaunchKernelGGL(hata::train_grad_runs_kernel<RR>, dim3(n_grad, RR / 32), dim3(hata::TrainShape<32>::THREADS), 0, st, \
+                               q, k, s, W, n, n_wgs, stages, run_len, hp->sigma, c_sim, block_query, n_queries, ctx->dw_part,       \
+                               ctx->colsum_part, ctx->loss_part, ctx->gram, ctx->fro_part, ctx->W_old);                             \
+        else if (cols == 32)                                                                                                        \
+            HATA_TRAIN_ONE(RR, 32);                                                                                                 \
+        else                                                                                                                        \
+            HATA_TRAIN_ONE(RR, (RR < 64 ? 32 : 64));                                                                                \
         break
     switch (r) {
-        case 32: HATA_TRAIN_GRAD(32, 32); break;
+        HATA_TRAIN_CASE(32);
         HATA_TRAIN_CASE(64);
         HATA_TRAIN_CASE(128);
         HATA_TRAIN_CASE(256);
     }
 #undef HATA_TRAIN_CASE
-#undef HATA_TRAIN_GRAD
+#undef HATA_TRAIN_ONE
     if (!few)
         hipLaunchKernelGGL(hata::train_colreduce_kernel, dim3((r + 63) / 64, n_queries), dim3(TR_REDUCE_WAVES * 64), 0, st,
                            ctx->colsum_part, r, n_wgs, block_query, n_queries, ctx->colsum);
-    hipLaunchKernelGGL(hata::train_update_kernel, dim3(HATA_D * r / 64 + (loss ? 1 : 0)), dim3(TR_UPDATE_WAVES * 64), 0, st, W, v, __builtin_ctz(r), n_wgs, pairs * col_groups,
+    hipLaunchKernelGGL(run_len > 1 ? hata::train_update_kernel<true> : hata::train_update_kernel<false>, dim3(HATA_D * r / 64 + (loss ? 1 : 0)),
+                       dim3(TR_UPDATE_WAVES * 64), 0, st, W, v, __builtin_ctz(r), n_wgs, n_grad_wgs * col_groups,
                        hp->sigma, hp->lam, c_sim, c_bal, hp->lr, hp->momentum, hp->weight_decay, ctx->dw_part,
                        ctx->colsum_part, colsum, block_query, n_queries, ctx->gram, ctx->fro_part, ctx->W_old,
-                       ctx->loss_part, grad, loss);
+                       ctx->loss_part, grad, loss, run_len, n_runs);
     return hipGetLastError() == hipSuccess ? HATA_OK : HATA_EHIP;
 }
 
