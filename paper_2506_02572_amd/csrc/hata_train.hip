@@ -1275,7 +1275,7 @@ __global__ __launch_bounds__(TR_UPDATE_WAVES * 64) __attribute__((amdgpu_waves_p
 // are not among the first tenth.  So three launches: the scores, with a coarse histogram of them; from the
 // histogram the bin the n_pos-th score lies in -- everything below it is -1, everything from it up goes into a
 // candidate list, in any order; ranks by counting inside that list (a hundredth of the compares where the scores
-// spread over the bins; m^2 again if they all fall into one).  18 us at m = 8192.
+// spread over the bins; m^2 again if they all fall into one).  14 us at m = 8192.
 #define LB_BINS 2048
 #define LB_COPIES 8     // of the histogram: scores crowd into a few dozen bins, and atomics on one word queue up
 #define LB_PASS 16      // scores of a workgroup in one pass
@@ -1402,37 +1402,38 @@ __global__ __launch_bounds__(256) void train_candidates_kernel(const double* __r
     }
 }
 
-// ranks inside the candidate list: 64 candidates per workgroup and turn, each counted by sixteen waves over a
-// sixteenth of the list; the histogram is cleared for the next call
+// ranks inside the candidate list: LB_RANKED candidates per workgroup and turn, a lane for each in every sixteen, each counted by 64
+// groups of lanes over a 64th of the list; the histogram is cleared for the next call.  Bound by the compares' instructions where
+// workgroups are few: 64 candidates a workgroup, each wave handing a sixteenth of the list round as scalars, were 27 workgroups at 8192 keys
+// and 9.2 us, these 104 take 5.1.
+#define LB_RANKED 16
 __global__ __launch_bounds__(1024) void train_labels_kernel(const LabelCand* __restrict__ cand, const uint32_t* __restrict__ n_cand,
                                                             int n_pos, uint32_t* __restrict__ bins, float* __restrict__ s) {
-    __shared__ int s_rank[16][64];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    __shared__ int s_rank[16][LB_RANKED];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, own = lane % LB_RANKED;
     if (blockIdx.x == gridDim.x - 1)
         for (int i = tid; i < LB_COPIES * LB_BINS; i += 1024) bins[i] = 0;
     const int nc = (int)*n_cand;
-    for (int c0 = blockIdx.x * 64; c0 < nc; c0 += gridDim.x * 64) {
-        const LabelCand me = cand[min(c0 + lane, nc - 1)];
+    for (int c0 = blockIdx.x * LB_RANKED; c0 < nc; c0 += gridDim.x * LB_RANKED) {
+        const LabelCand me = cand[min(c0 + own, nc - 1)];
         int rank = 0;
-        for (int j = wave * 64; j < nc; j += 16 * 64) {
-            // 64 entries, one per lane, handed round as scalars; key 0 (behind every score) past the end
-            const LabelCand o = cand[min(j + lane, nc - 1)];
-            const bool live = j + lane < nc;
-            const int klo = live ? (int)(uint32_t)o.key : 0, khi = live ? (int)(uint32_t)(o.key >> 32) : 0;
+        constexpr int UN = 8;  // entries of a lane in flight together
+        for (int j0 = tid / LB_RANKED; j0 < nc; j0 += 64 * UN) {
+            LabelCand o[UN];
 #pragma unroll
-            for (int t = 0; t < 64; ++t) {
-                const unsigned long long key = ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane(khi, t) << 32) |
-                                               (uint32_t)__builtin_amdgcn_readlane(klo, t);
-                const uint32_t row = (uint32_t)__builtin_amdgcn_readlane((int)o.row, t);
-                rank += (key > me.key || (key == me.key && row < me.row)) ? 1 : 0;
-            }
+            for (int t = 0; t < UN; ++t) o[t] = cand[min(j0 + 64 * t, nc - 1)];
+#pragma unroll
+            for (int t = 0; t < UN; ++t)
+                rank += j0 + 64 * t < nc && (o[t].key > me.key || (o[t].key == me.key && o[t].row < me.row)) ? 1 : 0;
         }
-        s_rank[wave][lane] = rank;
+        rank += __shfl_xor(rank, 16, 64);
+        rank += __shfl_xor(rank, 32, 64);
+        if (lane < LB_RANKED) s_rank[wave][lane] = rank;
         __syncthreads();
-        if (wave == 0 && c0 + lane < nc) {
+        if (tid < LB_RANKED && c0 + tid < nc) {
             rank = 0;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) rank += s_rank[i][lane];
+            for (int i = 0; i < 16; ++i) rank += s_rank[i][tid];
             s[me.row] = rank < n_pos ? rank_label(rank, n_pos) : -1.f;
         }
         __syncthreads();
@@ -1605,7 +1606,7 @@ int hata_train_make_labels(hata_train_ctx* ctx, const void* q, const void* K, in
     hipLaunchKernelGGL(hata::train_candidates_kernel, dim3((m + 255) / 256), dim3(256), 0, st, ctx->scores, m, n_pos,
                        ctx->bins, ctx->n_cand, ctx->cand, s);
     // enough workgroups for twice the expected list (they take more turns if it is longer)
-    hipLaunchKernelGGL(hata::train_labels_kernel, dim3(n_pos / 32 + 2), dim3(1024), 0, st, ctx->cand, ctx->n_cand, n_pos,
+    hipLaunchKernelGGL(hata::train_labels_kernel, dim3(n_pos / (LB_RANKED / 2) + 2), dim3(1024), 0, st, ctx->cand, ctx->n_cand, n_pos,
                        ctx->bins, s);
     const bool ok = hipGetLastError() == hipSuccess;
     ctx->bins_clear = ok && cleared;  // (after a call that failed half-way the next one clears again)
