@@ -114,6 +114,22 @@ struct UnitHash {
         }
         return acc;
     }
+    // This lane's part of ONE vector's projection (v: that vector's channels in every lane) on the vector ALU: column lane % 16, its
+    // own channels.  A pass of one vector takes the matrix instruction as long as one of four, this a quarter of that.
+    __device__ __forceinline__ double project_one(const Vector& v) const {
+        double acc = 0.0;
+#pragma unroll
+        for (int s = 0; s < CH; ++s)
+            acc = fma((double)w[s], (double)((s & 1) ? bf16_hi(v.x[s >> 1]) : bf16_lo(v.x[s >> 1])), acc);
+        return acc;
+    }
+    // sign bits of such a projection, the waves' parts added up
+    static __device__ __forceinline__ void store_bits_one(double acc, uint32_t* s_codes, int group, int vector) {
+        acc += __shfl_xor(acc, 16, 64);
+        acc += __shfl_xor(acc, 32, 64);
+        const unsigned long long bits = __builtin_amdgcn_ballot_w64(acc >= 0.0);
+        if ((threadIdx.x & 63) == 0) reinterpret_cast<uint16_t*>(s_codes)[vector * (R / 16) + group] = (uint16_t)bits;
+    }
     // sign bits of a whole projection: 16 bits of vector first + lane % 4 (below `last`), into s_codes[vector][R / 32]
     static __device__ __forceinline__ void store_bits(double acc, uint32_t* s_codes, int group, int first, int last) {
         const int lane = threadIdx.x & 63, v = first + lane;

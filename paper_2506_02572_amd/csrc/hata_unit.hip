@@ -5,8 +5,8 @@
 // workgroups that share a unit (hata_coop.hip).  With up to 4096 keys a compute unit reads a unit's codes (64 KB at
 // r = 128) in the time of one or two exchanges, so nothing is shared: every stage hands over in LDS, a barrier
 // apart.  No workgroup waits for another one either, so the grid need not be resident and the device may be shared.
-// us a layer, workgroups that share units / this: one sequence, eight KV heads, r = 128, 2048 keys 16.0 / 10.7, 4096 keys
-// 15.7 / 11.7, a group of eight 19.6 / 14.2, r = 256 18.2 / 15.4; 32 sequences of 4096 keys 22.8 / 13.5.
+// us a layer, workgroups that share units / this: one sequence, eight KV heads, r = 128, 2048 keys 16.0 / 10.3, 4096 keys
+// 15.7 / 11.3, a group of eight 19.6 / 13.7, r = 256 18.2 / 14.8; 32 sequences of 4096 keys 22.8 / 13.5.
 // Beyond that the unit's time is what one compute unit streams and gathers, so longer caches and large budgets take this
 // form only where the units are many: takes_unit_step in hata_api.hip, with both sides measured.
 #include "hata_attn_core.h"
@@ -58,7 +58,11 @@ __global__ __launch_bounds__(HATA_UNIT_THREADS) void decode_step_unit_kernel(con
     constexpr int UNR = LONG && WD <= 4 ? 8 : 4;  // keys of a thread whose codes are in flight together
     constexpr bool MFMA = G >= 4;             // matrix-core form of the attention core
     using Hash = UnitHash<R>;
-    constexpr int PASSES = G / 4 + 1;  // of four vectors: the query heads and the appended key
+    // Passes of four vectors, the query heads and the appended key.  Where the heads fill theirs, the key's goes over the vector
+    // ALU: alone it took the matrix instruction as long as four (16.6 cycles for an fp64 FMA's 4.4), and the waves of a compute unit were
+    // 0.45 us at it (us a layer, groups of four: 2048 keys 10.98 -> 10.57, 4096 11.88 -> 11.52, r = 256 14.61 -> 14.05; of eight
+    // 13.54 -> 13.08, 128 units of 4096 keys 16.01 -> 15.66).  One or two left-over heads too: no faster (11.85 / 12.05, a group of five).
+    constexpr int PASSES = G / 4 + 1;
     __shared__ __attribute__((aligned(16))) union {
         double part[PASSES][NW][64];  // projections, by the waves that share their columns
         uint16_t vt[MFMA ? NW * HATA_VT_WAVE : 8];
@@ -141,7 +145,8 @@ __global__ __launch_bounds__(HATA_UNIT_THREADS) void decode_step_unit_kernel(con
     double acc[PASSES];
 #pragma unroll
     for (int p = 0; p < PASSES; ++p)
-        if (4 * p < G || own) acc[p] = hash.project(x[p]);
+        if (4 * p < G) acc[p] = hash.project(x[p]);
+        else if (own) acc[p] = hash.project_one(x[p]);
     if constexpr (Hash::PARTS > 1) {
 #pragma unroll
         for (int p = 0; p < PASSES; ++p)
@@ -154,13 +159,15 @@ __global__ __launch_bounds__(HATA_UNIT_THREADS) void decode_step_unit_kernel(con
                 double t = U.part[p][group][lane];
 #pragma unroll
                 for (int i = 1; i < Hash::PARTS; ++i) t += U.part[p][group + i * Hash::GROUPS][lane];
-                Hash::store_bits(t, s_codes, group, 4 * p, vectors);
+                if (4 * p < G) Hash::store_bits(t, s_codes, group, 4 * p, vectors);
+                else Hash::store_bits_one(t, s_codes, group, G);
             }
         }
     } else {
 #pragma unroll
         for (int p = 0; p < PASSES; ++p)
-            if (4 * p < G || own) Hash::store_bits(acc[p], s_codes, group, 4 * p, vectors);
+            if (4 * p < G) Hash::store_bits(acc[p], s_codes, group, 4 * p, vectors);
+            else if (own) Hash::store_bits_one(acc[p], s_codes, group, G);
     }
     __syncthreads();
     if (tid < G * WD) a.qcodes[((int64_t)b * a.Hq + hq0) * WD + tid] = s_codes[tid];
