@@ -13,8 +13,11 @@ namespace hata {
 // not null) and n_new[b] <= max_new keys from row start[b] on (K not null; from_seq_len: the one key at row
 // start[b] - 1), four vectors at a time, the next four's channels fetched ahead.  Bound by latency, the
 // launch and two round trips to memory; a workgroup of 1024 threads per unit (queries) or per key on the vector
-// ALU took 4.0 and 11.5 us at 64 units, r = 128, this takes 3.9 for both.
-template <int COLS>
+// ALU took 4.0 and 11.5 us at 64 units, r = 128, this took 3.9 for both.
+// ONE: a launch that has at most one vector a unit, over the vector ALU (hash_one): 64 units, r = 128, a query and a key 0.4 us less
+// each, the five stage calls of two layers 51.9 -> 50.1 us.  (Chosen inside the kernel, for a last one behind the fours too, it cost the
+// launches of six vectors 0.2 us: their code is fetched anew every time.)
+template <int COLS, bool ONE>
 __global__ __launch_bounds__(256) void encode_few_kernel(
     const uint16_t* __restrict__ q, uint32_t* __restrict__ qcodes, const uint16_t* __restrict__ K,
     const int32_t* __restrict__ start, const int32_t* __restrict__ n_new, int max_new, int from_seq_len,
@@ -44,9 +47,10 @@ __global__ __launch_bounds__(256) void encode_few_kernel(
     if (nv <= 0) return;
     uint4 x[4], xn[4];
     load(0, x);
-    for (int v0 = 0; v0 < nv; v0 += 4) {
-        if (v0 + 4 < nv) load(v0 + 4, xn);
-        hash_pass<COLS>(hw, x, s_codes, WPS, v0, nv);
+    for (int v0 = 0; v0 < (ONE ? 1 : nv); v0 += 4) {
+        if (!ONE && v0 + 4 < nv) load(v0 + 4, xn);
+        if constexpr (ONE) hash_one<COLS>(hw, x, s_codes, WPS, v0);
+        else hash_pass<COLS>(hw, x, s_codes, WPS, v0, nv);
 #pragma unroll
         for (int i = 0; i < 4; ++i) x[i] = xn[i];
     }
@@ -586,8 +590,9 @@ hipError_t launch_encode_vectors(const hata_ctx* c, const void* q, uint32_t* qco
                                  const float* W_H, int B, hipStream_t s) {
     const hata_config& f = c->cfg;
     if (!q && !K) return hipSuccess;
+    const bool one = (q ? c->G : 0) + (K ? (from_seq_len ? 1 : max_new) : 0) == 1;
 #define HATA_LAUNCH_FEW(COLS)                                                                                       \
-    hipLaunchKernelGGL((encode_few_kernel<COLS>), dim3(f.r / COLS, B * f.Hkv), dim3(256), 0, s, (const uint16_t*)q, \
+    hipLaunchKernelGGL((one ? encode_few_kernel<COLS, true> : encode_few_kernel<COLS, false>), dim3(f.r / COLS, B * f.Hkv), dim3(256), 0, s, (const uint16_t*)q, \
                        qcodes, (const uint16_t*)K, start, n_new, max_new, from_seq_len, codes, W_H, f.Hq, f.Hkv,    \
                        c->G, f.r, f.L_cap, f.kv_stride_b, f.kv_stride_h, f.kv_stride_n)
     if (f.r % 64 == 0) HATA_LAUNCH_FEW(64);

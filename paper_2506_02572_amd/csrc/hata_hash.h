@@ -73,6 +73,28 @@ __device__ __forceinline__ void hash_pass(const HashWeights<COLS>& W, const uint
     if (lane < 4 && v < last && wave < COLS / 16) reinterpret_cast<uint16_t*>(s_codes)[v * pitch * 2 + wave] = (uint16_t)bits;
 }
 
+// One vector alone, over the vector ALU: a lane its column and its 32 channels of x.  The matrix instruction takes one vector as long
+// as four, and a wave alone on its SIMD waits 31 cycles for each before the next; an fp64 FMA takes 4.4.
+template <int COLS>
+__device__ __forceinline__ void hash_one(const HashWeights<COLS>& W, const uint4 (&x)[4], uint32_t* s_codes, int pitch, int vector) {
+    double acc[2] = {0.0, 0.0};
+#pragma unroll
+    for (int s = 0; s < 32; ++s) {
+        float w = W.w[s];
+        asm volatile("" : "+v"(w));  // (as above)
+        const uint4 q = x[s >> 3];
+        uint32_t pair = ((s >> 1) & 3) == 0 ? q.x : ((s >> 1) & 3) == 1 ? q.y : ((s >> 1) & 3) == 2 ? q.z : q.w;
+        asm volatile("" : "+v"(pair));
+        acc[s & 1] = fma((double)w, (double)((s & 1) ? bf16_hi(pair) : bf16_lo(pair)), acc[s & 1]);
+    }
+    double t = acc[0] + acc[1];
+    t += __shfl_xor(t, 16, 64);
+    t += __shfl_xor(t, 32, 64);
+    const unsigned long long bits = __builtin_amdgcn_ballot_w64(t >= 0.0);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (lane == 0 && wave < COLS / 16) reinterpret_cast<uint16_t*>(s_codes)[vector * pitch * 2 + wave] = (uint16_t)bits;
+}
+
 // ---- the same by 16 waves, each 16 columns and a part of the channels (r = 32 .. 256: 8, 4, 2 or 1 parts) ----
 template <int R>
 struct UnitHash {
