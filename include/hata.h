@@ -300,7 +300,7 @@ int hata_prefill_write_paged(hata_ctx* ctx, const void* K_new, const void* V_new
                              int32_t page_rows, int32_t n_pages, const float* W_H, void* stream);
 
 /* Host-side query of how hata_decode_step() runs a batch of B sequences; nothing is enqueued.
- * *n_launches: 1 (single-launch form) or 3 (three-launch form); *chunk: cached keys per scoring
+ * *n_launches: 1 (single-launch form) or 3 (three-launch form, whose first two go as one where the batch is small); *chunk: cached keys per scoring
  * workgroup for a batch of this size; *n_chunks: scoring workgroups per (sequence, KV head).  Any
  * output pointer (host) may be NULL. */
 int hata_step_plan(const hata_ctx* ctx, int32_t B, int32_t* n_launches, int32_t* chunk, int32_t* n_chunks);

@@ -559,13 +559,13 @@ int hata_decode_step(hata_ctx* ctx, const void* q, const void* K, const void* V,
         if (e == hipSuccess) return HATA_OK;
         if (e != hipErrorNotSupported) return HATA_EHIP;  // (not supported: no kernel for this shape, nothing was launched)
     }
-    // Alg. 3: HashEncode(Q), HashEncode(K_new) and the code-cache update, in one launch
-    hipError_t e = hata::launch_encode_vectors(ctx, q, ctx->qcodes, append ? K : nullptr, seq_len,
-                                               nullptr, 1, 1, codes, W_H, B, s);
-    if (e != hipSuccess) return HATA_EHIP;
-    // Three-launch path.  Hamming distances of every cached code (the new one included) and the chunks' cumulative
-    // histograms
-    e = hata::launch_score_select(ctx, codes, seq_len, k, B, s);
+    // Without waits: HashEncode(Q), HashEncode(K_new) and the code-cache update, then the Hamming distances of every
+    // cached code (the new one included) and the chunks' cumulative histograms, in one launch or in two
+    hipError_t e = hata::launch_encode_score(ctx, q, K, W_H, codes, append, seq_len, k, B, s);
+    if (e == hipErrorNotSupported) {
+        e = hata::launch_encode_vectors(ctx, q, ctx->qcodes, append ? K : nullptr, seq_len, nullptr, 1, 1, codes, W_H, B, s);
+        if (e == hipSuccess) e = hata::launch_score_select(ctx, codes, seq_len, k, B, s);
+    }
     if (e != hipSuccess) return HATA_EHIP;
     // TopK(S, N) compaction fused with the attention over the selected rows (gather fused too)
     e = hata::launch_attention(ctx, 2, q, K, V, ctx->idx, k, seq_len, B, sm_scale, out, out_f32, s);

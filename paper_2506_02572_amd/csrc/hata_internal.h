@@ -86,6 +86,8 @@ hipError_t launch_split_weights(const hata_ctx* c, const float* W_H, hipStream_t
 hipError_t launch_score(const hata_ctx* c, const uint32_t* qcodes, const uint32_t* codes, const int32_t* seq_len, int B,
                         uint16_t* scores, hipStream_t s);
 hipError_t launch_score_select(const hata_ctx* c, const uint32_t* codes, const int32_t* seq_len, const int32_t* k, int B, hipStream_t s);
+hipError_t launch_encode_score(const hata_ctx* c, const void* q, const void* K, const float* W_H, uint32_t* codes, int append,
+                               const int32_t* seq_len, const int32_t* k, int B, hipStream_t s);
 hipError_t prepare_dense();  // once per context
 hipError_t launch_dense(const hata_ctx* c, const void* q, const void* K, const void* V, const int32_t* seq_len, int B,
                         float sm_scale, void* out, float* out_f32, hipStream_t s);

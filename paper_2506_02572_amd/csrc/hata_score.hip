@@ -8,9 +8,10 @@
 // score_select_kernel is the scoring launch of the decode step without in-kernel waits: the workgroup also histograms its
 // chunk's scores in LDS and writes the CUMULATIVE histogram out (how many of the chunk's keys score at most s, 2 bytes per
 // s), from which the workgroups of the attention launch find the unit's threshold and their places in the index list
-// (hata_attn.hip).  (Every workgroup encoding its unit's queries for itself instead of a launch in front: 3.9 us of the
-// kernel, more than the launch takes: 2 x 20011 keys, a group of five, 23.7 us a step against 22.2.)
+// (hata_attn.hip).  encode_score_kernel is the same with the encoding in it, where one round of large workgroups covers the batch; with
+// workgroups of 256 threads, a chunk each, it was 3.9 us of the kernel, more than the launch in front takes.
 #include "hata_device.h"
+#include "hata_hash.h"
 #include "hata_internal.h"
 #include "hata_trace.h"
 
@@ -118,22 +119,25 @@ struct ScoreArgs {
 
 // The chunk's histogram in LDS (a multiple of 16 words, zero past its NB scores) -> its row of cumulative counts, and
 // the score at which these reach the chunk's share of the budget, if that were spread evenly over the unit's L keys: where the
-// next launch looks for the threshold.  256 threads, after a barrier; scan4: 4 words of LDS.
-__device__ __forceinline__ void store_cumulative(const ScoreArgs& a, const uint32_t* hist, int64_t u, int c, int b, int L, uint32_t* scan4) {
+// next launch looks for the threshold.  256 threads (t), after a barrier; scan4: 4 words of LDS.  Whoever is not `live` passes the
+// barrier only.
+__device__ __forceinline__ void store_cumulative(const ScoreArgs& a, const uint32_t* hist, int64_t u, int c, int b, int L, uint32_t* scan4,
+                                                 int t, bool live = true) {
     uint16_t* const row = a.cum + (u * a.n_chunks + c) * a.NBP;
     const int NBP = a.NBP, NBR = (a.NB + 15) / 16 * 16, n_keys = min(a.chunk, L - c * a.chunk);
     const int keff = min(clampi(a.kbud[b], 0, a.k_max), L);
     const uint32_t share = (uint32_t)min(n_keys, (int)((float)keff * (float)n_keys * __builtin_amdgcn_rcpf((float)L)) + 1);
-    const int tid = threadIdx.x, wv = tid >> 6, seg = ((NBR + 255) / 256 + 3) / 4 * 4, s0 = tid * seg;
+    const int wv = t >> 6, seg = ((NBR + 255) / 256 + 3) / 4 * 4, s0 = t * seg;
     uint32_t loc = 0;
-    for (int j = 0; j < seg; j += 4)
+    for (int j = 0; live && j < seg; j += 4)
         if (s0 + j < NBR) {
             const uint4 v = *reinterpret_cast<const uint4*>(&hist[s0 + j]);
             loc += v.x + v.y + v.z + v.w;
         }
     const uint32_t incl = wave_incl_scan(loc);
-    if ((tid & 63) == 63) scan4[wv] = incl;
+    if (live && (t & 63) == 63) scan4[wv] = incl;
     __syncthreads();
+    if (!live) return;
     uint32_t run = (wv > 0 ? scan4[0] : 0u) + (wv > 1 ? scan4[1] : 0u) + (wv > 2 ? scan4[2] : 0u) + incl - loc;
     for (int j = 0; j < seg; j += 4)
         if (s0 + j < NBP) {
@@ -168,7 +172,113 @@ __global__ __launch_bounds__(256) void score_select_kernel(const ScoreArgs a) {
         atomicAdd(&hist[s], 1u);
     });
     __syncthreads();
-    store_cumulative(a, hist, u, c, b, L, scan4);
+    store_cumulative(a, hist, u, c, b, L, scan4, tid);
+}
+
+struct EncodeScoreArgs {
+    ScoreArgs s;
+    const uint16_t* q;
+    const uint16_t* K;
+    const float* W_H;
+    uint32_t* codes;
+    uint32_t* qcodes;
+    int append, log2_threads;  // of a chunk
+    int64_t sb, sh, sn;
+};
+
+// The scoring launch with the encoding in it: a workgroup of 1024 threads encodes its unit's query vectors for itself (and the appended
+// key, where its chunks hold that row) as the workgroup per unit of hata_unit.hip does, its first codes on their way meanwhile, and
+// then has 1024, 512 or 256 threads for each of one, two or four chunks.  grid = (workgroups of a unit, Hkv, B).
+// What bounds it: the launch, the round trips to the weights and the appended row, half a microsecond of fp64 of every compute unit.
+// A launch in front of the scoring costs its own launch and round trips on top: 2 x 20011 keys, a group of five, 21.7 us a step with one,
+// 20.2 so (launch_encode_score has the rule).
+template <int WD, int G>
+__global__ __launch_bounds__(1024) void encode_score_kernel(const EncodeScoreArgs a) {
+    constexpr int R = WD * 32, NB = G * R + 1, NBR = (NB + 15) / 16 * 16, NW = 16, NT = 1024;
+    constexpr int PASSES = G / 4 + 1;  // of four vectors: the query heads and the appended key, which goes alone where the heads fill theirs
+    constexpr int UNR = 4;             // keys of a thread whose codes are in flight together
+    using Hash = UnitHash<R>;
+    static_assert(Hash::PARTS > 1, "the waves of a group of columns meet in LDS");
+    __shared__ double part[PASSES][NW][64];
+    __shared__ uint32_t s_codes[(G + 1) * WD];
+    __shared__ uint32_t scan4[4][4];
+    extern __shared__ __attribute__((aligned(16))) uint32_t hists[];  // [chunks of the workgroup][NBR]
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int h = blockIdx.y, b = blockIdx.z;
+    const int64_t u = (int64_t)b * a.s.Hkv + h;
+    Hash hash;
+    hash.fetch(a.W_H + (int64_t)h * HATA_D * R);
+    const uint16_t* qv = a.q + ((int64_t)b * a.s.Hq + (int64_t)h * G) * HATA_D;
+    typename Hash::Vector x[PASSES];
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p)
+        if (4 * p < G) x[p] = Hash::fetch_x(qv + min(4 * p + (lane & 3), G - 1) * HATA_D);
+    const int L = clampi(a.s.seq_len[b], 0, a.s.L_cap);
+    const int chunks = NT >> a.log2_threads, threads = 1 << a.log2_threads, sub = tid >> a.log2_threads, t = tid & (threads - 1);
+    const int first = blockIdx.x * chunks * a.s.chunk;
+    if (first >= L && blockIdx.x != 0) return;  // (the first workgroup writes the query codes of an empty sequence too)
+    const int c = blockIdx.x * chunks + sub, base = c * a.s.chunk, end = min(base + a.s.chunk, L);
+    const bool own = a.append && L - 1 >= first && L - 1 < first + chunks * a.s.chunk;  // row L - 1 is encoded here
+    if (own) {
+        const uint16_t* kx = a.K + b * a.sb + h * a.sh + (int64_t)(L - 1) * a.sn;
+        if (G % 4 == 0 || (lane & 3) == G % 4) x[PASSES - 1] = Hash::fetch_x(kx);
+    }
+    const uint32_t* const cp = a.s.codes + u * a.s.L_cap * WD;
+    const int stop = own ? min(end, L - 1) : end;
+    CodeVec<WD> kc[UNR];
+    auto load_codes = [&](int n0) {
+#pragma unroll
+        for (int j = 0; j < UNR; ++j) {
+            const int n = n0 + j * threads;
+            if (n < stop) kc[j] = load_code<WD>(cp + (int64_t)n * WD);
+        }
+    };
+    load_codes(base + t);
+    for (int i = tid; i < chunks * NBR; i += NT) hists[i] = 0;
+    const int vectors = own ? G + 1 : G, group = wave % Hash::GROUPS;
+    auto there = [&](int p) { return 4 * p < G || own; };
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p)
+        if (there(p)) part[p][wave][lane] = 4 * p < G ? hash.project(x[p]) : hash.project_one(x[p]);
+    __syncthreads();
+    // the waves of a group of columns share the passes
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) {
+        if (there(p) && p % Hash::PARTS == wave / Hash::GROUPS) {
+            double v = part[p][group][lane];
+#pragma unroll
+            for (int i = 1; i < Hash::PARTS; ++i) v += part[p][group + i * Hash::GROUPS][lane];
+            if (4 * p < G) Hash::store_bits(v, s_codes, group, 4 * p, vectors);
+            else Hash::store_bits_one(v, s_codes, group, G);
+        }
+    }
+    __syncthreads();
+    if (blockIdx.x == 0 && tid < G * WD) a.qcodes[((int64_t)b * a.s.Hq + (int64_t)h * G) * WD + tid] = s_codes[tid];
+    if (own && tid < WD) a.codes[(u * a.s.L_cap + L - 1) * WD + tid] = s_codes[G * WD + tid];
+    QuerySum<WD, G> sum;
+    sum.init(s_codes);
+    uint32_t* const hist = hists + sub * NBR;
+    uint16_t* const sp = a.s.scores + u * a.s.L_cap;
+    auto scored = [&](int n, const uint32_t (&k)[WD]) {
+        const uint32_t s = sum(k);
+        sp[n] = (uint16_t)s;
+        atomicAdd(&hist[s], 1u);
+    };
+    for (int n0 = base + t; n0 < stop;) {
+#pragma unroll
+        for (int j = 0; j < UNR; ++j)
+            if (n0 + j * threads < stop) scored(n0 + j * threads, kc[j].w);
+        n0 += threads * UNR;
+        if (n0 < stop) load_codes(n0);
+    }
+    if (own && t == 0 && L - 1 >= base && L - 1 < base + a.s.chunk) {
+        uint32_t kw[WD];
+#pragma unroll
+        for (int w = 0; w < WD; ++w) kw[w] = s_codes[G * WD + w];
+        scored(L - 1, kw);
+    }
+    __syncthreads();
+    store_cumulative(a.s, hist, u, c, b, L, scan4[sub], t, base < L && t < 256);
 }
 
 // Generic fallback: any WD <= 8 and G <= 16, query codes in LDS.
@@ -198,7 +308,7 @@ __global__ __launch_bounds__(256) void score_kernel_generic(const ScoreArgs a, i
     }
     if (a.kbud) {
         __syncthreads();
-        store_cumulative(a, hist, u, c, b, L, scan4);
+        store_cumulative(a, hist, u, c, b, L, scan4, tid);
     }
 }
 
@@ -252,6 +362,44 @@ hipError_t launch_score_select(const hata_ctx* c, const uint32_t* codes, const i
         default: launch_generic(c, a, B, s);
     }
     return hipGetLastError();
+}
+
+template <int WD>
+static const void* encode_score_fn(int G) {
+    switch (G) {
+        case 1: return (const void*)&encode_score_kernel<WD, 1>;
+        case 2: return (const void*)&encode_score_kernel<WD, 2>;
+        case 4: return (const void*)&encode_score_kernel<WD, 4>;
+        case 5: return (const void*)&encode_score_kernel<WD, 5>;
+        case 8: return (const void*)&encode_score_kernel<WD, 8>;
+        default: return nullptr;
+    }
+}
+
+// query codes, the appended key's code, scores and cumulative chunk histograms in one launch; hipErrorNotSupported: not this shape
+hipError_t launch_encode_score(const hata_ctx* c, const void* q, const void* K, const float* W_H, uint32_t* codes, int append,
+                               const int32_t* seq_len, const int32_t* k, int B, hipStream_t s) {
+    const hata_config& f = c->cfg;
+    const void* fn = c->Wd == 1 ? encode_score_fn<1>(c->G) : c->Wd == 2 ? encode_score_fn<2>(c->G) : c->Wd == 4 ? encode_score_fn<4>(c->G) : nullptr;
+    if (!fn) return hipErrorNotSupported;
+    // One round of workgroups, with as few chunks each as that allows: in more, every one of them encodes on the bandwidth's time (us a
+    // step, two launches / one: 160 units of 4096-key chunks, 32768 keys 49.6 / 52.1, 40 units of 131072 45.2 / 51.5; one head a
+    // unit, 256 of 32768, 64.9 / 64.0).  Up to it, r = 128: 8 units of 32768 keys 20.1 / 17.8, of 131072 23.9 / 21.1, 32 of
+    // 16000 21.3 / 19.1, groups of eight 16 of 32768 25.5 / 23.3, four chunks a workgroup 128 of 32768 45.4 / 42.9, one head a unit 33.1 / 31.9.
+    // r = 256 has twice the fp64, and the weights leave no registers to hide it behind the codes' loads: 8 units of 20000 keys 19.8 / 19.8, two
+    // heads a unit 19.2 / 20.0, 32 units of 131072 45.0 / 45.5, groups of eight 24.4 / 27.0 -- it keeps two launches.
+    int chunks = 1;
+    auto wgs = [&](int n) { return (int64_t)((c->n_chunks + n - 1) / n) * f.Hkv * B; };
+    while (chunks < 4 && wgs(chunks) > c->cus) chunks *= 2;
+    if (wgs(chunks) > c->cus) return hipErrorNotSupported;
+    EncodeScoreArgs a;
+    a.s = score_args(c, c->qcodes, codes, seq_len, c->scores, k);
+    a.q = (const uint16_t*)q; a.K = (const uint16_t*)K; a.W_H = W_H; a.codes = codes; a.qcodes = c->qcodes;
+    a.append = append;
+    a.log2_threads = chunks == 1 ? 10 : chunks == 2 ? 9 : 8;
+    a.sb = f.kv_stride_b; a.sh = f.kv_stride_h; a.sn = f.kv_stride_n;
+    void* args[] = {(void*)&a};
+    return hipLaunchKernel(fn, dim3((c->n_chunks + chunks - 1) / chunks, f.Hkv, B), dim3(1024), args, (size_t)chunks * ((c->NB + 15) / 16 * 64), s);
 }
 
 }  // namespace hata
