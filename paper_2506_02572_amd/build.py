@@ -28,9 +28,13 @@ PRELOAD_SOURCES = ["hata_encode.hip", "hata_score.hip", "hata_topk.hip"]
 def stale() -> bool:
     if not os.path.exists(LIB):
         return True
-    t = os.path.getmtime(LIB)
-    deps = [os.path.join(CSRC, s) for s in SOURCES + HEADERS]
-    return any(os.path.getmtime(d) > t for d in deps)
+    return any(stale_object(s, LIB) for s in SOURCES)
+
+
+def stale_object(src: str, obj: str) -> bool:
+    """Older than its source, a header or this file, which holds the flags (a source's own among them)."""
+    deps = [os.path.join(CSRC, s) for s in [src] + HEADERS] + [os.path.join(HERE, "build.py")]
+    return not os.path.exists(obj) or any(os.path.getmtime(d) > os.path.getmtime(obj) for d in deps)
 
 
 def build(force: bool = True, verbose: bool = False, trace: bool = False) -> str:
@@ -44,14 +48,12 @@ def build(force: bool = True, verbose: bool = False, trace: bool = False) -> str
         # one object per source, compiled side by side (objects of sources that did not change are
         # kept unless force is set), then one link
         os.makedirs(OBJ, exist_ok=True)
-        newest_header = max(os.path.getmtime(os.path.join(CSRC, h)) for h in HEADERS)
         compile_flags = [f for f in FLAGS if f != "-shared"] + ["-c"]
         cmds, objs = [], []
         for src in SOURCES:
             o = os.path.join(OBJ, src.replace(".hip", ".o"))
             objs.append(o)
-            fresh = os.path.exists(o) and os.path.getmtime(o) > max(newest_header, os.path.getmtime(os.path.join(CSRC, src)))
-            if force or not fresh:
+            if force or stale_object(src, o):
                 cmds.append([HIPCC] + compile_flags + (PRELOAD if src in PRELOAD_SOURCES else []) + [os.path.join(CSRC, src), "-o", o])
         link = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC"] + objs + ["-o", LIB]
 
