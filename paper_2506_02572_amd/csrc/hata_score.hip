@@ -218,7 +218,8 @@ __global__ __launch_bounds__(1024) void encode_score_kernel(const EncodeScoreArg
     const int first = blockIdx.x * chunks * a.s.chunk;
     if (first >= L && blockIdx.x != 0) return;  // (the first workgroup writes the query codes of an empty sequence too)
     const int c = blockIdx.x * chunks + sub, base = c * a.s.chunk, end = min(base + a.s.chunk, L);
-    const bool own = a.append && L - 1 >= first && L - 1 < first + chunks * a.s.chunk;  // row L - 1 is encoded here
+    // row L - 1 is encoded here (a sequence longer than its cache appends a row that is not there)
+    const bool own = a.append && a.s.seq_len[b] <= a.s.L_cap && L - 1 >= first && L - 1 < first + chunks * a.s.chunk;
     if (own) {
         const uint16_t* kx = a.K + b * a.sb + h * a.sh + (int64_t)(L - 1) * a.sn;
         if (G % 4 == 0 || (lane & 3) == G % 4) x[PASSES - 1] = Hash::fetch_x(kx);

@@ -57,3 +57,32 @@ def test_encode_and_score_in_one_launch(B, Hq, Hkv, r, L_cap, append):
         assert torch.equal(scores[b, :, :lens[b]], want_s[b, :, :lens[b]]), b
     assert torch.equal(idx.view(want_i.shape), want_i)
     ctx.close()
+
+
+@pytest.mark.parametrize("L_cap,G,r", [(17000, 4, 128), (16500, 1, 32), (20011, 5, 64), (20011, 4, 256)])
+def test_sequence_longer_than_its_cache_appends_nothing(L_cap, G, r):
+    """The appended row would lie past the cache: no code is written, and the rows that are there are scored with the codes they have."""
+    import torch
+    from paper_2506_02572_amd import hata
+    print(f"[encode_score] L_cap={L_cap} G={G} r={r}, lengths beyond it", flush=True)
+    B, Hkv, k_max = 2, 2, 64
+    g = torch.Generator(device="cuda").manual_seed(L_cap + r)
+    K, V = (torch.randn((B, Hkv, L_cap, 128), dtype=torch.bfloat16, device="cuda", generator=g) for _ in range(2))
+    q = torch.randn((B, Hkv * G, 128), dtype=torch.bfloat16, device="cuda", generator=g)
+    W = torch.randn((Hkv, 128, r), dtype=torch.float32, device="cuda", generator=g)
+    codes = torch.randint(-2**31, 2**31 - 1, (B, Hkv, L_cap, r // 32), dtype=torch.int32, device="cuda", generator=g)
+    seq = torch.tensor([L_cap + 1, L_cap + 500], dtype=torch.int32, device="cuda")
+    kb = torch.full((B,), k_max, dtype=torch.int32, device="cuda")
+    ctx = hata.Context(B, Hkv * G, Hkv, 128, r, L_cap, k_max, shared_device=True)
+    want = codes.clone()
+    out = torch.empty((B, Hkv * G, 128), dtype=torch.bfloat16, device="cuda")
+    ctx.hata_decode_step(q, K, V, W, codes, seq, kb, B, True, 1.0 / math.sqrt(128), out)
+    torch.cuda.synchronize()
+    assert torch.equal(codes, want)
+    qcodes, scores, idx = ctx.hata_step_buffers()
+    want_s, want_i = torch.zeros_like(scores).view(B, Hkv, L_cap), torch.zeros_like(idx).view(B, Hkv, k_max)
+    ctx.hata_hamming_score(qcodes.clone(), want, seq, B, want_s)
+    ctx.hata_topk(want_s, seq, kb, B, want_i)
+    torch.cuda.synchronize()
+    assert torch.equal(scores.view(want_s.shape), want_s) and torch.equal(idx.view(want_i.shape), want_i)
+    ctx.close()
