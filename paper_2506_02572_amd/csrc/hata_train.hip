@@ -627,7 +627,9 @@ __global__ __launch_bounds__(TrainShape<COLS>::THREADS) void train_grad_kernel(
 // `stages` pairs of blocks one after the other, a wave through a tile of 32 rows of each, and keeps the sums in registers for a run: up
 // to run_len pairs (a share of `stages`, at most TR_KEPT) of one query.  The partial of a run lies in its last pair's place.
 //
-// Whether a tile holds one query vector is a wave's own matter here; where one does not, the wave takes the run again the general way.
+// Whether a tile holds one query vector is a wave's own matter here; where one does not, the wave takes it and the rest of the run the
+// general way, whose sums are the same (the run again from its start, as it was: 256 blocks, r = 128, another vector in the last row of every
+// second pair 33.8 us a step, 29.6 so; 960 blocks, every fourth pair 89 and 67, none 64).
 //
 // What bounds it: a tile is 72 matrix instructions (48 of them the contractions, at the rate these sustain), 500 of the vector ALU
 // and 40 KB through LDS, 5 us for the eight waves together.  So the waves have nothing to wait for each other for until a run's sums are
@@ -775,16 +777,19 @@ __global__ __launch_bounds__(TrainShape<32>::THREADS) void train_grad_runs_kerne
         return __builtin_bit_cast(tr_bf16x8_t, make_uint4(lo.x, lo.y, hi.x, hi.y));
     };
     auto label_of = [&](int l, int i) { return s_lab[rg][8 * (i / 4) + 4 * (l >> 5) + i % 4]; };
-    // What both ways have in common: the tile's K and Q there, its labels, K's projection (then h(k)); whether it takes the general way
-    auto begin_tile = [&](int p, bool requested, tr_f32x16_t& zk) {
+    // What both ways have in common: the tile's K and Q there, its labels, K's projection (then h(k)); requested: Q is too
+    auto begin_tile = [&](int p, bool requested, bool with_piece, tr_f32x16_t& zk) {
         const int row0 = row_of(p);
         uint4 *const t = tile_of(p), *const tq = tile_of(p + 1);
         landed();
         const float lab = s[min(row0 + m, n - 1)];
-        if (!requested) request_tile(Q, row0, tq);
+        if (!requested) {
+            read_done();
+            request_tile(Q, row0, tq);
+        }
         if (row0 + 32 > n) zero_past_n(row0, t);
         zk = project_tile(t);
-        if (requested && p == p0 && has_piece) {
+        if (with_piece) {
             const double f = gram_piece<R>(W, wg, 64 * rg + fresh_lane(), gram, W_old);
             if (lane == 0) s_red[rg] = f;
         }
@@ -811,7 +816,6 @@ __global__ __launch_bounds__(TrainShape<32>::THREADS) void train_grad_runs_kerne
 #pragma unroll
                 for (int i = 0; i < 16; ++i) ke[ct][i] = dw[ct][i] = 0.f;
         };
-        float lsim_run = 0.f;
         // h(k) of the tile (zk: its projection) and the contractions with it.  Half of the rows' values are made under the products of the
         // other half: a wave issues a product and then what fits beside it.
         auto contract_keys = [&](const uint4* t, const tr_f32x16_t& zk, auto hash_of_key, auto hash_of_query, float& ssum, float& cs) {
@@ -827,7 +831,7 @@ __global__ __launch_bounds__(TrainShape<32>::THREADS) void train_grad_runs_kerne
                     cs += hk;  // (rows past n are zero: h = 0)
                     e[j] = fmaf(-hk, hk, 1.f);
                     ae[j] = -c_sim * sd * e[j];
-                    lsim_run = fmaf(sd, diff, lsim_run);
+                    lsim = fmaf(sd, diff, lsim);
                     ssum += sd;
                 }
                 split3_pair(e[0], e[1], be[ks][0][e2], be[ks][1][e2], be[ks][2][e2]);
@@ -858,6 +862,7 @@ __global__ __launch_bounds__(TrainShape<32>::THREADS) void train_grad_runs_kerne
                 }
             }
         };
+        int i = p;
         bool general = false;
         {
             clear_sums();
@@ -876,9 +881,9 @@ __global__ __launch_bounds__(TrainShape<32>::THREADS) void train_grad_runs_kerne
                 sum_q = 0.f;
             };
 #pragma clang loop unroll(disable)
-            for (int i = p; i < pe; ++i) {
+            for (; i < pe; ++i) {
                 tr_f32x16_t zk;
-                begin_tile(i, i == p, zk);
+                begin_tile(i, i == p, i == p0 && has_piece, zk);
                 const uint4* const tq = tile_of(i + 1);
                 const uint4 f = tq[lane & 15];  // the first row's piece lane % 16
                 uint32_t stray = 0;
@@ -910,17 +915,15 @@ __global__ __launch_bounds__(TrainShape<32>::THREADS) void train_grad_runs_kerne
                 cs += __shfl_xor(cs, 32, 64);
                 if (half == 0) s_col[i - p][rg][m] = cs;
             }
-            if (!general) add_query();
+            add_query();
         }
-        if (general) {  // the run again, from its start
-            clear_sums();
-            lsim_run = 0.f;
-            read_done();
-            request_tile(K, row_of(p), tile_of(p));
+        if (general) {  // from the tile that another vector was met in on, whose rows are there
+            bool there = true;
 #pragma clang loop unroll(disable)
-            for (int i = p; i < pe; ++i) {
+            for (; i < pe; ++i) {
                 tr_f32x16_t zk;
-                begin_tile(i, false, zk);
+                begin_tile(i, there, false, zk);
+                there = false;
                 squash(zk);
                 const uint4* const tq = tile_of(i + 1);
                 tr_f32x16_t zq = project_tile(tq), gq;  // then h(q);  the rows' dZ_q
@@ -949,7 +952,6 @@ __global__ __launch_bounds__(TrainShape<32>::THREADS) void train_grad_runs_kerne
                 if (half == 0) s_col[i - p][rg][m] = cs;
             }
         }
-        lsim += lsim_run;
         // The waves' sums, the first four the first block's, meet in the tiles' place; a wave adds up 16 channels
         __syncthreads();
         const int l = fresh_lane();
