@@ -40,7 +40,7 @@ struct hata_train_ctx {
     int n_wgs_max;
     float* colsum_part;  // [n_wgs_max, r]
     float* colsum;       // [queries (<= n_wgs_max), r]  sum of h(k_n) over the triplets of a query
-    float* dw_part;      // [pairs of blocks, 3, d, r]  K^T E, the rest of X^T dZ, K^T E of the second block if its query is another; of a run: in its last pair's place
+    float* dw_part;      // [pairs of blocks, 3, d, r]  K^T E, the rest of X^T dZ, K^T E of the second block if its query is another; a run's: in its last pair's place, the K^T E of a query that ends sooner in its own last pair's
     float* loss_part;    // [column groups, pairs of blocks]
     double* gram;        // [d, d]  W W^T
     double* fro_part;    // [2 d]  what its pieces add to ||W^T W - I||_F^2 - r
@@ -625,7 +625,10 @@ __global__ __launch_bounds__(TrainShape<COLS>::THREADS) void train_grad_kernel(
 
 // The same for batches of more than a round of workgroups: grid = (pairs / stages, groups of 32 hash columns), a workgroup goes through
 // `stages` pairs of blocks one after the other, a wave through a tile of 32 rows of each, and keeps the sums in registers for a run: up
-// to run_len pairs (a share of `stages`, at most TR_KEPT) of one query.  The partial of a run lies in its last pair's place.
+// to run_len pairs (a share of `stages`, at most TR_KEPT).  The partial of a run lies in its last pair's place.  Only K^T E has a factor per
+// query, so where the query changes inside a run it alone is stored, in the place of the last pair of the query that ends, and the rest
+// stays in registers (both stored there, and the update one such pair after the other: 960 blocks, r = 128, a query every 23 blocks 80 us, 69 so;
+// every 2 blocks 132 and 95, 1920 blocks at r = 32 147 and 82).
 //
 // Whether a tile holds one query vector is a wave's own matter here; where one does not, the wave takes it and the rest of the run the
 // general way, whose sums are the same (the run again from its start, as it was: 256 blocks, r = 128, another vector in the last row of every
@@ -803,19 +806,23 @@ __global__ __launch_bounds__(TrainShape<32>::THREADS) void train_grad_runs_kerne
         for (int i = 0; i < 16; ++i) z[i] = relaxed_sign(z[i], nsl);
     };
     __syncthreads();
+    // accumulators: channel 32 ct + 8 (ri / 4) + 4 half + ri % 4, this lane's column
+    tr_f32x16_t ke[4], dw[4];  // of a query, K^T E;  of the run, whoever's its rows are, Q^T dZ_q - K^T (A E)
+    auto clear = [](tr_f32x16_t (&x)[4]) {
+#pragma unroll
+        for (int ct = 0; ct < 4; ++ct)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) x[ct][i] = 0.f;
+    };
 #pragma clang loop unroll(disable)
     for (int p = p0, limit = p0; p < p1;) {
-        if (p == limit) limit = min(limit + run_len, p1);
+        if (p == limit) {
+            limit = min(limit + run_len, p1);
+            clear(dw);
+        }
+        clear(ke);
         const bool one_query = (others & 2u) == 0;
-        const int pe = one_query ? min(limit, others ? p + (__builtin_ctz(others) >> 1) : limit) : p + 1;  // past the run
-        // accumulators: channel 32 ct + 8 (ri / 4) + 4 half + ri % 4, this lane's column
-        tr_f32x16_t ke[4], dw[4];  // K^T E;  Q^T dZ_q - K^T (A E)
-        auto clear_sums = [&]() {
-#pragma unroll
-            for (int ct = 0; ct < 4; ++ct)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) ke[ct][i] = dw[ct][i] = 0.f;
-        };
+        const int pe = one_query ? min(limit, others ? p + (__builtin_ctz(others) >> 1) : limit) : p + 1;  // past the query's pairs in the run
         // h(k) of the tile (zk: its projection) and the contractions with it.  Half of the rows' values are made under the products of the
         // other half: a wave issues a product and then what fits beside it.
         auto contract_keys = [&](const uint4* t, const tr_f32x16_t& zk, auto hash_of_key, auto hash_of_query, float& ssum, float& cs) {
@@ -865,7 +872,6 @@ __global__ __launch_bounds__(TrainShape<32>::THREADS) void train_grad_runs_kerne
         int i = p;
         bool general = false;
         {
-            clear_sums();
             float sum_q = 0.f;  // of dZ_q, which the query has yet to be multiplied with
             // one product for 32 channels: the query in the first three places of the contraction, the planes of the sums
             auto add_query = [&]() {
@@ -995,10 +1001,12 @@ __global__ __launch_bounds__(TrainShape<32>::THREADS) void train_grad_runs_kerne
                 store(out + 2 * HATA_D * R, i4, y);
             }
         }
-        __syncthreads();
-        hand_over(dw);
+        if (pe == limit) {
+            __syncthreads();
+            hand_over(dw);
 #pragma unroll
-        for (int i4 = 0; i4 < 2; ++i4) store(out + HATA_D * R, i4, plus(block_sum(0, i4), block_sum(4, i4)));
+            for (int i4 = 0; i4 < 2; ++i4) store(out + HATA_D * R, i4, plus(block_sum(0, i4), block_sum(4, i4)));
+        }
         p = pe;
         if (p == p1) break;
         __syncthreads();  // (the tiles' places are free again)
@@ -1020,8 +1028,8 @@ __global__ __launch_bounds__(TrainShape<32>::THREADS) void train_grad_runs_kerne
 // dL/dW = sigma * (sum of the partials) + 2 lam W P / ||P||_F, and the SGD update from it; the last block writes
 // the loss terms.  64 elements per workgroup of 512 threads: a wave sums an eighth of the partials of each -- K^T E
 // times the column's factor, which the workgroup adds up first from the column sums of all blocks (colsum: already added up per
-// query) -- and the eighths meet in LDS in a fixed order.  Large batches are bound by reading the partials once (8.4 MB at r = 128
-// from 256 blocks on, in the caches) and the column sums by every workgroup, small ones by the round trips to what a wave reads: hence everything of the first 32 blocks
+// query) -- and the eighths meet in LDS in a fixed order.  Large batches are bound by reading the partials once (1 KB times r a run of up to four
+// pairs, in the caches: at r = 128 8.4 MB for 256 and 512 blocks, 15.7 for 960; more where queries end inside runs) and the column sums by every workgroup, small ones by the round trips to what a wave reads: hence everything of the first 32 blocks
 // is requested at once, queries are looked up by 32 blocks (a lane each), and the loss workgroup's waves have 64 columns of a
 // share of the blocks each instead of all columns one after the other (one block 6.5 -> 5.8 us, at r = 256 12.7 -> 8.7;
 // 960 blocks of four queries, r = 32 15.6 -> 9.4, r = 128 17.1 -> 13.1).
@@ -1099,7 +1107,7 @@ __global__ __launch_bounds__(TR_UPDATE_WAVES * 64) __attribute__((amdgpu_waves_p
         int ids = queries_from(b0, min(b0 + 2 * UN, b1));
         if (!colsum) request_columns(j, b0, b1);
         float ke[UN], dw[UN];
-        // what the last pairs of runs i, i + 1, ... hold: the whole run's sums where its query stays the same
+        // what the last pairs of runs i, i + 1, ... hold: the run's sums, of K^T E those of its last query
         auto fetch = [&](int i) {
 #pragma unroll
             for (int u = 0; u < UN; ++u) {
@@ -1109,20 +1117,19 @@ __global__ __launch_bounds__(TR_UPDATE_WAVES * 64) __attribute__((amdgpu_waves_p
                 dw[u] = at[count];
             }
         };
-        // the query of run i + lane % 16's first block; whether others follow in that run
-        auto queries_of = [&](int i, int& first, bool& broken) {
-            const int b = 2 * run_len * max(min(i + (el & (UN - 1)), r1 - 1), 0);
-            int id[2 * TR_KEPT];
-#pragma unroll
-            for (int k = 0; k < 2 * TR_KEPT; ++k) id[k] = block_query(block_group, min(b + min(k, 2 * run_len - 1), n_blocks - 1), n_groups);
-            first = id[0];
-            broken = false;
-#pragma unroll
-            for (int k = 1; k < 2 * TR_KEPT; ++k) broken |= id[k] != first;
+        // The pairs of runs i .. i + UN - 1, a lane each: the queries of its blocks, whether it is its run's last, whether its query ends with it
+        static_assert(UN * TR_KEPT <= 64, "a lane a pair");
+        struct RunPairs { int q0, q1; bool live, last, ends; };
+        auto pairs_from = [&](int i) {
+            int l = el;
+            asm volatile("" : "+v"(l));  // (made here, not in front of the loops)
+            const int own = i * run_len + l, p_end = min(min(i + UN, r1) * run_len, n_pairs);
+            auto query_of = [&](int k) { return block_query(block_group, max(min(min(2 * own + k, 2 * p_end - 1), n_blocks - 1), 0), n_groups); };
+            const int q0 = query_of(0), q1 = query_of(1), q2 = query_of(2), q3 = query_of(3);
+            return RunPairs{q0, q1, own < p_end, (l + 1) % run_len == 0 || own + 1 >= p_end, q1 != q0 || q2 != q0 || q3 != q0};
         };
-        int run_query = 0;
-        bool run_broken = false;
-        if constexpr (RUNS) queries_of(r0, run_query, run_broken);
+        RunPairs next_pairs;
+        if constexpr (RUNS) next_pairs = pairs_from(r0);
         fetch(r0);
         constexpr int NG = HATA_D / WAVES;
         float wo[NG];
@@ -1172,40 +1179,66 @@ __global__ __launch_bounds__(TR_UPDATE_WAVES * 64) __attribute__((amdgpu_waves_p
             }
         }
         for (int i = r0; i < (RUNS ? r1 : r0); i += UN) {
-            if (i != r0) {
-                queries_of(i, run_query, run_broken);
-                fetch(i);
-            }
-            const uint32_t broken = (uint32_t)__builtin_amdgcn_ballot_w64(run_broken) & ((1u << UN) - 1u);
-            if (broken == 0 && uniform(run_query)) {
-                const float fc = factor_of(__builtin_amdgcn_readfirstlane(run_query));
+            const RunPairs own = next_pairs;
+            const int first = __builtin_amdgcn_readfirstlane(own.q0), n_here = min(min(i + UN, r1) * run_len, n_pairs) - i * run_len;
+            if (__builtin_amdgcn_ballot_w64(own.q0 != first || own.q1 != first) == 0ull) {
+                const float fc = factor_of(first);
 #pragma unroll
                 for (int u = 0; u < UN; ++u) gp[u & 3] += i + u < r1 ? fmaf(fc, ke[u], dw[u]) : 0.f;
+                if (i + UN < r1) {
+                    next_pairs = pairs_from(i + UN);
+                    fetch(i + UN);
+                }
                 continue;
             }
-            float f[UN];
+            {
+                float f[UN];  // of the query that a run ends with
 #pragma unroll
-            for (int u = 0; u < UN; ++u) f[u] = factor_of(__builtin_amdgcn_readlane(run_query, u));
+                for (int u = 0; u < UN; ++u) f[u] = factor_of(__builtin_amdgcn_readlane(own.q0, min((u + 1) * run_len, n_here) - 1));
 #pragma unroll
-            for (int u = 0; u < UN; ++u) gp[u & 3] += i + u < r1 && !(broken >> u & 1u) ? fmaf(f[u], ke[u], dw[u]) : 0.f;
-            // a run with several queries: a pair has a place of its own where its query does not go on
+                for (int u = 0; u < UN; ++u) gp[u & 3] += i + u < r1 ? fmaf(f[u], ke[u], dw[u]) : 0.f;
+            }
+            // What else runs with several queries hold: a place where a query ends inside the run, and of pairs of two queries the second one's.
+            // UB of them in flight together, behind no branch (past the last one that one again)
+            constexpr int UB = 8;
+            float k[UB], f[UB];
+            auto request = [&](unsigned long long& left, int queries, int part_of_place, int u0, int u1) {
+#pragma unroll
+                for (int u = u0; u < u1; ++u) {
+                    const int p = left ? __builtin_ctzll(left) : 0;
+                    if (left & (left - 1)) left &= left - 1;
+                    k[u] = dp[((int64_t)(i * run_len + p) * 3 + part_of_place) * count];
+                    f[u] = factor_of(__builtin_amdgcn_readlane(queries, p));
+                }
+            };
+            auto add = [&](int u0, int u1, int n) {
+#pragma unroll
+                for (int u = u0; u < u1; ++u) gp[u & 3] += u - u0 < n ? f[u] * k[u] : 0.f;
+            };
+            unsigned long long places = __builtin_amdgcn_ballot_w64(own.live && own.ends && !own.last),
+                               mixed = __builtin_amdgcn_ballot_w64(own.live && own.q1 != own.q0);
+            int n_places = __builtin_popcountll(places), n_mixed = __builtin_popcountll(mixed);
+            if (i + UN < r1) next_pairs = pairs_from(i + UN);
+            if (n_places <= 2 && n_mixed <= 2) {
+                if (n_places + n_mixed > 0) {
+                    request(places, own.q0, 0, 0, 2);
+                    request(mixed, own.q1, 2, 2, 4);
+                    add(0, 2, n_places);
+                    add(2, 4, n_mixed);
+                }
+            } else {
 #pragma clang loop unroll(disable)
-            for (uint32_t left = broken; left; left &= left - 1) {
-                const int run = i + __builtin_ctz(left);
-                if (run >= r1) break;
-                const int p_last = min((run + 1) * run_len, n_pairs);
+                for (; n_places > 0; n_places -= UB) {
+                    request(places, own.q0, 0, 0, UB);
+                    add(0, UB, n_places);
+                }
 #pragma clang loop unroll(disable)
-                for (int p = run * run_len; p < p_last; ++p) {
-                    const int id = queries_from(2 * p, n_blocks);
-                    const int q0 = __builtin_amdgcn_readlane(id, 0), q1 = __builtin_amdgcn_readlane(id, 1);
-                    const bool goes_on = q1 == q0 && __builtin_amdgcn_readlane(id, 2) == q0 && __builtin_amdgcn_readlane(id, 3) == q0;
-                    if (goes_on && p + 1 < p_last) continue;
-                    const float* const at = dp + (int64_t)p * 3 * count;
-                    const float k0 = at[0], d0 = at[count], k1 = at[q1 != q0 ? 2 * count : 0];
-                    gp[0] += fmaf(factor_of(q0), k0, d0);
-                    if (q1 != q0) gp[0] = fmaf(factor_of(q1), k1, gp[0]);
+                for (; n_mixed > 0; n_mixed -= UB) {
+                    request(mixed, own.q1, 2, 0, UB);
+                    add(0, UB, n_mixed);
                 }
             }
+            if (i + UN < r1) fetch(i + UN);
         }
         double wp = 0.0;
 #pragma unroll

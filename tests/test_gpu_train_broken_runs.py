@@ -1,5 +1,5 @@
-"""Training steps whose workgroups go through runs of pairs of blocks, with query vectors that change under one name: the gradient without
-the uncorrelation term against the fp64 oracle."""
+"""Training steps whose workgroups go through runs of pairs of blocks, with queries that change inside a pair, inside a run and at a run's
+end, and with query vectors that change under one name; the gradient without the uncorrelation term against the fp64 oracle."""
 import numpy as np
 import pytest
 
@@ -20,6 +20,12 @@ def form(r, blocks, queries):
     runs = -(-least // 4)
     length = -(-least // runs)
     return runs * length, length
+
+
+def broken(lengths, run_len):
+    """Runs that hold more than one query."""
+    names = np.repeat(np.arange(len(lengths)), lengths)
+    return sum(len(set(names[b:b + 2 * run_len])) > 1 for b in range(0, len(names), 2 * run_len))
 
 
 def gradient_and_bound(Q, K, s, W, hp, group):
@@ -68,6 +74,21 @@ def step(r, lengths, named=True, change=(), loose=0, queries=None):
     assert err <= 2.0 ** -21
     np.testing.assert_allclose(H.to_host(ld)[:2], terms[:2], rtol=2e-5)
     ctx.close()
+
+
+@pytest.mark.parametrize("r", [32, 64, 128, 256])
+@pytest.mark.parametrize("lengths", ["one", "two", "uneven", "by150", "by23", "by7", "mixed"])
+def test_queries_that_end_anywhere(r, lengths):
+    rounds = 256 * 32 // r * 2  # blocks of a round
+    blocks = 2 * rounds if r > 64 else rounds + rounds // 2
+    if lengths == "one": lengths = [blocks + 1]
+    elif lengths == "two": lengths = [blocks // 2 - 3, blocks // 2 + 4]
+    elif lengths == "uneven": lengths = [1, blocks // 3, 2, blocks // 4 + 1, 5, blocks - blocks // 3 - blocks // 4 - 9]
+    elif lengths == "mixed": lengths = [11, 1, 1, 4, 3, 8, 16, 2, 2, 31, blocks - 79]
+    else: lengths = [int(lengths[2:])] * (blocks // int(lengths[2:]) + 1)
+    stages, run_len = form(r, sum(lengths), len(lengths))
+    print(f"[train] r={r} queries of {lengths if len(lengths) < 12 else lengths[0]} blocks: {stages} pairs a workgroup, runs of {run_len}, {broken(lengths, run_len)} broken", flush=True)
+    step(r, lengths, loose=37)
 
 
 def rows_of(pair, *rows):
