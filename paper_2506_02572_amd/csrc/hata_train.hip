@@ -1571,13 +1571,20 @@ int hata_train_step(hata_train_ctx* ctx, const void* Q, const void* K, const flo
     // The gradient launch.  A workgroup per pair of blocks and 32 hash columns where that is at most one round of the chip, which is through
     // sooner than one of 64 (us a step, one query vector a block / others: one block r = 64 20.3 / 26.4 -> 16.6 / 19.5, r = 256 24.3 / 30.1 ->
     // 20.2 / 23.0; 64 blocks r = 128 23.5 / 29.1 -> 19.9 / 22.6).  Beyond, a workgroup goes through as many pairs as one round takes, in
-    // runs of at most TR_KEPT -- but where two would do and a query need not end with a run, a pair and 64 columns: a second query in a
-    // workgroup's pairs costs it 5 us (r = 128, all runs whole / not, 64 columns / two pairs: 192 blocks 28.1 / 27.0, 202 29.5 / 32.5, 256
-    // 28.5 / 27.2, 250 31.5 / 33.8; r = 256 128 blocks 33.9 / 32.9; r = 64 512 blocks 32.8 / 30.6; whole runs are what the host
-    // can tell, queries of equal shares).  At least a piece of W W^T each: workgroups behind the pairs have nothing else.
+    // runs of at most TR_KEPT, unless queries that end inside its pairs cost it more than that saves, of which the host knows the number alone
+    // (a pair and 64 columns, at r = 32 32 / runs):
+    // - queries of less than eight blocks on average: every 3 blocks, r = 64, 1030 blocks 74.0 / 80.0, r = 256, 256 blocks 52.0 / 56.4; the latter
+    //   every 7 blocks 47.1 / 50.0, every 9 57.7 / 59.3, which is the worst of them (r = 128, 384 to 1536 blocks, every 7 to 23: 6 to 24 % less)
+    // - where two pairs would do, several queries: such an end costs as much there as runs save, so up to four of them, where the second round is
+    //   as good as full, and none below.  r = 128, 256 blocks: equal shares 27.8 .. 29.8 / 26.4 .. 27.9, uneven ones 28.4 .. 30.9 / 28.6 .. 30.2 by
+    //   where the buffers lie; 192 blocks, uneven 27.5 .. 28.0 / 28.5 .. 29.4; r = 64 512 blocks 29.5 .. 31.1 / 30.1 .. 31.7, 450 30.0 / 31.1; r = 256
+    //   128 blocks 35.0 / 34.9, 120 35.2 / 35.6.  One query: r = 128 132 blocks 26.3 / 26.2, 192 27.8 / 27.2; r = 256 128 33.5 / 32.2
+    // At least a piece of W W^T each: workgroups behind the pairs have nothing else.
     const int pairs = (n_wgs + 1) / 2, pairs_32 = pairs * (r / 32);
-    const bool one_stage = pairs_32 <= TR_ONE_ROUND || (r > 32 && pairs_32 <= 2 * TR_ONE_ROUND && n_wgs % (4 * n_queries) != 0);
-    const int cols = one_stage && pairs_32 > TR_ONE_ROUND ? 64 : 32, col_groups = r / cols;
+    const bool two_pairs = r > 32 && pairs_32 <= 2 * TR_ONE_ROUND;
+    const bool one_stage = pairs_32 <= TR_ONE_ROUND || n_wgs < 8 * n_queries ||
+                           (two_pairs && n_queries > (pairs_32 > 2 * TR_ONE_ROUND / 64 * 63 ? 4 : 1));
+    const int cols = one_stage && r > 32 && pairs_32 > TR_ONE_ROUND ? 64 : 32, col_groups = r / cols;
     const int least = one_stage ? 1 : (pairs * col_groups + TR_ONE_ROUND - 1) / TR_ONE_ROUND;
     const int runs_each = (least + TR_KEPT - 1) / TR_KEPT, run_len = (least + runs_each - 1) / runs_each, stages = runs_each * run_len;
     const int n_runs = (pairs + run_len - 1) / run_len, n_grad_wgs = (pairs + stages - 1) / stages;

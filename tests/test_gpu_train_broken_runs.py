@@ -14,7 +14,9 @@ def form(r, blocks, queries):
     """The gradient launch's rule (hata_train_step): pairs of blocks a workgroup goes through, pairs of a run; (1, 1): no runs."""
     pairs = (blocks + 1) // 2
     pairs_32 = pairs * (r // 32)
-    if pairs_32 <= 256 or (r > 32 and pairs_32 <= 512 and blocks % (4 * queries)):
+    if pairs_32 <= 256 or blocks < 8 * queries:
+        return 1, 1
+    if r > 32 and pairs_32 <= 512 and queries > (4 if pairs_32 > 504 else 1):
         return 1, 1
     least = -(-pairs_32 // 256)
     runs = -(-least // 4)
@@ -76,19 +78,39 @@ def step(r, lengths, named=True, change=(), loose=0, queries=None):
     ctx.close()
 
 
+def split(kind, blocks):
+    """Blocks of each query."""
+    if kind == "one": return [blocks + 1]
+    if kind == "two": return [blocks // 2 - 3, blocks - blocks // 2 + 3]
+    if kind == "four": return [1, blocks // 3, 7, blocks - blocks // 3 - 8]
+    if kind == "uneven": return [1, blocks // 3, 2, blocks // 4 + 1, 5, blocks - blocks // 3 - blocks // 4 - 9]
+    if kind == "mixed": return [11, 1, 1, 4, 3, 8, 16, 2, 2, 31, blocks - 79]
+    return [int(kind[2:])] * -(-blocks // int(kind[2:]))
+
+
 @pytest.mark.parametrize("r", [32, 64, 128, 256])
-@pytest.mark.parametrize("lengths", ["one", "two", "uneven", "by150", "by23", "by7", "mixed"])
-def test_queries_that_end_anywhere(r, lengths):
-    rounds = 256 * 32 // r * 2  # blocks of a round
-    blocks = 2 * rounds if r > 64 else rounds + rounds // 2
-    if lengths == "one": lengths = [blocks + 1]
-    elif lengths == "two": lengths = [blocks // 2 - 3, blocks // 2 + 4]
-    elif lengths == "uneven": lengths = [1, blocks // 3, 2, blocks // 4 + 1, 5, blocks - blocks // 3 - blocks // 4 - 9]
-    elif lengths == "mixed": lengths = [11, 1, 1, 4, 3, 8, 16, 2, 2, 31, blocks - 79]
-    else: lengths = [int(lengths[2:])] * (blocks // int(lengths[2:]) + 1)
+@pytest.mark.parametrize("kind", ["one", "two", "uneven", "mixed", "by150", "by23", "by9", "by7"])
+def test_queries_that_end_anywhere(r, kind):
+    """Batches of two and a half rounds of workgroups and more, at r = 32 of one and a half."""
+    lengths = split(kind, 768 if r == 32 else 1280 * 32 // r)
     stages, run_len = form(r, sum(lengths), len(lengths))
-    print(f"[train] r={r} queries of {lengths if len(lengths) < 12 else lengths[0]} blocks: {stages} pairs a workgroup, runs of {run_len}, {broken(lengths, run_len)} broken", flush=True)
+    print(f"[train] r={r} {kind}: {sum(lengths)} blocks, {stages} pairs a workgroup, runs of {run_len}, {broken(lengths, run_len)} broken", flush=True)
+    if kind != "by7":  # (a pair a workgroup)
+        assert run_len >= 2 and (broken(lengths, run_len) > 0 or kind in ("one", "by150"))
     step(r, lengths, loose=37)
+
+
+@pytest.mark.parametrize("r", [64, 128, 256])
+@pytest.mark.parametrize("kind,short,runs", [("one", 1, True), ("two", 0, True), ("four", 0, True), ("uneven", 0, False), ("four", 1, False), ("four", 2, False), ("one", 3, True)])
+def test_two_rounds(r, kind, short, runs):
+    """Two rounds of workgroups, and a sixteenth, a quarter and almost a half of the pairs less."""
+    pairs = 512 // (r // 32)
+    blocks = 2 * (pairs - (0, pairs // 16, pairs // 4, pairs // 2 - 1)[short])
+    lengths = split(kind, blocks - (kind == "one"))
+    stages, run_len = form(r, sum(lengths), len(lengths))
+    print(f"[train] r={r} {kind}: {sum(lengths)} blocks, {stages} pairs a workgroup, {broken(lengths, 2)} of two broken", flush=True)
+    assert (run_len == 2) == runs
+    step(r, lengths, loose=5)
 
 
 def rows_of(pair, *rows):
