@@ -1437,21 +1437,30 @@ __global__ __launch_bounds__(256) void train_candidates_kernel(const double* __r
     }
 }
 
-// ranks inside the candidate list: LB_RANKED candidates per workgroup and turn, a lane for each in every sixteen, each counted by 64
-// groups of lanes over a 64th of the list; the histogram is cleared for the next call.  Bound by the compares' instructions where
+// ranks inside the candidate list: LB_RANKED * PER candidates per workgroup and turn, a lane for PER of them in every sixteen, each counted
+// by 64 groups of lanes over a 64th of the list; the histogram is cleared for the next call.  Bound by the compares' instructions where
 // workgroups are few: 64 candidates a workgroup, each wave handing a sixteenth of the list round as scalars, were 27 workgroups at 8192 keys
-// and 9.2 us, these 104 take 5.1.
+// and 9.2 us, these 104 take 5.1.  Long lists are bound by their reads, the whole of it a workgroup: PER = 4 from LB_LONG expected on (us a
+// call, scalars / one / four a lane: 52000 keys 49.4 / 36.4 / 35.2, 100000 87 / 81 / 59, 1000000 4450 / 4760 / 2380; all 65536 scores equal 2010 / 2400 / 1060).
 #define LB_RANKED 16
+#define LB_LONG 5120
+template <int PER>
 __global__ __launch_bounds__(1024) void train_labels_kernel(const LabelCand* __restrict__ cand, const uint32_t* __restrict__ n_cand,
                                                             int n_pos, uint32_t* __restrict__ bins, float* __restrict__ s) {
-    __shared__ int s_rank[16][LB_RANKED];
+    __shared__ int s_rank[16][LB_RANKED * PER];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, own = lane % LB_RANKED;
     if (blockIdx.x == gridDim.x - 1)
         for (int i = tid; i < LB_COPIES * LB_BINS; i += 1024) bins[i] = 0;
     const int nc = (int)*n_cand;
-    for (int c0 = blockIdx.x * LB_RANKED; c0 < nc; c0 += gridDim.x * LB_RANKED) {
-        const LabelCand me = cand[min(c0 + own, nc - 1)];
-        int rank = 0;
+    for (int c0 = blockIdx.x * LB_RANKED * PER; c0 < nc; c0 += gridDim.x * LB_RANKED * PER) {
+        unsigned long long key[PER];
+        uint32_t row[PER];
+        int rank[PER];
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const LabelCand me = cand[min(c0 + own + LB_RANKED * k, nc - 1)];
+            key[k] = me.key; row[k] = me.row; rank[k] = 0;
+        }
         constexpr int UN = 8;  // entries of a lane in flight together
         for (int j0 = tid / LB_RANKED; j0 < nc; j0 += 64 * UN) {
             LabelCand o[UN];
@@ -1459,17 +1468,28 @@ __global__ __launch_bounds__(1024) void train_labels_kernel(const LabelCand* __r
             for (int t = 0; t < UN; ++t) o[t] = cand[min(j0 + 64 * t, nc - 1)];
 #pragma unroll
             for (int t = 0; t < UN; ++t)
-                rank += j0 + 64 * t < nc && (o[t].key > me.key || (o[t].key == me.key && o[t].row < me.row)) ? 1 : 0;
-        }
-        rank += __shfl_xor(rank, 16, 64);
-        rank += __shfl_xor(rank, 32, 64);
-        if (lane < LB_RANKED) s_rank[wave][lane] = rank;
-        __syncthreads();
-        if (tid < LB_RANKED && c0 + tid < nc) {
-            rank = 0;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) rank += s_rank[i][tid];
-            s[me.row] = rank < n_pos ? rank_label(rank, n_pos) : -1.f;
+                for (int k = 0; k < PER; ++k)
+                    if constexpr (PER > 1)  // (no branches: with them 41.6 us at 52000 keys)
+                        rank[k] += (int)(j0 + 64 * t < nc) & ((int)(o[t].key > key[k]) | ((int)(o[t].key == key[k]) & (int)(o[t].row < row[k])));
+                    else
+                        rank[k] += j0 + 64 * t < nc && (o[t].key > key[k] || (o[t].key == key[k] && o[t].row < row[k])) ? 1 : 0;
+        }
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            rank[k] += __shfl_xor(rank[k], 16, 64);
+            rank[k] += __shfl_xor(rank[k], 32, 64);
+            if (lane < LB_RANKED) s_rank[wave][LB_RANKED * k + lane] = rank[k];
+        }
+        __syncthreads();
+        if (tid < LB_RANKED * PER && c0 + tid < nc) {
+            uint32_t at = row[0];
+            int sum = 0;
+#pragma unroll
+            for (int k = 1; k < PER; ++k) at = tid / LB_RANKED == k ? row[k] : at;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) sum += s_rank[i][tid];
+            s[at] = sum < n_pos ? rank_label(sum, n_pos) : -1.f;
         }
         __syncthreads();
     }
@@ -1647,9 +1667,9 @@ int hata_train_make_labels(hata_train_ctx* ctx, const void* q, const void* K, in
                        (const uint16_t*)q, (const uint16_t*)K, m, passes, ctx->scores, ctx->bins, ctx->n_cand);
     hipLaunchKernelGGL(hata::train_candidates_kernel, dim3((m + 255) / 256), dim3(256), 0, st, ctx->scores, m, n_pos,
                        ctx->bins, ctx->n_cand, ctx->cand, s);
-    // enough workgroups for twice the expected list (they take more turns if it is longer)
-    hipLaunchKernelGGL(hata::train_labels_kernel, dim3(n_pos / (LB_RANKED / 2) + 2), dim3(1024), 0, st, ctx->cand, ctx->n_cand, n_pos,
-                       ctx->bins, s);
+    // enough workgroups for twice the expected list, and for short ones of equal scores (they take more turns if it is longer)
+    hipLaunchKernelGGL(n_pos > LB_LONG ? hata::train_labels_kernel<4> : hata::train_labels_kernel<1>, dim3(n_pos / (LB_RANKED / 2) + 8), dim3(1024), 0, st,
+                       ctx->cand, ctx->n_cand, n_pos, ctx->bins, s);
     const bool ok = hipGetLastError() == hipSuccess;
     ctx->bins_clear = ok && cleared;  // (after a call that failed half-way the next one clears again)
     return ok ? HATA_OK : HATA_EHIP;

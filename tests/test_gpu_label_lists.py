@@ -26,3 +26,9 @@ def test_labels_of_a_list_of_this_length(m, listed):
     torch.cuda.synchronize()
     assert np.array_equal(H.to_host(s), T.make_labels(col).astype(np.float32))
     ctx.close()
+
+
+# n_pos = 5121: four candidates a lane from here on; lists of the expected length, of one more than a whole number of turns, of every score
+@pytest.mark.parametrize("m,listed", [(51210, 5120), (51210, 5121), (51210, 5185), (51209, 5185), (51210, 20000), (51210, 51210), (51209, 51209), (60000, 6000), (60007, 30001)])
+def test_labels_of_a_long_list(m, listed):
+    test_labels_of_a_list_of_this_length(m, listed)
