@@ -82,6 +82,7 @@ def split(kind, blocks):
     """Blocks of each query."""
     if kind == "one": return [blocks + 1]
     if kind == "two": return [blocks // 2 - 3, blocks - blocks // 2 + 3]
+    if kind == "quarters": return [blocks // 4] * 4
     if kind == "four": return [1, blocks // 3, 7, blocks - blocks // 3 - 8]
     if kind == "uneven": return [1, blocks // 3, 2, blocks // 4 + 1, 5, blocks - blocks // 3 - blocks // 4 - 9]
     if kind == "mixed": return [11, 1, 1, 4, 3, 8, 16, 2, 2, 31, blocks - 79]
@@ -101,7 +102,7 @@ def test_queries_that_end_anywhere(r, kind):
 
 
 @pytest.mark.parametrize("r", [64, 128, 256])
-@pytest.mark.parametrize("kind,short,runs", [("one", 1, True), ("two", 0, True), ("four", 0, True), ("uneven", 0, False), ("four", 1, False), ("four", 2, False), ("one", 3, True)])
+@pytest.mark.parametrize("kind,short,runs", [("one", 1, True), ("two", 0, True), ("quarters", 0, True), ("four", 0, True), ("uneven", 0, False), ("four", 1, False), ("four", 2, False), ("one", 3, True)])
 def test_two_rounds(r, kind, short, runs):
     """Two rounds of workgroups, and a sixteenth, a quarter and almost a half of the pairs less."""
     pairs = 512 // (r // 32)
