@@ -387,6 +387,8 @@ hipError_t launch_encode_score(const hata_ctx* c, const void* q, const void* K, 
     // step, two launches / one: 160 units of 4096-key chunks, 32768 keys 49.6 / 52.1, 40 units of 131072 45.2 / 51.5; one head a
     // unit, 256 of 32768, 64.9 / 64.0).  Up to it, r = 128: 8 units of 32768 keys 20.1 / 17.8, of 131072 23.9 / 21.1, 32 of
     // 16000 21.3 / 19.1, groups of eight 16 of 32768 25.5 / 23.3, four chunks a workgroup 128 of 32768 45.4 / 42.9, one head a unit 33.1 / 31.9.
+    // r = 64 and 32, 8 units of 32768 keys: groups of four 19.1 / 16.6 and 19.0 / 16.1, of eight 25.6 / 22.7 and 25.4 / 21.8, one head 15.9 / 14.5 and
+    // 15.7 / 13.9; four chunks a workgroup, one head, 32 units of 131072 30.7 / 29.5 and 28.2 / 26.5 (r = 128 38.8 / 39.1).
     // r = 256 has twice the fp64, and the weights leave no registers to hide it behind the codes' loads: 8 units of 20000 keys 19.8 / 19.8, two
     // heads a unit 19.2 / 20.0, 32 units of 131072 45.0 / 45.5, groups of eight 24.4 / 27.0 -- it keeps two launches.
     int chunks = 1;

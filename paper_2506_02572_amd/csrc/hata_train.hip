@@ -1119,14 +1119,16 @@ __global__ __launch_bounds__(TR_UPDATE_WAVES * 64) __attribute__((amdgpu_waves_p
         };
         // The pairs of runs i .. i + UN - 1, a lane each: the queries of its blocks, whether it is its run's last, whether its query ends with it
         static_assert(UN * TR_KEPT <= 64, "a lane a pair");
-        struct RunPairs { int q0, q1; bool live, last, ends; };
+        struct RunPairs { int q0, q1; bool live, last, ends; int run_query; };
         auto pairs_from = [&](int i) {
             int l = el;
             asm volatile("" : "+v"(l));  // (made here, not in front of the loops)
             const int own = i * run_len + l, p_end = min(min(i + UN, r1) * run_len, n_pairs);
             auto query_of = [&](int k) { return block_query(block_group, max(min(min(2 * own + k, 2 * p_end - 1), n_blocks - 1), 0), n_groups); };
             const int q0 = query_of(0), q1 = query_of(1), q2 = query_of(2), q3 = query_of(3);
-            return RunPairs{q0, q1, own < p_end, (l + 1) % run_len == 0 || own + 1 >= p_end, q1 != q0 || q2 != q0 || q3 != q0};
+            const int run_end = min((i + (l & (UN - 1)) + 1) * run_len, p_end);  // of run i + lane % UN, whose last pair's first query is
+            const int run_query = block_query(block_group, max(2 * run_end - 2, 0), n_groups);
+            return RunPairs{q0, q1, own < p_end, (l + 1) % run_len == 0 || own + 1 >= p_end, q1 != q0 || q2 != q0 || q3 != q0, run_query};
         };
         RunPairs next_pairs;
         if constexpr (RUNS) next_pairs = pairs_from(r0);
@@ -1180,7 +1182,7 @@ __global__ __launch_bounds__(TR_UPDATE_WAVES * 64) __attribute__((amdgpu_waves_p
         }
         for (int i = r0; i < (RUNS ? r1 : r0); i += UN) {
             const RunPairs own = next_pairs;
-            const int first = __builtin_amdgcn_readfirstlane(own.q0), n_here = min(min(i + UN, r1) * run_len, n_pairs) - i * run_len;
+            const int first = __builtin_amdgcn_readfirstlane(own.q0);
             if (__builtin_amdgcn_ballot_w64(own.q0 != first || own.q1 != first) == 0ull) {
                 const float fc = factor_of(first);
 #pragma unroll
@@ -1192,9 +1194,9 @@ __global__ __launch_bounds__(TR_UPDATE_WAVES * 64) __attribute__((amdgpu_waves_p
                 continue;
             }
             {
-                float f[UN];  // of the query that a run ends with
+                float f[UN];  // of the query that a run ends with (of two the first one)
 #pragma unroll
-                for (int u = 0; u < UN; ++u) f[u] = factor_of(__builtin_amdgcn_readlane(own.q0, min((u + 1) * run_len, n_here) - 1));
+                for (int u = 0; u < UN; ++u) f[u] = factor_of(__builtin_amdgcn_readlane(own.run_query, u));
 #pragma unroll
                 for (int u = 0; u < UN; ++u) gp[u & 3] += i + u < r1 ? fmaf(f[u], ke[u], dw[u]) : 0.f;
             }
