@@ -182,13 +182,52 @@ struct EncodeScoreArgs {
     const float* W_H;
     uint32_t* codes;
     uint32_t* qcodes;
-    int append, log2_threads;  // of a chunk
+    int append, log2_threads;  // of a chunk, by the cache's size
     int64_t sb, sh, sn;
 };
 
+// Where the cache's size gives a workgroup several chunks: how few the sequences' lengths allow, and which workgroup of which sequence this
+// one is then; each sequence has one at least, which writes its query codes.  By position alone a long sequence among short ones was left to two
+// workgroups of a unit while most compute units had nothing (r = 128, one of 32768 keys, fifteen of 500, us a step: two launches 40.4, by position
+// 42.2, so 37.2; groups of eight 45.0, 48.6, 42.2).  Where all are long the places are those by position.  own: sequence lane's length,
+// loaded ahead of the weights; false: nothing left for this one.
+struct EncodeScorePlace { int b, x, log2_chunks, length; };
+__device__ __forceinline__ bool place_by_length(const ScoreArgs& a, int most, int own, EncodeScorePlace& at) {
+    const int lane = threadIdx.x & 63, B = gridDim.z, slots = gridDim.x * B, log2_chunk = __builtin_ctz(a.chunk);
+    auto length_of = [&](int b0) { return b0 == 0 ? own : a.seq_len[min(b0 + lane, B - 1)]; };
+    auto workgroups = [&](int b0) {
+        const int n = (clampi(length_of(b0), 0, a.L_cap) + a.chunk - 1) >> log2_chunk;
+        return b0 + lane < B ? (uint32_t)max((n + (1 << at.log2_chunks) - 1) >> at.log2_chunks, 1) : 0u;
+    };
+    uint32_t upto;  // workgroups of the sequences up to this lane's, of the last 64 looked at
+    for (at.log2_chunks = 0;; ++at.log2_chunks) {
+        int n = 0;
+        for (int b0 = 0; b0 < B; b0 += 64) {
+            upto = wave_incl_scan(workgroups(b0));
+            n += __builtin_amdgcn_readlane((int)upto, 63);
+        }
+        if (n <= slots || at.log2_chunks == most) break;  // (as many as the cache's size gives fit)
+    }
+    int left = blockIdx.z * gridDim.x + blockIdx.x;
+    for (int b0 = 0; b0 < B; b0 += 64) {
+        if (B > 64) upto = wave_incl_scan(workgroups(b0));
+        const int n = __builtin_amdgcn_readlane((int)upto, 63);
+        if (left < n) {
+            const int l = __builtin_ctzll(__builtin_amdgcn_ballot_w64((int)upto > left));
+            at.b = b0 + l;
+            at.x = left - (l ? __builtin_amdgcn_readlane((int)upto, max(l - 1, 0)) : 0);
+            at.length = __builtin_amdgcn_readlane(length_of(b0), l);
+            return true;
+        }
+        left -= n;
+    }
+    return false;
+}
+
 // The scoring launch with the encoding in it: a workgroup of 1024 threads encodes its unit's query vectors for itself (and the appended
 // key, where its chunks hold that row) as the workgroup per unit of hata_unit.hip does, its first codes on their way meanwhile, and
-// then has 1024, 512 or 256 threads for each of one, two or four chunks.  grid = (workgroups of a unit, Hkv, B).
+// then has 1024, 512 or 256 threads for each of one, two or four chunks.  grid = (workgroups of a unit, Hkv, B), dealt out by the lengths where
+// these are not one chunk each.
 // What bounds it: the launch, the round trips to the weights and the appended row, half a microsecond of fp64 of every compute unit.
 // A launch in front of the scoring costs its own launch and round trips on top: 2 x 20011 keys, a group of five, 21.7 us a step with one,
 // 20.2 so (launch_encode_score has the rule).
@@ -204,22 +243,28 @@ __global__ __launch_bounds__(1024) void encode_score_kernel(const EncodeScoreArg
     __shared__ uint32_t scan4[4][4];
     extern __shared__ __attribute__((aligned(16))) uint32_t hists[];  // [chunks of the workgroup][NBR]
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int h = blockIdx.y, b = blockIdx.z;
-    const int64_t u = (int64_t)b * a.s.Hkv + h;
+    const int h = blockIdx.y, most = 10 - a.log2_threads;
+    EncodeScorePlace at;
+    int own_length = 0;
+    if (most > 0) own_length = a.s.seq_len[min(lane, (int)gridDim.z - 1)];
     Hash hash;
     hash.fetch(a.W_H + (int64_t)h * HATA_D * R);
+    if (most == 0) at = {(int)blockIdx.z, (int)blockIdx.x, 0, a.s.seq_len[blockIdx.z]};
+    else if (!place_by_length(a.s, most, own_length, at)) return;
+    const int b = at.b, log2_threads = 10 - at.log2_chunks;
+    const int64_t u = (int64_t)b * a.s.Hkv + h;
     const uint16_t* qv = a.q + ((int64_t)b * a.s.Hq + (int64_t)h * G) * HATA_D;
     typename Hash::Vector x[PASSES];
 #pragma unroll
     for (int p = 0; p < PASSES; ++p)
         if (4 * p < G) x[p] = Hash::fetch_x(qv + min(4 * p + (lane & 3), G - 1) * HATA_D);
-    const int L = clampi(a.s.seq_len[b], 0, a.s.L_cap);
-    const int chunks = NT >> a.log2_threads, threads = 1 << a.log2_threads, sub = tid >> a.log2_threads, t = tid & (threads - 1);
-    const int first = blockIdx.x * chunks * a.s.chunk;
-    if (first >= L && blockIdx.x != 0) return;  // (the first workgroup writes the query codes of an empty sequence too)
-    const int c = blockIdx.x * chunks + sub, base = c * a.s.chunk, end = min(base + a.s.chunk, L);
+    const int L = clampi(at.length, 0, a.s.L_cap);
+    const int chunks = NT >> log2_threads, threads = 1 << log2_threads, sub = tid >> log2_threads, t = tid & (threads - 1);
+    const int first = at.x * chunks * a.s.chunk;
+    if (first >= L && at.x != 0) return;  // (the first workgroup writes the query codes of an empty sequence too)
+    const int c = at.x * chunks + sub, base = c * a.s.chunk, end = min(base + a.s.chunk, L);
     // row L - 1 is encoded here (a sequence longer than its cache appends a row that is not there)
-    const bool own = a.append && a.s.seq_len[b] <= a.s.L_cap && L - 1 >= first && L - 1 < first + chunks * a.s.chunk;
+    const bool own = a.append && at.length <= a.s.L_cap && L - 1 >= first && L - 1 < first + chunks * a.s.chunk;
     if (own) {
         const uint16_t* kx = a.K + b * a.sb + h * a.sh + (int64_t)(L - 1) * a.sn;
         if (G % 4 == 0 || (lane & 3) == G % 4) x[PASSES - 1] = Hash::fetch_x(kx);
@@ -254,7 +299,7 @@ __global__ __launch_bounds__(1024) void encode_score_kernel(const EncodeScoreArg
         }
     }
     __syncthreads();
-    if (blockIdx.x == 0 && tid < G * WD) a.qcodes[((int64_t)b * a.s.Hq + (int64_t)h * G) * WD + tid] = s_codes[tid];
+    if (at.x == 0 && tid < G * WD) a.qcodes[((int64_t)b * a.s.Hq + (int64_t)h * G) * WD + tid] = s_codes[tid];
     if (own && tid < WD) a.codes[(u * a.s.L_cap + L - 1) * WD + tid] = s_codes[G * WD + tid];
     QuerySum<WD, G> sum;
     sum.init(s_codes);
