@@ -10,6 +10,8 @@
 // s), from which the workgroups of the attention launch find the unit's threshold and their places in the index list
 // (hata_attn.hip).  encode_score_kernel is the same with the encoding in it, where one round of large workgroups covers the batch; with
 // workgroups of 256 threads, a chunk each, it was 3.9 us of the kernel, more than the launch in front takes.
+#include <type_traits>
+
 #include "hata_device.h"
 #include "hata_hash.h"
 #include "hata_internal.h"
@@ -182,17 +184,18 @@ struct EncodeScoreArgs {
     const float* W_H;
     uint32_t* codes;
     uint32_t* qcodes;
-    int append, log2_threads;  // of a chunk, by the cache's size
+    int append, log2_chunks;  // of a workgroup, by the cache's size
     int64_t sb, sh, sn;
 };
 
-// Where the cache's size gives a workgroup several chunks: how few the sequences' lengths allow, and which workgroup of which sequence this
-// one is then; each sequence has one at least, which writes its query codes.  By position alone a long sequence among short ones was left to two
-// workgroups of a unit while most compute units had nothing (r = 128, one of 32768 keys, fifteen of 500, us a step: two launches 40.4, by position
-// 42.2, so 37.2; groups of eight 45.0, 48.6, 42.2).  Where all are long the places are those by position.  own: sequence lane's length,
-// loaded ahead of the weights; false: nothing left for this one.
+// Where the cache's size gives a workgroup four chunks: how few the sequences' lengths allow in the same grid, and which workgroup of which
+// sequence this one is then; each sequence has one at least, which writes its query codes.  By position alone a long sequence among short ones was
+// left to a quarter of the workgroups while most compute units had nothing (r = 128, 16 sequences, one of 32768 keys, the others of 500,
+// us a step: two launches 41.4, by position 43.6, so 38.4; groups of eight 47.6, 50.4, 44.6; all of 16384, 47.3, 45.0, 40.5; all full 46.5, 44.7,
+// 45.5).  Where no less than four will do the places are those by position.  own: sequence lane's length, loaded ahead of the weights;
+// false: nothing left for this one.
 struct EncodeScorePlace { int b, x, log2_chunks, length; };
-__device__ __forceinline__ bool place_by_length(const ScoreArgs& a, int most, int own, EncodeScorePlace& at) {
+__device__ __forceinline__ bool place_by_length(const ScoreArgs& a, int own, EncodeScorePlace& at) {
     const int lane = threadIdx.x & 63, B = gridDim.z, slots = gridDim.x * B, log2_chunk = __builtin_ctz(a.chunk);
     auto length_of = [&](int b0) { return b0 == 0 ? own : a.seq_len[min(b0 + lane, B - 1)]; };
     auto workgroups = [&](int b0) {
@@ -200,13 +203,19 @@ __device__ __forceinline__ bool place_by_length(const ScoreArgs& a, int most, in
         return b0 + lane < B ? (uint32_t)max((n + (1 << at.log2_chunks) - 1) >> at.log2_chunks, 1) : 0u;
     };
     uint32_t upto;  // workgroups of the sequences up to this lane's, of the last 64 looked at
-    for (at.log2_chunks = 0;; ++at.log2_chunks) {
+    for (at.log2_chunks = 0; at.log2_chunks < 2; ++at.log2_chunks) {
         int n = 0;
         for (int b0 = 0; b0 < B; b0 += 64) {
             upto = wave_incl_scan(workgroups(b0));
             n += __builtin_amdgcn_readlane((int)upto, 63);
         }
-        if (n <= slots || at.log2_chunks == most) break;  // (as many as the cache's size gives fit)
+        if (n <= slots) break;
+    }
+    if (at.log2_chunks == 2) {  // by position
+        at.b = blockIdx.z;
+        at.x = blockIdx.x;
+        at.length = __builtin_amdgcn_readlane(length_of(at.b & ~63), at.b & 63);
+        return true;
     }
     int left = blockIdx.z * gridDim.x + blockIdx.x;
     for (int b0 = 0; b0 < B; b0 += 64) {
@@ -226,12 +235,12 @@ __device__ __forceinline__ bool place_by_length(const ScoreArgs& a, int most, in
 
 // The scoring launch with the encoding in it: a workgroup of 1024 threads encodes its unit's query vectors for itself (and the appended
 // key, where its chunks hold that row) as the workgroup per unit of hata_unit.hip does, its first codes on their way meanwhile, and
-// then has 1024, 512 or 256 threads for each of one, two or four chunks.  grid = (workgroups of a unit, Hkv, B), dealt out by the lengths where
-// these are not one chunk each.
+// then has 1024, 512 or 256 threads for each of one, two or four chunks.  grid = (workgroups of a unit, Hkv, B); FOUR: dealt out by the lengths
+// (which costs two chunks a workgroup 0.4 us a launch and saves them less).
 // What bounds it: the launch, the round trips to the weights and the appended row, half a microsecond of fp64 of every compute unit.
 // A launch in front of the scoring costs its own launch and round trips on top: 2 x 20011 keys, a group of five, 21.7 us a step with one,
 // 20.2 so (launch_encode_score has the rule).
-template <int WD, int G>
+template <int WD, int G, bool FOUR>
 __global__ __launch_bounds__(1024) void encode_score_kernel(const EncodeScoreArgs a) {
     constexpr int R = WD * 32, NB = G * R + 1, NBR = (NB + 15) / 16 * 16, NW = 16, NT = 1024;
     constexpr int PASSES = G / 4 + 1;  // of four vectors: the query heads and the appended key, which goes alone where the heads fill theirs
@@ -243,14 +252,17 @@ __global__ __launch_bounds__(1024) void encode_score_kernel(const EncodeScoreArg
     __shared__ uint32_t scan4[4][4];
     extern __shared__ __attribute__((aligned(16))) uint32_t hists[];  // [chunks of the workgroup][NBR]
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int h = blockIdx.y, most = 10 - a.log2_threads;
+    const int h = blockIdx.y;
     EncodeScorePlace at;
     int own_length = 0;
-    if (most > 0) own_length = a.s.seq_len[min(lane, (int)gridDim.z - 1)];
+    if constexpr (FOUR) own_length = a.s.seq_len[min(lane, (int)gridDim.z - 1)];
     Hash hash;
     hash.fetch(a.W_H + (int64_t)h * HATA_D * R);
-    if (most == 0) at = {(int)blockIdx.z, (int)blockIdx.x, 0, a.s.seq_len[blockIdx.z]};
-    else if (!place_by_length(a.s, most, own_length, at)) return;
+    if constexpr (FOUR) {
+        if (!place_by_length(a.s, own_length, at)) return;
+    } else {
+        at = {(int)blockIdx.z, (int)blockIdx.x, a.log2_chunks, 0};
+    }
     const int b = at.b, log2_threads = 10 - at.log2_chunks;
     const int64_t u = (int64_t)b * a.s.Hkv + h;
     const uint16_t* qv = a.q + ((int64_t)b * a.s.Hq + (int64_t)h * G) * HATA_D;
@@ -258,6 +270,7 @@ __global__ __launch_bounds__(1024) void encode_score_kernel(const EncodeScoreArg
 #pragma unroll
     for (int p = 0; p < PASSES; ++p)
         if (4 * p < G) x[p] = Hash::fetch_x(qv + min(4 * p + (lane & 3), G - 1) * HATA_D);
+    if constexpr (!FOUR) at.length = a.s.seq_len[b];
     const int L = clampi(at.length, 0, a.s.L_cap);
     const int chunks = NT >> log2_threads, threads = 1 << log2_threads, sub = tid >> log2_threads, t = tid & (threads - 1);
     const int first = at.x * chunks * a.s.chunk;
@@ -410,14 +423,14 @@ hipError_t launch_score_select(const hata_ctx* c, const uint32_t* codes, const i
     return hipGetLastError();
 }
 
-template <int WD>
+template <int WD, bool FOUR>
 static const void* encode_score_fn(int G) {
     switch (G) {
-        case 1: return (const void*)&encode_score_kernel<WD, 1>;
-        case 2: return (const void*)&encode_score_kernel<WD, 2>;
-        case 4: return (const void*)&encode_score_kernel<WD, 4>;
-        case 5: return (const void*)&encode_score_kernel<WD, 5>;
-        case 8: return (const void*)&encode_score_kernel<WD, 8>;
+        case 1: return (const void*)&encode_score_kernel<WD, 1, FOUR>;
+        case 2: return (const void*)&encode_score_kernel<WD, 2, FOUR>;
+        case 4: return (const void*)&encode_score_kernel<WD, 4, FOUR>;
+        case 5: return (const void*)&encode_score_kernel<WD, 5, FOUR>;
+        case 8: return (const void*)&encode_score_kernel<WD, 8, FOUR>;
         default: return nullptr;
     }
 }
@@ -426,8 +439,6 @@ static const void* encode_score_fn(int G) {
 hipError_t launch_encode_score(const hata_ctx* c, const void* q, const void* K, const float* W_H, uint32_t* codes, int append,
                                const int32_t* seq_len, const int32_t* k, int B, hipStream_t s) {
     const hata_config& f = c->cfg;
-    const void* fn = c->Wd == 1 ? encode_score_fn<1>(c->G) : c->Wd == 2 ? encode_score_fn<2>(c->G) : c->Wd == 4 ? encode_score_fn<4>(c->G) : nullptr;
-    if (!fn) return hipErrorNotSupported;
     // One round of workgroups, with as few chunks each as that allows: in more, every one of them encodes on the bandwidth's time (us a
     // step, two launches / one: 160 units of 4096-key chunks, 32768 keys 49.6 / 52.1, 40 units of 131072 45.2 / 51.5; one head a
     // unit, 256 of 32768, 64.9 / 64.0).  Up to it, r = 128: 8 units of 32768 keys 20.1 / 17.8, of 131072 23.9 / 21.1, 32 of
@@ -439,12 +450,17 @@ hipError_t launch_encode_score(const hata_ctx* c, const void* q, const void* K, 
     int chunks = 1;
     auto wgs = [&](int n) { return (int64_t)((c->n_chunks + n - 1) / n) * f.Hkv * B; };
     while (chunks < 4 && wgs(chunks) > c->cus) chunks *= 2;
-    if (wgs(chunks) > c->cus) return hipErrorNotSupported;
+    auto of_width = [&](auto four) {
+        constexpr bool F = decltype(four)::value;
+        return c->Wd == 1 ? encode_score_fn<1, F>(c->G) : c->Wd == 2 ? encode_score_fn<2, F>(c->G) : c->Wd == 4 ? encode_score_fn<4, F>(c->G) : nullptr;
+    };
+    const void* fn = chunks == 4 ? of_width(std::true_type{}) : of_width(std::false_type{});
+    if (!fn || wgs(chunks) > c->cus) return hipErrorNotSupported;
     EncodeScoreArgs a;
     a.s = score_args(c, c->qcodes, codes, seq_len, c->scores, k);
     a.q = (const uint16_t*)q; a.K = (const uint16_t*)K; a.W_H = W_H; a.codes = codes; a.qcodes = c->qcodes;
     a.append = append;
-    a.log2_threads = chunks == 1 ? 10 : chunks == 2 ? 9 : 8;
+    a.log2_chunks = __builtin_ctz(chunks);
     a.sb = f.kv_stride_b; a.sh = f.kv_stride_h; a.sn = f.kv_stride_n;
     void* args[] = {(void*)&a};
     return hipLaunchKernel(fn, dim3((c->n_chunks + chunks - 1) / chunks, f.Hkv, B), dim3(1024), args, (size_t)chunks * ((c->NB + 15) / 16 * 64), s);

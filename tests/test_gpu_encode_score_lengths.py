@@ -1,5 +1,5 @@
-"""The launch that encodes and scores, with its workgroups dealt out by the sequences' lengths: one, two or four chunks a workgroup in the same
-grid, against the stage calls -- codes, every score and the selection are the same words."""
+"""The launch that encodes and scores, with its workgroups dealt out by the sequences' lengths where the cache's size gives them four chunks: one,
+two or four in the same grid, against the stage calls -- codes, every score and the selection are the same words."""
 import math
 
 import pytest
@@ -11,6 +11,8 @@ from tests.test_gpu_encode_score import chunks_of_a_workgroup
 
 def chunks_by_length(n_chunks, chunk, most, lens):
     """The rule (place_by_length): the fewest chunks a workgroup with which the lengths' workgroups fit the grid that the cache's size gives."""
+    if most < 4:
+        return most
     slots = -(-n_chunks // most) * len(lens)
     return next(c for c in (1, 2, 4) if c == most or sum(max(1, -(-(-(-n // chunk)) // c)) for n in lens) <= slots)
 
@@ -27,10 +29,10 @@ def batch(kind, B, L_cap):
 
 @pytest.mark.parametrize("append", [True, False])
 @pytest.mark.parametrize("B,Hq,Hkv,r,L_cap,kind,chunks", [
-    (4, 32, 8, 128, 17000, "one", 1), (4, 40, 8, 64, 17000, "half", 1), (4, 8, 8, 32, 17000, "all", 2),                        # two by the cache's size
+    (4, 32, 8, 128, 17000, "one", 2), (70, 2, 1, 64, 17000, "half", 2),                                                      # two by the cache's size
     (16, 32, 8, 128, 17000, "one", 1), (16, 64, 8, 128, 17000, "first", 1), (16, 32, 8, 64, 17000, "half", 2),               # four
     (16, 40, 8, 128, 17000, "most", 4), (16, 8, 8, 128, 17000, "beyond", 1), (12, 16, 8, 32, 17000, "all", 4),
-    (70, 2, 1, 64, 17000, "one", 1), (70, 2, 1, 64, 17000, "most", 2), (100, 1, 1, 32, 17000, "beyond", 1), (100, 1, 1, 32, 17000, "half", 2), (100, 1, 1, 32, 17000, "most", 4)])  # more than 64 sequences
+    (90, 2, 1, 64, 17000, "one", 1), (128, 1, 1, 128, 17000, "most", 4), (100, 1, 1, 32, 17000, "beyond", 1), (100, 1, 1, 32, 17000, "half", 2), (100, 1, 1, 32, 17000, "most", 4)])  # more than 64 sequences
 def test_workgroups_by_length(B, Hq, Hkv, r, L_cap, kind, chunks, append):
     import torch
     from paper_2506_02572_amd import hata
