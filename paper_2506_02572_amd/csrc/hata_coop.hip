@@ -29,6 +29,7 @@
 // The waits need every workgroup of a unit to be running; the host launches this kernel
 // only when the whole grid can be resident at once.  The wait is bounded anyway: a workgroup that
 // gives up sets the context's error word and runs to its end, so every wave always terminates.
+#include <algorithm>
 #include <type_traits>
 
 #include "hata_attn_core.h"
@@ -1239,7 +1240,12 @@ int coop_capacity(const hata_ctx* c, bool paged, int chunk) {
     // (more than 64 KB of dynamic LDS has to be asked for)
     if (lds > 65536 && hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) return 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, 256, lds) != hipSuccess) return 0;
-    return per_cu * c->cus;
+    // A compute unit gives its 160 KB of LDS out in units of 320 words, which that query does not round up to: three workgroups of 53840 bytes are
+    // two on the device, and a grid of what the query says waited for workgroups that could not start.
+    hipFuncAttributes at;
+    if (hipFuncGetAttributes(&at, fn) != hipSuccess) return 0;
+    const size_t unit = 320 * 4, block = (at.sharedSizeBytes + lds + unit - 1) / unit * unit;
+    return std::min(per_cu, (int)(160 * 1024 / block)) * c->cus;
 }
 
 hipError_t launch_coop_step(const hata_ctx* c, const void* q, const void* K, const void* V,
