@@ -265,8 +265,9 @@ __device__ __forceinline__ void coop_encode_vec(const float* __restrict__ Wh, co
 // three -- with the scores in dynamic LDS the compiler would otherwise squeeze that form into the
 // registers of a fourth, which costs it 1.3 us; the narrower forms fit four as they are, and a batch of
 // 128 units at 4096 keys per chunk needs the four)
+constexpr int coop_most_per_cu(int WD) { return WD >= 8 ? 3 : 4; }
 template <int WD, int G, bool PAGED, bool BIG = false>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((G >= 16 ? 2 : 3), (WD >= 8 ? 3 : 4))))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((G >= 16 ? 2 : 3), coop_most_per_cu(WD))))
 void decode_step_coop_kernel(const CoopArgs a) {
     static_assert(G * WD <= 64, "query code words of a unit are collected by one wave");
     // dynamic LDS: the chunk's scores (2 bytes per key; later the selected rows as offsets in the
@@ -1245,6 +1246,9 @@ int coop_capacity(const hata_ctx* c, bool paged, int chunk) {
     hipFuncAttributes at;
     if (hipFuncGetAttributes(&at, fn) != hipSuccess) return 0;
     const size_t unit = 320 * 4, block = (at.sharedSizeBytes + lds + unit - 1) / unit * unit;
+    // Nor does it know the most that the kernel asks for, which is kept by allocating more registers than it uses: one of 85 is given 104 and
+    // fits four times, the query says five.
+    per_cu = std::min(per_cu, coop_most_per_cu(c->Wd));
     return std::min(per_cu, (int)(160 * 1024 / block)) * c->cus;
 }
 

@@ -1,5 +1,5 @@
-"""Grids of the single-launch step between what fits the device at two and at three workgroups a compute unit, where a workgroup's LDS is just
-below a third of it: the step finishes, and selects what the stage calls select."""
+"""Grids of the single-launch step just above what fits the device, at the sizes where that is hard to tell -- a workgroup's LDS just below a third of
+a compute unit's, registers of a kernel that asks for four workgroups at most --: the step finishes, and selects what the stage calls select."""
 import math
 
 import pytest
@@ -23,7 +23,9 @@ def selection(torch, hata, B, Hq, Hkv, r, L_cap, k, q, W, codes, seq, kb):
 
 @pytest.mark.parametrize("Hq,r,L,paged", [
     (32, 128, 40529, True),   # 8192 keys a workgroup, 53840 bytes: 640 workgroups, 512 of them resident
-    (32, 128, 40960, True), (64, 64, 40529, False), (32, 128, 40529, False)])
+    (32, 128, 40960, True), (64, 64, 40529, False), (32, 128, 40529, False),
+    (8, 64, 40529, False), (16, 32, 40529, False), (8, 32, 36865, True), (16, 64, 38000, True),  # 85 registers or fewer: 1280 workgroups, 1024 resident
+    (16, 64, 77000, True), (16, 32, 77000, True)])                                              # both (16384 keys a workgroup, or 4096)
 def test_grid_above_what_is_resident(Hq, r, L, paged):
     import torch
     from paper_2506_02572_amd import hata
