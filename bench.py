@@ -78,7 +78,7 @@ def parse():
                          "(the paper keeps them dense, Sec. 5.1); 0 skips the leg")
     ap.add_argument("--step-mode", type=int, default=0, choices=(0, 1, 3),
                     help="hata_set_step_mode: 0 = single-launch form, a batch too large to be resident in "
-                         "slices (default); 1 = the whole batch as one grid; 3 = three-launch form")
+                         "slices (default); 1 = the whole batch as one grid; 3 = the form without waits, two or three launches")
     ap.add_argument("--chunk", type=int, default=0, choices=(0, 1024, 2048, 4096, 8192, 16384, 32768),
                     help="hata_tuning.chunk: cached keys per scoring workgroup (0 = the library's choice)")
     ap.add_argument("--paged", type=int, default=0, metavar="PAGE_ROWS",
@@ -243,7 +243,7 @@ class Bench:
 
     def plan(self):
         n_launches, chunk, n_chunks = self.ctx.hata_step_plan(self.w.B)
-        n_sub = self.ctx.hata_step_sub_batches(self.w.B)  # launches of the single-launch form (batch slices), 0 = three-launch form
+        n_sub = self.ctx.hata_step_sub_batches(self.w.B)  # launches of the single-launch form (batch slices), 0 = form without waits
         return n_launches, chunk, n_chunks, n_sub
 
     # ---- N layer steps in one HIP graph (launch gaps out of the way), with and without the dense first layers
@@ -640,7 +640,7 @@ def per_config_entry(name, args):
     traffic = HBM_TRAFFIC_BYTES.get(w.name, {}).get("step")
     ideal_dense = w.dense_bytes(1 if w.append_steps else 0) / (HBM_PEAK_GBPS * 1e9) * 1e6
     e = {"workload": w.name, "us_per_step": round(us_step, 3), "steps": PER_CONFIG_STEPS, "warmup": PER_CONFIG_WARMUP,
-         "layers_rotated": b.n_layers, "launches_per_step": n_sub if n_launches == 1 else n_launches,
+         "layers_rotated": b.n_layers, "launches_per_step": n_sub if n_launches == 1 else "2 or 3",
          "chunk": chunk, "chunks_per_unit": n_chunks,
          "algorithmic_bytes_per_step": b.alg_bytes, "achieved_GBps": round(gbps, 1),
          "frac": round(gbps / HBM_PEAK_GBPS, 4), "traffic": traffic,
@@ -734,7 +734,7 @@ def main():
                    "k": list(w.k) if len(set(w.k)) > 1 else w.k[0],
                    "layers_rotated": b.n_layers, "first_pass_untimed": b.n_combo, "append_per_step": True,
                    "kv_cache": "pinned host memory (rows gathered over the bus)" if args.kv_host else "HBM",
-                   "launches_per_step": n_sub if n_launches == 1 else n_launches, "step_mode": args.step_mode,
+                   "launches_per_step": n_sub if n_launches == 1 else "2 or 3", "step_mode": args.step_mode,
                    "chunk": plan_chunk,
                    "chunks_per_unit": plan_n_chunks},
         "achieved_GBps": round(step_gbps, 1),

@@ -95,10 +95,10 @@ typedef struct {
                             * call, the size that needs the fewest launches for the batch), else 1024, 2048,
                             * 4096 or 8192 for every kernel, or 16384 / 32768 for the single-launch step alone
                             * (the other kernels keep their default) */
-    int32_t attn_rows;     /* selected rows per attention workgroup of the three-launch form: 0 = default, else a power of two in 16..256 */
+    int32_t attn_rows;     /* selected rows per attention workgroup of the form without waits: 0 = default, else a power of two in 16..256 */
     int32_t par_merge;     /* single-launch form, merge of a unit's partials: -1 = default, 0 = by the last workgroup to arrive, 1 = a query head per workgroup (taken for launches with more than four chunks per unit; the default when a group has two heads or more) */
     int32_t shared_device; /* != 0: other work may run on the device beside the step: no in-kernel waits unless hata_set_step_mode asks for them
-                            * (three launches, short caches a workgroup per unit: see hata_decode_step) */
+                            * (two or three launches, short caches a workgroup per unit: see hata_decode_step) */
 } hata_tuning;
 
 /* hata_workspace_bytes / hata_create with the launch shapes of `tuning` (host pointer, may be
@@ -238,7 +238,8 @@ int hata_dense_decode(hata_ctx* ctx, const void* q, const void* K, const void* V
  * with NaN (out: bf16 0x7fc0, out_f32: NaN), so the failure shows in the data itself (the idx
  * rows of such a step are unspecified: -1 where the unit could still be marked, else whatever its
  * workgroups wrote), and the next hata_check() returns HATA_ETIMEOUT.  Otherwise
- * the step is three launches (encode; score; threshold + select + attend) with no in-kernel wait.
+ * the step is three launches (encode; score; threshold + select + attend) with no in-kernel wait, or two, the first one encoding and scoring,
+ * for r <= 128 and groups of 1, 2, 4, 5 or 8 heads where a workgroup per compute unit with at most four chunks each covers the batch.
  * The residency test assumes the device runs nothing else at that moment and that the context is
  * used on the device that was current in hata_create(): a process that overlaps other kernels
  * with the step (other streams, other processes) should create the context with
@@ -261,7 +262,7 @@ int hata_decode_step(hata_ctx* ctx, const void* q, const void* K, const void* V,
  * hata_gather_rows while another layer computes.  ONE launch of the single-launch kernel of
  * hata_decode_step, stopped after the selection, with the same residency rule, bounded waits and
  * hata_check() reporting (the lists of a unit whose workgroup gave up are unspecified);
- * HATA_EUNSUPPORTED for the shapes and batches whose step takes three launches. */
+ * HATA_EUNSUPPORTED for the shapes and batches whose step has no single-launch form. */
 int hata_select_step(hata_ctx* ctx, const void* q, const void* K, const float* W_H, uint32_t* codes,
                      const int32_t* seq_len, const int32_t* k, int32_t B, int32_t append, int32_t* idx,
                      void* stream);
@@ -300,15 +301,16 @@ int hata_prefill_write_paged(hata_ctx* ctx, const void* K_new, const void* V_new
                              int32_t page_rows, int32_t n_pages, const float* W_H, void* stream);
 
 /* Host-side query of how hata_decode_step() runs a batch of B sequences; nothing is enqueued.
- * *n_launches: 1 (single-launch form) or 3 (three-launch form, whose first two go as one where the batch is small); *chunk: cached keys per scoring
- * workgroup for a batch of this size; *n_chunks: scoring workgroups per (sequence, KV head).  Any
+ * *n_launches: 1 (single-launch form) or 3 (the form without in-kernel waits, also where its first two launches go as one: see
+ * hata_decode_step); *chunk: cached keys per scoring workgroup for a batch of this size (the launch that encodes and scores may give one up
+ * to four of these); *n_chunks: scoring workgroups per (sequence, KV head).  Any
  * output pointer (host) may be NULL. */
 int hata_step_plan(const hata_ctx* ctx, int32_t B, int32_t* n_launches, int32_t* chunk, int32_t* n_chunks);
 
 /* A batch with more (sequence, KV head) units than one launch can keep resident still runs in the
  * single-launch form, as consecutive launches over equal slices of the batch (each a whole step
  * for its sequences).  *n_sub (host): the number of such launches for a batch of B, 1 when the
- * batch fits one launch, 0 when hata_decode_step() uses the three-launch form. */
+ * batch fits one launch, 0 when hata_decode_step() uses the form without waits. */
 int hata_step_sub_batches(const hata_ctx* ctx, int32_t B, int32_t* n_sub);
 
 /* mode 0 (default): hata_decode_step() uses the single-launch form whenever it fits, a batch too
@@ -322,14 +324,14 @@ int hata_step_sub_batches(const hata_ctx* ctx, int32_t B, int32_t* n_sub);
  *   and finish -- which is how the hardware dispatches a grid, not a guarantee of the
  *   programming model: should a wait ever give up, hata_check() reports it (HATA_ETIMEOUT) and
  *   the step must be repeated in mode 0 or 3;
- * mode 3: always the three-launch form (no in-kernel waits).
+ * mode 3: always the form without in-kernel waits (two or three launches).
  * (Modes 1 and 3, once asked for, rule out the workgroup per unit of short caches too; a context made for a shared device
  * starts without waits but with that form.) */
 int hata_set_step_mode(hata_ctx* ctx, int32_t mode);
 
 /* The Hamming scores of a step are an intermediate: the single-launch forms keep them on chip and
  * write the score region of the workspace only if asked to (keep != 0; default off, which saves
- * 2 bytes of HBM writes per cached key).  The three-launch form always writes it (its last
+ * 2 bytes of HBM writes per cached key).  The form without waits always writes it (its last
  * launch reads it back), and so does every hata_decode_step of a context made for a shared device, whatever
  * form it takes (unless hata_set_step_mode asked for mode 0 or 1). */
 int hata_keep_step_scores(hata_ctx* ctx, int32_t keep);
@@ -344,7 +346,7 @@ int hata_set_wait_limit(hata_ctx* ctx, int32_t polls);
  * this context gave up an in-kernel wait since the last check: HATA_OK, or HATA_ETIMEOUT (the
  * flag and the workspace's control words are cleared; the outputs of the steps since the last
  * check must be discarded).  The only synchronous call of the library besides hata_create();
- * never needed for the three-launch form. */
+ * never needed for the form without waits. */
 int hata_check(hata_ctx* ctx, void* stream);
 
 /* KV cache in host memory (the paper's offloading variant, Sec. 5.3: hash codes stay on the GPU,

@@ -115,7 +115,7 @@ int make_plan(const hata_config* f, const hata_tuning* t, Plan* p) {
     if (p->sparse_splits > 256) return HATA_EUNSUPPORTED;  // budget above 65536 rows
     int max_splits = p->sparse_splits;
     if (p->n_chunks > max_splits) max_splits = p->n_chunks;  // the cooperative step: one slice per chunk
-    // the three-launch step: the chunks, and the further pieces of those with many selected rows (launch_attention)
+    // the step without waits: the chunks, and the further pieces of those with many selected rows (launch_attention)
     int pieces = p->n_chunks > f->k_max / 512 ? p->n_chunks : f->k_max / 512;
     if (pieces > f->k_max / 64) pieces = f->k_max / 64;
     if (p->n_chunks + pieces > max_splits) max_splits = p->n_chunks + pieces;
@@ -198,7 +198,7 @@ inline int coop_sub_batches(const hata_ctx* c, int B, bool paged, int* chunk_out
 // four unless noted: 64 units of 6000 keys 15.0 / 14.9; 128 of 8192 18.5 / 17.1 (r = 256 23.1 / 22.7, ragged 17.6 / 16.8, one head a
 // unit 14.6 / 12.9), of 16384 23.4 / 26.5; 256 of 16384 37.5 / 30.9 (r = 256 51.3 / 44.8); 264 of 10000 30.6 / 37.5; 384 of 12000, one
 // head a unit, 28.9 / 32.9; 512 of 8000, one head a unit, 24.1 / 27.5; 448 of up to 12000 at r = 256, one head a unit,
-// 40.0 / 37.1.  On a shared device, three launches / one per unit: 8 units of 8192 keys 18.3 / 17.5 (r = 256 18.8 / 20.6), 96 of
+// 40.0 / 37.1.  On a shared device, three launches (not the two that small batches have now) / one per unit: 8 units of 8192 keys 18.3 / 17.5 (r = 256 18.8 / 20.6), 96 of
 // 12000 26.3 / 21.4, 128 of 16384 28.2 / 25.6 (r = 256 34.3 / 30.9), one of them that long and the others of 500 21.9 / 23.6.
 //
 // Rows: the other forms gather a unit's rows by several workgroups, the more the longer the cache, unless the units are as many as
@@ -334,7 +334,7 @@ int hata_create_tuned(hata_ctx** ctx_out, const hata_config* cfg, const hata_tun
         c->coop_opt_cap[o] = hata::coop_capacity(c, false, c->coop_opt_chunk[o]);
         c->coop_opt_cap_paged[o] = hata::coop_capacity(c, true, c->coop_opt_chunk[o]);
     }
-    // a device shared with other work cannot promise that a whole grid is resident: three launches
+    // a device shared with other work cannot promise that a whole grid is resident: two or three launches
     c->shared = tuning && tuning->shared_device;
     c->step_mode = c->shared ? 3 : 0;
     c->mode_asked = 0;

@@ -5,7 +5,7 @@
 //   ROWS_IDX     rows come from an index list in memory            (hata_sparse_decode)
 //   ROWS_SELECT  the rows of one chunk of the cache (a few, of a very long one) that the unit
 //                threshold selects: ordered compaction of the chunk's stored scores; its part of
-//                the index list is written as a by-product  (hata_decode_step, three-launch form)
+//                the index list is written as a by-product  (hata_decode_step, form without waits)
 //
 // Split over the rows: every workgroup handles a slice of a unit's rows for HT query heads of
 // the group at once (each K/V row is read once for all of them), keeps an online-softmax

@@ -47,7 +47,7 @@ struct hata_ctx {
     int spin_limit;          // polls an in-kernel wait makes before it gives up (0 = the default)
     int keep_scores;         // single-launch step also writes the score array
     int par_merge;           // single-launch step merges the heads of a unit in several workgroups
-    int step_mode;           // 0 = single launch when it fits, 3 = always three launches
+    int step_mode;           // 0 = single launch when it fits, 3 = always the form without waits
     int unit_keys;           // keys a workgroup per unit handles (0: that form is not available, or the caller asked for a launch shape)
     int shared;              // hata_tuning.shared_device
     int mode_asked;          // step_mode was set by the caller (and is not just that of a shared device)

@@ -313,9 +313,8 @@ __device__ __forceinline__ double gram_piece(const float* __restrict__ W, int c,
 // general way has 72 more, and stages the keys twice) with the exponentials and the splits, to its sums.  So the reads are
 // requested together, behind no branch, and small batches have workgroups of 32 columns, half the way.  Kernel time at r = 128, us,
 // one query vector a block / others: one block 11.0 / 13.6 (64 columns 14.5 / 20.1), 256 blocks 20.0 / 25.4 (21.1 / 26.9 with
-// the reads one after the other), 960 blocks, four rounds, 74 / 97 (79 / 100).  A step of 960 blocks 87 / 107; with a launch for the
-// column sums, two workgroups a CU and both tiles side by side it was 95 of either kind: there the general way is behind, and in
-// the smallest batches of r = 32 (one block 19.1 for 16.7).
+// the reads one after the other).  Larger batches, unless their queries are short, take train_grad_runs_kernel.  With a launch for the column sums
+// in front and both tiles side by side the general way was ahead in the smallest batches of r = 32 (one block a step 16.7, 19.1 so).
 template <int R, int COLS>
 __global__ __launch_bounds__(TrainShape<COLS>::THREADS) void train_grad_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const float* __restrict__ s, const float* __restrict__ W,

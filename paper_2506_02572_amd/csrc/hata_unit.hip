@@ -412,7 +412,7 @@ hipError_t launch_unit_step(const hata_ctx* c, const void* q, const void* K, con
     a.log2_kpt = unit_log2_kpt(f.L_cap);
     a.q = (const uint16_t*)q; a.K = (const uint16_t*)K; a.V = (const uint16_t*)V; a.W_H = W_H;
     a.seq_len = seq_len; a.kbud = k; a.codes = codes; a.qcodes = c->qcodes;
-    // a shared device's contiguous cache takes three launches for any other shape, and these always leave the scores in the workspace
+    // a shared device's contiguous cache takes two or three launches for any other shape, and these always leave the scores in the workspace
     a.scores = c->keep_scores || (!pages && c->step_mode == 3) ? c->scores : nullptr;
     a.idx = c->idx; a.out = (uint16_t*)out; a.out_f32 = out_f32;
     a.Hq = f.Hq; a.Hkv = f.Hkv; a.L_cap = f.L_cap; a.k_max = f.k_max; a.append = append;

@@ -305,7 +305,7 @@ class Context:
         return n.value, c.value, nc.value
 
     def hata_step_sub_batches(self, B):
-        """Launches of the single-launch form for a batch of B (0: the three-launch form is used)."""
+        """Launches of the single-launch form for a batch of B (0: the form without waits is used)."""
         n = _i32(0)
         rc = self._lib.hata_step_sub_batches(self._h, B, ctypes.byref(n))
         if rc:
